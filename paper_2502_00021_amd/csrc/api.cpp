@@ -296,19 +296,31 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
     sk.F = k->n_free;
     if ((uint64_t)sk.J + 7ull * sk.F + 7ull * K > 630ull || pxr::fk_lds_bytes(sk) > 160u * 1024u)
         return fail(PXR_ERR_UNSUPPORTED, "pxr_set_skeleton: 64 frames of this skeleton do not fit 160 KB of LDS");
-    // one allocation: parent[K], slot[K], hinge[K][9]
-    std::vector<uint32_t> staging((size_t)K * 11);
-    for (uint32_t b = 0; b < K; ++b) {
-        staging[b] = (uint32_t)k->parent[b];
-        staging[K + b] = (uint32_t)k->slot[b];
-        float h[9];
-        for (int c = 0; c < 3; ++c) {
-            h[c] = k->anchor[b * 3 + c];
-            h[3 + c] = k->axis[b * 3 + c];
-            h[6 + c] = k->offset[b * 3 + c];
+    // one allocation: the records in order of depth (a parent precedes its child, so one pass finds the depths), then
+    // where each depth begins
+    std::vector<uint32_t> depth(K), begin(1, 0u);
+    std::vector<pxr::SkeletonRecord> records;
+    for (uint32_t b = 0; b < K; ++b) depth[b] = k->parent[b] < 0 ? 0u : depth[(uint32_t)k->parent[b]] + 1u;
+    for (uint32_t d = 0; records.size() < K; ++d) {
+        for (uint32_t b = 0; b < K; ++b) {
+            if (depth[b] != d) continue;
+            pxr::SkeletonRecord r{};
+            r.body = b;
+            r.parent = k->parent[b];
+            r.slot = k->slot[b];
+            for (int c = 0; c < 3; ++c) {
+                r.anchor[c] = k->anchor[b * 3 + c];
+                r.axis[c] = k->axis[b * 3 + c];
+                r.offset[c] = k->offset[b * 3 + c];
+            }
+            records.push_back(r);
         }
-        std::memcpy(&staging[2 * (size_t)K + (size_t)b * 9], h, sizeof(h));
+        begin.push_back((uint32_t)records.size());
     }
+    sk.depths = (uint32_t)begin.size() - 1u;
+    std::vector<uint32_t> staging(K * (sizeof(pxr::SkeletonRecord) / 4) + begin.size());
+    std::memcpy(staging.data(), records.data(), K * sizeof(pxr::SkeletonRecord));
+    std::memcpy(staging.data() + K * (sizeof(pxr::SkeletonRecord) / 4), begin.data(), begin.size() * 4);
     std::string err;
     int rc = pxr::prepare_fk_kernel(err);
     if (rc != PXR_OK) return fail(rc, "pxr_set_skeleton: " + err);
@@ -331,9 +343,8 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
     }
     if (s->d_skeleton) (void)hipFree(s->d_skeleton);
     s->d_skeleton = d;
-    sk.parent = static_cast<const int32_t*>(d);
-    sk.slot = sk.parent + K;
-    sk.hinge = reinterpret_cast<const float*>(sk.slot + K);
+    sk.records = static_cast<const pxr::SkeletonRecord*>(d);
+    sk.depth_begin = reinterpret_cast<const uint32_t*>(sk.records + K);
     s->sk = sk;
     return PXR_OK;
 }

@@ -3,13 +3,20 @@
 // 2502.00021, section 1: the whole loop, environment step included, stays on
 // the accelerator).  gfx950 only.
 //
-// One lane per frame.  A frame's kinematic tree is a serial chain of
-// dependent quaternion products, so the parallel axis is the batch: 64 frames
-// per wavefront, every lane walking the same skeleton in lock-step (the
-// skeleton tables are wave-uniform and arrive through scalar loads).  The
-// poses of a workgroup's 64 frames live in LDS as pose[k][component][lane]
-// (row stride 65 floats: conflict-free both for the per-lane walk and for the
-// transposed, fully coalesced copy to HBM at the end).
+// A workgroup of four wavefronts takes 64 frames, one per lane, and shares out their bodies: the skeleton's
+// records come in order of depth (free bodies, then their children, ...), a depth's bodies are dealt to the four
+// wavefronts, and a barrier separates the depths.  What does not depend on the parent - the free poses, sine and
+// cosine of every half angle - is done for all bodies at once before the first of them.  What bounds the stage is
+// latency, not work: a frame is a chain of dependent quaternion products, and its length here is the tree's depth
+// (4 for a humanoid of 15 bodies) instead of its number of bodies.  Measured on that
+// skeleton against one wavefront that walked all bodies of its 64 frames with staged inputs: 30 frames 12.0 -> 4.5 us
+// (an empty-handed launch takes 4), 196 608 frames 50.7 -> 21.1 us = 4.9 TB/s, what a large copy reaches; the 7-link
+// chain, whose depth is its length, 8.8 -> 4.8 us for 256 frames.
+// The records are wave-uniform and arrive through scalar loads, a depth's first one before the barrier that opens
+// it.  Angles and free poses are read from memory as each lane needs them (a workgroup's are a contiguous few KB:
+// every line is fetched once).  The poses of the 64 frames live in LDS as the image of the output chunk they become,
+// one row of 7 K floats per frame; an even row gets one float of padding, so that the row stride is odd and the
+// lanes of a wavefront, one row each, use different banks.
 //
 // Arithmetic: fp32, explicit fmaf, no contraction.  sin and cos of half the
 // hinge angle come from a two-constant Cody-Waite reduction by pi/2 and two
@@ -24,9 +31,10 @@
 namespace pxr {
 namespace {
 
-constexpr uint32_t kFkLanes = 64;            // frames per workgroup (one wavefront)
-constexpr uint32_t kFkStride = kFkLanes + 1; // LDS row stride in floats
-constexpr uint32_t kFkBatch = 16;            // memory requests a lane has in flight per array in the copy stages
+constexpr uint32_t kFkFrames = 64;    // frames per workgroup: one per lane of a wavefront
+constexpr uint32_t kFkWaves = 4;      // wavefronts that share the frames' bodies
+constexpr uint32_t kFkThreads = kFkFrames * kFkWaves;
+constexpr uint32_t kFkAhead = 4;      // bodies a wavefront has requests in flight for before the first depth
 
 constexpr float kMaxHingeAngle = 65536.0f;  // radians; the reduction below is accurate up to here
 
@@ -63,122 +71,113 @@ __device__ __forceinline__ void rotate(float w, float x, float y, float z, float
     out[2] = __builtin_fmaf(m20, v0, __builtin_fmaf(m21, v1, m22 * v2));
 }
 
-__global__ __launch_bounds__(kFkLanes) void fk_kernel(const SkeletonConsts sk, const float* __restrict__ free_poses,
-                                                      const float* __restrict__ angles, uint32_t n_frames,
-                                                      float* __restrict__ poses) {
+__device__ __forceinline__ void hinge_pose(const SkeletonRecord& t, float* row) {
+    const float* pp = row + t.parent * 7;
+    float* o = row + t.body * 7u;
+    const float ppx = pp[0], ppy = pp[1], ppz = pp[2], pw = pp[3], px = pp[4], py = pp[5], pz = pp[6];
+    const float cs = o[3], sn = o[4];  // left there for all bodies before the first depth
+    const float jw = cs, jx = sn * t.axis[0], jy = sn * t.axis[1], jz = sn * t.axis[2];
+    // body orientation = parent orientation (x) hinge rotation (Hamilton product)
+    const float qw = __builtin_fmaf(-pz, jz, __builtin_fmaf(-py, jy, __builtin_fmaf(-px, jx, pw * jw)));
+    const float qx = __builtin_fmaf(py, jz, __builtin_fmaf(-pz, jy, __builtin_fmaf(px, jw, pw * jx)));
+    const float qy = __builtin_fmaf(pz, jx, __builtin_fmaf(-px, jz, __builtin_fmaf(py, jw, pw * jy)));
+    const float qz = __builtin_fmaf(px, jy, __builtin_fmaf(-py, jx, __builtin_fmaf(pz, jw, pw * jz)));
+    float t1[3], t2[3];
+    rotate(pw, px, py, pz, t.anchor[0], t.anchor[1], t.anchor[2], t1);  // hinge position, parent frame -> world
+    rotate(qw, qx, qy, qz, t.offset[0], t.offset[1], t.offset[2], t2);  // body centre relative to the hinge
+    o[0] = (ppx + t1[0]) + t2[0];
+    o[1] = (ppy + t1[1]) + t2[1];
+    o[2] = (ppz + t1[2]) + t2[2];
+    o[3] = qw;
+    o[4] = qx;
+    o[5] = qy;
+    o[6] = qz;
+}
+
+__global__ __launch_bounds__(kFkThreads) void fk_kernel(const SkeletonConsts sk, const float* __restrict__ free_poses,
+                                                        const float* __restrict__ angles, uint32_t n_frames,
+                                                        float* __restrict__ poses) {
     extern __shared__ __align__(16) unsigned char lds[];
-    float* pose = reinterpret_cast<float*>(lds);              // [K*7][kFkStride]
-    float* ang = pose + (size_t)sk.K * 7 * kFkStride;         // [J][kFkStride]
-    float* fre = ang + (size_t)sk.J * kFkStride;              // [F*7][kFkStride]
+    float* pose = reinterpret_cast<float*>(lds);  // [kFkFrames][stride]
+    const uint32_t n_row = sk.K * 7u, stride = n_row | 1u;
 
-    const uint32_t lane = threadIdx.x;
-    const uint32_t f0 = blockIdx.x * kFkLanes;                // first frame of this workgroup
-    const uint32_t nf = min(kFkLanes, n_frames - f0);         // frames it holds (ragged tail)
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t f0 = blockIdx.x * kFkFrames;               // first frame of this workgroup
+    const uint32_t nf = min(kFkFrames, n_frames - f0);        // frames it holds (ragged tail)
+    float* row = pose + lane * stride;
 
-    // Coalesced loads of the workgroup's contiguous input chunks, transposed into LDS.  A batch of requests goes out
-    // before the first answer is used: one request per trip, each waited for, made this stage a chain of two dozen
-    // memory round trips, which was most of the kernel's time.  (Lanes past the end of a chunk ask for its last
-    // element again and drop the answer; index / row length by multiplication: indices stay below 64 * row length,
-    // far inside the exact range.)
+    // ---- what depends on no parent, all bodies at once (lanes past the last frame repeat it and are not stored)
     {
-        const uint32_t row_f = sk.F * 7;
-        const uint32_t n_a = nf * sk.J, n_f = nf * row_f;
-        const float* src_a = angles + (size_t)f0 * sk.J;
-        const float* src_f = free_poses + (size_t)f0 * row_f;
-        const uint32_t magic_j = sk.J > 1u ? 0xFFFFFFFFu / sk.J + 1u : 0u;  // (ceil(2^32 / J); J == 1 needs none)
-        const uint32_t magic_f = row_f ? 0xFFFFFFFFu / row_f + 1u : 0u;     // (rows are multiples of 7)
-        for (uint32_t base = 0; base < max(n_a, n_f); base += kFkLanes * kFkBatch) {
-            float ta[kFkBatch], tf[kFkBatch];
-            if (base < n_a) {
+        const size_t frame = f0 + min(lane, nf - 1u);
+        const float* my_angles = angles + frame * sk.J;
+        const float* my_free = free_poses + frame * (sk.F * 7u);
+        for (uint32_t i0 = wave; i0 < sk.K; i0 += kFkWaves * kFkAhead) {
+            float theta[kFkAhead];
 #pragma unroll
-                for (uint32_t u = 0; u < kFkBatch; ++u) ta[u] = src_a[min(base + u * kFkLanes + lane, n_a - 1u)];
+            for (uint32_t u = 0; u < kFkAhead; ++u) {
+                const uint32_t i = min(i0 + u * kFkWaves, sk.K - 1u);
+                const SkeletonRecord& t = sk.records[i];
+                theta[u] = 0.0f;
+                if (t.parent >= 0 && t.slot >= 0) theta[u] = my_angles[t.slot];
             }
-            if (base < n_f) {
 #pragma unroll
-                for (uint32_t u = 0; u < kFkBatch; ++u) tf[u] = src_f[min(base + u * kFkLanes + lane, n_f - 1u)];
-            }
-            if (base < n_a) {
+            for (uint32_t u = 0; u < kFkAhead; ++u) {
+                const uint32_t i = i0 + u * kFkWaves;
+                if (i >= sk.K) break;
+                const SkeletonRecord& t = sk.records[i];
+                float* o = row + t.body * 7u;
+                if (t.parent < 0) {
+                    const float* src = my_free + t.slot * 7;
+                    float v[7];
 #pragma unroll
-                for (uint32_t u = 0; u < kFkBatch; ++u) {
-                    const uint32_t i = base + u * kFkLanes + lane;
-                    const uint32_t n = sk.J > 1u ? __umulhi(i, magic_j) : i, j = i - n * sk.J;
-                    if (i < n_a) ang[j * kFkStride + n] = ta[u];
-                }
-            }
-            if (base < n_f) {
+                    for (int c = 0; c < 7; ++c) v[c] = src[c];
 #pragma unroll
-                for (uint32_t u = 0; u < kFkBatch; ++u) {
-                    const uint32_t i = base + u * kFkLanes + lane;
-                    const uint32_t n = __umulhi(i, magic_f), j = i - n * row_f;
-                    if (i < n_f) fre[j * kFkStride + n] = tf[u];
+                    for (int c = 0; c < 7; ++c) o[c] = v[c];
+                } else {
+                    sincos_half(theta[u], o[4], o[3]);
                 }
             }
         }
     }
-    __syncthreads();
 
-    if (lane < nf) {
-        for (uint32_t k = 0; k < sk.K; ++k) {
-            const int parent = sk.parent[k], slot = sk.slot[k];   // wave-uniform
-            float* o = pose + (size_t)k * 7 * kFkStride + lane;
-            if (parent < 0) {
-                const float* src = fre + (size_t)slot * 7 * kFkStride + lane;
-#pragma unroll
-                for (int c = 0; c < 7; ++c) o[c * kFkStride] = src[c * kFkStride];
-                continue;
-            }
-            const float* pp = pose + (size_t)parent * 7 * kFkStride + lane;
-            const float ppx = pp[0], ppy = pp[kFkStride], ppz = pp[2 * kFkStride];
-            const float pw = pp[3 * kFkStride], px = pp[4 * kFkStride], py = pp[5 * kFkStride], pz = pp[6 * kFkStride];
-            const float theta = slot >= 0 ? ang[(size_t)slot * kFkStride + lane] : 0.0f;
-            float sn, cs;
-            sincos_half(theta, sn, cs);
-            const float* tb = sk.hinge + (size_t)k * 9;           // anchor, axis, offset
-            const float jw = cs, jx = sn * tb[3], jy = sn * tb[4], jz = sn * tb[5];
-            // body orientation = parent orientation (x) hinge rotation (Hamilton product)
-            const float qw = __builtin_fmaf(-pz, jz, __builtin_fmaf(-py, jy, __builtin_fmaf(-px, jx, pw * jw)));
-            const float qx = __builtin_fmaf(py, jz, __builtin_fmaf(-pz, jy, __builtin_fmaf(px, jw, pw * jx)));
-            const float qy = __builtin_fmaf(pz, jx, __builtin_fmaf(-px, jz, __builtin_fmaf(py, jw, pw * jy)));
-            const float qz = __builtin_fmaf(px, jy, __builtin_fmaf(-py, jx, __builtin_fmaf(pz, jw, pw * jz)));
-            float t1[3], t2[3];
-            rotate(pw, px, py, pz, tb[0], tb[1], tb[2], t1);      // hinge position, parent frame -> world
-            rotate(qw, qx, qy, qz, tb[6], tb[7], tb[8], t2);      // body centre relative to the hinge
-            o[0] = (ppx + t1[0]) + t2[0];
-            o[kFkStride] = (ppy + t1[1]) + t2[1];
-            o[2 * kFkStride] = (ppz + t1[2]) + t2[2];
-            o[3 * kFkStride] = qw;
-            o[4 * kFkStride] = qx;
-            o[5 * kFkStride] = qy;
-            o[6 * kFkStride] = qz;
+    // ---- the tree, depth by depth
+    uint32_t begin = sk.depth_begin[1];
+    for (uint32_t d = 1; d < sk.depths; ++d) {
+        const uint32_t end = sk.depth_begin[d + 1];
+        uint32_t i = begin + wave;
+        SkeletonRecord t = sk.records[min(i, sk.K - 1u)];
+        __syncthreads();
+        while (i < end) {
+            hinge_pose(t, row);
+            i += kFkWaves;
+            if (i < end) t = sk.records[i];
         }
+        begin = end;
     }
     __syncthreads();
 
-    // coalesced store of the workgroup's contiguous output chunk (a batch of LDS reads, then the batch's stores)
-    {
-        const uint32_t row = sk.K * 7, n_o = nf * row;
-        const uint32_t magic = 0xFFFFFFFFu / row + 1u;
-        float* dst = poses + (size_t)f0 * row;
-        for (uint32_t base = 0; base < n_o; base += kFkLanes * kFkBatch) {
-            float t[kFkBatch];
-#pragma unroll
-            for (uint32_t u = 0; u < kFkBatch; ++u) {
-                const uint32_t i = min(base + u * kFkLanes + lane, n_o - 1u);
-                const uint32_t n = __umulhi(i, magic), j = i - n * row;
-                t[u] = pose[j * kFkStride + n];
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < kFkBatch; ++u) {
-                const uint32_t i = base + u * kFkLanes + lane;
-                if (i < n_o) dst[i] = t[u];
-            }
-        }
+    // ---- the workgroup's contiguous output chunk
+    const uint32_t n_o = nf * n_row;
+    float* dst = poses + (size_t)f0 * n_row;
+    if (stride == n_row && (reinterpret_cast<uintptr_t>(poses) & 15u) == 0u) {
+        // (no padding: LDS holds the chunk as it is.  A chunk starts 64 rows, a multiple of 16 bytes, after another.)
+        const uint32_t n_quads = n_o >> 2;
+        for (uint32_t i = threadIdx.x; i < n_quads; i += kFkThreads)
+            reinterpret_cast<float4*>(dst)[i] = reinterpret_cast<const float4*>(pose)[i];
+        const uint32_t i = (n_quads << 2) + threadIdx.x;
+        if (i < n_o) dst[i] = pose[i];
+    } else {
+        const uint32_t pad = stride - n_row;
+        const uint32_t magic = 0xFFFFFFFFu / n_row + 1u;  // (i / n_row by multiplication: i < 64 * n_row, rows of 7 floats and more)
+#pragma unroll 4
+        for (uint32_t i = threadIdx.x; i < n_o; i += kFkThreads) dst[i] = pose[i + pad * __umulhi(i, magic)];
     }
 }
 
 }  // namespace
 
-uint32_t fk_lds_bytes(const SkeletonConsts& sk) { return (sk.K * 7 + sk.J + sk.F * 7) * kFkStride * 4u; }
+uint32_t fk_lds_bytes(const SkeletonConsts& sk) { return kFkFrames * (sk.K * 7u | 1u) * 4u; }
 
 int prepare_fk_kernel(std::string& err) {
     const hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&fk_kernel),
@@ -192,8 +191,8 @@ int prepare_fk_kernel(std::string& err) {
 
 int launch_fk(const SkeletonConsts& sk, const float* d_free_poses, const float* d_angles, uint32_t n_frames,
               float* d_poses, void* stream, std::string& err) {
-    const uint32_t blocks = (n_frames + kFkLanes - 1) / kFkLanes;
-    hipLaunchKernelGGL(fk_kernel, dim3(blocks), dim3(kFkLanes), fk_lds_bytes(sk), reinterpret_cast<hipStream_t>(stream), sk,
+    const uint32_t blocks = (n_frames + kFkFrames - 1) / kFkFrames;
+    hipLaunchKernelGGL(fk_kernel, dim3(blocks), dim3(kFkThreads), fk_lds_bytes(sk), reinterpret_cast<hipStream_t>(stream), sk,
                        d_free_poses, d_angles, n_frames, d_poses);
     const hipError_t rc = hipGetLastError();
     if (rc != hipSuccess) {

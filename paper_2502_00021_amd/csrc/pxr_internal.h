@@ -96,11 +96,19 @@ struct DistractConsts {
 };
 
 // Skeleton bound by pxr_set_skeleton (device tables live in their own allocation).
+struct SkeletonRecord {
+    uint32_t body;    // index of the body in a frame's poses
+    int32_t parent;   // body it hangs from, -1 = free body
+    int32_t slot;     // free: index of its pose; hinged: index of its angle, -1 = rigid
+    float anchor[3];  // hinge position in the parent's frame
+    float axis[3];    // unit hinge axis
+    float offset[3];  // body centre relative to the hinge, body frame
+};
 struct SkeletonConsts {
-    uint32_t K, J, F;        // bodies, hinge angles per frame, free poses per frame
-    const int32_t* parent;   // [K]  -1 = free body
-    const int32_t* slot;     // [K]  free: index of its pose; hinged: index of its angle, -1 = rigid
-    const float* hinge;      // [K][9]  anchor (parent frame), unit axis, body centre relative to the hinge (body frame)
+    uint32_t K, J, F;                // bodies, hinge angles per frame, free poses per frame
+    uint32_t depths;                 // number of depths; depth 0 = the free bodies
+    const SkeletonRecord* records;   // [K], in order of depth
+    const uint32_t* depth_begin;     // [depths + 1] first record of each depth
 };
 
 // Host-side result of tessellation + camera derivation.

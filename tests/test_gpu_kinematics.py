@@ -207,6 +207,33 @@ def test_random_trees(torch, pxr, orc, seed):
     sc.close()
 
 
+@pytest.mark.parametrize("K", [1, 4, 5, 6, 17])  # odd rows leave LDS as they are, even ones carry padding
+@pytest.mark.parametrize("N", [1, 3, 64, 65, 127])
+def test_output_chunks_at_any_alignment(torch, pxr, orc, K, N):
+    """The same bits whether the poses start at a multiple of 16 bytes (wide stores, a remainder) or 4 bytes past one."""
+    rng = np.random.default_rng(100 * K + N)
+    skel = wl._skeleton(K)
+    skel["slot"][0] = 0
+    for k in range(1, K):  # depths of one, two and more than four bodies
+        wl._hinge(skel, k, parent=(k - 1) // 2 if k < 4 else 3, slot=k - 1, anchor=rng.uniform(-0.3, 0.3, 3),
+                  axis=wl.q_normalize(rng.standard_normal(3)), offset=rng.uniform(-0.3, 0.3, 3))
+    free = np.concatenate([rng.uniform(-1, 1, (N, 1, 3)), wl.random_quats(rng, (N, 1))], axis=-1).astype(np.float32)
+    ang = rng.uniform(-3, 3, (N, K - 1)).astype(np.float32)
+    sc = pxr.Scene(wl.default_scene(16, 16, [wl.sphere(0.05, (0.5, 0.5, 0.5), 3, 1) for _ in range(K)]))
+    sc.set_skeleton(skel, 1, K - 1)
+    tf, ta = torch.from_numpy(free).cuda(), torch.from_numpy(ang).cuda() if K > 1 else None
+    got = []
+    for skip in (0, 1):
+        room = torch.full((skip + N * K * 7 + 8,), 7.0, device="cuda")
+        out = room[skip:skip + N * K * 7].view(N, K, 7)
+        assert out.data_ptr() % 16 == 4 * skip
+        got.append(sc.pose_batch(tf, ta, poses=out).cpu().numpy())
+        assert bool((room[:skip] == 7.0).all()) and bool((room[skip + N * K * 7:] == 7.0).all())
+    assert np.array_equal(_bits(got[0]), _bits(got[1]))
+    assert_poses_close(got[0], orc.fk(skel, free, ang), skel)
+    sc.close()
+
+
 @pytest.mark.parametrize("cfg,B", [(2, 40), (3, 24), (4, 20), (5, 16)])
 def test_angles_to_frames_match_oracle(torch, pxr, orc, cfg, B):
     from test_gpu_parity import _bind, assert_parity
