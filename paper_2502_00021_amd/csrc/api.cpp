@@ -75,8 +75,7 @@ uint32_t pick_block_threads(const pxr::SceneConsts& sc) {
     const uint32_t groups_per_cu = (160u * 1024u) / (sc.lds_total ? sc.lds_total : 1u);
     if (groups_per_cu >= 8) return 256;
     if (groups_per_cu >= 3) return 512;
-    // the banded kernel variants need more than 64 registers: two groups of 768 threads then
-    if (groups_per_cu == 2 && sc.band_rows < sc.H) return 768;
+    if (groups_per_cu == 2 && sc.key_capacity && sc.npix < pxr::kWideWindowedFrom) return 768;
     return 1024;
 }
 
@@ -155,6 +154,7 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
     // the lanes of the kernel's set-up phase that take one row each.
     std::vector<float> body_dev(hs.body_const);
     for (const float* row : {hs.c.Rt, hs.c.Up, hs.c.Fw, hs.c.l}) body_dev.insert(body_dev.end(), row, row + 3);
+    body_dev.insert(body_dev.end(), hs.body_bound.begin(), hs.body_bound.end());
     Part parts[6] = {{vtmpl_dev.data(), vtmpl_dev.size() * 4, 0},
                      {hs.tri_idx.data(), hs.tri_idx.size() * 4, 0},
                      {hs.tri_shade.data(), hs.tri_shade.size() * 4, 0},

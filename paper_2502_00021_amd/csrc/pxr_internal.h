@@ -29,11 +29,22 @@ constexpr uint32_t kTinyMaxPixels = 3;
 constexpr uint32_t kSmallMaxPixels = 128;
 constexpr uint32_t kSmallLanesLog2 = 2;
 constexpr uint32_t kNoTriangle = 0xFFFFu;
-// Banded frames: a band picks the triangles that touch its rows out of the frame's bins in rounds of one per lane;
-// a round's lists therefore never hold more than the largest workgroup has lanes.
+// Windowed frames: a band picks the triangles that touch its rows out of the frame's bins in rounds of one per lane;
+// a round's lists therefore never hold more than the largest workgroup has lanes ...
 constexpr uint32_t kBandListEntries = 1024;
-// ... which pays from this many bands on; with fewer, every band walks all bins (lds_blist == 0).
-constexpr uint32_t kBandListsFrom = 6;
+// ... which pays if walking the bins for one band costs this many turns of a wavefront (a triangle of the large bin is a
+// turn, 16 small ones are one).  Humanoid and box, us per launch with 80 / 160 / 240 / 400: 256x256 141 / 139 / 139 / 139,
+// 384x384 142 / 142 / 147 / 147, 512x512 125 / 125 / 140 / 150; a mesh scene at 512x512 138 / 138 / 147 / 194.
+constexpr uint32_t kBandListsFrom = 160;
+// Windowed frames take half a compute unit's LDS (two workgroups cover each other's barriers) if that leaves room for this
+// share of the frame's keys, in per cent, and all of it otherwise (fewer bands).  us per launch, half / all, and the share
+// that half leaves: humanoid and box 128x128 157 / 201 (20 %), 160x160 142 / 151 (12), 192x192 150 / 145 (8.2), 256x256
+// 160 / 140 (4.3); a mesh scene 256x256 119 / 134 (11); quadrupeds 256x256 92 / 99 (7.7).
+constexpr uint32_t kHalfKeysFrom = 8;
+// ... and run 768 threads below this many pixels (two workgroups then have registers to spare), 1024 from there on (more
+// lanes for the pixels).  us per launch, 768 / 1024: 84x84 over a clip 418 / 450, 96x96 190 / 188, 128x128 156 / 157,
+// 160x160 144 / 142, 192x192 155 / 150, 256x256 180 / 166.
+constexpr uint32_t kWideWindowedFrom = 20000;
 
 // Per-body record kept in LDS for the duration of one frame (floats).
 //   [0..8]  M  = view rotation * body rotation, row-major
@@ -57,8 +68,11 @@ struct SceneConsts {
     uint32_t checker_short_form;  // cell == 1 and z_far <= 2^64: no division, and ground points of a frame whose eye is no NaN are no NaNs
     // sizes
     uint32_t W, H, npix, K, root, V, T, P;  // P = entries of the pair table (on the device: padded to a multiple of 64)
-    uint32_t band_rows;                     // rows of the frame held by the LDS key buffer at a time
-    uint32_t first_band_rows;               // rows of the first band (<= band_rows); later bands have band_rows
+    uint32_t key_capacity;                  // windowed frames: pixel keys that the LDS buffer holds; 0 = it holds the whole frame
+    uint32_t band_rows;                     // rows of the frame's full width that the key buffer holds at least
+    uint32_t first_band_rows;               // (the same: every band may have as many)
+    uint32_t pitch;                         // keys per row where the buffer holds the whole frame: W rounded up to a multiple of 4
+    uint32_t magic_groups;                  // ceil(2^32 / (pitch / 4)): g / (pitch / 4) == mulhi(g, magic_groups) for every group of four pixels
     uint32_t magicW;  // ceil(2^32 / W): p / W == mulhi(p, magicW) for every pixel index p < 512 * W
     // device tables
     const float* vtmpl;       // [V][4]  ux,uy,uz, bits = (LDS byte address of the body's record)<<2 | s as a 2-bit signed number
@@ -69,12 +83,13 @@ struct SceneConsts {
                               //         code of vertex q_i; the host-side table holds q_i itself): two triangles sharing the
                               //         edge q0-q2, or one triangle (q3 = q2, triB = kNoTriangle); the device copy ends with padding entries
     //         (no triangles; the four addresses are that of the word after the last vertex's code, which holds code 0)
-    const float* body_const;  // [K][8]  shape a,b,c,h ; rgb r,g,b,0   then, on the device, [4][3]: Rt, Up, Fw, l
+    const float* body_const;  // [K][8]  shape a,b,c,h ; rgb r,g,b,0   then, on the device, [4][3]: Rt, Up, Fw, l, and
+                              // [K][4]  largest |u_x|, |u_y|, |u_z| and |u| of the body's template vertices
     const float* cxcy;        // [W+H]   pixel-centre ray slopes
     // LDS carve-up (byte offsets into the dynamic segment)
     // the lds_keys region first holds the per-vertex cell codes (u32[V]) and the candidate list (u16[T])
     uint32_t lds_keys, lds_vxy, lds_vd, lds_body, lds_list, lds_large, lds_cxcy, lds_rows, lds_misc, lds_total;
-    uint32_t lds_blist, lds_blist2;  // banded frames: one band round's lists (kBandListEntries u16 each)
+    uint32_t lds_blist, lds_blist2;  // windowed frames: one band round's lists (kBandListEntries u16 each)
     uint32_t lds_vlut;  // video-blend tables (kVideoTableBytes), or 0 if the frame's LDS has no room for them
 };
 
@@ -119,6 +134,7 @@ struct HostScene {
     std::vector<float> tri_shade;
     std::vector<uint32_t> pair_tbl;
     std::vector<float> body_const;
+    std::vector<float> body_bound;
     std::vector<float> cxcy;
 };
 

@@ -31,6 +31,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "arith.h"
 #include "pxr_internal.h"
 
@@ -88,6 +90,12 @@ struct TriSetup {
     int i0, i1, j0, j1;
 };
 
+// The pixels the key buffer stands for: columns [x_lo, x_hi] and rows [y_lo, y_hi] of the frame, `pitch` keys per row.
+struct RasterWindow {
+    int x_lo, x_hi, y_lo, y_hi;
+    uint32_t pitch;
+};
+
 // Edge pq is "top-left" when it points up, or is horizontal pointing right
 // (y grows downwards): pixels exactly on it belong to the triangle.
 __device__ __forceinline__ int edge_bias(int dx, int dy) { return (dy < 0 || (dy == 0 && dx > 0)) ? 0 : -1; }
@@ -116,8 +124,8 @@ __device__ __forceinline__ long long emul<long long>(int a, int b) {
 // Edge functions carry their fill-rule bias and are stepped incrementally; a
 // pixel centre is covered when all three are >= 0.
 template <typename I>
-__device__ __forceinline__ void raster_rows(const TriSetup& s, uint32_t tri, uint32_t W, u64* keys, int r, int shift,
-                                            int row_lo, int c = 0, int cshift = 0) {
+__device__ __forceinline__ void raster_rows(const TriSetup& s, uint32_t tri, const RasterWindow& win, u64* keys, int r,
+                                            int shift, int c = 0, int cshift = 0) {
     int j = s.j0 + r;
     if (j > s.j1) return;
     const int dx_ab = s.bx - s.ax, dy_ab = s.by - s.ay;
@@ -134,7 +142,7 @@ __device__ __forceinline__ void raster_rows(const TriSetup& s, uint32_t tri, uin
     const I sy_ab = (I)dx_ab << (8 + shift), sy_bc = (I)dx_bc << (8 + shift), sy_ca = (I)dx_ca << (8 + shift);
     for (;;) {
         I e_ab = f_ab, e_bc = f_bc, e_ca = f_ca;
-        uint32_t pix = (uint32_t)(j - row_lo) * W + (uint32_t)(s.i0 + c);  // the key buffer holds rows from row_lo on
+        uint32_t pix = (uint32_t)(j - win.y_lo) * win.pitch + (uint32_t)(s.i0 + c - win.x_lo);
         for (int i = s.i0 + c; i <= s.i1; i += 1 << cshift, pix += 1u << cshift) {
             if ((e_ab | e_bc | e_ca) >= 0) {
                 const float beta = (float)(e_ca - b_ca) * invA, gamma = (float)(e_ab - b_ab) * invA;
@@ -162,12 +170,12 @@ __device__ __forceinline__ void wave_team(int n_rows, int lane, int& r, int& shi
     c = lane >> shift;
 }
 
-// Gather the snapped vertices of a triangle (ti = its entry of the index table) and its clamped pixel-centre range.
+// Gather the snapped vertices of a triangle (ti = its entry of the index table) and its pixel-centre range, clamped to the window.
 // Returns kTriNone if a vertex is unusable, all of them lie behind the near plane or no pixel centre is
 // inside the bounding box; kTriClip if the triangle straddles the near plane (nothing else is valid
 // then); kTriPlain otherwise.  `small_extent` = both fixed-point extents below 2^15.
 enum { kTriNone = 0, kTriPlain = 1, kTriClip = 2 };
-__device__ __forceinline__ int tri_gather(const SceneConsts& sc, const uint2 ti, const int2* vxy, TriSetup& s,
+__device__ __forceinline__ int tri_gather(const RasterWindow& win, const uint2 ti, const int2* vxy, TriSetup& s,
                                           uint32_t& v0, uint32_t& v1, uint32_t& v2, bool& small_extent) {
     v0 = ti.x & 0xFFFFu;
     v1 = ti.x >> 16;
@@ -188,23 +196,23 @@ __device__ __forceinline__ int tri_gather(const SceneConsts& sc, const uint2 ti,
     s.cy = (int)(uint32_t)(c >> 32);
     const int miny = imin3(s.ay, s.by, s.cy), maxy = imax3(s.ay, s.by, s.cy);
     // pixel centres sit at 256 i + 128: first centre >= min, last centre <= max
-    s.i0 = max(0, (minx + 127) >> 8);
-    s.i1 = min((int)sc.W - 1, (maxx - 128) >> 8);
-    s.j0 = max(0, (miny + 127) >> 8);
-    s.j1 = min((int)sc.H - 1, (maxy - 128) >> 8);
+    s.i0 = max(win.x_lo, (minx + 127) >> 8);
+    s.i1 = min(win.x_hi, (maxx - 128) >> 8);
+    s.j0 = max(win.y_lo, (miny + 127) >> 8);
+    s.j1 = min(win.y_hi, (maxy - 128) >> 8);
     small_extent = ((maxx - minx) | (maxy - miny)) < 32768;
     return (s.i0 <= s.i1 && s.j0 <= s.j1) ? kTriPlain : kTriNone;
 }
 
-// Which image rows a binned triangle can touch: kTriPlain with [j0, j1] (clamped to the image), or kTriClip for a
+// Which image rows a binned triangle can touch: kTriPlain with [j0, j1] (not clamped), or kTriClip for a
 // triangle that straddles the near plane (its snapped corners say nothing: it counts for every row).
-__device__ __forceinline__ int tri_rows(const SceneConsts& sc, const uint2 ti, const int2* vxy, int& j0, int& j1) {
+__device__ __forceinline__ int tri_rows(const uint2 ti, const int2* vxy, int& j0, int& j1) {
     const u64 a = reinterpret_cast<const u64*>(vxy)[ti.x & 0xFFFFu], b = reinterpret_cast<const u64*>(vxy)[ti.y & 0xFFFFu],
               c = reinterpret_cast<const u64*>(vxy)[ti.x >> 16];
     if (imin3((int)(uint32_t)a, (int)(uint32_t)b, (int)(uint32_t)c) <= kBehindX) return kTriClip;
     const int ay = (int)(uint32_t)(a >> 32), by = (int)(uint32_t)(b >> 32), cy = (int)(uint32_t)(c >> 32);
-    j0 = max(0, (imin3(ay, by, cy) + 127) >> 8);
-    j1 = min((int)sc.H - 1, (imax3(ay, by, cy) - 128) >> 8);
+    j0 = (imin3(ay, by, cy) + 127) >> 8;
+    j1 = (imax3(ay, by, cy) - 128) >> 8;
     return kTriPlain;
 }
 
@@ -228,18 +236,17 @@ __device__ __forceinline__ void view_position(const SceneConsts& sc, uint32_t v,
 }
 
 // One piece (a, b, c in screen order) of a clipped triangle, rastered by a whole wavefront.
-__device__ __forceinline__ void raster_piece(const SceneConsts& sc, uint32_t t, int ax, int ay, float Da, int bx, int by,
-                                             float Db, int cx, int cy, float Dc, bool usable, u64* keys, int lane,
-                                             int row_lo, int row_hi) {
+__device__ __forceinline__ void raster_piece(const RasterWindow& win, uint32_t t, int ax, int ay, float Da, int bx, int by,
+                                             float Db, int cx, int cy, float Dc, bool usable, u64* keys, int lane) {
     if (!usable) return;
     if (!((long long)(bx - ax) * (long long)(cy - ay) > (long long)(by - ay) * (long long)(cx - ax))) return;  // back face
     TriSetup s;
     s.ax = ax; s.ay = ay; s.bx = bx; s.by = by; s.cx = cx; s.cy = cy;
     const int minx = imin3(ax, bx, cx), maxx = imax3(ax, bx, cx), miny = imin3(ay, by, cy), maxy = imax3(ay, by, cy);
-    s.i0 = max(0, (minx + 127) >> 8);
-    s.i1 = min((int)sc.W - 1, (maxx - 128) >> 8);
-    s.j0 = max(max(0, (miny + 127) >> 8), row_lo);
-    s.j1 = min(min((int)sc.H - 1, (maxy - 128) >> 8), row_hi - 1);
+    s.i0 = max(win.x_lo, (minx + 127) >> 8);
+    s.i1 = min(win.x_hi, (maxx - 128) >> 8);
+    s.j0 = max(win.y_lo, (miny + 127) >> 8);
+    s.j1 = min(win.y_hi, (maxy - 128) >> 8);
     if (s.i0 > s.i1 || s.j0 > s.j1) return;
     s.Da = Da;
     s.dDb = Db - Da;
@@ -247,9 +254,9 @@ __device__ __forceinline__ void raster_piece(const SceneConsts& sc, uint32_t t, 
     int r, shift, c, cshift;
     wave_team(s.j1 - s.j0 + 1, lane, r, shift, c, cshift);
     if (((maxx - minx) | (maxy - miny)) < 32768)
-        raster_rows<int>(s, t, sc.W, keys, r, shift, row_lo, c, cshift);
+        raster_rows<int>(s, t, win, keys, r, shift, c, cshift);
     else
-        raster_rows<long long>(s, t, sc.W, keys, r, shift, row_lo, c, cshift);
+        raster_rows<long long>(s, t, win, keys, r, shift, c, cshift);
 }
 
 // A triangle with corners on both sides of the near plane (every lane of the wavefront computes the
@@ -264,8 +271,8 @@ __device__ __forceinline__ void raster_piece(const SceneConsts& sc, uint32_t t, 
 // code per corner (P << 2 | Q, P == Q for a kept vertex), four corners per pattern, patterns indexed by
 // the in-front mask (bit e = vertex e in front).  Corners are recomputed per piece rather than kept, so
 // that this rarely taken path does not raise the kernel's register count.
-__device__ __forceinline__ void raster_clipped(const SceneConsts& sc, uint32_t t, const int2* vxy,
-                                               const float* vd, u64* keys, int lane, int row_lo, int row_hi) {
+__device__ __forceinline__ void raster_clipped(const SceneConsts& sc, const RasterWindow& win, uint32_t t, const int2* vxy,
+                                               const float* vd, u64* keys, int lane) {
 #pragma unroll 1
     for (uint32_t piece = 0; piece < 2u; ++piece) {
         // everything is re-derived per piece so that nothing but `t` stays live across the raster loops
@@ -311,37 +318,34 @@ __device__ __forceinline__ void raster_clipped(const SceneConsts& sc, uint32_t t
                 cD[c] = sc.z_near * inv;
             }
         }
-        raster_piece(sc, t, cX[0], cY[0], cD[0], cX[1], cY[1], cD[1], cX[2], cY[2], cD[2], usable, keys, lane, row_lo, row_hi);
+        raster_piece(win, t, cX[0], cY[0], cD[0], cX[1], cY[1], cD[1], cX[2], cY[2], cD[2], usable, keys, lane);
     }
 }
 
-// Raster one binned triangle with lane `r` of the 2^shift lanes that share it, restricted to
-// the rows [row_lo, row_hi) that the key buffer currently holds.
+// Raster one binned triangle with lane `r` of the 2^shift lanes that share it, restricted to the window that the key
+// buffer currently holds.
 // MAY_CLIP: the bin (the wave-per-triangle one) also holds the triangles that straddle the near plane.
 template <bool MAY_CLIP>
-__device__ __forceinline__ void raster_binned(const SceneConsts& sc, uint32_t t, const uint2 ti,
-                                              const int2* vxy, const float* vd, u64* keys, int r, int shift, int row_lo,
-                                              int row_hi) {
+__device__ __forceinline__ void raster_binned(const SceneConsts& sc, const RasterWindow& win, uint32_t t, const uint2 ti,
+                                              const int2* vxy, const float* vd, u64* keys, int r, int shift) {
     TriSetup s;
     uint32_t v0, v1, v2;
     bool small_extent;
-    const int kind = tri_gather(sc, ti, vxy, s, v0, v1, v2, small_extent);
+    const int kind = tri_gather(win, ti, vxy, s, v0, v1, v2, small_extent);
     if (MAY_CLIP && kind == kTriClip) {
-        raster_clipped(sc, t, vxy, vd, keys, r, row_lo, row_hi);
+        raster_clipped(sc, win, t, vxy, vd, keys, r);
         return;
     }
-    s.j0 = max(s.j0, row_lo);
-    s.j1 = min(s.j1, row_hi - 1);
-    if (s.j0 > s.j1) return;
+    if (kind != kTriPlain) return;
     s.Da = vd[v0];
     s.dDb = vd[v2] - s.Da;
     s.dDc = vd[v1] - s.Da;
     int c = 0, cshift = 0;
     if (MAY_CLIP) wave_team(s.j1 - s.j0 + 1, r, r, shift, c, cshift);  // (the wave-per-triangle bin: r is the lane)
     if (small_extent)
-        raster_rows<int>(s, t, sc.W, keys, r, shift, row_lo, c, cshift);
+        raster_rows<int>(s, t, win, keys, r, shift, c, cshift);
     else
-        raster_rows<long long>(s, t, sc.W, keys, r, shift, row_lo, c, cshift);
+        raster_rows<long long>(s, t, win, keys, r, shift, c, cshift);
 }
 
 // Per-axis cell code of a snapped coordinate for an image of n pixels:
@@ -413,9 +417,18 @@ struct FrameUniforms {  // written in phase 0 (one lane) or by LDS atomics, read
     float base_col[3][3];     // background, ground grey 0, ground grey 1 after the colour distractor
     uint32_t base_packed[3];  // the same three, quantised: R | G<<8 | B<<16
     float eye[3];             // camera position (written by the first lane in phase 0 for phase 4)
-    uint32_t pad_;
-    u64 band_bins[2];         // banded frames: the three counters of one band round's lists, double-buffered by round
+    uint32_t ticket;          // windowed frames: next chunk of the pixels outside the window
+    u64 band_bins[2];         // windowed frames: the three counters of one band round's lists, double-buffered by round
+    uint32_t reach[4];        // windowed frames: columns [0], [1) and rows [2], [3) that the bodies can touch
+    // ... and the window made of them, in groups of four columns (written by one lane in phase 1):
+    uint32_t win_x0;          // first column (a multiple of 4)
+    uint32_t win_groups;      // groups per row of the window (2 or more)
+    uint32_t win_y0, win_rows;
+    uint32_t band_rows;       // rows of it that the key buffer holds at a time
+    uint32_t win_magic;       // ceil(2^32 / win_groups)
+    uint32_t side_magic;      // ceil(2^32 / groups of a row beside the window), 0 = none
 };
+static_assert(sizeof(FrameUniforms) <= 64 * 4, "the frame's uniforms have 256 bytes of LDS");
 
 // Everything phase 4 needs that is uniform over the frame.
 static_assert((offsetof(FrameUniforms, base_packed) + 4) % 8 == 0, "the first grey's word must be 8-byte aligned");
@@ -487,15 +500,14 @@ __device__ __forceinline__ uint32_t checker_cells(const SceneConsts& sc, const R
     return (uint32_t)(int)__builtin_floorf(wx / sc.cell) + (uint32_t)(int)__builtin_floorf(wy / sc.cell);
 }
 
-// DEFER_TRIANGLES: a triangle pixel returns 0 here; the caller shades it (compacted over the wavefront).
-template <bool UNIT_CELL, bool VIDEO, bool DEFER_TRIANGLES = false>
-__device__ __forceinline__ uint32_t resolve_pixel(const SceneConsts& sc, const ResolveCtx& rc, const float* body, u64 key,
-                                                  u64 gkey, float tg, float dwx, float dwy, uint32_t vbytes, uint32_t& low,
-                                                  u64& tri_lanes) {
+// (A triangle pixel returns 0: the caller shades it, compacted over the wavefront.)
+template <bool UNIT_CELL, bool VIDEO>
+__device__ __forceinline__ uint32_t resolve_pixel(const SceneConsts& sc, const ResolveCtx& rc, u64 key, u64 gkey, float tg,
+                                                  float dwx, float dwy, uint32_t vbytes, uint32_t& low, u64& tri_lanes) {
     key = key > gkey ? key : gkey;
     low = (uint32_t)key;
     tri_lanes = __ballot(low > 1u);  // (taken here, beside the branch on the same comparison, it costs nothing)
-    if (low > 1u) return DEFER_TRIANGLES ? 0u : shade_triangle<VIDEO>(sc, rc, body, 0xFFFFFFFFu - low);
+    if (low > 1u) return 0u;
     // background or ground: one of three colours per frame (consecutive in LDS: background, grey 0, grey 1)
     if (!VIDEO) {
         uint32_t word = rc.packed_addr;
@@ -520,19 +532,88 @@ __device__ __forceinline__ uint32_t resolve_pixel(const SceneConsts& sc, const R
     return rgb;
 }
 
-// Phase 4 for images whose width is a multiple of 4: four consecutive pixels of one row per
-// lane.  The row part of the ray is shared, and without camera roll (NO_ROLL: the right vector is
-// horizontal) so is the whole ground test, which then costs one division per lane, not four.
-template <int NT, bool UNIT_CELL, bool NO_ROLL, bool VIDEO, bool SELF_CLEAR>
-__device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const ResolveCtx& rc, const float* body,
-                                              const float* cxcy, const float4* rows, u64* keys, uint8_t* out,
-                                              uint32_t* out_ids, uint32_t tid, uint32_t p_begin, uint32_t p_end) {
-    // pixels [p_begin, p_end) of the frame; keys[0] belongs to pixel p_begin
+// The groups of four pixels that a call of resolve_groups takes.
+//   kWholeFrame     every group of the frame; the key buffer holds the frame
+//   kInsideWindow   the groups of the window's current band; the key buffer holds exactly these, in this order
+//   kBesideWindow   the groups that no triangle can touch (sky, ground, clip: no key is looked at), handed out in
+//                   chunks of 64 to whichever wavefront comes next
+enum ResolvePart { kWholeFrame = 0, kInsideWindow = 1, kBesideWindow = 2 };
+struct ResolveRange {
+    uint32_t x0, groups, magic;         // window: first column, groups per row, ceil(2^32 / groups)
+    uint32_t y0, rows;                  // its rows (inside: of the band)
+    uint32_t first_row, end_row;        // beside: rows of the frame this workgroup renders
+    uint32_t side_groups, side_magic;   // beside: groups of a row left and right of the window, ceil(2^32 / that) or 0
+    uint32_t* ticket;
+};
+
+// Phase 4: four consecutive pixels of one row (a group) per lane.  The row part of the ray is shared, and without camera
+// roll (NO_ROLL: the right vector is horizontal) so is the whole ground test, which then costs one division per image
+// row, not one per pixel.
+// RAGGED: the width is no multiple of 4.  A row's last group is then partial, and a group's twelve bytes start at any
+// byte: they leave as one unaligned 12-byte store, the last group's pixels byte by byte.  (One pixel per lane with byte
+// stores and a ground test with its division per pixel, which such widths took before: 11 840 quadruped frames of 71x71
+// with the colour distractor 254 us, now 201.)
+template <int NT, bool UNIT_CELL, bool NO_ROLL, bool VIDEO, bool RAGGED, ResolvePart PART>
+__device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const ResolveCtx& rc, const float* body,
+                                               const float* cxcy, const float4* rows, u64* keys, uint8_t* out,
+                                               uint32_t* out_ids, uint32_t tid, const ResolveRange& range) {
+    constexpr bool HAS_KEYS = PART != kBesideWindow;
     const uint32_t lane = tid & 63u;
-    for (uint32_t q = (p_begin >> 2) + tid; q * 4 < p_end; q += NT) {
-        const uint32_t p0 = q * 4;
-        const uint32_t j = __umulhi(p0, sc.magicW);
-        const uint32_t i0 = p0 - j * sc.W;
+    const uint32_t row_groups = (sc.W + 3u) >> 2;
+    // how many groups there are, and (beside the window) how many of them lie above it and left or right of it
+    uint32_t n_groups, n_above = 0, n_side = 0;
+    if (PART == kWholeFrame) {
+        n_groups = row_groups * sc.H;
+    } else if (PART == kInsideWindow) {
+        n_groups = range.groups * range.rows;
+    } else {
+        n_above = (range.y0 - range.first_row) * row_groups;
+        n_side = range.rows * range.side_groups;
+        n_groups = (range.end_row - range.first_row - range.rows) * row_groups + n_side;
+    }
+    uint32_t g = tid;
+    for (;;) {
+        if (PART == kBesideWindow) {
+            uint32_t chunk = 0;
+            if (lane == 0) chunk = atomicAdd(range.ticket, 1u);
+            g = ((uint32_t)__builtin_amdgcn_readfirstlane((int)chunk) << 6) + lane;
+            if (g - lane >= n_groups) return;
+            g = min(g, n_groups - 1u);  // (the last chunk's spare lanes repeat its last group: the same bytes)
+        } else if (g >= n_groups) {
+            return;
+        }
+        // ---- where the group lies: row j, first column i0, first pixel p0
+        uint32_t j, i0, p0;
+        if (PART == kWholeFrame && !RAGGED) {
+            p0 = g * 4u;
+            j = __umulhi(p0, sc.magicW);
+            i0 = p0 - j * sc.W;
+        } else if (PART == kInsideWindow) {
+            const uint32_t r = __umulhi(g, range.magic);
+            j = range.y0 + r;
+            i0 = range.x0 + (g - r * range.groups) * 4u;
+            p0 = j * sc.W + i0;
+        } else {
+            uint32_t c;
+            const uint32_t m = g - n_above;
+            if (PART == kBesideWindow && m < n_side) {  // (above the window m wraps round and is not below)
+                uint32_t r = range.side_magic ? __umulhi(m, range.side_magic) : 0u;
+                c = m - r * range.side_groups;
+                c += c * 4u >= range.x0 ? range.groups : 0u;
+                j = range.y0 + r;
+            } else {
+                uint32_t q = g;
+                if (PART == kBesideWindow) {
+                    q += range.first_row * row_groups;
+                    if (g >= n_above) q += range.rows * range.groups;  // below: the window's groups lie in between
+                }
+                j = __umulhi(q, sc.magic_groups);
+                c = q - j * row_groups;
+            }
+            i0 = c * 4u;
+            p0 = j * sc.W + i0;
+        }
+        const bool whole = !RAGGED || i0 + 4u <= sc.W;  // all four pixels exist
         // what is shared by a row's pixels was worked out once per row in phase 0
         const float4 row = rows[j];
         const float rx = row.x, ry = row.y;
@@ -541,10 +622,25 @@ __device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const Resol
         const float cxs[4] = {cx4.x, cx4.y, cx4.z, cx4.w};
         uint32_t vid[3] = {0u, 0u, 0u};
         if (VIDEO) {
-            const uint32_t* vsrc = reinterpret_cast<const uint32_t*>(rc.vframe) + q * 3;
-            vid[0] = vsrc[0];
-            vid[1] = vsrc[1];
-            vid[2] = vsrc[2];
+            if (!RAGGED) {
+                const uint32_t* vsrc = reinterpret_cast<const uint32_t*>(rc.vframe) + (p0 >> 2) * 3u;
+                vid[0] = vsrc[0];
+                vid[1] = vsrc[1];
+                vid[2] = vsrc[2];
+            } else {
+                const uint8_t* vsrc = rc.vframe + p0 * 3u;
+                if (whole) {
+                    __builtin_memcpy(vid, vsrc, 12);
+                } else {
+                    const uint32_t n_bytes = (sc.W - i0) * 3u;  // 3, 6 or 9
+                    for (uint32_t b = 0; b < n_bytes; ++b) {
+                        const uint32_t v = (uint32_t)vsrc[b] << (8u * (b & 3u));
+                        vid[0] |= b < 4u ? v : 0u;
+                        vid[1] |= b >= 4u && b < 8u ? v : 0u;
+                        vid[2] |= b >= 8u ? v : 0u;
+                    }
+                }
+            }
         }
         const uint32_t vb[4] = {vid[0] & 0xFFFFFFu, (vid[0] >> 24) | ((vid[1] & 0xFFFFu) << 8),
                                 (vid[1] >> 16) | ((vid[2] & 0xFFu) << 16), vid[2] >> 8};
@@ -553,12 +649,19 @@ __device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const Resol
         // (a miss has depth bits 0 in the table: the key is 0 then)
         const u64 gkey_row = NO_ROLL ? (((u64)__float_as_uint(row.w) << 32) | (tg_row != 0.0f ? 1ull : 0ull)) : 0ull;
         // the lane's four keys are 32 contiguous, aligned bytes: two 16-byte LDS reads
-        const uint4 k01 = reinterpret_cast<const uint4*>(keys + (p0 - p_begin))[0], k23 = reinterpret_cast<const uint4*>(keys + (p0 - p_begin))[1];
-        const u64 key4[4] = {((u64)k01.y << 32) | k01.x, ((u64)k01.w << 32) | k01.z, ((u64)k23.y << 32) | k23.x, ((u64)k23.w << 32) | k23.z};
+        u64 key4[4] = {0ull, 0ull, 0ull, 0ull};
+        u64* own_keys = keys + g * 4u;
+        if (HAS_KEYS) {
+            const uint4 k01 = reinterpret_cast<const uint4*>(own_keys)[0], k23 = reinterpret_cast<const uint4*>(own_keys)[1];
+            key4[0] = ((u64)k01.y << 32) | k01.x;
+            key4[1] = ((u64)k01.w << 32) | k01.z;
+            key4[2] = ((u64)k23.y << 32) | k23.x;
+            key4[3] = ((u64)k23.w << 32) | k23.z;
+        }
         uint32_t rgb[4] = {0u, 0u, 0u, 0u}, low[4];
         uint32_t ow[3] = {0u, 0u, 0u};  // the 12 bytes that leave
         bool direct = false;            // they were put together as they were looked up (rgb[] is not used)
-        u64 tri_lanes[4];
+        u64 tri_lanes[4] = {0ull, 0ull, 0ull, 0ull};
         if (!VIDEO) {
             // One of the frame's three colours (background, two greys: consecutive words in LDS), without a branch
             // per pixel.  A triangle pixel picks up one of them as well, to be overwritten below.  Without roll a
@@ -574,9 +677,9 @@ __device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const Resol
                 float tg = tg_row;
                 u64 gkey = gkey_row;
                 if (!NO_ROLL) gkey = ground_key(sc, rc, -__builtin_fmaf(sc.Rt[2], cxs[k], rz), tg);
-                const u64 key = key4[k] > gkey ? key4[k] : gkey;
+                const u64 key = HAS_KEYS && key4[k] > gkey ? key4[k] : gkey;
                 low[k] = (uint32_t)key;
-                tri_lanes[k] = __ballot(low[k] > 1u);
+                if (HAS_KEYS) tri_lanes[k] = __ballot(low[k] > 1u);
                 uint32_t word = lane_word;
                 if (ground_in_sight) {
                     const float dwx = __builtin_fmaf(sc.Rt[0], cxs[k], rx);
@@ -602,9 +705,9 @@ __device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const Resol
             uint32_t base[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const u64 key = key4[k] > gkey_row ? key4[k] : gkey_row;
+                const u64 key = HAS_KEYS && key4[k] > gkey_row ? key4[k] : gkey_row;
                 low[k] = (uint32_t)key;
-                tri_lanes[k] = __ballot(low[k] > 1u);
+                if (HAS_KEYS) tri_lanes[k] = __ballot(low[k] > 1u);
                 const float dwx = __builtin_fmaf(sc.Rt[0], cxs[k], rx);
                 const float dwy = __builtin_fmaf(sc.Rt[1], cxs[k], ry);
                 uint32_t odd = checker_cells<UNIT_CELL>(sc, rc, tg_row, dwx, dwy) & 1u;
@@ -630,15 +733,15 @@ __device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const Resol
                 if (!NO_ROLL) gkey = ground_key(sc, rc, -__builtin_fmaf(sc.Rt[2], cxs[k], rz), tg);
                 const float dwx = __builtin_fmaf(sc.Rt[0], cxs[k], rx);
                 const float dwy = __builtin_fmaf(sc.Rt[1], cxs[k], ry);
-                rgb[k] = resolve_pixel<UNIT_CELL, VIDEO, true>(sc, rc, body, key4[k], gkey, tg, dwx, dwy, vb[k], low[k], tri_lanes[k]);
+                rgb[k] = resolve_pixel<UNIT_CELL, VIDEO>(sc, rc, key4[k], gkey, tg, dwx, dwy, vb[k], low[k], tri_lanes[k]);
             }
         }
         // Triangle pixels are few and clustered: instead of every lane walking the shading code four
         // times, the wavefront compacts its triangle pixels into a list (in the LDS of its own, already
         // consumed, pixel keys), shades the list densely, and the owners pick their colours up.
         const u64 m0 = tri_lanes[0], m1 = tri_lanes[1], m2 = tri_lanes[2], m3 = tri_lanes[3];
-        if (m0 | m1 | m2 | m3) {
-            uint32_t* list = reinterpret_cast<uint32_t*>(keys + ((q - lane) * 4 - p_begin));  // 256 keys = 512 words
+        if (HAS_KEYS && (m0 | m1 | m2 | m3)) {
+            uint32_t* list = reinterpret_cast<uint32_t*>(keys + (g - lane) * 4u);  // 256 keys = 512 words
             const uint32_t n0 = (uint32_t)__popcll(m0), n1 = n0 + (uint32_t)__popcll(m1), n2 = n1 + (uint32_t)__popcll(m2);
             const uint32_t total = n2 + (uint32_t)__popcll(m3);
             const uint32_t slot[4] = {lanes_below(m0), n0 + lanes_below(m1), n1 + lanes_below(m2), n2 + lanes_below(m3)};
@@ -671,33 +774,156 @@ __device__ __forceinline__ void resolve_rows4(const SceneConsts& sc, const Resol
                 if (low[3] > 1u) ow[2] = (ow[2] & 0x000000FFu) | (rgb[3] << 8);
             }
         }
-        if (SELF_CLEAR) {
-            // banded frames: the lane leaves its four keys cleared for the next band (nobody else touches them)
-            reinterpret_cast<uint4*>(keys + (p0 - p_begin))[0] = make_uint4(0u, 0u, 0u, 0u);
-            reinterpret_cast<uint4*>(keys + (p0 - p_begin))[1] = make_uint4(0u, 0u, 0u, 0u);
+        if (PART == kInsideWindow) {
+            // the lane leaves its four keys cleared for the next band (nobody else touches them)
+            reinterpret_cast<uint4*>(own_keys)[0] = make_uint4(0u, 0u, 0u, 0u);
+            reinterpret_cast<uint4*>(own_keys)[1] = make_uint4(0u, 0u, 0u, 0u);
         }
         if (!(VIDEO && direct)) {
             ow[0] = rgb[0] | (rgb[1] << 24);
             ow[1] = (rgb[1] >> 8) | (rgb[2] << 16);
             ow[2] = (rgb[2] >> 16) | (rgb[3] << 8);
         }
-        struct alignas(4) U3 {
-            uint32_t a, b, c;
-        };
-        *reinterpret_cast<U3*>(reinterpret_cast<uint32_t*>(out) + q * 3) = U3{ow[0], ow[1], ow[2]};
-        if (out_ids)
-            reinterpret_cast<uint4*>(out_ids)[q] =
-                make_uint4(0xFFFFFFFFu - low[0], 0xFFFFFFFFu - low[1], 0xFFFFFFFFu - low[2], 0xFFFFFFFFu - low[3]);
+        if (!RAGGED) {
+            struct alignas(4) U3 {
+                uint32_t a, b, c;
+            };
+            *reinterpret_cast<U3*>(reinterpret_cast<uint32_t*>(out) + (p0 >> 2) * 3u) = U3{ow[0], ow[1], ow[2]};
+            if (out_ids)
+                reinterpret_cast<uint4*>(out_ids)[p0 >> 2] =
+                    make_uint4(0xFFFFFFFFu - low[0], 0xFFFFFFFFu - low[1], 0xFFFFFFFFu - low[2], 0xFFFFFFFFu - low[3]);
+        } else {
+            uint8_t* dst = out + p0 * 3u;
+            if (whole) {
+                __builtin_memcpy(dst, ow, 12);
+            } else {
+#pragma unroll
+                for (uint32_t b = 0; b < 9u; ++b)
+                    if (b < (sc.W - i0) * 3u) dst[b] = (uint8_t)(ow[b >> 2] >> (8u * (b & 3u)));
+            }
+            if (out_ids) {
+#pragma unroll
+                for (uint32_t k = 0; k < 4u; ++k)
+                    if (k == 0u || i0 + k < sc.W) out_ids[p0 + k] = 0xFFFFFFFFu - low[k];
+            }
+        }
+        if (PART != kBesideWindow) g += NT;
     }
+}
+
+// The value of another lane of the same four (quad permutation: lane i of the four gets lane (SEL >> 2 i) & 3's).
+template <int SEL>
+__device__ __forceinline__ float from_quad(float x) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), SEL, 0xF, 0xF, true));
+}
+
+// Which pixels of the frame the bodies can touch, as a bound that errs outwards (one wavefront; four lanes per body,
+// lanes 0 to 2 of the four take an axis each).
+//
+// Posed template points have view-space coordinates t_i + sum_c M_ic shape_c u_c + M_i2 shape_3 s with |u_c| <= bound_c,
+// |u| <= bound_3 and |s| <= 1, so they lie within t_i +- e_i, e_i = the smaller of sum_c |M_ic shape_c| bound_c and
+// bound_3 |(M_ic shape_c)_c|, plus |M_i2 shape_3|.  (M is whatever the pose's quaternion makes of it, unit or not.)
+// Rounding, here (hardware reciprocals and square roots: 1 ulp) and where the vertices are computed, is below 2^-20 of the
+// terms' magnitudes: e_i is widened by 2^-18 of them.  If the box lies in front of the near plane as a whole, its
+// projection lies between the extremes of x / z over it; one pixel is added on each side for the projection's own
+// rounding (2^-20 of at most 512 pixels) and for the distance from a coordinate to the next pixel centre.  In every other
+// case - the box reaches the near plane, or something is not a number - every pixel counts; a box behind the plane as a
+// whole shows nothing.
+__device__ __forceinline__ void add_reach(const SceneConsts& sc, const float* body, uint32_t* reach, uint32_t lane) {
+    const uint32_t axis = lane & 3u;
+    for (uint32_t k0 = 0; k0 < sc.K; k0 += 16u) {
+        const uint32_t k = k0 + (lane >> 2);
+        const uint32_t i = min(axis, 2u);
+        const float* record = body + min(k, sc.K - 1u) * kBodyStride;
+        const float4 bound = reinterpret_cast<const float4*>(sc.body_const + sc.K * 8u + 12u)[min(k, sc.K - 1u)];
+        const float t = record[9u + i], m2 = __builtin_fabsf(record[3u * i + 2u]);
+        const float p = __builtin_fabsf(record[3u * i] * record[16]), q = __builtin_fabsf(record[3u * i + 1u] * record[17]);
+        const float r = __builtin_fabsf(m2 * record[18]);
+        const float sum = p * bound.x + q * bound.y + r * bound.z;
+        const float ball = bound.w * __builtin_amdgcn_sqrtf(p * p + q * q + r * r);
+        float e = ball >= 0x1p-40f && ball < sum ? ball : sum;  // (tiny squares may vanish: not below 2^-40)
+        e += __builtin_fabsf(m2 * record[19]);
+        e += 0x1p-18f * (e + sum + __builtin_fabsf(t));
+        const float lo = t - e, hi = t + e;
+        const float z_lo = from_quad<0xAA>(lo), z_hi = from_quad<0xAA>(hi);
+        const float near_inv = __builtin_amdgcn_rcpf(z_lo), far_inv = __builtin_amdgcn_rcpf(z_hi);
+        // lane 0: columns, lane 1: rows (the y axis points up)
+        const float side = axis == 0u ? lo : -hi, other = axis == 0u ? hi : -lo, half = axis == 0u ? sc.halfW : sc.halfH;
+        const float first = __builtin_fmaf(sc.f, side * (side > 0.0f ? far_inv : near_inv), half);
+        const float last = __builtin_fmaf(sc.f, other * (other > 0.0f ? near_inv : far_inv), half);
+        const uint32_t n = axis == 0u ? sc.W : sc.H;
+        uint32_t begin = 0u, end = n;
+        const bool bounded = z_lo > sc.z_near && first <= last;  // (of this axis; not if anything is not a number)
+        if (bounded) {
+            begin = (uint32_t)__builtin_fminf(__builtin_fmaxf(first - 1.0f, 0.0f), 512.0f);
+            end = min((uint32_t)__builtin_fminf(__builtin_fmaxf(last + 2.0f, 0.0f), 512.0f), n);
+        }
+        const bool hidden = z_hi < sc.z_near;
+        if (k < sc.K && axis < 2u && !hidden) {
+            atomicMin(&reach[2u * axis], begin);
+            atomicMax(&reach[2u * axis + 1u], end);
+        }
+    }
+}
+
+// The frame's window from the bodies' reach, and how many of its rows the key buffer holds at a time (one wavefront; the
+// reach's begin may lie past its end: nothing to be seen).
+__device__ __forceinline__ void make_window(const SceneConsts& sc, FrameUniforms* fu, uint32_t first_row, uint32_t end_row,
+                                            uint32_t lane) {
+    const uint32_t row_groups = (sc.W + 3u) >> 2;
+    const uint32_t x0 = fu->reach[0], x1 = fu->reach[1];
+    uint32_t g0 = x0 >> 2, g1 = min((x1 + 3u) >> 2, row_groups);
+    uint32_t y0 = max(fu->reach[2], first_row), y1 = min(fu->reach[3], end_row);
+    if (x0 >= x1 || y0 >= y1) {
+        g0 = 0u;
+        g1 = 2u;
+        y0 = y1 = first_row;
+    }
+    if (g1 - g0 < 2u) {  // (two groups or more, so that the magic number below exists; frames have two or more)
+        g0 = min(g0, row_groups - 2u);
+        g1 = g0 + 2u;
+    }
+    if (g1 - g0 + 1u == row_groups) {  // (likewise beside the window: none or two and more)
+        g0 = 0u;
+        g1 = row_groups;
+    }
+    const uint32_t groups = g1 - g0, side = row_groups - groups, rows = y1 - y0;
+    // one division, three lanes: ceil(2^32 / groups), ceil(2^32 / side), rows that the buffer holds (at least one)
+    const uint32_t of = lane == 2u ? sc.key_capacity : 0xFFFFFFFFu, by = lane == 0u ? groups : (lane == 1u ? max(side, 1u) : groups * 4u);
+    const uint32_t quotient = of / by;
+    const uint32_t held = (uint32_t)__builtin_amdgcn_readlane((int)quotient, 2);
+    uint32_t band_rows = rows;
+    if (rows > held) {  // even bands
+        const uint32_t bands = (rows + held - 1u) / held;
+        band_rows = (rows + bands - 1u) / bands;
+    }
+    if (lane == 0u) {
+        fu->win_x0 = g0 * 4u;
+        fu->win_groups = groups;
+        fu->win_y0 = y0;
+        fu->win_rows = rows;
+        fu->band_rows = band_rows;
+        fu->win_magic = quotient + 1u;
+    }
+    if (lane == 1u) fu->side_magic = side ? quotient + 1u : 0u;
 }
 
 // Register budget: two 80 KB workgroups share a compute unit, so 1024-thread groups need all
 // 8 wave slots per SIMD (<= 64 VGPRs); the smaller groups may use more registers.
-// BANDED: the key buffer holds only `band_rows` rows at a time and phases 3-4 loop over bands.
-template <int NT, int PX, bool BANDED, bool VIDEO>
+// RAGGED: the width is no multiple of 4 (resolve_groups).
+// WINDOWED: the key buffer does not hold the frame but the part of it that the bodies can touch (its window, found per
+// frame in phase 1), a band of rows at a time if need be; the other pixels need no keys at all and are resolved by
+// whichever wavefronts are done with the raster phase first.  The bodies of the articulated scenes touch 7 to 17 % of a
+// frame, so most windows fit in one piece where the whole frame took two to five bands, each a walk over all binned
+// triangles and three barriers.  Against bands of whole rows: 16 384 humanoid frames of 84x84 over a clip 493 -> 415 us,
+// 1024 humanoid-and-box frames of 256x256 242 -> 163 us, 3648 of 128x128 237 -> 157 us, quadrupeds of 256x256 184 -> 100 us.
+// Frames whose keys fit as a whole beside a second workgroup (64x64) do not take it: the same number of instructions, and
+// the few wavefronts that get the window's pixels shade them all (65 536 x 3 frames 3.53 -> 3.81 ms).
+// 1 << slabs_log2 workgroups share a windowed frame, each takes a run of its rows (and repeats the geometry).
+template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ? 8 : (NT >= 768 ? 6 : 4)))) void render_kernel(
     const SceneConsts sc, const DistractConsts dc, const float* __restrict__ poses, const float* __restrict__ shapes,
-    uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids) {
+    uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2) {
     extern __shared__ __align__(16) unsigned char lds[];
     // the key buffer's LDS holds the cell codes and the candidate list until the keys are cleared
     uint32_t* vm = reinterpret_cast<uint32_t*>(lds + sc.lds_keys);
@@ -713,7 +939,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
 
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
-    const uint32_t frame = frame_of_block(blockIdx.x, gridDim.x);
+    const uint32_t block = frame_of_block(blockIdx.x, gridDim.x);
+    const uint32_t frame = WINDOWED ? block >> slabs_log2 : block;
     const uint32_t e = frame / S;
     const uint32_t step = step0 + (frame - e * S);
     const uint32_t env = env0 + e;
@@ -828,7 +1055,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     if (tid == kDrawLane) {
         fu->bins = 0ull;
         fu->n_cand = 0;
-        if (BANDED) fu->band_bins[0] = fu->band_bins[1] = 0ull;
+        if (WINDOWED) {
+            fu->band_bins[0] = fu->band_bins[1] = 0ull;
+            fu->ticket = 0u;
+            fu->reach[0] = fu->reach[2] = 0xFFFFFFFFu;
+            fu->reach[1] = fu->reach[3] = 0u;
+        }
         if (VIDEO) {
             uint32_t first;
             if (dc.env_offset) {
@@ -912,6 +1144,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
 
     // ---- phase 1: instancing + projection + snap + cell code (one lane per template vertex)
     const bool recip_long_form = !(sc.z_near >= kRecipMin);
+    if (WINDOWED && tid >= NT - 64u) {
+        // what the bodies can touch, by the last wavefront (the vertices of most scenes give it a trip less)
+        add_reach(sc, body, fu->reach, lane);
+    }
     if (tid == NT - 1) vm[sc.V] = 0u;  // the code that the padding of the pair table points at: no pixel centre on either axis
     for (uint32_t v = tid; v < sc.V; v += NT) {
         float pvx, pvy, pvz;
@@ -995,11 +1231,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // ---- phase 2b: exact binning, one lane per candidate triangle: reject, area sign, pixel range,
     // then one of three bins by the number of candidate pixel centres (one packed LDS atomic per wave).
     const uint32_t n_cand = fu->n_cand;
+    // (the whole frame, or its columns and this workgroup's rows)
+    RasterWindow image = {0, (int)sc.W - 1, 0, (int)sc.H - 1, sc.pitch};
+    if (WINDOWED) {
+        const uint32_t slab = block & ((1u << slabs_log2) - 1u);
+        image.y_lo = (int)((slab * sc.H) >> slabs_log2);
+        image.y_hi = (int)(((slab + 1u) * sc.H) >> slabs_log2) - 1;
+    }
     // (Where the candidates take several trips - smaller workgroups, taller frames - a lane's candidate and its entry
     // of the index table are requested a trip ahead, without a branch: a lane past the end reads a list entry that
-    // nobody wrote and clamps it into the table.  The 1024-thread unbanded kernel sees its ~900 candidates in one trip
+    // nobody wrote and clamps it into the table.  The 1024-thread whole-frame kernel sees its ~900 candidates in one trip
     // and is bound by instruction issue: it keeps the plain form.)
-    constexpr bool kAhead = NT < 1024 || BANDED;
+    constexpr bool kAhead = NT < 1024 || WINDOWED;
     uint32_t t_ahead = 0;
     uint2 ti_ahead = make_uint2(0u, 0u);
     if (kAhead) {
@@ -1024,7 +1267,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             TriSetup s;
             uint32_t v0, v1, v2;
             bool small_extent;
-            const int kind = tri_gather(sc, ti, vxy, s, v0, v1, v2, small_extent);
+            const int kind = tri_gather(image, ti, vxy, s, v0, v1, v2, small_extent);
             if (kind == kTriClip) cls = 3;  // clipped, then rastered, by a whole wavefront
             if (kind == kTriPlain) {
                 bool front;
@@ -1051,21 +1294,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             if (cls == 3) list2[old_hi + lanes_below(m3)] = (uint16_t)t;
         }
     }
+    // (the frame's window, made of what was found in phase 1: the last wavefront has the fewest candidates)
+    if (WINDOWED && tid >= NT - 64u) make_window(sc, fu, (uint32_t)image.y_lo, (uint32_t)image.y_hi + 1u, lane);
     PXR_TIMED_BARRIER(3);
     PXR_PHASE_MARK(3);
 
-    // Tall frames are rendered in horizontal bands so that the key buffer stays small enough for two
-    // workgroups per compute unit; geometry work (phases 0-2) is done once, raster and resolve per band.
-    uint32_t row_lo = 0;
-    uint32_t band_round = 0;  // banded frames: rounds of the band-list builder so far (picks the counter slot)
+    // Windowed frames whose window does not fit the key buffer are rendered a band of its rows at a time: geometry
+    // work (phases 0-2) is done once, raster and resolve per band.
+    uint32_t bands_done = 0;
+    uint32_t band_round = 0;  // rounds of the band-list builder so far (picks the counter slot)
     const uint32_t tid_kept = tid;
+    bool more_bands;
     do {
-        const SceneConsts& scb = BANDED ? argument_reloaded<SceneConsts>(kSceneArgAt) : sc;
-        const DistractConsts& dcb = BANDED ? argument_reloaded<DistractConsts>(kDistractArgAt) : dc;
+        const SceneConsts& scb = WINDOWED ? argument_reloaded<SceneConsts>(kSceneArgAt) : sc;
+        const DistractConsts& dcb = WINDOWED ? argument_reloaded<DistractConsts>(kDistractArgAt) : dc;
         // (In the band loop everything is derived again from the reloaded arguments and from a thread index the
-        // compiler cannot see through: nothing but the row counter and the index stays live from band to band.)
+        // compiler cannot see through: nothing but the band counter and the index stays live from band to band.)
         uint32_t tid = tid_kept;
-        if (BANDED) asm volatile("" : "+v"(tid));
+        if (WINDOWED) asm volatile("" : "+v"(tid));
         const uint32_t lane = tid & 63u;
         u64* keys = reinterpret_cast<u64*>(lds + scb.lds_keys);
         int2* vxy = reinterpret_cast<int2*>(lds + scb.lds_vxy);
@@ -1076,15 +1322,78 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         FrameUniforms* fu = reinterpret_cast<FrameUniforms*>(lds + scb.lds_misc);
         uint16_t* list = reinterpret_cast<uint16_t*>(lds + scb.lds_list);
         uint16_t* list2 = reinterpret_cast<uint16_t*>(lds + scb.lds_large);
-        const uint32_t row_hi = BANDED ? min(scb.H, row_lo + (row_lo ? scb.band_rows : scb.first_band_rows)) : scb.H;
-        const uint32_t p_begin = row_lo * scb.W, p_end = row_hi * scb.W;
-        // keys to clear before the first band: all the buffer holds (a later band may be taller than the first, and
-        // every lane only leaves the keys it resolved cleared)
-        const uint32_t n_keys = BANDED ? scb.band_rows * scb.W : p_end - p_begin;
-        if (!BANDED || scb.lds_blist == 0) {
-            // Unbanded frames, and frames of a few bands (every band walks all bins: cheaper than picking a band's
-            // triangles out while a triangle's rows are looked at by two or three bands only).
-            if (BANDED && row_lo) __syncthreads();  // the previous band is resolved (its lanes left their keys cleared)
+        RasterWindow win = {0, (int)scb.W - 1, 0, (int)scb.H - 1, scb.pitch};
+        ResolveRange range = {};
+        uint32_t n_keys = scb.pitch * scb.H;
+        bool by_lists = false;
+        if (WINDOWED) {
+            const auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+            range.x0 = uniform(fu->win_x0);
+            range.groups = uniform(fu->win_groups);
+            range.magic = uniform(fu->win_magic);
+            const uint32_t y0 = uniform(fu->win_y0), n_rows = uniform(fu->win_rows), held = uniform(fu->band_rows);
+            range.y0 = y0 + bands_done * held;
+            range.rows = min(held, n_rows - bands_done * held);
+            more_bands = (bands_done + 1u) * held < n_rows;
+            win.pitch = range.groups * 4u;
+            win.x_lo = (int)range.x0;
+            win.x_hi = (int)min(range.x0 + win.pitch, scb.W) - 1;
+            win.y_lo = (int)range.y0;
+            win.y_hi = (int)(range.y0 + range.rows) - 1;
+            n_keys = win.pitch * held;
+            const u64 bins = fu->bins;
+            by_lists = scb.lds_blist != 0 && n_rows > held &&
+                       uniform((uint32_t)(bins >> 32) + (((uint32_t)bins >> 16) >> (6u - kSmallLanesLog2))) >= kBandListsFrom;
+        } else {
+            more_bands = false;
+        }
+        const auto resolve = [&](auto part, const ResolveRange& r) {
+            constexpr ResolvePart PART = decltype(part)::value;
+            ResolveCtx rc;
+            const float eye_x = fu->eye[0], eye_y = fu->eye[1], eye_z = fu->eye[2];
+            rc.eye_x = eye_x;
+            rc.eye_y = eye_y;
+            rc.eye_z = eye_z;
+            const bool no_roll = scb.Rt[2] == 0.0f;
+            rc.inv_ez = 0.0f;
+            if (!no_roll) {  // (without roll the row table already holds the ground test)
+                asm volatile("" ::: "memory");  // (a branch, not a select: the compiler would do the division either way)
+                rc.inv_ez = 1.0f / eye_z;
+            }
+            rc.ground_ok = scb.ground_on && eye_z > 0.0f;
+            rc.mode = dcb.mode;
+            rc.alpha = dcb.alpha;
+            rc.vframe = nullptr;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                rc.scale[c] = fu->scale[c];
+                rc.offs[c] = fu->offs[c];
+            }
+            rc.col_addr = scb.lds_misc + (uint32_t)offsetof(FrameUniforms, base_col);
+            rc.packed_addr = scb.lds_misc + (uint32_t)offsetof(FrameUniforms, base_packed);
+            rc.vlut = scb.lds_vlut;
+            if (VIDEO) rc.vframe = dcb.video + (size_t)fu->video_frame * scb.npix * 3;
+            uint8_t* out = frames + (size_t)frame * scb.npix * 3;
+            uint32_t* out_ids = ids ? ids + (size_t)frame * scb.npix : nullptr;
+            // uniform scene properties select a specialised loop (kept out of the per-pixel code)
+            // (an eye that is a NaN makes ground points NaNs: such a frame takes the general loop, which is exact
+            // for a unit cell as well)
+            if (scb.checker_short_form && eye_x == eye_x && eye_y == eye_y) {
+                if (no_roll)
+                    resolve_groups<NT, true, true, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                else
+                    resolve_groups<NT, true, false, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+            } else {
+                if (no_roll)
+                    resolve_groups<NT, false, true, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                else
+                    resolve_groups<NT, false, false, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+            }
+        };
+        if (!by_lists) {
+            // Windows in one piece, and in bands if walking all bins for every band costs less than picking a band's
+            // triangles out.
+            if (WINDOWED && bands_done) __syncthreads();  // the previous band is resolved (its lanes left their keys cleared)
             // The bins are complete: each lane asks now for the first triangle it will raster from the small and from the
             // tiny bin (its list entry, then its entry of the index table), so that they come in from memory while the keys
             // are cleared and the barrier is waited at.
@@ -1100,7 +1409,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
 
             // codes and candidates are dead: clear the pixel keys they shared LDS with (0 = background at depth 0)
             // (two keys per store; the region is padded to 16 bytes, so an odd count may clear one key more)
-            if (!BANDED || row_lo == 0) {
+            if (!WINDOWED || bands_done == 0) {
                 for (uint32_t p = tid; p < (n_keys + 1u) >> 1; p += NT)
                     reinterpret_cast<uint4*>(keys)[p] = make_uint4(0u, 0u, 0u, 0u);
                 PXR_TIMED_BARRIER(4);
@@ -1114,8 +1423,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // small: a team of lanes per triangle, from the first lane up
             // (a lane's first triangle of each was requested before the barrier; the next one is at the loop's end)
             for (uint32_t k = tid >> kSmallLanesLog2; k < n_small;) {
-                raster_binned<false>(scb, t_small, ti_small, vxy, vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2,
-                                     (int)row_lo, (int)row_hi);
+                raster_binned<false>(scb, win, t_small, ti_small, vxy, vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
                 k += NT >> kSmallLanesLog2;
                 if (k < n_small) {
                     t_small = list[scb.T - 1 - k];
@@ -1124,7 +1432,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             }
             // tiny: one lane per triangle, from the last lane down
             for (uint32_t k = NT - 1 - tid; k < n_tiny;) {
-                raster_binned<false>(scb, t_tiny, ti_tiny, vxy, vd, keys, 0, 0, (int)row_lo, (int)row_hi);
+                raster_binned<false>(scb, win, t_tiny, ti_tiny, vxy, vd, keys, 0, 0);
                 k += NT;
                 if (k < n_tiny) {
                     t_tiny = list[k];
@@ -1133,17 +1441,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             }
             // large: a whole wave per triangle, starting in the middle waves
             for (uint32_t k = ((tid >> 6) + NT / 128) % (NT / 64); k < n_large; k += NT / 64)
-                raster_binned<true>(scb, list2[k], tri_table[list2[k]], vxy, vd, keys, (int)lane, 6, (int)row_lo, (int)row_hi);
-            PXR_TIMED_BARRIER(5);
-            PXR_PHASE_MARK(5);
-
+                raster_binned<true>(scb, win, list2[k], tri_table[list2[k]], vxy, vd, keys, (int)lane, 6);
         } else {
-            // Frames of many bands.  Every band walks the frame's bins again, but only to pick out the triangles that can
+            // Windows in bands of many triangles.  Every band walks the frame's bins again, but only to pick out the triangles that can
             // touch its rows: a dense pass, one lane per binned triangle and round of NT, that compacts them (ballot,
             // one packed atomic per wavefront) into the round's own short lists, from which the raster loops then
-            // work as in the unbanded kernel.  A band that holds a twentieth of the frame's triangles rasters a
+            // work as above.  A band that holds a twentieth of the frame's triangles rasters a
             // twentieth of them, not all.
-            if (row_lo) __syncthreads();  // the previous band is resolved (its lanes left their keys cleared)
+            if (bands_done) __syncthreads();  // the previous band is resolved (its lanes left their keys cleared)
             uint16_t* blist = reinterpret_cast<uint16_t*>(lds + scb.lds_blist);    // tiny up, small down: kBandListEntries
             uint16_t* blist2 = reinterpret_cast<uint16_t*>(lds + scb.lds_blist2);  // large: kBandListEntries
             const u64 bins = fu->bins;
@@ -1151,16 +1456,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             const uint32_t n_binned = n_tiny + n_small + n_large;
             constexpr uint32_t kTeam = 1u << kSmallLanesLog2;
             const uint2* tri_table = reinterpret_cast<const uint2*>(scb.tri_idx);
-            if (row_lo == 0) {
+            if (bands_done == 0) {
                 // the first band's keys share LDS with the cell codes and the candidate list, dead by now
                 for (uint32_t p = tid; p < (n_keys + 1u) >> 1; p += NT)
                     reinterpret_cast<uint4*>(keys)[p] = make_uint4(0u, 0u, 0u, 0u);
             }
             uint32_t base = 0;
             do {
-                // ---- this round's share of the bins -> the triangles among them that touch rows [row_lo, row_hi)
+                if (base) __syncthreads();  // (the lists of the round before are read)
+                // ---- this round's share of the bins -> the triangles among them that touch the band's rows
                 const uint32_t slot = band_round & 1u;
-                if (tid == 0) fu->band_bins[slot ^ 1u] = 0ull;  // (last read before the barrier that ended the round before this one)
+                if (tid == 0) fu->band_bins[slot ^ 1u] = 0ull;  // (last read before the barrier behind the round before this one)
                 const uint32_t k = base + tid;
                 int cls = 0;
                 uint32_t t = 0;
@@ -1168,7 +1474,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                     cls = k < n_tiny ? 1 : (k < n_tiny + n_small ? 2 : 3);
                     t = cls == 1 ? list[k] : (cls == 2 ? list[scb.T - 1 - (k - n_tiny)] : list2[k - n_tiny - n_small]);
                     int j0 = 0, j1 = 0;
-                    if (tri_rows(scb, tri_table[t], vxy, j0, j1) == kTriPlain && (j0 >= (int)row_hi || j1 < (int)row_lo)) cls = 0;
+                    if (tri_rows(tri_table[t], vxy, j0, j1) == kTriPlain && (j0 > win.y_hi || j1 < win.y_lo)) cls = 0;
                 }
                 const u64 m1 = __ballot(cls == 1), m2 = __ballot(cls == 2), m3 = __ballot(cls == 3);
                 if (m1 | m2 | m3) {
@@ -1185,107 +1491,56 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                 PXR_TIMED_BARRIER(4);
                 PXR_PHASE_MARK(4);
 
-                // ---- phase 3 from the round's lists (lane teams as in the unbanded kernel)
+                // ---- phase 3 from the round's lists (lane teams as above)
                 const u64 bb = fu->band_bins[slot];
                 const uint32_t b_tiny = (uint32_t)bb & 0xFFFFu, b_small = (uint32_t)bb >> 16, b_large = (uint32_t)(bb >> 32);
                 for (uint32_t i = tid >> kSmallLanesLog2; i < b_small; i += NT >> kSmallLanesLog2) {
                     const uint32_t ts = blist[kBandListEntries - 1 - i];
-                    raster_binned<false>(scb, ts, tri_table[ts], vxy, vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2,
-                                         (int)row_lo, (int)row_hi);
+                    raster_binned<false>(scb, win, ts, tri_table[ts], vxy, vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
                 }
                 if (NT - 1 - tid < b_tiny) {
                     const uint32_t tt = blist[NT - 1 - tid];
-                    raster_binned<false>(scb, tt, tri_table[tt], vxy, vd, keys, 0, 0, (int)row_lo, (int)row_hi);
+                    raster_binned<false>(scb, win, tt, tri_table[tt], vxy, vd, keys, 0, 0);
                 }
                 for (uint32_t i = ((tid >> 6) + NT / 128) % (NT / 64); i < b_large; i += NT / 64)
-                    raster_binned<true>(scb, blist2[i], tri_table[blist2[i]], vxy, vd, keys, (int)lane, 6, (int)row_lo, (int)row_hi);
-                PXR_TIMED_BARRIER(5);
-                PXR_PHASE_MARK(5);
+                    raster_binned<true>(scb, win, blist2[i], tri_table[blist2[i]], vxy, vd, keys, (int)lane, 6);
                 ++band_round;
                 base += NT;
             } while (base < n_binned);
         }
+        if (WINDOWED && bands_done == 0) {
+            // The first band's raster phase ends with the pixels beside the window, in chunks for whichever wavefront is
+            // done: they cover the wait for the phase's longest chains.
+            const uint32_t slab = frame_of_block(blockIdx.x, gridDim.x) & ((1u << slabs_log2) - 1u);
+            ResolveRange beside = range;
+            beside.rows = (uint32_t)__builtin_amdgcn_readfirstlane((int)fu->win_rows);
+            beside.first_row = (slab * scb.H) >> slabs_log2;
+            beside.end_row = ((slab + 1u) * scb.H) >> slabs_log2;
+            beside.side_groups = ((scb.W + 3u) >> 2) - range.groups;
+            beside.side_magic = (uint32_t)__builtin_amdgcn_readfirstlane((int)fu->side_magic);
+            beside.ticket = &fu->ticket;
+            resolve(std::integral_constant<ResolvePart, kBesideWindow>{}, beside);
+        }
+        PXR_TIMED_BARRIER(5);
+        PXR_PHASE_MARK(5);
 
         // ---- phase 4: resolve + shade + distractor + pack + store
-        ResolveCtx rc;
-        const float eye_x = fu->eye[0], eye_y = fu->eye[1], eye_z = fu->eye[2];
-        rc.eye_x = eye_x;
-        rc.eye_y = eye_y;
-        rc.eye_z = eye_z;
-        const bool no_roll = scb.Rt[2] == 0.0f;
-        rc.inv_ez = 0.0f;
-        if (!(PX == 4 && no_roll)) {  // (without roll the row table already holds the ground test)
-            asm volatile("" ::: "memory");  // (a branch, not a select: the compiler would do the division either way)
-            rc.inv_ez = 1.0f / eye_z;
-        }
-        rc.ground_ok = scb.ground_on && eye_z > 0.0f;
-        rc.mode = dcb.mode;
-        rc.alpha = dcb.alpha;
-        rc.vframe = nullptr;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            rc.scale[c] = fu->scale[c];
-            rc.offs[c] = fu->offs[c];
-        }
-        rc.col_addr = scb.lds_misc + (uint32_t)offsetof(FrameUniforms, base_col);
-        rc.packed_addr = scb.lds_misc + (uint32_t)offsetof(FrameUniforms, base_packed);
-        rc.vlut = scb.lds_vlut;
-        if (VIDEO) rc.vframe = dcb.video + (size_t)fu->video_frame * scb.npix * 3;
-        uint8_t* out = frames + (size_t)frame * scb.npix * 3;
-        uint32_t* out_ids = ids ? ids + (size_t)frame * scb.npix : nullptr;
-        if (PX == 4) {
-            // uniform scene properties select a specialised loop (kept out of the per-pixel code)
-            // (an eye that is a NaN makes ground points NaNs: such a frame takes the general loop, which is exact
-            // for a unit cell as well)
-            if (scb.checker_short_form && eye_x == eye_x && eye_y == eye_y) {
-                if (no_roll)
-                    resolve_rows4<NT, true, true, VIDEO, BANDED>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, p_begin, p_end);
-                else
-                    resolve_rows4<NT, true, false, VIDEO, BANDED>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, p_begin, p_end);
-            } else {
-                if (no_roll)
-                    resolve_rows4<NT, false, true, VIDEO, BANDED>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, p_begin, p_end);
-                else
-                    resolve_rows4<NT, false, false, VIDEO, BANDED>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, p_begin, p_end);
-            }
-        } else {
-            // any image shape: one pixel per lane, byte stores
-            for (uint32_t p = p_begin + tid; p < p_end; p += NT) {
-                const uint32_t j = __umulhi(p, scb.magicW);
-                const uint32_t i = p - j * scb.W;
-                const float cxi = cxcy[i], cyj = cxcy[scb.W + j];
-                const float dwx = __builtin_fmaf(scb.Rt[0], cxi, __builtin_fmaf(scb.Up[0], cyj, scb.Fw[0]));
-                const float dwy = __builtin_fmaf(scb.Rt[1], cxi, __builtin_fmaf(scb.Up[1], cyj, scb.Fw[1]));
-                const float dwz = __builtin_fmaf(scb.Rt[2], cxi, __builtin_fmaf(scb.Up[2], cyj, scb.Fw[2]));
-                float tg;
-                const u64 gkey = ground_key(scb, rc, -dwz, tg);
-                uint32_t vbytes = 0;
-                if (VIDEO) {
-                    const uint8_t* v = rc.vframe + (size_t)p * 3;
-                    vbytes = (uint32_t)v[0] | ((uint32_t)v[1] << 8) | ((uint32_t)v[2] << 16);
-                }
-                uint32_t low;
-                u64 unused;
-                const uint32_t rgb = resolve_pixel<false, VIDEO>(scb, rc, body, keys[p - p_begin], gkey, tg, dwx, dwy, vbytes, low, unused);
-                out[(size_t)p * 3 + 0] = (uint8_t)(rgb & 0xFFu);
-                out[(size_t)p * 3 + 1] = (uint8_t)((rgb >> 8) & 0xFFu);
-                out[(size_t)p * 3 + 2] = (uint8_t)(rgb >> 16);
-                if (out_ids) out_ids[p] = 0xFFFFFFFFu - low;
-                if (BANDED) keys[p - p_begin] = 0ull;  // cleared for the next band by the lane that read it
-            }
-        }
-        row_lo = row_hi;
-    } while (BANDED && row_lo < argument_reloaded<SceneConsts>(kSceneArgAt).H);
+        if (WINDOWED)
+            resolve(std::integral_constant<ResolvePart, kInsideWindow>{}, range);
+        else
+            resolve(std::integral_constant<ResolvePart, kWholeFrame>{}, range);
+        ++bands_done;
+    } while (WINDOWED && more_bands);
     PXR_PHASE_MARK(6);
     PXR_PHASE_END();
 }
 
-template <int NT, int PX, bool BANDED, bool VIDEO>
+template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
 int launch_one(const SceneConsts& sc, const DistractConsts& dc, const float* d_poses, const float* d_shapes,
                uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
-               hipStream_t stream, std::string& err) {
-    hipLaunchKernelGGL((render_kernel<NT, PX, BANDED, VIDEO>), dim3(n_frames), dim3(NT), sc.lds_total, stream, sc, dc,
-                       d_poses, d_shapes, S, step0, env0, d_frames, d_ids);
+               uint32_t slabs_log2, hipStream_t stream, std::string& err) {
+    hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
+                       sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2);
     const hipError_t rc = hipGetLastError();
     if (rc != hipSuccess) {
         err = std::string("kernel launch failed: ") + hipGetErrorString(rc);
@@ -1294,15 +1549,15 @@ int launch_one(const SceneConsts& sc, const DistractConsts& dc, const float* d_p
     return PXR_OK;
 }
 
-template <int NT, int PX, bool BANDED, bool VIDEO>
+template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
 int prepare_one(uint32_t lds_bytes, std::string& err) {
     hipFuncAttributes attr;
-    if (hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&render_kernel<NT, PX, BANDED, VIDEO>)) != hipSuccess ||
+    if (hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&render_kernel<NT, RAGGED, WINDOWED, VIDEO>)) != hipSuccess ||
         attr.sharedSizeBytes != 0) {
         err = "the render kernel has static LDS in front of its dynamic segment (LDS addresses in the tables assume none)";
         return PXR_ERR_DEVICE;
     }
-    const hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&render_kernel<NT, PX, BANDED, VIDEO>),
+    const hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&render_kernel<NT, RAGGED, WINDOWED, VIDEO>),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (rc != hipSuccess) {
         err = std::string("hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: ") + hipGetErrorString(rc);
@@ -1314,14 +1569,14 @@ int prepare_one(uint32_t lds_bytes, std::string& err) {
 template <int NT>
 int prepare_all(uint32_t cap, std::string& err) {
     int rc;
-    if ((rc = prepare_one<NT, 4, false, false>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 4, true, false>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 1, false, false>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 1, true, false>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 4, false, true>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 4, true, true>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 1, false, true>(cap, err))) return rc;
-    if ((rc = prepare_one<NT, 1, true, true>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, false, false, false>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, false, true, false>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, true, false, false>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, true, true, false>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, false, false, true>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, false, true, true>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, true, false, true>(cap, err))) return rc;
+    if ((rc = prepare_one<NT, true, true, true>(cap, err))) return rc;
     return PXR_OK;
 }
 
@@ -1347,15 +1602,14 @@ int launch_render(const SceneConsts& sc, const DistractConsts& dc, const float* 
                   uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
                   uint32_t block_threads, void* stream, std::string& err) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // four pixels per lane: they must share a row and frames must stay dword-aligned
-    const bool quad = (sc.W % 4u) == 0u;
-    const bool banded = sc.band_rows < sc.H;
+    const bool ragged = (sc.W % 4u) != 0u, windowed = sc.key_capacity != 0u;
     // (the video distractor has kernels of its own: the others carry none of its code, and the other way round)
     const bool video = dc.mode == PXR_DISTRACT_VIDEO;
-#define PXR_ARGS sc, dc, d_poses, d_shapes, n_frames, S, step0, env0, d_frames, d_ids, st, err
-#define PXR_LAUNCH_V(NT, V)                                                                            \
-    return quad ? (banded ? launch_one<NT, 4, true, V>(PXR_ARGS) : launch_one<NT, 4, false, V>(PXR_ARGS)) \
-                : (banded ? launch_one<NT, 1, true, V>(PXR_ARGS) : launch_one<NT, 1, false, V>(PXR_ARGS))
+    uint32_t slabs_log2 = 0;
+#define PXR_ARGS sc, dc, d_poses, d_shapes, n_frames, S, step0, env0, d_frames, d_ids, slabs_log2, st, err
+#define PXR_LAUNCH_V(NT, V)                                                                                      \
+    return ragged ? (windowed ? launch_one<NT, true, true, V>(PXR_ARGS) : launch_one<NT, true, false, V>(PXR_ARGS)) \
+                  : (windowed ? launch_one<NT, false, true, V>(PXR_ARGS) : launch_one<NT, false, false, V>(PXR_ARGS))
 #define PXR_LAUNCH(NT)                   \
     if (video) PXR_LAUNCH_V(NT, true);   \
     PXR_LAUNCH_V(NT, false)

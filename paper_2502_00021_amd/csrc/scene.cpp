@@ -313,6 +313,8 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
     c.K = d.n_bodies;
     c.root = d.root_body;
     c.magicW = (uint32_t)((0x100000000ull + d.width - 1) / d.width);
+    c.pitch = (d.width + 3u) & ~3u;
+    c.magic_groups = (uint32_t)((0x100000000ull + c.pitch / 4u - 1) / (c.pitch / 4u));
 
     // ---- meshes
     uint32_t vbase = 0, tbase = 0;
@@ -374,6 +376,15 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
             err = "scene exceeds 65535 vertices or triangles";
             return PXR_ERR_UNSUPPORTED;
         }
+        // (a little more than the vertices' own: the bound errs outwards)
+        double bound[4] = {0.0, 0.0, 0.0, 0.0};
+        for (const Vec3d& u : m.pos) {
+            bound[0] = std::fmax(bound[0], std::fabs(u.x));
+            bound[1] = std::fmax(bound[1], std::fabs(u.y));
+            bound[2] = std::fmax(bound[2], std::fabs(u.z));
+            bound[3] = std::fmax(bound[3], norm(u));
+        }
+        for (double r : bound) hs.body_bound.push_back((float)(r * (1.0 + 0x1p-20)));
         for (uint32_t v = 0; v < nv; ++v) {
             hs.vtmpl.push_back((float)m.pos[v].x);
             hs.vtmpl.push_back((float)m.pos[v].y);
@@ -460,26 +471,12 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
     c.gs[1] = std::fmin(1.0f, (float)((double)d.ground_grey[1] * lit));
     for (int i = 0; i < 3; ++i) c.bg[i] = d.background_rgb[i];
 
-    // ---- LDS carve-up of one frame workgroup.  The pixel keys dominate for tall frames; they are
-    // kept for `band_rows` rows at a time.  Prefer the fewest bands that let two workgroups share a
-    // compute unit (80 KB each); failing that, the fewest bands that fit at all.
+    // ---- LDS carve-up of one frame workgroup.  The pixel keys dominate for large frames.
     auto align = [](uint32_t x, uint32_t a) { return (x + a - 1) / a * a; };
-    auto layout = [&](uint32_t n_bands, bool whole_trips = false) {
-        c.band_rows = (c.H + n_bands - 1) / n_bands;
-        c.first_band_rows = c.band_rows;
-        if (whole_trips) {
-            // Two bands: the resolve loop of the 768-thread workgroups such frames run takes 768 x 4 pixels a trip.
-            // A first band of whole trips (and a taller second one) saves the nearly empty trip that an even split
-            // ends both bands with: 84 x 84 as 36 + 48 rows is three trips instead of four (+2.4 %).
-            const uint32_t rows_per_trip = (768u * 4u) / c.W;
-            const uint32_t first = rows_per_trip ? c.band_rows / rows_per_trip * rows_per_trip : 0u;
-            if (n_bands != 2 || (c.W & 3u) || first == 0 || first == c.band_rows) return 0xFFFFFFFFu;  // nothing to gain
-            c.first_band_rows = first;
-            c.band_rows = c.H - first;
-        }
+    auto layout = [&](uint32_t key_bytes, bool band_lists) {
         uint32_t o = 0;
         c.lds_keys = o;  // 16-byte aligned regions first
-        o += align(std::max(c.band_rows * c.W * 8, c.V * 4 + 4 + c.T * 2), 16);  // (V codes, one word of code 0, T candidates)
+        o += align(std::max(key_bytes, c.V * 4 + 4 + c.T * 2), 16);  // (V codes, one word of code 0, T candidates)
         c.lds_cxcy = o;
         o += align((c.W + c.H) * 4, 16);
         c.lds_rows = o;  // float4 per image row
@@ -497,42 +494,56 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
         c.lds_large = o;
         o += align(c.T * 2, 4);
         c.lds_blist = c.lds_blist2 = 0;
-        if (n_bands >= kBandListsFrom) {  // a band round's lists
+        if (band_lists) {  // a band round's lists
             c.lds_blist = o;
             o += kBandListEntries * 2;
             c.lds_blist2 = o;
             o += kBandListEntries * 2;
         }
         c.lds_total = align(o, 16);
-        // Video distractor: blended byte by (colour under the clip, clip byte), nine tables of 256 bytes
-        // (background r, g, b, and each of the two greys three times, so that "channel" is the same address offset
-        // whatever lies under the clip).  Taken only where it costs no workgroup per compute unit.
+        return c.lds_total;
+    };
+    // Video distractor: blended byte by (colour under the clip, clip byte), nine tables of 256 bytes
+    // (background r, g, b, and each of the two greys three times, so that "channel" is the same address offset
+    // whatever lies under the clip).  Taken only where it costs no workgroup per compute unit.
+    auto add_video_tables = [&]() {
         c.lds_vlut = 0;
         const uint32_t with_tables = c.lds_total + kVideoTableBytes;
         if (with_tables <= 160u * 1024u && (160u * 1024u) / with_tables == (160u * 1024u) / c.lds_total) {
             c.lds_vlut = c.lds_total;
             c.lds_total = with_tables;
         }
-        return c.lds_total;
     };
-    const uint32_t kHalf = 80u * 1024u, kAll = 160u * 1024u, kMaxBands = 128;
-    uint32_t chosen = 0;
-    bool whole_trips = false;
-    for (uint32_t nb = 1; nb <= kMaxBands && !chosen; ++nb) {
-        if (layout(nb) <= kHalf) chosen = nb;
-        if (chosen == 2 && layout(2, true) <= kHalf) whole_trips = true;
+    const uint32_t kHalf = 80u * 1024u, kAll = 160u * 1024u;
+    const uint32_t frame_keys = c.pitch * c.H * 8u;
+    c.key_capacity = 0;
+    c.band_rows = c.first_band_rows = c.H;
+    if (layout(frame_keys, false) <= kHalf) {  // the whole frame's keys, and two workgroups or more per compute unit
+        add_video_tables();
+        return PXR_OK;
     }
-    // A frame that would need many bands at half a compute unit's LDS is better off with all of it: a third of the
-    // bands (each costs a pass over the bins and three barriers) outweighs having no second workgroup to overlap
-    // with (measured: 192x192 +19 %, 256x256 +25 %, 512x512 x2.1; 128x128 and smaller lose 8-15 %).
-    if (chosen >= kBandListsFrom) chosen = 0;
-    for (uint32_t nb = 1; nb <= kMaxBands && !chosen; ++nb)
-        if (layout(nb) <= kAll) chosen = nb;
-    if (!chosen) {
-        err = "scene needs " + std::to_string(layout(kMaxBands)) + " bytes of LDS per frame; the limit is 163840";
+    // What fits at all: some split of the frame into up to 128 bands of full width.
+    bool fits = false;
+    for (uint32_t nb = 1; nb <= 128 && !fits; ++nb) fits = layout((c.H + nb - 1) / nb * c.W * 8u, nb >= 6) <= kAll;
+    if (!fits) {
+        err = "scene needs " + std::to_string(c.lds_total) + " bytes of LDS per frame; the limit is 163840";
         return PXR_ERR_UNSUPPORTED;
     }
-    layout(chosen, whole_trips && chosen == 2);
+    // The keys of the frame's window instead (at least a row of the frame's full width), as many as there is room for in
+    // half a compute unit's LDS, or in all of it where half would leave too few (kHalfKeysFrom).
+    bool lists = true;
+    uint32_t share = kHalf;
+    const uint32_t others = layout(0, true) - align(c.V * 4 + 4 + c.T * 2, 16) + kVideoTableBytes;
+    if (others + kHalfKeysFrom * c.pitch * c.H / 100u * 8u > kHalf || layout(c.pitch * 8u, true) > kHalf) share = kAll;
+    if (layout(c.pitch * 8u, lists) > share) lists = false;  // (a scene at the very limit, of an odd width)
+    const uint32_t used = layout(c.pitch * 8u, lists), region = c.lds_cxcy;
+    uint32_t key_bytes = region + (share - used);
+    if (key_bytes >= region + kVideoTableBytes) key_bytes -= kVideoTableBytes;
+    key_bytes = std::min(key_bytes, frame_keys) & ~15u;
+    layout(key_bytes, lists);
+    c.key_capacity = c.lds_cxcy / 8u;
+    c.band_rows = c.first_band_rows = std::min(c.H, c.key_capacity / c.pitch);
+    add_video_tables();
     return PXR_OK;
 }
 

@@ -168,6 +168,43 @@ def test_frames_larger_than_one_key_buffer(torch, pxr, orc, cfg, W, H, B):
     assert_parity(gpu_render(torch, pxr, w, step0=1), ref)
 
 
+def _scattered(W, H, rng, B=6):
+    """Bodies of every kind around the camera: in view, cut by each edge of the frame, outside it, behind the camera and
+    (last environment) nothing in view at all; quaternions of any length, shapes of either sign."""
+    bodies = [wl.capsule(0.1, 0.25, (0.8, 0.3, 0.3), 7, 3), wl.sphere(0.2, (0.3, 0.8, 0.3), 9, 4), wl.box(0.15, 0.1, 0.2, (0.3, 0.3, 0.8), 2)]
+    tv, tt = wl.torus_mesh(0.3, 0.1, 9, 6)
+    bodies.append(wl.mesh(tv, tt, (0.7, 0.7, 0.2), scale=(1.0, 1.5, 0.5)))
+    poses = np.zeros((B, 1, 4, 7), np.float32)
+    poses[:, 0, 0, :3] = (0, 0, 1)
+    spread = np.array([[0.3], [1.0], [2.0], [4.0], [1.5], [0.0]])[:B, :, None]
+    poses[:, 0, :, :3] += (spread * rng.uniform(-1.0, 1.0, (B, 4, 3))).astype(np.float32)
+    poses[:, 0, 0, :3] = (0, 0, 1)  # (the root: the camera stays where it is)
+    poses[:, 0, :, 3:] = wl.random_quats(rng, (B, 4)) * rng.uniform(0.6, 1.5, (B, 4, 1))
+    shapes = np.array([b["shape"] for b in bodies], np.float32)[None] * rng.choice([-1.0, 1.0], (B, 4, 4)).astype(np.float32)
+    shapes[:, 0] = np.abs(shapes[:, 0])
+    poses[5, 0, 1:, 0] = -20.0 - np.arange(3)  # behind the camera ...
+    shapes[5, 0] = 0.0                         # ... and a root without extent
+    return dict(desc=wl.default_scene(W, H, bodies), poses=poses, shapes=np.ascontiguousarray(shapes), distractor=None)
+
+
+@pytest.mark.parametrize("W,H", [(84, 120), (161, 160), (162, 90), (163, 200), (260, 8), (9, 300), (320, 200), (511, 130)])
+@pytest.mark.parametrize("mode", ["none", "color", "video"])
+def test_key_window_of_large_frames(torch, pxr, orc, W, H, mode):
+    """Frames whose keys do not fit the LDS keep those of the pixels that the bodies can touch: every place such a window
+    can have (inside, cut by each edge, the whole frame, nothing), rows in several bands, widths with a remainder."""
+    w = _scattered(W, H, np.random.default_rng(W * 1000 + H))
+    if mode == "color":
+        w["desc"]["cam_up"] = (0.1, 0.2, 1.0)
+        w["distractor"] = dict(mode="color", seed=3, scale=(0.5, 1.5), offset=(-0.2, 0.2))
+    if mode == "video":
+        video = np.random.default_rng(1).integers(0, 256, (3, H, W, 3), dtype=np.uint8)
+        w["distractor"] = dict(mode="video", seed=5, video=video, alpha=0.5, env_offset=None)
+    ref = oracle_render(orc, w, step0=1)
+    assert (ref["ids"] < GROUND).any() and (ref["ids"][5] >= GROUND).all()
+    assert_parity(gpu_render(torch, pxr, w, step0=1), ref)
+    assert_parity(gpu_render(torch, pxr, w, step0=1, threads=256), ref)
+
+
 def test_close_up_at_512(torch, pxr, orc):
     """Triangles hundreds of pixels wide crossing many bands."""
     rng = np.random.default_rng(77)
