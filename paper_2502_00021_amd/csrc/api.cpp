@@ -19,6 +19,7 @@ struct pxr_scene {
     int device = 0;
     uint32_t block_threads = 0;
     uint32_t default_threads = 0;
+    uint32_t n_cus = 0;
 };
 
 namespace {
@@ -63,7 +64,7 @@ int pxr::render_envs(pxr_scene* s, const float* d_poses, const float* d_shapes, 
     pxr::DistractConsts dc = s->dc;  // the per-environment arrays follow the environments
     if (dc.env_offset) dc.env_offset += e0;
     if (dc.env_video) dc.env_video += e0;
-    return pxr::launch_render(s->sc, dc, poses, shapes, n * S, S, step0, env0 + e0, frames, ids, s->block_threads, stream, err);
+    return pxr::launch_render(s->sc, dc, poses, shapes, n * S, S, step0, env0 + e0, frames, ids, s->block_threads, s->n_cus, stream, err);
 }
 
 namespace {
@@ -122,10 +123,13 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
     pxr_scene* s = new (std::nothrow) pxr_scene();
     if (!s) return fail(PXR_ERR_OOM, "pxr_create_scene: host allocation failed");
     s->sc = hs.c;
-    if (hipGetDevice(&s->device) != hipSuccess) {
+    int n_cus = 0;
+    if (hipGetDevice(&s->device) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess) {
         delete s;
         return fail(PXR_ERR_DEVICE, "pxr_create_scene: no HIP device");
     }
+    s->n_cus = (uint32_t)n_cus;
     std::vector<uint32_t> pair_dev(hs.pair_tbl);
     for (size_t p = 0; p < pair_dev.size() / 4; ++p)
         for (int w = 0; w < 2; ++w) {

@@ -142,10 +142,10 @@ struct HostScene {
 // left for the caller).  Returns a PXR_* code and a message on failure.
 int build_host_scene(const pxr_scene_desc& desc, HostScene& hs, std::string& err);
 
-// render.hip: enqueue one batch.  `block_threads` in {256,512,768,1024}.
+// render.hip: enqueue one batch.  `block_threads` in {256,512,768,1024}; `n_cus` compute units of the device.
 int launch_render(const SceneConsts& sc, const DistractConsts& dc, const float* d_poses, const float* d_shapes,
                   uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
-                  uint32_t block_threads, void* stream, std::string& err);
+                  uint32_t block_threads, uint32_t n_cus, void* stream, std::string& err);
 
 // render.hip: raise the dynamic-LDS limit of every kernel instantiation on the current device (the caller sees
 // to it that this runs once per device).

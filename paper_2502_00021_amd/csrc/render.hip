@@ -1600,12 +1600,18 @@ int prepare_kernels(std::string& err) {
 
 int launch_render(const SceneConsts& sc, const DistractConsts& dc, const float* d_poses, const float* d_shapes,
                   uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
-                  uint32_t block_threads, void* stream, std::string& err) {
+                  uint32_t block_threads, uint32_t n_cus, void* stream, std::string& err) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const bool ragged = (sc.W % 4u) != 0u, windowed = sc.key_capacity != 0u;
     // (the video distractor has kernels of its own: the others carry none of its code, and the other way round)
     const bool video = dc.mode == PXR_DISTRACT_VIDEO;
+    // A windowed frame is shared by several workgroups while that gives every workgroup of the launch a compute unit of its
+    // own: geometry is repeated, raster and resolve, which dominate large frames, are split.  us per launch without / with
+    // 2 / 4 / 8 / 16 slabs, humanoid and box: 256x256, 8 frames 33.8 / 26.1 / 24.6 / 20.0 / 17.7, 32 frames 43.2 / 27.9 /
+    // 25.7 / 20.8 / 29.6, 100 frames 45.1 / 30.1 / 46.1 / 51.1 / 74.5, 200 frames 46.6 / 50.5 and up; 128x128, 32 frames 21.2 /
+    // 17.4 / 14.5 / 13.3 / 14.7; quadruped 84x84, 64 frames 10.8 / 10.2 / 10.1 / 11.7 / 20.0.  (A slab has 4 rows or more.)
     uint32_t slabs_log2 = 0;
+    while (windowed && slabs_log2 < 5u && ((uint64_t)n_frames << (slabs_log2 + 1u)) <= n_cus && (sc.H >> (slabs_log2 + 1u)) >= 4u) ++slabs_log2;
 #define PXR_ARGS sc, dc, d_poses, d_shapes, n_frames, S, step0, env0, d_frames, d_ids, slabs_log2, st, err
 #define PXR_LAUNCH_V(NT, V)                                                                                      \
     return ragged ? (windowed ? launch_one<NT, true, true, V>(PXR_ARGS) : launch_one<NT, true, false, V>(PXR_ARGS)) \

@@ -205,6 +205,25 @@ def test_key_window_of_large_frames(torch, pxr, orc, W, H, mode):
     assert_parity(gpu_render(torch, pxr, w, step0=1, threads=256), ref)
 
 
+@pytest.mark.parametrize("W,H,video", [(256, 256, False), (163, 200, True), (84, 84, True), (300, 37, False)])
+def test_large_frames_shared_by_workgroups_or_not(torch, pxr, orc, W, H, video):
+    """Small batches give a large frame's rows to several workgroups, large ones a frame to each: the same frames, and the
+    oracle's."""
+    w = _scattered(W, H, np.random.default_rng(W + H))
+    if video:
+        clip = np.random.default_rng(2).integers(0, 256, (3, H, W, 3), dtype=np.uint8)
+        w["distractor"] = dict(mode="video", seed=5, video=clip, alpha=0.5, env_offset=np.zeros(6, np.uint32))
+    ref = oracle_render(orc, w)
+    for copies in (1, 3, 14, 50):  # 6, 18, 84 and 300 frames: 32, 8, 2 and no slabs
+        many = dict(w, poses=np.tile(w["poses"], (copies, 1, 1, 1)), shapes=np.tile(w["shapes"], (copies, 1, 1)))
+        if video:
+            many["distractor"] = dict(w["distractor"], env_offset=np.zeros(6 * copies, np.uint32))
+        got = gpu_render(torch, pxr, many)
+        assert_parity(dict(frames=got["frames"][:6], ids=got["ids"][:6]), ref)
+        assert np.array_equal(got["frames"], np.tile(got["frames"][:6], (copies, 1, 1, 1, 1)))
+        assert np.array_equal(got["ids"], np.tile(got["ids"][:6], (copies, 1, 1, 1)))
+
+
 def test_close_up_at_512(torch, pxr, orc):
     """Triangles hundreds of pixels wide crossing many bands."""
     rng = np.random.default_rng(77)
