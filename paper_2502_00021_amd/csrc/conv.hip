@@ -18,11 +18,16 @@
 //   load   the band's input rows of all S frames: 12-byte loads (4 RGB pixels),
 //          issued one work item ahead into registers, then uint8 -> bf16
 //          (exact) and written to LDS as [frame][row][pixel][R,G,B,0]
-//   mma    one wavefront per (output row, 32-pixel tile): for each (frame, ky)
+//   mma    one wavefront per tile of 32 consecutive pixels of the band (a tile may
+//          run over the end of a row into the next): for each (frame, ky)
 //          ONE aligned 16-byte LDS read per lane is the B operand
 //          (2 pixels x 4 channels; lanes 0-31 take pixels 2ox, 2ox+1, lanes
 //          32-63 take 2ox+2, 2ox+3; the weights of pixel 2ox+3 and of channel 3
-//          are zero), A = the weights: 3S instructions per tile
+//          are zero), A = the weights: 3S instructions per tile.  (A band's rows leave
+//          back to back, so a tile need not end with a row: 41-pixel rows took two
+//          tiles each, 10 for a band of 5, now 7.  256 stacks of four 84x84 frames
+//          14.0 -> 12.0 us, 2048 of them 94 -> 79 us = 5.0 TB/s; rows of 31 or 63
+//          pixels, which fill their tiles, are unchanged.)
 //   store  fma(acc, 1/255, bias), ReLU, bf16 (round to nearest even), staged
 //          through 2 KB of wave-private LDS so that a tile leaves as two
 //          contiguous 1 KB stores
@@ -68,6 +73,12 @@ __device__ __forceinline__ void store_streaming_b128(void* dst, u32x4 v) {
     asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" : : "v"(dst), "v"(v) : "memory");
 }
 
+// First output row of a band: the rows are dealt evenly (41 rows in bands of up to 5 are 5 x 5 + 4 x 4, not 8 x 5 + 1), the
+// first `extra_rows` bands have one more.
+__device__ __forceinline__ uint32_t first_row(const ConvConsts& cc, uint32_t band) {
+    return band * (cc.band_rows - (cc.extra_rows ? 1u : 0u)) + min(band, cc.extra_rows);
+}
+
 template <int S, bool RELU>
 __global__ __launch_bounds__(kConvThreads) void conv_kernel(const ConvConsts cc, const uint8_t* __restrict__ frames,
                                                             uint32_t n_items, uint16_t* __restrict__ out) {
@@ -104,8 +115,8 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const ConvConsts cc,
     Quad pre[kConvTrips];
     const uint32_t quads_per_row = cc.W >> 2;
     auto fetch = [&](uint32_t item) {
-        const uint32_t env = item / cc.bands, oy0 = (item - env * cc.bands) * cc.band_rows;
-        const uint32_t n_quads = (2u * min(cc.band_rows, cc.Ho - oy0) + 1u) * quads_per_row;
+        const uint32_t env = item / cc.bands, band = item - env * cc.bands, oy0 = first_row(cc, band);
+        const uint32_t n_quads = (2u * (first_row(cc, band + 1u) - oy0) + 1u) * quads_per_row;
         // (an environment's S frames are at most 1.5 MB: offsets inside them fit 32 bits)
         const unsigned char* base = frames + (size_t)env * (S * cc.H * cc.W * 3u) + 2u * oy0 * cc.W * 3u;
         const uint32_t frame_bytes = cc.H * cc.W * 3u;
@@ -130,8 +141,7 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const ConvConsts cc,
     if (item < n_items) fetch(item);
     while (item < n_items) {
         const uint32_t env = item / cc.bands, band = item - env * cc.bands;
-        const uint32_t oy0 = band * cc.band_rows;
-        const uint32_t rows_out = min(cc.band_rows, cc.Ho - oy0);
+        const uint32_t oy0 = first_row(cc, band), rows_out = first_row(cc, band + 1u) - oy0;
         const uint32_t n_quads = (2u * rows_out + 1u) * quads_per_row;
 
         // ---- convert the fetched quads to bf16 and lay them out in LDS
@@ -160,11 +170,11 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const ConvConsts cc,
         const uint32_t next = item + gridDim.x;
         if (next < n_items) fetch(next);
 
-        // ---- one wavefront per (output row, 32-pixel tile)
-        const uint32_t n_tasks = rows_out * cc.tiles_x;
-        for (uint32_t task = wave; task < n_tasks; task += kConvThreads / 64) {
-            const uint32_t r_out = __umul24(task, cc.tiles_magic) >> 16, tx = task - __umul24(r_out, cc.tiles_x);  // task / tiles_x
-            const uint32_t ox = min(tx * 32u + n, cc.Wo - 1u);  // lanes past the row's end recompute its last pixel
+        // ---- one wavefront per tile of 32 pixels, in the order in which they leave
+        const uint32_t n_pixels = rows_out * cc.Wo;
+        for (uint32_t p0 = wave * 32u; p0 < n_pixels; p0 += kConvThreads / 64 * 32u) {
+            const uint32_t p = min(p0 + n, n_pixels - 1u);  // lanes past the band's end recompute its last pixel
+            const uint32_t r_out = __umul24(p, cc.wo_magic) >> 20, ox = p - __umul24(r_out, cc.Wo);  // p / Wo
             const unsigned char* bsrc = lds + (__umul24(2u * r_out, cc.W) + 2u * ox + 2u * g) * 8u;
             f32x16 acc = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -191,10 +201,10 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const ConvConsts cc,
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint32_t n_bytes = min(32u, cc.Wo - tx * 32u) * 64u;
+            const uint32_t n_bytes = min(32u, n_pixels - p0) * 64u;
             // (an environment's features are below 2 GB: 32-bit offsets from its base)
             unsigned char* dst = reinterpret_cast<unsigned char*>(out) + (size_t)env * (cc.Ho * cc.Wo * 64u) +
-                                 (__umul24(oy0 + r_out, cc.Wo) + tx * 32u) * 64u;
+                                 (__umul24(oy0, cc.Wo) + p0) * 64u;
 #pragma unroll
             for (uint32_t h = 0; h < 2; ++h) {
                 const uint32_t off = h * 1024u + lane * 16u;

@@ -32,6 +32,7 @@ void plan(pxr_conv* c, uint32_t band_rows) {
     cc.bands = (cc.Ho + band_rows - 1) / band_rows;
     cc.band_rows = (cc.Ho + cc.bands - 1) / cc.bands;  // even out the bands
     cc.bands = (cc.Ho + cc.band_rows - 1) / cc.band_rows;
+    cc.extra_rows = cc.Ho % cc.bands;
     cc.rows_in = 2 * cc.band_rows + 1;
 }
 
@@ -83,8 +84,7 @@ int pxr_conv_create(const pxr_conv_desc* d, pxr_conv** out) {
     cc.S = S;
     cc.Ho = (cc.H - 3) / 2 + 1;
     cc.Wo = (cc.W - 3) / 2 + 1;
-    cc.tiles_x = (cc.Wo + 31) / 32;
-    cc.tiles_magic = (65536u + cc.tiles_x - 1) / cc.tiles_x;
+    cc.wo_magic = ((1u << 20) + cc.Wo - 1) / cc.Wo;
     cc.relu = d->relu ? 1u : 0u;
     // band height: about 40 KB of LDS per workgroup so that four of them share a compute unit
     uint32_t band = 1;

@@ -156,10 +156,11 @@ int prepare_kernels(std::string& err);
 struct ConvConsts {
     uint32_t H, W, S;        // input frames [S,H,W,3] per environment
     uint32_t Ho, Wo;         // output size
-    uint32_t tiles_x;        // 32-pixel tiles per output row
-    uint32_t tiles_magic;    // ceil(2^16 / tiles_x): task / tiles_x == (task * tiles_magic) >> 16 for task < 2^13
-    uint32_t band_rows;      // output rows per work item
+    uint32_t wo_magic;       // ceil(2^20 / Wo): p / Wo == (p * wo_magic) >> 20 for every pixel p of a band (p * Wo < 2^20: a band's
+                             // input has at most 4096 pixels, its output a quarter of that, and Wo is at most 127)
+    uint32_t band_rows;      // output rows of a work item, at most
     uint32_t bands;          // work items per environment
+    uint32_t extra_rows;     // this many bands have band_rows rows, the others one less; 0 = all have band_rows
     uint32_t rows_in;        // input rows held in LDS per frame = 2 * band_rows + 1
     uint32_t relu;
     const uint32_t* wtab;    // [3S][64 lanes][4] the A operands of the matrix instruction, bf16 pairs

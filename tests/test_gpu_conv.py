@@ -78,6 +78,17 @@ def test_random_frames_match_oracle(torch, pxr, S, H, W, B):
     assert_conv_parity(oc, _run(torch, pxr, frames, w, b, relu=False), frames, w, b, relu=False)
 
 
+@pytest.mark.parametrize("S,H,W,B,band", [(4, 84, 84, 3, 0), (3, 96, 96, 2, 0), (2, 7, 4, 5, 0), (1, 5, 8, 3, 0), (1, 40, 256, 2, 0),
+                                          (3, 45, 100, 2, 4), (4, 84, 84, 2, 1), (1, 84, 44, 2, 41), (2, 31, 132, 2, 7)])
+def test_tiles_that_run_over_row_ends(torch, pxr, S, H, W, B, band):
+    """Rows of 1, 3, 21, 41, 47, 49, 65 and 127 output pixels in bands of one and of two heights."""
+    from oracle import conv as oc
+    rng = np.random.default_rng(S * 1000 + H * 10 + W)
+    frames = rng.integers(0, 256, (B, S, H, W, 3), dtype=np.uint8)
+    w, b = _layer(rng, S)
+    assert_conv_parity(oc, _run(torch, pxr, frames, w, b, tuning=(band, 0) if band else None), frames, w, b)
+
+
 def test_exact_cases(torch, pxr):
     """Results that are exactly representable must come out bit-exact: delta kernels with weight 255/256... and bias."""
     from oracle import conv as oc
