@@ -253,7 +253,8 @@ int pxr_conv_set_tuning(pxr_conv* c, uint32_t band_rows, uint32_t n_groups);
  * and its conv layer follows on a second stream (created here, default priority) while chunk c + 1 is rendered;
  * ordering is by events only, and the caller's stream is made to wait for the last layer before the call
  * returns (enqueue only, no host synchronisation, no allocation).  Frames and features are byte for byte those
- * of pxr_render_batch followed by pxr_conv_forward.  n_chunks = 1 is that serial order. */
+ * of pxr_render_batch followed by pxr_conv_forward.  n_chunks = 1 is that serial order, and
+ * so is a step of fewer than 400 million pixels (B * S * H * W), where overlapping costs more than it gains. */
 typedef struct pxr_pipeline pxr_pipeline; /* opaque, owned by the library; borrows the scene and the layer */
 
 /* Host only: one stream and n_chunks + 1 events.  The layer's input size must be the scene's frame size; its

@@ -22,6 +22,17 @@ struct pxr_pipeline {
     hipEvent_t consumed = nullptr;
 };
 
+namespace {
+
+// Overlap pays from this many rendered pixels on.  What it gains (a few per cent: a conv workgroup gets onto a compute
+// unit only in a render workgroup's place) grows with the batch; what it costs does not: an event and a wait per chunk,
+// more launches, each with a last wave of workgroups that leaves compute units empty.  64x64 frames of the humanoid and
+// box, stacks of three, us per step in order / with 2 / 4 / 8 chunks: 65 536 environments 4997 / 4939 / 4904 / 4875,
+// 16 384 1224 / 1221 / 1290 / 1276, 2048 150 / 180 / 205 / 258; 64 quadruped environments 15 / 68 / 115 / 205.
+constexpr uint64_t kOverlapFromPixels = 400000000ull;
+
+}  // namespace
+
 extern "C" {
 
 int pxr_pipeline_create(pxr_scene* s, pxr_conv* c, uint32_t n_chunks, pxr_pipeline** out) {
@@ -84,9 +95,16 @@ int pxr_pipeline_step(pxr_pipeline* p, const float* d_poses, const float* d_shap
     pxr::scene_shape(p->scene, &K, &H, &W);
     pxr::conv_shape(p->conv, &cH, &cW, &S, &Ho, &Wo);
     hipStream_t main = reinterpret_cast<hipStream_t>(hip_stream);
+    std::string err;
+    if (p->n_chunks == 1 || (uint64_t)B * S * H * W < kOverlapFromPixels) {
+        // both stages in order on the caller's stream: no events, no second launch of either
+        int rc = pxr::render_envs(p->scene, d_poses, d_shapes, 0, B, S, step0, env0, d_frames, nullptr, main, err);
+        if (rc == PXR_OK) rc = pxr::conv_envs(p->conv, d_frames, 0, B, d_features, main, err);
+        if (rc != PXR_OK) return set_error(rc, "pxr_pipeline_step: " + err);
+        return PXR_OK;
+    }
     // chunks of whole multiples of four environments (every chunk's buffers keep the 16-byte alignment of the batch's)
     const uint32_t per = ((B + p->n_chunks - 1) / p->n_chunks + 3u) & ~3u;
-    std::string err;
     uint32_t used = 0;
     for (uint32_t e0 = 0; e0 < B; e0 += per, ++used) {
         const uint32_t n = B - e0 < per ? B - e0 : per;

@@ -72,6 +72,30 @@ def test_pipeline_equals_serial_order(torch, pxr, cfg, B, chunks):
     sc.close()
 
 
+@pytest.mark.parametrize("chunks", [1, 4, 7])
+def test_pipeline_of_a_batch_large_enough_to_overlap(torch, pxr, chunks):
+    """Just above the 400 million pixels from which a step is cut into chunks on two streams (a ragged last chunk)."""
+    B = 100003
+    poses = torch.from_numpy(wl.make(1, B=16)["poses"]).cuda()
+    poses = (poses[torch.arange(B, device="cuda") % 16] + torch.linspace(0, 0.3, B, device="cuda")[:, None, None, None] *
+             torch.tensor([1.0, 1, 1, 0, 0, 0, 0], device="cuda")).contiguous()
+    sc = pxr.Scene(dict(wl.make(1, B=1)["desc"], width=64, height=64))
+    rng = np.random.default_rng(8)
+    conv = pxr.Conv(64, 64, 1, (rng.standard_normal((3, 3, 3, 32)) * 0.15).astype(np.float32), np.zeros(32, np.float32))
+    assert B * 64 * 64 >= 400_000_000
+    ref_frames, _ = sc.render_batch(poses)
+    ref_feat = conv.forward(ref_frames)
+    pipe = pxr.Pipeline(sc, conv, chunks)
+    frames, feat = torch.full_like(ref_frames, 0x5A), torch.full_like(ref_feat, -1.0)
+    for rep in range(2):
+        pipe.step(poses, None, frames, feat)
+    torch.cuda.synchronize()
+    assert torch.equal(frames, ref_frames) and torch.equal(feat.view(torch.int16), ref_feat.view(torch.int16))
+    pipe.close()
+    conv.close()
+    sc.close()
+
+
 def test_pipeline_argument_errors(torch, pxr):
     sc, conv, poses, shapes = _make(torch, pxr, 5, 8)
     L = pxr.lib()
