@@ -6,6 +6,7 @@ render_batch_kinematic (+ scene_info, set_block_threads, host_tables).  PyTorch 
 There is no fallback: a missing library or a failing call raises.
 """
 import ctypes as C
+import math
 import os
 
 import numpy as np
@@ -124,6 +125,22 @@ def lib():
             getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
+
+
+_torch = None
+
+
+def _torch_module():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
+def _current_stream(tensor):
+    """The raw handle of the current stream of a tensor's GPU (without building a Stream object on every call)."""
+    return _torch._C._cuda_getCurrentRawStream(tensor.get_device())
 
 
 def _check(rc):
@@ -271,30 +288,29 @@ class Scene:
     def render_batch(self, poses, shapes=None, step0=0, env0=0, frames=None, ids=None, want_ids=False, stream=None):
         """poses: CUDA float32 [B,S,K,7]; shapes: CUDA float32 [B,K,4] or None.
         Returns (frames uint8 [B,S,H,W,3], ids int32-typed uint32 bits [B,S,H,W] or None); enqueue only."""
-        import torch
+        torch = _torch or _torch_module()
         assert poses.is_cuda and poses.dtype == torch.float32 and poses.is_contiguous()
-        B, S = int(poses.shape[0]), int(poses.shape[1])
-        assert tuple(poses.shape) == (B, S, self.K, 7), tuple(poses.shape)
+        B, S = poses.shape[0], poses.shape[1]
+        assert poses.shape == (B, S, self.K, 7), tuple(poses.shape)
         if shapes is not None:
             assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous()
-            assert tuple(shapes.shape) == (B, self.K, 4)
+            assert shapes.shape == (B, self.K, 4)
         if frames is None:
             frames = torch.empty((B, S, self.H, self.W, 3), dtype=torch.uint8, device=poses.device)
         else:
             assert frames.is_cuda and frames.is_contiguous() and frames.dtype == torch.uint8
-            assert tuple(frames.shape) == (B, S, self.H, self.W, 3)
+            assert frames.shape == (B, S, self.H, self.W, 3)
         if ids is None and want_ids:
             ids = torch.empty((B, S, self.H, self.W), dtype=torch.int32, device=poses.device)
         if ids is not None:
             assert ids.is_cuda and ids.is_contiguous() and ids.dtype == torch.int32
-            assert tuple(ids.shape) == (B, S, self.H, self.W)
+            assert ids.shape == (B, S, self.H, self.W)
         if stream is None:
-            stream = torch.cuda.current_stream(poses.device).cuda_stream
-        _check(lib().pxr_render_batch(self._h, poses.data_ptr(), None if shapes is None else shapes.data_ptr(),
-                                      B, S, int(step0), int(env0), frames.data_ptr(),
-                                      None if ids is None else ids.data_ptr(), C.c_void_p(stream)))
+            stream = _current_stream(poses)
+        _check(_lib.pxr_render_batch(self._h, poses.data_ptr(), None if shapes is None else shapes.data_ptr(),
+                                     B, S, int(step0), int(env0), frames.data_ptr(),
+                                     None if ids is None else ids.data_ptr(), stream))
         return frames, ids
-
 
     # ---- kinematics stage
 
@@ -310,56 +326,55 @@ class Scene:
         self._skel = (int(n_free), int(n_angles))
 
     def _fk_args(self, free_poses, angles):
-        import torch
+        torch = _torch or _torch_module()
         if self._skel is None:
             raise PxrError(ERR_INVALID_ARG, "no skeleton bound (Scene.set_skeleton)")
         F, J = self._skel
         lead = tuple(free_poses.shape[:-2]) if F else tuple(angles.shape[:-1])
-        n = int(np.prod(lead))
+        n = math.prod(lead)
         if F:
             assert free_poses.is_cuda and free_poses.dtype == torch.float32 and free_poses.is_contiguous()
-            assert tuple(free_poses.shape) == lead + (F, 7), tuple(free_poses.shape)
+            assert free_poses.shape == lead + (F, 7), tuple(free_poses.shape)
         if J:
             assert angles.is_cuda and angles.dtype == torch.float32 and angles.is_contiguous()
-            assert tuple(angles.shape) == lead + (J,), tuple(angles.shape)
-        dev = free_poses.device if F else angles.device
-        return lead, n, dev, (free_poses.data_ptr() if F else None), (angles.data_ptr() if J else None)
+            assert angles.shape == lead + (J,), tuple(angles.shape)
+        return lead, n, free_poses if F else angles, (free_poses.data_ptr() if F else None), (angles.data_ptr() if J else None)
 
     def pose_batch(self, free_poses, angles, poses=None, stream=None):
         """free_poses: CUDA float32 [..., F, 7]; angles: CUDA float32 [..., J] -> poses [..., K, 7]; enqueue only."""
-        import torch
-        lead, n, dev, pf, pa = self._fk_args(free_poses, angles)
+        torch = _torch or _torch_module()
+        lead, n, source, pf, pa = self._fk_args(free_poses, angles)
         if poses is None:
-            poses = torch.empty(lead + (self.K, 7), dtype=torch.float32, device=dev)
+            poses = torch.empty(lead + (self.K, 7), dtype=torch.float32, device=source.device)
         else:
             assert poses.is_cuda and poses.is_contiguous() and poses.dtype == torch.float32
-            assert tuple(poses.shape) == lead + (self.K, 7)
+            assert poses.shape == lead + (self.K, 7)
         if stream is None:
-            stream = torch.cuda.current_stream(dev).cuda_stream
-        _check(lib().pxr_pose_batch(self._h, pf, pa, n, poses.data_ptr(), C.c_void_p(stream)))
+            stream = _current_stream(source)
+        _check(_lib.pxr_pose_batch(self._h, pf, pa, n, poses.data_ptr(), stream))
         return poses
 
     def render_batch_kinematic(self, free_poses, angles, shapes=None, step0=0, env0=0, poses=None, frames=None,
                                want_ids=False, stream=None):
         """free_poses [B,S,F,7], angles [B,S,J] -> (frames, ids or None, poses [B,S,K,7]); enqueue only."""
-        import torch
-        lead, n, dev, pf, pa = self._fk_args(free_poses, angles)
+        torch = _torch or _torch_module()
+        lead, n, source, pf, pa = self._fk_args(free_poses, angles)
         B, S = lead
         if poses is None:
-            poses = torch.empty((B, S, self.K, 7), dtype=torch.float32, device=dev)
+            poses = torch.empty((B, S, self.K, 7), dtype=torch.float32, device=source.device)
         if frames is None:
-            frames = torch.empty((B, S, self.H, self.W, 3), dtype=torch.uint8, device=dev)
-        assert poses.is_contiguous() and tuple(poses.shape) == (B, S, self.K, 7) and poses.dtype == torch.float32
-        assert frames.is_contiguous() and tuple(frames.shape) == (B, S, self.H, self.W, 3) and frames.dtype == torch.uint8
+            frames = torch.empty((B, S, self.H, self.W, 3), dtype=torch.uint8, device=source.device)
+        assert poses.is_contiguous() and poses.shape == (B, S, self.K, 7) and poses.dtype == torch.float32
+        assert frames.is_contiguous() and frames.shape == (B, S, self.H, self.W, 3) and frames.dtype == torch.uint8
         if shapes is not None:
             assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous()
-            assert tuple(shapes.shape) == (B, self.K, 4)
-        ids = torch.empty((B, S, self.H, self.W), dtype=torch.int32, device=dev) if want_ids else None
+            assert shapes.shape == (B, self.K, 4)
+        ids = torch.empty((B, S, self.H, self.W), dtype=torch.int32, device=source.device) if want_ids else None
         if stream is None:
-            stream = torch.cuda.current_stream(dev).cuda_stream
-        _check(lib().pxr_render_batch_kinematic(self._h, pf, pa, None if shapes is None else shapes.data_ptr(), B, S,
-                                                int(step0), int(env0), poses.data_ptr(), frames.data_ptr(),
-                                                None if ids is None else ids.data_ptr(), C.c_void_p(stream)))
+            stream = _current_stream(source)
+        _check(_lib.pxr_render_batch_kinematic(self._h, pf, pa, None if shapes is None else shapes.data_ptr(), B, S,
+                                               int(step0), int(env0), poses.data_ptr(), frames.data_ptr(),
+                                               None if ids is None else ids.data_ptr(), stream))
         return frames, ids, poses
 
 
@@ -367,8 +382,8 @@ class Scene:
                                       stream=None):
         """pxr_render_batch_kinematic_static: like render_batch_kinematic, the poses staying in the library's own
         static device buffer.  `frames` (and `ids`, if wanted) must be given: this call allocates nothing."""
-        import torch
-        lead, n, dev, pf, pa = self._fk_args(free_poses, angles)
+        torch = _torch or _torch_module()
+        lead, n, source, pf, pa = self._fk_args(free_poses, angles)
         B, S = lead
         assert frames is not None and frames.is_cuda and frames.is_contiguous() and frames.dtype == torch.uint8
         assert tuple(frames.shape) == (B, S, self.H, self.W, 3)
@@ -378,10 +393,10 @@ class Scene:
             assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous()
             assert tuple(shapes.shape) == (B, self.K, 4)
         if stream is None:
-            stream = torch.cuda.current_stream(dev).cuda_stream
-        _check(lib().pxr_render_batch_kinematic_static(self._h, pf, pa, None if shapes is None else shapes.data_ptr(), B, S,
-                                                       int(step0), int(env0), frames.data_ptr(),
-                                                       None if ids is None else ids.data_ptr(), C.c_void_p(stream)))
+            stream = _current_stream(source)
+        _check(_lib.pxr_render_batch_kinematic_static(self._h, pf, pa, None if shapes is None else shapes.data_ptr(), B, S,
+                                                      int(step0), int(env0), frames.data_ptr(),
+                                                      None if ids is None else ids.data_ptr(), stream))
         return frames, ids
 
 
@@ -424,18 +439,18 @@ class Conv:
 
     def forward(self, frames, out=None, stream=None):
         """frames: CUDA uint8 [B,S,H,W,3] -> CUDA bfloat16 [B,Ho,Wo,32]; enqueue only."""
-        import torch
+        torch = _torch or _torch_module()
         assert frames.is_cuda and frames.dtype == torch.uint8 and frames.is_contiguous()
-        B = int(frames.shape[0])
-        assert tuple(frames.shape) == (B, self.S, self.H, self.W, 3), tuple(frames.shape)
+        B = frames.shape[0]
+        assert frames.shape == (B, self.S, self.H, self.W, 3), tuple(frames.shape)
         if out is None:
             out = torch.empty((B, self.Ho, self.Wo, self.C), dtype=torch.bfloat16, device=frames.device)
         else:
             assert out.is_cuda and out.is_contiguous() and out.dtype == torch.bfloat16
-            assert tuple(out.shape) == (B, self.Ho, self.Wo, self.C)
+            assert out.shape == (B, self.Ho, self.Wo, self.C)
         if stream is None:
-            stream = torch.cuda.current_stream(frames.device).cuda_stream
-        _check(lib().pxr_conv_forward(self._h, frames.data_ptr(), B, out.data_ptr(), C.c_void_p(stream)))
+            stream = _current_stream(frames)
+        _check(_lib.pxr_conv_forward(self._h, frames.data_ptr(), B, out.data_ptr(), stream))
         return out
 
 
@@ -460,19 +475,19 @@ class Pipeline:
 
     def step(self, poses, shapes, frames, features, step0=0, env0=0, stream=None):
         """poses [B,S,K,7], shapes [B,K,4] or None -> frames [B,S,H,W,3] uint8, features [B,Ho,Wo,32] bf16 (both given)."""
-        import torch
+        torch = _torch or _torch_module()
         sc, cv = self.scene, self.conv
-        B = int(poses.shape[0])
-        assert poses.is_cuda and poses.dtype == torch.float32 and poses.is_contiguous() and tuple(poses.shape) == (B, cv.S, sc.K, 7)
+        B = poses.shape[0]
+        assert poses.is_cuda and poses.dtype == torch.float32 and poses.is_contiguous() and poses.shape == (B, cv.S, sc.K, 7)
         if shapes is not None:
-            assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous() and tuple(shapes.shape) == (B, sc.K, 4)
-        assert frames.is_cuda and frames.is_contiguous() and frames.dtype == torch.uint8 and tuple(frames.shape) == (B, cv.S, sc.H, sc.W, 3)
+            assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous() and shapes.shape == (B, sc.K, 4)
+        assert frames.is_cuda and frames.is_contiguous() and frames.dtype == torch.uint8 and frames.shape == (B, cv.S, sc.H, sc.W, 3)
         assert features.is_cuda and features.is_contiguous() and features.dtype == torch.bfloat16
-        assert tuple(features.shape) == (B, cv.Ho, cv.Wo, cv.C)
+        assert features.shape == (B, cv.Ho, cv.Wo, cv.C)
         if stream is None:
-            stream = torch.cuda.current_stream(poses.device).cuda_stream
-        _check(lib().pxr_pipeline_step(self._h, poses.data_ptr(), None if shapes is None else shapes.data_ptr(), B,
-                                       int(step0), int(env0), frames.data_ptr(), features.data_ptr(), C.c_void_p(stream)))
+            stream = _current_stream(poses)
+        _check(_lib.pxr_pipeline_step(self._h, poses.data_ptr(), None if shapes is None else shapes.data_ptr(), B,
+                                      int(step0), int(env0), frames.data_ptr(), features.data_ptr(), stream))
         return frames, features
 
 
