@@ -550,9 +550,9 @@ struct ResolveRange {
 // roll (NO_ROLL: the right vector is horizontal) so is the whole ground test, which then costs one division per image
 // row, not one per pixel.
 // RAGGED: the width is no multiple of 4.  A row's last group is then partial, and a group's twelve bytes start at any
-// byte: they leave as one unaligned 12-byte store, the last group's pixels byte by byte.  (One pixel per lane with byte
+// byte: they leave as one unaligned 12-byte store, the last group's pixels as two shorter ones.  (One pixel per lane with byte
 // stores and a ground test with its division per pixel, which such widths took before: 11 840 quadruped frames of 71x71
-// with the colour distractor 254 us, now 201.)
+// with the colour distractor 254 us, now 196.)
 template <int NT, bool UNIT_CELL, bool NO_ROLL, bool VIDEO, bool RAGGED, ResolvePart PART>
 __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const ResolveCtx& rc, const float* body,
                                                const float* cxcy, const float4* rows, u64* keys, uint8_t* out,
@@ -632,12 +632,18 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
                 if (whole) {
                     __builtin_memcpy(vid, vsrc, 12);
                 } else {
-                    const uint32_t n_bytes = (sc.W - i0) * 3u;  // 3, 6 or 9
-                    for (uint32_t b = 0; b < n_bytes; ++b) {
-                        const uint32_t v = (uint32_t)vsrc[b] << (8u * (b & 3u));
-                        vid[0] |= b < 4u ? v : 0u;
-                        vid[1] |= b >= 4u && b < 8u ? v : 0u;
-                        vid[2] |= b >= 8u ? v : 0u;
+                    // (the twelve bytes that end with the row - it has eight pixels or more -, moved down to their place)
+                    uint32_t end[3];
+                    __builtin_memcpy(end, vsrc - (4u - (sc.W & 3u)) * 3u, 12);
+                    if ((sc.W & 3u) == 3u) {
+                        vid[0] = __builtin_amdgcn_alignbit(end[1], end[0], 24u);
+                        vid[1] = __builtin_amdgcn_alignbit(end[2], end[1], 24u);
+                        vid[2] = end[2] >> 24;
+                    } else if ((sc.W & 3u) == 2u) {
+                        vid[0] = __builtin_amdgcn_alignbit(end[2], end[1], 16u);
+                        vid[1] = end[2] >> 16;
+                    } else {
+                        vid[0] = end[2] >> 8;
                     }
                 }
             }
@@ -794,17 +800,27 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
                     make_uint4(0xFFFFFFFFu - low[0], 0xFFFFFFFFu - low[1], 0xFFFFFFFFu - low[2], 0xFFFFFFFFu - low[3]);
         } else {
             uint8_t* dst = out + p0 * 3u;
+            const uint32_t id4[4] = {0xFFFFFFFFu - low[0], 0xFFFFFFFFu - low[1], 0xFFFFFFFFu - low[2], 0xFFFFFFFFu - low[3]};
             if (whole) {
                 __builtin_memcpy(dst, ow, 12);
-            } else {
-#pragma unroll
-                for (uint32_t b = 0; b < 9u; ++b)
-                    if (b < (sc.W - i0) * 3u) dst[b] = (uint8_t)(ow[b >> 2] >> (8u * (b & 3u)));
-            }
-            if (out_ids) {
-#pragma unroll
-                for (uint32_t k = 0; k < 4u; ++k)
-                    if (k == 0u || i0 + k < sc.W) out_ids[p0 + k] = 0xFFFFFFFFu - low[k];
+                if (out_ids) __builtin_memcpy(out_ids + p0, id4, 16);
+            } else {  // 1, 2 or 3 pixels, the same number for every row's last group
+                const uint16_t high = (uint16_t)(ow[0] >> 16), low1 = (uint16_t)ow[1];
+                if ((sc.W & 3u) == 1u) {
+                    __builtin_memcpy(dst, ow, 2);
+                    dst[2] = (uint8_t)high;
+                } else if ((sc.W & 3u) == 2u) {
+                    __builtin_memcpy(dst, ow, 4);
+                    __builtin_memcpy(dst + 4, &low1, 2);
+                } else {
+                    __builtin_memcpy(dst, ow, 8);
+                    dst[8] = (uint8_t)ow[2];
+                }
+                if (out_ids) {
+                    out_ids[p0] = id4[0];
+                    if ((sc.W & 3u) > 1u) out_ids[p0 + 1u] = id4[1];
+                    if ((sc.W & 3u) > 2u) out_ids[p0 + 2u] = id4[2];
+                }
             }
         }
         if (PART != kBesideWindow) g += NT;
