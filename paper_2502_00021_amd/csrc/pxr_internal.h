@@ -36,6 +36,10 @@ constexpr uint32_t kBandListEntries = 1024;
 // turn, 16 small ones are one).  Humanoid and box, us per launch with 80 / 160 / 240 / 400: 256x256 141 / 139 / 139 / 139,
 // 384x384 142 / 142 / 147 / 147, 512x512 125 / 125 / 140 / 150; a mesh scene at 512x512 138 / 138 / 147 / 194.
 constexpr uint32_t kBandListsFrom = 160;
+// ... or this many, if one round (one triangle per lane) looks at all of the frame's.  A mesh scene, without lists / with
+// them from 50 / from 30 turns: 160x160 132 / 133 / 125, 192x192 130 / 130 / 121, 256x256 137 / 120 / 119, 320x320 164 / 147 /
+// 147; quadrupeds 192x192 86 / 85 / 85; everything else within 1 %.
+constexpr uint32_t kBandListsFromOneRound = 30;
 // Windowed frames take half a compute unit's LDS (two workgroups cover each other's barriers) if that leaves room for this
 // share of the frame's keys, in per cent, and all of it otherwise (fewer bands).  us per launch, half / all, and the share
 // that half leaves: humanoid and box 128x128 157 / 201 (20 %), 160x160 142 / 151 (12), 192x192 150 / 145 (8.2), 256x256

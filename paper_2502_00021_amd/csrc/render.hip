@@ -1357,9 +1357,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             win.y_lo = (int)range.y0;
             win.y_hi = (int)(range.y0 + range.rows) - 1;
             n_keys = win.pitch * held;
-            const u64 bins = fu->bins;
+            const uint32_t n_tiny = uniform((uint32_t)fu->bins & 0xFFFFu), n_small = uniform((uint32_t)fu->bins >> 16),
+                           n_large = uniform((uint32_t)(fu->bins >> 32));
             by_lists = scb.lds_blist != 0 && n_rows > held &&
-                       uniform((uint32_t)(bins >> 32) + (((uint32_t)bins >> 16) >> (6u - kSmallLanesLog2))) >= kBandListsFrom;
+                       n_large + (n_small >> (6u - kSmallLanesLog2)) >= (n_tiny + n_small + n_large <= NT ? kBandListsFromOneRound : kBandListsFrom);
         } else {
             more_bands = false;
         }
