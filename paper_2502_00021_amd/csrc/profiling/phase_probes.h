@@ -30,7 +30,7 @@ __device__ unsigned long long g_wave_arrival[1024 * 8 * 16];  // per barrier and
 #else
 #define PXR_TIMED_BARRIER(i)                                                                              \
     {                                                                                                         \
-        unsigned long long* arr = reinterpret_cast<unsigned long long*>(lds + sc.lds_misc + 128);             \
+        unsigned long long* arr = reinterpret_cast<unsigned long long*>(lds + sc.lds_misc + 256);             \
         if (lane == 0) arr[tid >> 6] = __builtin_readcyclecounter();                                          \
         __syncthreads();                                                                                      \
         if (tid < NT / 64) {                                                                                  \

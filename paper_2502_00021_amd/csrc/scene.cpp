@@ -483,6 +483,9 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
         o += c.H * 16;
         c.lds_misc = o;
         o += 64 * 4;
+#ifdef PXR_PROFILING_BUILD
+        o += 16 * 8;  // (the wavefronts' arrival times, behind the frame's uniforms)
+#endif
         c.lds_body = o;
         o += c.K * kBodyStride * 4;
         c.lds_vxy = o;  // (x, y) pairs: 8-byte aligned, as everything before it is a multiple of 16
