@@ -843,8 +843,9 @@ __device__ __forceinline__ float from_quad(float x) {
 // terms' magnitudes: e_i is widened by 2^-18 of them.  If the box lies in front of the near plane as a whole, its
 // projection lies between the extremes of x / z over it; one pixel is added on each side for the projection's own
 // rounding (2^-20 of at most 512 pixels) and for the distance from a coordinate to the next pixel centre.  In every other
-// case - the box reaches the near plane, or something is not a number - every pixel counts; a box behind the plane as a
-// whole shows nothing.
+// case - the box reaches the near plane, something is not a number, or a depth is beyond the range in which the hardware's
+// reciprocal is known to be good (beyond 2^126 it returns 0, and half the box would project to the frame's centre) - every
+// pixel counts; a box behind the plane as a whole shows nothing.
 __device__ __forceinline__ void add_reach(const SceneConsts& sc, const float* body, uint32_t* reach, uint32_t lane) {
     const uint32_t axis = lane & 3u;
     for (uint32_t k0 = 0; k0 < sc.K; k0 += 16u) {
@@ -869,7 +870,8 @@ __device__ __forceinline__ void add_reach(const SceneConsts& sc, const float* bo
         const float last = __builtin_fmaf(sc.f, other * (other > 0.0f ? near_inv : far_inv), half);
         const uint32_t n = axis == 0u ? sc.W : sc.H;
         uint32_t begin = 0u, end = n;
-        const bool bounded = z_lo > sc.z_near && first <= last;  // (of this axis; not if anything is not a number)
+        // (of this axis; not if anything is not a number)
+        const bool bounded = z_lo > sc.z_near && z_lo >= kRecipMin && z_hi <= kRecipMax && first <= last;
         if (bounded) {
             begin = (uint32_t)__builtin_fminf(__builtin_fmaxf(first - 1.0f, 0.0f), 512.0f);
             end = min((uint32_t)__builtin_fminf(__builtin_fmaxf(last + 2.0f, 0.0f), 512.0f), n);

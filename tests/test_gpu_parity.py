@@ -205,6 +205,26 @@ def test_key_window_of_large_frames(torch, pxr, orc, W, H, mode):
     assert_parity(gpu_render(torch, pxr, w, step0=1, threads=256), ref)
 
 
+@pytest.mark.parametrize("exponent", [99, 100, 124, 125, -100, -128])
+def test_key_window_at_the_ends_of_the_float_range(torch, pxr, orc, exponent):
+    """Scenes in units of 2^99 m and more, 2^-100 m and less: multiplied by a power of two every step of the geometry is
+    the same, but reciprocals of depths vanish or overflow.  (From 2^125 on the windows once cut pixels off: the
+    hardware's reciprocal of a depth beyond 2^126 is 0.)"""
+    w = _scattered(256, 200, np.random.default_rng(5))
+    unit = np.float32(2.0 ** exponent)
+    w["poses"][..., :3] = np.float32([0, 0, 1]) + np.float32(0.45) * (w["poses"][..., :3] - np.float32([0, 0, 1]))
+    w["poses"][5, 0, 1:, 0] = -3.1  # (still behind the camera)
+    w["poses"][..., :3] *= unit  # (a few units from the origin: nothing overflows)
+    w["shapes"] = w["shapes"] * unit
+    d = w["desc"]
+    d["cam_offset"] = tuple(float(np.float32(c) * unit) for c in d["cam_offset"])
+    d["z_near"], d["z_far"] = float(np.float32(d["z_near"]) * unit), min(50.0 * 2.0 ** exponent, 3e38)
+    assert np.isfinite(w["poses"]).all()
+    ref = oracle_render(orc, w)
+    assert ((ref["ids"][:5] < GROUND).sum(axis=(1, 2, 3)) > 300).all()
+    assert_parity(gpu_render(torch, pxr, w), ref)
+
+
 @pytest.mark.parametrize("W,H,video", [(256, 256, False), (163, 200, True), (84, 84, True), (300, 37, False)])
 def test_large_frames_shared_by_workgroups_or_not(torch, pxr, orc, W, H, video):
     """Small batches give a large frame's rows to several workgroups, large ones a frame to each: the same frames, and the
