@@ -835,9 +835,9 @@ __device__ __forceinline__ float from_quad(float x) {
 }
 
 // Which pixels of the frame the bodies can touch (reach.h; one wavefront; four lanes per body, lanes 0 to 2 of the four take
-// an axis each).  A body that is out of view along one axis of the image touches nothing along the other either: without
-// that, one far to a side stretched the window up to the frame's edge (4096 quadruped frames of 192x192 with a leg above the
-// frame 148 us, now @Q@).
+// an axis each).  A body that is out of view along one axis of the image touches nothing along the other either: counted
+// all the same, one beside the frame stretches the window up to the frame's edge (the box out of view to the right / left /
+// above, 1472 humanoid-and-box frames of 128x128 75 / 77 / 84 us, now 63.5; 320 of 256x256 85 / 84 / 96 us, now 69.5).
 __device__ __forceinline__ void add_reach(const SceneConsts& sc, const float* body, uint32_t* reach, uint32_t lane) {
     const uint32_t axis = lane & 3u;
     for (uint32_t k0 = 0; k0 < sc.K; k0 += 16u) {
