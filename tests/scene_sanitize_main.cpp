@@ -35,6 +35,19 @@ pxr_scene_desc scene(uint32_t W, uint32_t H, const std::vector<pxr_body_desc>& b
     return s;
 }
 
+// Which layout a scene gets: `layout` looks at the constants of the scene that was built.
+template <class Layout>
+int expect_layout(const pxr_scene_desc& d, const char* what, const Layout& layout) {
+    pxr::HostScene hs;
+    std::string err;
+    if (pxr::build_host_scene(d, hs, err) != PXR_OK || !layout(hs.c)) {
+        std::fprintf(stderr, "%s: %u bytes of LDS, %u keys, rows of %u: not the layout expected %s\n", what, hs.c.lds_total,
+                     hs.c.key_capacity, hs.c.pitch, err.c_str());
+        return 1;
+    }
+    return 0;
+}
+
 int expect(const pxr_scene_desc& d, bool ok, const char* what) {
     pxr::HostScene hs;
     std::string err;
@@ -119,6 +132,11 @@ int main() {
       bad += expect(scene(64, 64, b), false, "negative multiplier"); ++n; }
     { std::vector<pxr_body_desc> heavy(40, body(PXR_SPHERE, 0.2f, 0.2f, 0.2f, 0.0f, 64, 32));
       bad += expect(scene(64, 64, heavy), false, "more geometry than LDS holds"); ++n; }
+
+    // layouts
+    const std::vector<pxr_body_desc> fine = {body(PXR_SPHERE, 0.5f, 0.5f, 0.5f, 0.0f, 64, 32), body(PXR_CAPSULE, 0.2f, 0.2f, 0.2f, 0.4f, 64, 8)};
+    bad += expect_layout(scene(84, 84, fine), "5060 vertices: one workgroup per compute unit, whole frames",
+                         [](const pxr::SceneConsts& c) { return c.key_capacity == 0 && c.lds_total > 80u * 1024u; }); ++n;
     if (bad) return 1;
     std::printf("ok %d\n", n);
     return 0;
