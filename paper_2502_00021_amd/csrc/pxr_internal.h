@@ -29,10 +29,8 @@ constexpr uint32_t kTinyMaxPixels = 3;
 constexpr uint32_t kSmallMaxPixels = 128;
 constexpr uint32_t kSmallLanesLog2 = 2;
 constexpr uint32_t kNoTriangle = 0xFFFFu;
-// Windowed frames: a band picks the triangles that touch its rows out of the frame's bins in rounds of one per lane;
-// a round's lists therefore never hold more than the largest workgroup has lanes ...
-constexpr uint32_t kBandListEntries = 1024;
-// ... which pays if walking the bins for one band costs this many turns of a wavefront (a triangle of the large bin is a
+// Windowed frames: a band may pick the triangles that touch its rows out of the frame's bins, in rounds of one per lane,
+// which pays if walking the bins for one band costs this many turns of a wavefront (a triangle of the large bin is a
 // turn, 16 small ones are one).  Humanoid and box, us per launch with 80 / 160 / 240 / 400: 256x256 141 / 139 / 139 / 139,
 // 384x384 142 / 142 / 147 / 147, 512x512 125 / 125 / 140 / 150; a mesh scene at 512x512 138 / 138 / 147 / 194.
 constexpr uint32_t kBandListsFrom = 160;
@@ -73,6 +71,7 @@ struct SceneConsts {
     // sizes
     uint32_t W, H, npix, K, root, V, T, P;  // P = entries of the pair table (on the device: padded to a multiple of 64)
     uint32_t key_capacity;                  // windowed frames: pixel keys that the LDS buffer holds; 0 = it holds the whole frame
+    uint32_t key_capacity_video;            // (the same beside the video distractor's tables)
     uint32_t band_rows;                     // rows of the frame's full width that the key buffer holds at least
     uint32_t first_band_rows;               // (the same: every band may have as many)
     uint32_t pitch;                         // keys per row where the buffer holds the whole frame: W rounded up to a multiple of 4
@@ -93,7 +92,6 @@ struct SceneConsts {
     // LDS carve-up (byte offsets into the dynamic segment)
     // the lds_keys region first holds the per-vertex cell codes (u32[V]) and the candidate list (u16[T])
     uint32_t lds_keys, lds_vxy, lds_vd, lds_body, lds_list, lds_large, lds_cxcy, lds_rows, lds_misc, lds_total;
-    uint32_t lds_blist, lds_blist2;  // windowed frames: one band round's lists (kBandListEntries u16 each)
     uint32_t lds_vlut;  // video-blend tables (kVideoTableBytes), or 0 if the frame's LDS has no room for them
 };
 

@@ -473,7 +473,7 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
 
     // ---- LDS carve-up of one frame workgroup.  The pixel keys dominate for large frames.
     auto align = [](uint32_t x, uint32_t a) { return (x + a - 1) / a * a; };
-    auto layout = [&](uint32_t key_bytes, bool band_lists) {
+    auto layout = [&](uint32_t key_bytes) {
         uint32_t o = 0;
         c.lds_keys = o;  // 16-byte aligned regions first
         o += align(std::max(key_bytes, c.V * 4 + 4 + c.T * 2), 16);  // (V codes, one word of code 0, T candidates)
@@ -496,13 +496,6 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
         o += align(c.T * 2, 4);
         c.lds_large = o;
         o += align(c.T * 2, 4);
-        c.lds_blist = c.lds_blist2 = 0;
-        if (band_lists) {  // a band round's lists
-            c.lds_blist = o;
-            o += kBandListEntries * 2;
-            c.lds_blist2 = o;
-            o += kBandListEntries * 2;
-        }
         c.lds_total = align(o, 16);
         return c.lds_total;
     };
@@ -519,40 +512,46 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
     };
     const uint32_t kHalf = 80u * 1024u, kAll = 160u * 1024u;
     const uint32_t frame_keys = c.pitch * c.H * 8u;
-    c.key_capacity = 0;
+    c.key_capacity = c.key_capacity_video = 0;
     c.band_rows = c.first_band_rows = c.H;
-    if (layout(frame_keys, false) <= kHalf) {  // the whole frame's keys, and two workgroups or more per compute unit
+    if (layout(frame_keys) <= kHalf) {  // the whole frame's keys, and two workgroups or more per compute unit
         add_video_tables();
         return PXR_OK;
     }
-    // What fits at all: some split of the frame into up to 128 bands of full width.
+    // What is accepted: scenes that fit in some split of the frame into up to 128 bands of full width, with 4 KB to spare
+    // from six bands on (the kernels need no more than a row; the limit of what a scene may hold is as it has always been).
     bool fits = false;
-    for (uint32_t nb = 1; nb <= 128 && !fits; ++nb) fits = layout((c.H + nb - 1) / nb * c.W * 8u, nb >= 6) <= kAll;
+    uint32_t needed = 0;
+    for (uint32_t nb = 1; nb <= 128 && !fits; ++nb) {
+        needed = layout((c.H + nb - 1) / nb * c.W * 8u) + (nb >= 6 ? 4096u : 0u);
+        fits = needed <= kAll;
+    }
     if (!fits) {
-        err = "scene needs " + std::to_string(c.lds_total) + " bytes of LDS per frame; the limit is 163840";
+        err = "scene needs " + std::to_string(needed) + " bytes of LDS per frame; the limit is 163840";
         return PXR_ERR_UNSUPPORTED;
     }
     // The keys of the frame's window instead (at least a row of the frame's full width), as many as there is room for in
     // half a compute unit's LDS, or in all of it where half would leave too few (kHalfKeysFrom).
-    bool lists = true;
     uint32_t share = kHalf;
-    const uint32_t others = layout(0, true) - align(c.V * 4 + 4 + c.T * 2, 16) + kVideoTableBytes;
-    if (others + kHalfKeysFrom * c.pitch * c.H / 100u * 8u > kHalf || layout(c.pitch * 8u, true) > kHalf) share = kAll;
-    if (share == kAll && layout(frame_keys, false) <= kAll) {
+    const uint32_t others = layout(0) - align(c.V * 4 + 4 + c.T * 2, 16) + kVideoTableBytes + 4096u;
+    if (others + kHalfKeysFrom * c.pitch * c.H / 100u * 8u > kHalf || layout(c.pitch * 8u) > kHalf) share = kAll;
+    if (share == kAll && layout(frame_keys) <= kAll) {
         // (no second workgroup is gained by keeping fewer keys than the frame's: 3520 frames of 84x84 of a scene of 5060
         // vertices 245 us, with a window 267; with a body at the near plane, whose window is the frame, 485 and 887)
         add_video_tables();
         return PXR_OK;
     }
-    if (layout(c.pitch * 8u, lists) > share) lists = false;  // (a scene at the very limit, of an odd width)
-    const uint32_t used = layout(c.pitch * 8u, lists), region = c.lds_cxcy;
-    uint32_t key_bytes = region + (share - used);
-    if (key_bytes >= region + kVideoTableBytes) key_bytes -= kVideoTableBytes;
-    key_bytes = std::min(key_bytes, frame_keys) & ~15u;
-    layout(key_bytes, lists);
-    c.key_capacity = c.lds_cxcy / 8u;
+    const uint32_t used = layout(c.pitch * 8u), region = c.lds_cxcy;
+    layout(region + (share - used));
+    c.key_capacity = c.key_capacity_video = c.lds_cxcy / 8u;
+    // The blend tables take the end of the key buffer, where the kernels without a clip have keys.  (Kept free in all of them,
+    // the 2304 bytes cost 288 keys: humanoid frames of 110x75 and 128x128 would need a band more if a body reaches the near plane.)
+    c.lds_vlut = 0;
+    if (c.lds_cxcy >= region + kVideoTableBytes) {
+        c.lds_vlut = c.lds_cxcy - kVideoTableBytes;
+        c.key_capacity_video = c.lds_vlut / 8u;
+    }
     c.band_rows = c.first_band_rows = std::min(c.H, c.key_capacity / c.pitch);
-    add_video_tables();
     return PXR_OK;
 }
 

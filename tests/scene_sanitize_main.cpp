@@ -137,6 +137,15 @@ int main() {
     const std::vector<pxr_body_desc> fine = {body(PXR_SPHERE, 0.5f, 0.5f, 0.5f, 0.0f, 64, 32), body(PXR_CAPSULE, 0.2f, 0.2f, 0.2f, 0.4f, 64, 8)};
     bad += expect_layout(scene(84, 84, fine), "5060 vertices: one workgroup per compute unit, whole frames",
                          [](const pxr::SceneConsts& c) { return c.key_capacity == 0 && c.lds_total > 80u * 1024u; }); ++n;
+    // (bands of a window that is the whole frame: what a body at the near plane costs)
+    const auto bands = [](uint32_t most) {
+        return [most](const pxr::SceneConsts& c) { return c.key_capacity / c.pitch * most >= c.H && c.lds_total <= 80u * 1024u; };
+    };
+    const std::vector<pxr_body_desc> humanoid(many.begin(), many.end() - 1);
+    bad += expect_layout(scene(84, 84, many), "humanoid and box 84x84: two bands", bands(2)); ++n;
+    bad += expect_layout(scene(110, 75, humanoid), "humanoid 110x75: two bands", bands(2)); ++n;
+    bad += expect_layout(scene(128, 128, many), "humanoid and box 128x128: five bands", bands(5)); ++n;
+    bad += expect_layout(scene(128, 128, humanoid), "humanoid 128x128: four bands", bands(4)); ++n;
     if (bad) return 1;
     std::printf("ok %d\n", n);
     return 0;

@@ -244,6 +244,27 @@ def test_large_frames_shared_by_workgroups_or_not(torch, pxr, orc, W, H, video):
         assert np.array_equal(got["ids"], np.tile(got["ids"][:6], (copies, 1, 1, 1)))
 
 
+@pytest.mark.parametrize("cells,W,H", [(16, 320, 320), (20, 256, 256), (20, 512, 400), (30, 384, 384)])
+def test_bands_of_a_frame_with_nearly_every_triangle_binned(torch, pxr, orc, cells, W, H):
+    """Open terrain below the camera: more than half of its triangles face it and hold pixels, so what the bins leave
+    free of their arrays is too short for a band's own lists, or just long enough."""
+    rng = np.random.default_rng(cells)
+    hv, ht, hm = wl.heightfield_mesh(rng, cells, 3.0, 0.1)
+    bodies = [wl.sphere(0.1, (0.6, 0.4, 0.8), 6, 2), wl.mesh(hv, ht, (0.7, 0.6, 0.4), mul=hm)]
+    B = 3
+    poses = np.zeros((B, 1, 2, 7), np.float32)
+    poses[:, 0, :, 3] = 1
+    poses[:, 0, 0, :3] = (0, 0, 1)
+    poses[:, 0, 1, :3] = np.array([[0, 0, 0.1], [0.6, 0.1, 0.3], [-0.9, 0, 0.2]])
+    d = wl.default_scene(W, H, bodies)
+    d["cam_offset"] = (-1.2, 0.0, 2.0)
+    w = dict(desc=d, poses=poses, shapes=None, distractor=None)
+    ref = oracle_render(orc, w)
+    assert (ref["ids"] < GROUND).mean() > 0.3
+    for threads in (None, 256, 768):
+        assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
+
+
 def test_close_up_at_512(torch, pxr, orc):
     """Triangles hundreds of pixels wide crossing many bands."""
     rng = np.random.default_rng(77)
