@@ -39,10 +39,17 @@ constexpr uint32_t kBandListsFrom = 160;
 // 147; quadrupeds 192x192 86 / 85 / 85; everything else within 1 %.
 constexpr uint32_t kBandListsFromOneRound = 30;
 // Windowed frames take half a compute unit's LDS (two workgroups cover each other's barriers) if that leaves room for this
-// share of the frame's keys, in per cent, and all of it otherwise (fewer bands).  us per launch, half / all, and the share
-// that half leaves: humanoid and box 128x128 157 / 201 (20 %), 160x160 142 / 151 (12), 192x192 150 / 145 (8.2), 256x256
-// 160 / 140 (4.3); a mesh scene 256x256 119 / 134 (11); quadrupeds 256x256 92 / 99 (7.7).
-constexpr uint32_t kHalfKeysFrom = 8;
+// share of the frame's keys, in per cent, and all of it otherwise (fewer bands).  us per launch of 25 million pixels, half /
+// all, and the share that half leaves (%):
+//   humanoid and box  128x128 64/83 (23)    144x144 66/75 (18)    160x160 64/67 (14)    176x176 67/60 (12)    192x192 74/65 (10)
+//   64 bodies         160x160 107/115 (22)  192x192 101/104 (15)  224x224 108/105 (11)  256x256 123/105 (8)
+//   quadrupeds        176x176 39/53 (19)    192x192 42/53 (16)    224x224 43/45 (11)    256x256 49.6/49.8 (8)  288x288 49/34 (7)
+//   meshes            192x192 62/66 (21)    224x224 58/62 (15)    256x256 72/70 (11)    288x288 66/53 (9)
+//   capsules          224x224 31/34 (17)    256x256 35/37 (13)    288x288 34/28 (10)
+// No share is right for every scene: 12 costs the quadrupeds of 224x224 5 %, a line at 11 would cost the humanoids of 176x176 11 %.
+// What a body at the near plane costs (the window is the frame then): humanoid and box 144x144 247/171, 160x160 241/151, but
+// quadrupeds 224x224 400/431, capsules 160x160 305/484.
+constexpr uint32_t kHalfKeysFrom = 12;
 // ... and run 768 threads below this many pixels (two workgroups then have registers to spare), 1024 from there on (more
 // lanes for the pixels).  us per launch, 768 / 1024: 84x84 over a clip 418 / 450, 96x96 190 / 188, 128x128 156 / 157,
 // 160x160 144 / 142, 192x192 155 / 150, 256x256 180 / 166.
