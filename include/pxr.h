@@ -254,7 +254,8 @@ int pxr_conv_set_tuning(pxr_conv* c, uint32_t band_rows, uint32_t n_groups);
  * ordering is by events only, and the caller's stream is made to wait for the last layer before the call
  * returns (enqueue only, no host synchronisation, no allocation).  Frames and features are byte for byte those
  * of pxr_render_batch followed by pxr_conv_forward.  n_chunks = 1 is that serial order, and
- * so is a step of fewer than 400 million pixels (B * S * H * W), where overlapping costs more than it gains. */
+ * so is a step whose frames and features take fewer than 2.4 GB (B * (3 * S * H * W + 64 * Ho * Wo) bytes), where
+ * overlapping costs more than it gains, unless pxr_pipeline_set_overlap_from says otherwise. */
 typedef struct pxr_pipeline pxr_pipeline; /* opaque, owned by the library; borrows the scene and the layer */
 
 /* Host only: one stream and n_chunks + 1 events.  The layer's input size must be the scene's frame size; its
@@ -267,6 +268,11 @@ int pxr_pipeline_destroy(pxr_pipeline* p);
  * one pipeline must be ordered among themselves (one stream, or events): they share the second stream. */
 int pxr_pipeline_step(pxr_pipeline* p, const float* d_poses, const float* d_shapes, uint32_t B, uint32_t step0,
                       uint32_t env0, uint8_t* d_frames, uint16_t* d_features, void* hip_stream);
+/* Bytes of frames and features from which later steps are cut into chunks (host only; 0 = every step, UINT64_MAX = none;
+ * no passage of the paper).  The output does not depend on it.  Errors: INVALID_ARG (null). */
+int pxr_pipeline_set_overlap_from(pxr_pipeline* p, uint64_t bytes);
+/* Into how many chunks a step of B environments is cut (host only; no passage of the paper).  Errors: INVALID_ARG. */
+int pxr_pipeline_info(const pxr_pipeline* p, uint32_t B, uint32_t* chunks);
 
 /* Scene facts for callers and tests (sizes of what pxr_create_scene built; no passage of the paper): total
  * template vertices and triangles, dynamic LDS bytes per frame workgroup, threads per workgroup.  Any out

@@ -20,16 +20,33 @@ struct pxr_pipeline {
     hipStream_t side = nullptr;
     hipEvent_t rendered[pxr::kMaxPipelineChunks] = {};
     hipEvent_t consumed = nullptr;
+    uint64_t overlap_from;  // bytes of frames and features from which a step is cut into chunks
 };
 
 namespace {
 
-// Overlap pays from this many rendered pixels on.  What it gains (a few per cent: a conv workgroup gets onto a compute
-// unit only in a render workgroup's place) grows with the batch; what it costs does not: an event and a wait per chunk,
-// more launches, each with a last wave of workgroups that leaves compute units empty.  64x64 frames of the humanoid and
-// box, stacks of three, us per step in order / with 2 / 4 / 8 chunks: 65 536 environments 4997 / 4939 / 4904 / 4875,
-// 16 384 1224 / 1221 / 1290 / 1276, 2048 150 / 180 / 205 / 258; 64 quadruped environments 15 / 68 / 115 / 205.
-constexpr uint64_t kOverlapFromPixels = 400000000ull;
+// Overlap pays from this many bytes of frames and features on.  What it gains (a few per cent where rendering takes most
+// of the step, because a conv workgroup gets onto a compute unit only in a render workgroup's place, and up to ten where the
+// layer does) grows with the batch; what it costs does not: an event and a wait per chunk, more launches, each with a last
+// wave of workgroups that leaves compute units empty.  Time in order over time with 4 chunks (2 / 8), at GB of both:
+//   humanoid and box, 64x64 x 3    1.6 0.96 (1.02 0.97)   2.0 0.98 (0.99 0.95)   2.4 1.01 (1.00 0.98)   3.2 1.02 (1.00 0.96)   6.4 1.02 (1.01 1.03)
+//   quadrupeds, 64x64 x 3          1.6 0.95 (1.01 0.92)   3.2 1.01 (1.00 0.95)   4.8 1.02 (1.01 1.01)   6.4 1.02 (1.01 1.03)
+//   humanoids, 84x84 x 4, clip     1.6 0.95 (0.97 0.90)   2.4 0.96 (0.99 0.93)   3.1 0.99 (1.00 0.95)   4.7 1.01 (1.01 0.98)
+//   quadrupeds, 128x128 x 1        0.6 0.91 (0.96 0.84)   1.2 1.03 (0.98 0.91)   2.5 1.10 (1.07 1.15)   5.0 1.06 (1.00 1.11)
+//   capsules, 128x128 x 1          0.6 0.87 (0.92 0.84)   1.2 0.98 (0.96 0.92)   2.5 1.07 (1.04 1.13)   5.0 1.06 (0.99 1.10)
+//   64 quadruped environments, 64x64 x 3: 15 us in order, 68 / 115 / 205 with 2 / 4 / 8 chunks.
+constexpr uint64_t kOverlapFromBytes = 2400000000ull;
+
+uint32_t chunk_envs(const pxr_pipeline* p, uint32_t B) {
+    // whole multiples of four environments (every chunk's buffers keep the 16-byte alignment of the batch's); a whole batch
+    // where overlapping does not pay
+    uint32_t K, H, W, cH, cW, S, Ho, Wo;
+    pxr::scene_shape(p->scene, &K, &H, &W);
+    pxr::conv_shape(p->conv, &cH, &cW, &S, &Ho, &Wo);
+    const uint64_t bytes = (uint64_t)B * (3ull * S * H * W + 64ull * Ho * Wo);
+    if (p->n_chunks == 1 || bytes < p->overlap_from) return B;
+    return ((uint32_t)(((uint64_t)B + p->n_chunks - 1) / p->n_chunks) + 3u) & ~3u;
+}
 
 }  // namespace
 
@@ -49,6 +66,7 @@ int pxr_pipeline_create(pxr_scene* s, pxr_conv* c, uint32_t n_chunks, pxr_pipeli
     p->scene = s;
     p->conv = c;
     p->n_chunks = n_chunks;
+    p->overlap_from = kOverlapFromBytes;
     hipError_t rc = hipGetDevice(&p->device);
     // (default priority: streams of different priorities must not be mixed on these machines)
     if (rc == hipSuccess) rc = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
@@ -91,20 +109,18 @@ int pxr_pipeline_step(pxr_pipeline* p, const float* d_poses, const float* d_shap
     if ((reinterpret_cast<uintptr_t>(d_poses) & 3u) || (reinterpret_cast<uintptr_t>(d_shapes) & 15u) ||
         (reinterpret_cast<uintptr_t>(d_frames) & 3u) || (reinterpret_cast<uintptr_t>(d_features) & 15u))
         return set_error(PXR_ERR_INVALID_ARG, "pxr_pipeline_step: poses/frames must be 4-byte and shapes/features 16-byte aligned");
-    uint32_t K, H, W, cH, cW, S, Ho, Wo;
-    pxr::scene_shape(p->scene, &K, &H, &W);
+    uint32_t cH, cW, S, Ho, Wo;
     pxr::conv_shape(p->conv, &cH, &cW, &S, &Ho, &Wo);
     hipStream_t main = reinterpret_cast<hipStream_t>(hip_stream);
     std::string err;
-    if (p->n_chunks == 1 || (uint64_t)B * S * H * W < kOverlapFromPixels) {
+    const uint32_t per = chunk_envs(p, B);
+    if (per >= B) {
         // both stages in order on the caller's stream: no events, no second launch of either
         int rc = pxr::render_envs(p->scene, d_poses, d_shapes, 0, B, S, step0, env0, d_frames, nullptr, main, err);
         if (rc == PXR_OK) rc = pxr::conv_envs(p->conv, d_frames, 0, B, d_features, main, err);
         if (rc != PXR_OK) return set_error(rc, "pxr_pipeline_step: " + err);
         return PXR_OK;
     }
-    // chunks of whole multiples of four environments (every chunk's buffers keep the 16-byte alignment of the batch's)
-    const uint32_t per = ((B + p->n_chunks - 1) / p->n_chunks + 3u) & ~3u;
     uint32_t used = 0;
     for (uint32_t e0 = 0; e0 < B; e0 += per, ++used) {
         const uint32_t n = B - e0 < per ? B - e0 : per;
@@ -120,6 +136,19 @@ int pxr_pipeline_step(pxr_pipeline* p, const float* d_poses, const float* d_shap
     hipError_t hrc = hipEventRecord(p->consumed, p->side);
     if (hrc == hipSuccess) hrc = hipStreamWaitEvent(main, p->consumed, 0);
     if (hrc != hipSuccess) return set_error(PXR_ERR_DEVICE, std::string("pxr_pipeline_step: ") + hipGetErrorString(hrc));
+    return PXR_OK;
+}
+
+int pxr_pipeline_set_overlap_from(pxr_pipeline* p, uint64_t bytes) {
+    if (!p) return pxr::set_error(PXR_ERR_INVALID_ARG, "pxr_pipeline_set_overlap_from: null handle");
+    p->overlap_from = bytes;
+    return PXR_OK;
+}
+
+int pxr_pipeline_info(const pxr_pipeline* p, uint32_t B, uint32_t* chunks) {
+    if (!p || !chunks || B == 0) return pxr::set_error(PXR_ERR_INVALID_ARG, "pxr_pipeline_info: null argument or B == 0");
+    const uint32_t per = chunk_envs(p, B);
+    *chunks = per >= B ? 1u : (uint32_t)(((uint64_t)B + per - 1) / per);
     return PXR_OK;
 }
 

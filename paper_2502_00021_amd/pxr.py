@@ -112,7 +112,10 @@ def lib():
         L.pxr_pipeline_create.argtypes = [vp, vp, u32, C.POINTER(vp)]
         L.pxr_pipeline_destroy.argtypes = [vp]
         L.pxr_pipeline_step.argtypes = [vp, vp, vp, u32, u32, u32, vp, vp, vp]
-        for name in ("pxr_pipeline_create", "pxr_pipeline_destroy", "pxr_pipeline_step"):
+        L.pxr_pipeline_set_overlap_from.argtypes = [vp, C.c_uint64]
+        L.pxr_pipeline_info.argtypes = [vp, u32, C.POINTER(u32)]
+        for name in ("pxr_pipeline_create", "pxr_pipeline_destroy", "pxr_pipeline_step", "pxr_pipeline_set_overlap_from",
+                     "pxr_pipeline_info"):
             getattr(L, name).restype = C.c_int
         L.pxr_selftest_arithmetic.argtypes = [vp]
         L.pxr_selftest_arithmetic.restype = C.c_int
@@ -472,6 +475,16 @@ class Pipeline:
             self.close()
         except Exception:
             pass
+
+    def set_overlap_from(self, n_bytes):
+        """Bytes of frames and features from which steps are cut into chunks (0 = always)."""
+        _check(lib().pxr_pipeline_set_overlap_from(self._h, int(n_bytes)))
+
+    def chunks(self, B):
+        """Into how many chunks a step of B environments is cut."""
+        n = C.c_uint32()
+        _check(lib().pxr_pipeline_info(self._h, int(B), C.byref(n)))
+        return n.value
 
     def step(self, poses, shapes, frames, features, step0=0, env0=0, stream=None):
         """poses [B,S,K,7], shapes [B,K,4] or None -> frames [B,S,H,W,3] uint8, features [B,Ho,Wo,32] bf16 (both given)."""

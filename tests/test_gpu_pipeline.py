@@ -51,6 +51,8 @@ def test_pipeline_equals_serial_order(torch, pxr, cfg, B, chunks):
     ref_feat = conv.forward(ref_frames)
     torch.cuda.synchronize()
     pipe = pxr.Pipeline(sc, conv, chunks)
+    pipe.set_overlap_from(0)  # (by default batches as small as these run in order)
+    assert pipe.chunks(B) == -(-B // (-(-B // chunks) + 3 & ~3))
     frames = torch.full_like(ref_frames, 0x5A)
     feat = torch.full_like(ref_feat, -1.0)
     for rep in range(3):  # steps in a row share the second stream and the events
@@ -67,6 +69,14 @@ def test_pipeline_equals_serial_order(torch, pxr, cfg, B, chunks):
         pipe.step(poses, shapes, frames, feat, step0=7, env0=5)
     side.synchronize()
     assert torch.equal(frames, ref_frames) and torch.equal(feat.view(torch.int16), ref_feat.view(torch.int16))
+    # and in order
+    pipe.set_overlap_from(2 ** 64 - 1)
+    assert pipe.chunks(B) == 1
+    frames.fill_(0)
+    feat.fill_(0)
+    pipe.step(poses, shapes, frames, feat, step0=7, env0=5)
+    torch.cuda.synchronize()
+    assert torch.equal(frames, ref_frames) and torch.equal(feat.view(torch.int16), ref_feat.view(torch.int16))
     pipe.close()
     conv.close()
     sc.close()
@@ -74,7 +84,8 @@ def test_pipeline_equals_serial_order(torch, pxr, cfg, B, chunks):
 
 @pytest.mark.parametrize("chunks", [1, 4, 7])
 def test_pipeline_of_a_batch_large_enough_to_overlap(torch, pxr, chunks):
-    """Just above the 400 million pixels from which a step is cut into chunks on two streams (a ragged last chunk)."""
+    """Above the 2.4 GB of frames and features from which a step is cut into chunks on two streams (a ragged last chunk),
+    one frame per environment; a smaller batch runs in order."""
     B = 100003
     poses = torch.from_numpy(wl.make(1, B=16)["poses"]).cuda()
     poses = (poses[torch.arange(B, device="cuda") % 16] + torch.linspace(0, 0.3, B, device="cuda")[:, None, None, None] *
@@ -82,10 +93,12 @@ def test_pipeline_of_a_batch_large_enough_to_overlap(torch, pxr, chunks):
     sc = pxr.Scene(dict(wl.make(1, B=1)["desc"], width=64, height=64))
     rng = np.random.default_rng(8)
     conv = pxr.Conv(64, 64, 1, (rng.standard_normal((3, 3, 3, 32)) * 0.15).astype(np.float32), np.zeros(32, np.float32))
-    assert B * 64 * 64 >= 400_000_000
     ref_frames, _ = sc.render_batch(poses)
     ref_feat = conv.forward(ref_frames)
     pipe = pxr.Pipeline(sc, conv, chunks)
+    per_env = 3 * 64 * 64 + 64 * 31 * 31
+    assert B * per_env > 2_400_000_000 and pipe.chunks(B) == chunks
+    assert pipe.chunks(2_400_000_000 // per_env) == 1 and pipe.chunks(2_400_000_000 // per_env + 1) == chunks
     frames, feat = torch.full_like(ref_frames, 0x5A), torch.full_like(ref_feat, -1.0)
     for rep in range(2):
         pipe.step(poses, None, frames, feat)
@@ -113,6 +126,10 @@ def test_pipeline_argument_errors(torch, pxr):
     assert L.pxr_pipeline_step(pipe._h, None, None, 8, 0, 0, frames.data_ptr(), feat.data_ptr(), None) == pxr.ERR_INVALID_ARG
     assert L.pxr_pipeline_step(pipe._h, poses.data_ptr(), None, 0, 0, 0, frames.data_ptr(), feat.data_ptr(), None) == pxr.ERR_INVALID_ARG
     assert L.pxr_pipeline_step(pipe._h, poses.data_ptr(), None, 8, 0, 0, frames.data_ptr(), feat.data_ptr() + 2, None) == pxr.ERR_INVALID_ARG
+    assert L.pxr_pipeline_set_overlap_from(None, 0) == pxr.ERR_INVALID_ARG
+    n = C.c_uint32()
+    assert L.pxr_pipeline_info(pipe._h, 0, C.byref(n)) == pxr.ERR_INVALID_ARG
+    assert L.pxr_pipeline_info(None, 8, C.byref(n)) == pxr.ERR_INVALID_ARG
     assert L.pxr_pipeline_destroy(None) == pxr.OK
     torch.cuda.synchronize()
     pipe.close()
