@@ -141,9 +141,12 @@ def _torch_module():
     return _torch
 
 
-def _current_stream(tensor):
-    """The raw handle of the current stream of a tensor's GPU (without building a Stream object on every call)."""
-    return _torch._C._cuda_getCurrentRawStream(tensor.get_device())
+def _stream_handle(stream, tensor):
+    """The caller's stream handle (an integer), or that of the current stream of the tensor's GPU (without building a
+    Stream object on every call)."""
+    if stream is None:
+        return _torch._C._cuda_getCurrentRawStream(tensor.get_device())
+    return C.c_void_p(stream)  # (an integer or a TypeError: as a pointer argument, ctypes would take text and bytes)
 
 
 def _check(rc):
@@ -308,8 +311,7 @@ class Scene:
         if ids is not None:
             assert ids.is_cuda and ids.is_contiguous() and ids.dtype == torch.int32
             assert ids.shape == (B, S, self.H, self.W)
-        if stream is None:
-            stream = _current_stream(poses)
+        stream = _stream_handle(stream, poses)
         _check(_lib.pxr_render_batch(self._h, poses.data_ptr(), None if shapes is None else shapes.data_ptr(),
                                      B, S, int(step0), int(env0), frames.data_ptr(),
                                      None if ids is None else ids.data_ptr(), stream))
@@ -352,8 +354,7 @@ class Scene:
         else:
             assert poses.is_cuda and poses.is_contiguous() and poses.dtype == torch.float32
             assert poses.shape == lead + (self.K, 7)
-        if stream is None:
-            stream = _current_stream(source)
+        stream = _stream_handle(stream, source)
         _check(_lib.pxr_pose_batch(self._h, pf, pa, n, poses.data_ptr(), stream))
         return poses
 
@@ -373,8 +374,7 @@ class Scene:
             assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous()
             assert shapes.shape == (B, self.K, 4)
         ids = torch.empty((B, S, self.H, self.W), dtype=torch.int32, device=source.device) if want_ids else None
-        if stream is None:
-            stream = _current_stream(source)
+        stream = _stream_handle(stream, source)
         _check(_lib.pxr_render_batch_kinematic(self._h, pf, pa, None if shapes is None else shapes.data_ptr(), B, S,
                                                int(step0), int(env0), poses.data_ptr(), frames.data_ptr(),
                                                None if ids is None else ids.data_ptr(), stream))
@@ -395,8 +395,7 @@ class Scene:
         if shapes is not None:
             assert shapes.is_cuda and shapes.dtype == torch.float32 and shapes.is_contiguous()
             assert tuple(shapes.shape) == (B, self.K, 4)
-        if stream is None:
-            stream = _current_stream(source)
+        stream = _stream_handle(stream, source)
         _check(_lib.pxr_render_batch_kinematic_static(self._h, pf, pa, None if shapes is None else shapes.data_ptr(), B, S,
                                                       int(step0), int(env0), frames.data_ptr(),
                                                       None if ids is None else ids.data_ptr(), stream))
@@ -451,8 +450,7 @@ class Conv:
         else:
             assert out.is_cuda and out.is_contiguous() and out.dtype == torch.bfloat16
             assert out.shape == (B, self.Ho, self.Wo, self.C)
-        if stream is None:
-            stream = _current_stream(frames)
+        stream = _stream_handle(stream, frames)
         _check(_lib.pxr_conv_forward(self._h, frames.data_ptr(), B, out.data_ptr(), stream))
         return out
 
@@ -497,8 +495,7 @@ class Pipeline:
         assert frames.is_cuda and frames.is_contiguous() and frames.dtype == torch.uint8 and frames.shape == (B, cv.S, sc.H, sc.W, 3)
         assert features.is_cuda and features.is_contiguous() and features.dtype == torch.bfloat16
         assert features.shape == (B, cv.Ho, cv.Wo, cv.C)
-        if stream is None:
-            stream = _current_stream(poses)
+        stream = _stream_handle(stream, poses)
         _check(_lib.pxr_pipeline_step(self._h, poses.data_ptr(), None if shapes is None else shapes.data_ptr(), B,
                                       int(step0), int(env0), frames.data_ptr(), features.data_ptr(), stream))
         return frames, features

@@ -176,3 +176,21 @@ def test_two_scenes_on_two_streams_and_two_host_threads():
     t.start()
     t.join()
     assert b"pxr_scene_info" in seen["bad"]
+
+
+def test_calls_without_a_stream_go_to_the_current_one():
+    import torch
+    from paper_2502_00021_amd import pxr
+    w = wl.make(1, B=4)
+    sc = pxr.Scene(w["desc"])
+    poses = torch.from_numpy(w["poses"]).cuda()
+    sc.render_batch(poses)
+    assert pxr._stream_handle(None, poses) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert pxr._stream_handle(None, poses) == side.cuda_stream != 0
+    assert pxr._stream_handle(None, poses) == torch.cuda.current_stream().cuda_stream
+    with pytest.raises(TypeError):
+        sc.render_batch(poses, stream=side)  # (its .cuda_stream is what is taken)
+    torch.cuda.synchronize()
+    sc.close()

@@ -198,3 +198,14 @@ def test_profiling_builds_do_not_replace_the_library():
     r = subprocess.run([sys.executable, "-m", "paper_2502_00021_amd.build", "--define", "PXR_STOP_AFTER=1"],
                        cwd=ROOT, capture_output=True, text=True)
     assert r.returncode != 0 and "--out" in r.stderr
+
+
+def test_a_stream_is_an_integer_handle():
+    """What is not one is refused before anything is enqueued (as a pointer argument ctypes would take the address of a
+    text)."""
+    from paper_2502_00021_amd import pxr
+    assert pxr._stream_handle(0x1234, None).value == 0x1234
+    assert pxr._stream_handle(0, None).value is None
+    for wrong in (b"stream", "stream", 1.5, [1]):
+        with pytest.raises(TypeError):
+            pxr._stream_handle(wrong, None)
