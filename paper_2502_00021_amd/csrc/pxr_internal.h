@@ -79,8 +79,6 @@ struct SceneConsts {
     uint32_t W, H, npix, K, root, V, T, P;  // P = entries of the pair table (on the device: padded to a multiple of 64)
     uint32_t key_capacity;                  // windowed frames: pixel keys that the LDS buffer holds; 0 = it holds the whole frame
     uint32_t key_capacity_video;            // (the same beside the video distractor's tables)
-    uint32_t band_rows;                     // rows of the frame's full width that the key buffer holds at least
-    uint32_t first_band_rows;               // (the same: every band may have as many)
     uint32_t pitch;                         // keys per row where the buffer holds the whole frame: W rounded up to a multiple of 4
     uint32_t magic_groups;                  // ceil(2^32 / (pitch / 4)): g / (pitch / 4) == mulhi(g, magic_groups) for every group of four pixels
     uint32_t magicW;  // ceil(2^32 / W): p / W == mulhi(p, magicW) for every pixel index p < 512 * W

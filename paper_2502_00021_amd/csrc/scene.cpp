@@ -513,7 +513,6 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
     const uint32_t kHalf = 80u * 1024u, kAll = 160u * 1024u;
     const uint32_t frame_keys = c.pitch * c.H * 8u;
     c.key_capacity = c.key_capacity_video = 0;
-    c.band_rows = c.first_band_rows = c.H;
     if (layout(frame_keys) <= kHalf) {  // the whole frame's keys, and two workgroups or more per compute unit
         add_video_tables();
         return PXR_OK;
@@ -551,7 +550,6 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
         c.lds_vlut = c.lds_cxcy - kVideoTableBytes;
         c.key_capacity_video = c.lds_vlut / 8u;
     }
-    c.band_rows = c.first_band_rows = std::min(c.H, c.key_capacity / c.pitch);
     return PXR_OK;
 }
 

@@ -70,7 +70,23 @@ int expect(const pxr_scene_desc& d, bool ok, const char* what) {
                 return 1;
             }
         }
-        if (hs.c.lds_total > 160u * 1024u || hs.c.band_rows == 0 || hs.c.band_rows > hs.c.H || hs.c.first_band_rows > hs.c.band_rows + hs.c.H) {
+        // What the kernel takes for granted of the key buffer, the bytes in front of lds_cxcy: it holds the frame's keys or, of a
+        // windowed frame, key_capacity of them, a row of the frame's width at least; codes and candidates fit as well; and
+        // the blend tables of a windowed frame lie behind key_capacity_video keys and behind the codes and candidates.
+        const pxr::SceneConsts& c = hs.c;
+        const uint32_t codes = c.V * 4 + 4 + c.T * 2;
+        bool fits = c.lds_total <= 160u * 1024u && c.pitch >= c.W && c.pitch % 4 == 0 && c.lds_cxcy % 16 == 0 && codes <= c.lds_cxcy &&
+                    c.lds_large + c.T * 2 <= c.lds_total;
+        if (c.key_capacity == 0) {
+            fits = fits && c.pitch * c.H * 8u <= c.lds_cxcy && c.key_capacity_video == 0 &&
+                   (c.lds_vlut == 0 || (c.lds_vlut >= c.lds_large + c.T * 2 && c.lds_vlut + pxr::kVideoTableBytes <= c.lds_total));
+        } else {
+            fits = fits && c.key_capacity * 8u <= c.lds_cxcy && c.key_capacity_video <= c.key_capacity && c.key_capacity_video >= c.pitch;
+            if (c.lds_vlut)
+                fits = fits && c.lds_vlut % 16 == 0 && c.key_capacity_video * 8u <= c.lds_vlut && codes <= c.lds_vlut &&
+                       c.lds_vlut + pxr::kVideoTableBytes <= c.lds_cxcy;
+        }
+        if (!fits) {
             std::fprintf(stderr, "%s: LDS layout out of range\n", what);
             return 1;
         }
@@ -106,6 +122,33 @@ int main() {
     bad += expect(scene(84, 84, many), true, "humanoid and box, banded"); ++n;
     std::vector<pxr_body_desc> sixty_four(64, body(PXR_SPHERE, 0.05f, 0.05f, 0.05f, 0.0f, 4, 2));
     bad += expect(scene(32, 32, sixty_four), true, "sixty-four bodies"); ++n;
+
+    // every kind of layout: odd and narrow sizes, scenes up to the limit of what LDS holds (the last ones are turned down)
+    {
+        int taken = 0, windowed = 0, without_tables = 0, refused = 0;
+        for (uint32_t lat = 2; lat <= 32; lat += 5)
+            for (uint32_t bodies = 1; bodies <= 7; bodies += 2)
+                for (const uint32_t w : {8u, 9u, 12u, 13u, 63u, 64u, 129u, 511u, 512u})
+                    for (const uint32_t h : {8u, 9u, 64u, 131u, 300u, 512u}) {
+                        const std::vector<pxr_body_desc> round(bodies, body(PXR_SPHERE, 0.2f, 0.2f, 0.2f, 0.0f, 64, lat));
+                        const pxr_scene_desc d = scene(w, h, round);
+                        pxr::HostScene hs;
+                        std::string err;
+                        if (pxr::build_host_scene(d, hs, err) != PXR_OK) {
+                            ++refused;
+                            continue;
+                        }
+                        ++taken;
+                        windowed += hs.c.key_capacity != 0;
+                        without_tables += hs.c.key_capacity != 0 && hs.c.lds_vlut == 0;
+                        bad += expect(d, true, "layout sweep");
+                    }
+        if (taken < 200 || windowed < 100 || without_tables < 1 || refused < 100) {
+            std::fprintf(stderr, "layout sweep: %d taken, %d windowed, %d without tables, %d refused\n", taken, windowed, without_tables, refused);
+            ++bad;
+        }
+        n += taken;
+    }
 
     // descriptions the builder must turn down (with a message, without touching anything out of bounds)
     { auto d = scene(64, 64, mix); d.n_bodies = 0; bad += expect(d, false, "no bodies"); ++n; }
