@@ -177,13 +177,12 @@ typedef struct {
 /* Bind (or with k == NULL remove) the scene's skeleton.  Host only; one small allocation and upload.  The
  * caller must have synchronised streams still using the previous skeleton.
  * Errors: INVALID_ARG (null array, n_bodies != the scene's, parent[k] >= k, slot out of range, non-finite
- * entry); UNSUPPORTED (the 64 frames a wavefront poses at a time do not fit the 160 KB of LDS:
- * (7*n_bodies + 7*n_free + n_angles) * 260 bytes); OOM; DEVICE. */
+ * entry); UNSUPPORTED (7*n_bodies + 7*n_free + n_angles above 630); OOM; DEVICE. */
 int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k);
 
 /* Forward kinematics for N frames: d_free_poses [N,n_free,7] and d_angles [N,n_angles] (may be NULL when
  * the count is 0) -> d_poses [N,n_bodies,7] (xyz, wxyz), all fp32 device buffers, 4-byte aligned.  One kernel,
- * one lane per frame; enqueue only.  Errors: INVALID_ARG (no skeleton bound, null or misaligned buffer,
+ * four wavefronts per 64 frames; enqueue only.  Errors: INVALID_ARG (no skeleton bound, null or misaligned buffer,
  * N == 0); DEVICE. */
 int pxr_pose_batch(pxr_scene* s, const float* d_free_poses, const float* d_angles, uint32_t n_frames,
                    float* d_poses, void* hip_stream);

@@ -298,8 +298,9 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
     sk.K = K;
     sk.J = k->n_angles;
     sk.F = k->n_free;
-    if ((uint64_t)sk.J + 7ull * sk.F + 7ull * K > 630ull || pxr::fk_lds_bytes(sk) > 160u * 1024u)
-        return fail(PXR_ERR_UNSUPPORTED, "pxr_set_skeleton: 64 frames of this skeleton do not fit 160 KB of LDS");
+    // (a limit of the interface: the kernel itself keeps only the poses in LDS, 64 * (7 K | 1) floats, for K <= 64 at most 115 KB)
+    if ((uint64_t)sk.J + 7ull * sk.F + 7ull * K > 630ull)
+        return fail(PXR_ERR_UNSUPPORTED, "pxr_set_skeleton: 7*n_bodies + 7*n_free + n_angles must not exceed 630");
     // one allocation: the records in order of depth (a parent precedes its child, so one pass finds the depths), then
     // where each depth begins
     std::vector<uint32_t> depth(K), begin(1, 0u);

@@ -193,7 +193,7 @@ int measure_peaks(double* fma_tlaneops, double* imad_tlaneops, double* copy_gbs,
 // (counts: reciprocal mismatches, floor-convert mismatches, patterns looked at by each check).
 int selftest_arithmetic(unsigned long long counts[4], std::string& err);
 
-// kinematics.hip: joint angles -> poses, one lane per frame.
+// kinematics.hip: joint angles -> poses, 64 frames per workgroup.
 uint32_t fk_lds_bytes(const SkeletonConsts& sk);
 int prepare_fk_kernel(std::string& err);
 int launch_fk(const SkeletonConsts& sk, const float* d_free_poses, const float* d_angles, uint32_t n_frames,

@@ -294,6 +294,27 @@ def test_full_size_pose_batch(torch, pxr, orc):
     sc.close()
 
 
+def test_skeleton_size_limit(torch, pxr, orc):
+    """7 n_bodies + 7 n_free + n_angles up to 630: 64 bodies, 26 of them free; one angle more is refused."""
+    rng = np.random.default_rng(630)
+    K, F = 64, 26
+    sc = pxr.Scene(wl.default_scene(32, 32, [wl.sphere(0.05, (0.5, 0.5, 0.5), 3, 1)] * K))
+    skel = wl._skeleton(K)
+    skel["slot"][:F] = rng.permutation(F)
+    for k in range(F, K):
+        wl._hinge(skel, k, parent=int(rng.integers(0, k)), slot=-1, anchor=rng.uniform(-0.2, 0.2, 3), axis=(0, 1, 0), offset=rng.uniform(-0.2, 0.2, 3))
+    with pytest.raises(pxr.PxrError) as e:
+        sc.set_skeleton(skel, F, 1)
+    assert e.value.code == pxr.ERR_UNSUPPORTED and "630" in str(e.value)
+    sc.set_skeleton(skel, F, 0)
+    free = rng.normal(size=(70, F, 7)).astype(np.float32)
+    free[..., 3:] /= np.linalg.norm(free[..., 3:], axis=-1, keepdims=True)
+    angles = np.zeros((70, 0), np.float32)
+    got = sc.pose_batch(torch.from_numpy(free).cuda(), torch.from_numpy(angles).cuda()).cpu().numpy()
+    assert_poses_close(got, orc.fk(skel, free, angles), skel)
+    sc.close()
+
+
 def test_skeleton_argument_errors(torch, pxr):
     w = wl.make(3, B=4)
     fk = w["fk"]
