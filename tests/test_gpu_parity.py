@@ -191,8 +191,10 @@ def _scattered(W, H, rng, B=6):
 @pytest.mark.parametrize("mode", ["none", "color", "video"])
 def test_key_window_of_large_frames(torch, pxr, orc, W, H, mode):
     """Frames whose keys do not fit the LDS keep those of the pixels that the bodies can touch: every place such a window
-    can have (inside, cut by each edge, the whole frame, nothing), rows in several bands, widths with a remainder."""
+    can have (inside, cut by each edge, the whole frame, nothing), rows in several bands, widths with a remainder.  (The two
+    smallest sizes keep all keys.)"""
     w = _scattered(W, H, np.random.default_rng(W * 1000 + H))
+    assert _windowed(pxr, w["desc"]) == (min(W, H) > 9)
     if mode == "color":
         w["desc"]["cam_up"] = (0.1, 0.2, 1.0)
         w["distractor"] = dict(mode="color", seed=3, scale=(0.5, 1.5), offset=(-0.2, 0.2))
@@ -228,13 +230,14 @@ def test_key_window_at_the_ends_of_the_float_range(torch, pxr, orc, exponent):
 @pytest.mark.parametrize("W,H,video", [(256, 256, False), (163, 200, True), (84, 84, True), (300, 37, False)])
 def test_large_frames_shared_by_workgroups_or_not(torch, pxr, orc, W, H, video):
     """Small batches give a large frame's rows to several workgroups, large ones a frame to each: the same frames, and the
-    oracle's."""
+    oracle's.  (84x84 frames of this scene keep all their keys and are not shared.)"""
     w = _scattered(W, H, np.random.default_rng(W + H))
+    assert _windowed(pxr, w["desc"]) == (W * H > 84 * 84)
     if video:
         clip = np.random.default_rng(2).integers(0, 256, (3, H, W, 3), dtype=np.uint8)
         w["distractor"] = dict(mode="video", seed=5, video=clip, alpha=0.5, env_offset=np.zeros(6, np.uint32))
     ref = oracle_render(orc, w)
-    for copies in (1, 3, 14, 50):  # 6, 18, 84 and 300 frames: 32, 8, 2 and no slabs
+    for copies in (1, 3, 14, 50):  # 6, 18, 84 and 300 frames: 32, 8, 2 and no slabs at 256x256, 8, 8, 2 and none at 300x37
         many = dict(w, poses=np.tile(w["poses"], (copies, 1, 1, 1)), shapes=np.tile(w["shapes"], (copies, 1, 1)))
         if video:
             many["distractor"] = dict(w["distractor"], env_offset=np.zeros(6 * copies, np.uint32))
@@ -263,6 +266,95 @@ def test_bands_of_a_frame_with_nearly_every_triangle_binned(torch, pxr, orc, cel
     assert (ref["ids"] < GROUND).mean() > 0.3
     for threads in (None, 256, 768):
         assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
+
+
+def _windowed(pxr, desc):
+    """Whether the scene's frames keep a window of their keys: with all of them, its LDS would be larger than it is."""
+    sc = pxr.Scene(desc)
+    info = sc.info()
+    sc.close()
+    W, H, K, V, T = desc["width"], desc["height"], len(desc["bodies"]), info["n_verts"], info["n_tris"]
+    up = lambda n, a: -(-n // a) * a
+    return info["lds_bytes"] < up(W, 4) * H * 8 + up(4 * (W + H), 16) + 16 * H + 256 + 96 * K + 12 * V + 2 * up(2 * T, 4)
+
+
+@pytest.mark.parametrize("W,H,lat", [(12, 512, 10), (9, 512, 10), (12, 512, 11), (64, 300, 12), (130, 64, 13), (300, 64, 13)])
+@pytest.mark.parametrize("mode", ["color", "video"])
+def test_key_window_of_scenes_at_the_lds_limit(torch, pxr, orc, W, H, lat, mode):
+    """More than 5300 vertices: frames three groups of pixels wide are windowed, and from 11 rings on there is no room for
+    the blend tables behind the keys."""
+    bodies = [wl.sphere(0.3, (0.7, 0.4, 0.3), 64, 32), wl.capsule(0.15, 0.3, (0.3, 0.6, 0.8), 64, lat)]
+    rng = np.random.default_rng(W + lat)
+    B = 5
+    poses = np.zeros((B, 1, 2, 7), np.float32)
+    poses[:, 0, :, 3:] = wl.random_quats(rng, (B, 2))
+    poses[:, 0, 0, :3] = (0, 0, 1)
+    poses[:, 0, 1, :3] = np.array([0.0, 0.0, 1.0]) + np.array([[0, 0, 0.5], [-1, 0, 0.4], [-2.4, 0, 1], [0, 9, 0], [-9, 0, 0]])
+    w = dict(desc=wl.default_scene(W, H, bodies), poses=poses, shapes=None)
+    if mode == "color":
+        w["distractor"] = dict(mode="color", seed=3, scale=(0.5, 1.5), offset=(-0.2, 0.2))
+    else:
+        w["distractor"] = dict(mode="video", seed=5, video=rng.integers(0, 256, (3, H, W, 3), dtype=np.uint8), alpha=0.5, env_offset=None)
+    assert _windowed(pxr, w["desc"])
+    ref = oracle_render(orc, w, step0=1)
+    assert (ref["ids"] < GROUND).any(axis=(1, 2, 3)).all()
+    assert_parity(gpu_render(torch, pxr, w, step0=1), ref)
+    assert_parity(gpu_render(torch, pxr, w, step0=1, threads=256), ref)
+
+
+@pytest.mark.parametrize("W,H", [(256, 256), (163, 130)])
+def test_key_window_with_non_finite_and_collapsed_poses(torch, pxr, orc, W, H):
+    """The inputs of test_rejected_and_degenerate_inputs in windowed frames: NaN and infinite positions and quaternions,
+    bodies behind the camera, through the near plane, without extent, far to a side."""
+    w = wl.make(2, B=14)
+    w["desc"].update(width=W, height=H)
+    assert _windowed(pxr, w["desc"])
+    p = w["poses"].copy()
+    p[0, 0, 0, 0] = np.nan
+    p[1, 0, 1:, 0] = -5.0
+    p[2, 0, 3, :3] = np.nan
+    p[3, 0, 2, 3:] = np.nan
+    p[4, 0, 0, 2] = -3.0
+    p[5, 0, 4, :3] = p[5, 0, 0, :3] + np.array([-2.45, 0, 1.0], np.float32)
+    p[6, 0, :, 3:] = 0.0
+    p[7, 0, 5, 1] = 1e6
+    p[8, 0, 3, 0] = np.inf
+    p[9, 0, 3, 2] = -np.inf
+    p[10, 0, 2, 4] = np.inf
+    p[11, 0, 2, 3:] *= 1e19     # (the rotation's entries overflow)
+    p[12, 0, 1, 3:] *= 1e-25    # (its squares vanish)
+    p[13, 0, 2:5, 3] = np.nan
+    w["poses"] = p
+    assert_parity(gpu_render(torch, pxr, w), oracle_render(orc, w))
+
+
+def test_key_window_of_sixty_four_bodies(torch, pxr, orc):
+    """Bodies past the sixteen that a wavefront bounds at a time decide the window."""
+    rng = np.random.default_rng(64)
+    bodies = [[wl.capsule(0.05, 0.12, (0.8, 0.3, 0.3), 5, 2), wl.sphere(0.08, (0.3, 0.8, 0.3), 6, 2), wl.box(0.07, 0.05, 0.06, (0.3, 0.3, 0.8), 1)][k % 3]
+              for k in range(64)]
+    B = 64
+    poses = np.zeros((B, 1, 64, 7), np.float32)
+    poses[..., :3] = np.array([0.0, 0.0, 1.0]) + rng.uniform(-0.1, 0.1, (B, 1, 64, 3))
+    for e in range(B):  # one body a long way from the others, another one in each environment
+        poses[e, 0, e, :3] += np.array([0.2, 0.9 * (-1) ** e, 0.5])
+    poses[..., 3:] = wl.random_quats(rng, (B, 1, 64))
+    w = dict(desc=wl.default_scene(200, 160, bodies, root_body=63), poses=poses, shapes=None, distractor=None)
+    assert _windowed(pxr, w["desc"])
+    ref = oracle_render(orc, w)
+    assert_parity(gpu_render(torch, pxr, w), ref)
+
+
+def test_video_frames_of_84_pixels_shared_by_workgroups(torch, pxr, orc):
+    """84x84 frames of a humanoid are windowed: 5 of them are shared by 16 workgroups each, 300 are not shared."""
+    w = wl.make(4, B=5)
+    assert _windowed(pxr, w["desc"])
+    w["distractor"] = dict(w["distractor"], env_offset=np.zeros(5, np.uint32))
+    ref = oracle_render(orc, w, step0=3)
+    assert_parity(gpu_render(torch, pxr, w, step0=3), ref)
+    many = dict(w, poses=np.tile(w["poses"], (60, 1, 1, 1)), distractor=dict(w["distractor"], env_offset=np.zeros(300, np.uint32)))
+    got = gpu_render(torch, pxr, many, step0=3)
+    assert np.array_equal(got["frames"], np.tile(ref["frames"], (60, 1, 1, 1, 1))) and np.array_equal(got["ids"], np.tile(ref["ids"], (60, 1, 1, 1)))
 
 
 def test_close_up_at_512(torch, pxr, orc):
