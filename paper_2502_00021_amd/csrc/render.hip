@@ -1337,13 +1337,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             win.y_lo = (int)range.y0;
             win.y_hi = (int)(range.y0 + range.rows) - 1;
             n_keys = win.pitch * held;
-            const uint32_t n_tiny = uniform((uint32_t)fu->bins & 0xFFFFu), n_small = uniform((uint32_t)fu->bins >> 16),
-                           n_large = uniform((uint32_t)(fu->bins >> 32));
-            // (the lists live in what the bins leave free of their arrays; at most half of a closed body's triangles are binned)
-            const uint32_t n_binned = n_tiny + n_small + n_large;
-            const bool room = n_binned - n_large + min(n_binned - n_large, (uint32_t)NT) <= scb.T && n_large + min(n_large, (uint32_t)NT) <= scb.T;
-            by_lists = n_rows > held && room &&
-                       n_large + (n_small >> (6u - kSmallLanesLog2)) >= (n_binned <= NT ? kBandListsFromOneRound : kBandListsFrom);
+            if (__builtin_expect(n_rows > held, 0)) {  // (most windows fit in one piece: 16 384 frames of 84x84 424 us without the branch, now 415)
+                const uint32_t n_tiny = uniform((uint32_t)fu->bins & 0xFFFFu), n_small = uniform((uint32_t)fu->bins >> 16),
+                               n_large = uniform((uint32_t)(fu->bins >> 32)), n_binned = n_tiny + n_small + n_large;
+                // (the lists live in what the bins leave free of their arrays; at most half of a closed body's triangles are binned)
+                const bool room = n_tiny + n_small + min(n_tiny, (uint32_t)NT) <= scb.T && n_large + min(n_small + n_large, (uint32_t)NT) <= scb.T;
+                by_lists = room && n_large + (n_small >> (6u - kSmallLanesLog2)) >= (n_binned <= NT ? kBandListsFromOneRound : kBandListsFrom);
+            }
         } else {
             more_bands = false;
         }
@@ -1448,8 +1448,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // one packed atomic per wavefront) into the round's own short lists, from which the raster loops then
             // work as above.  A band that holds a twentieth of the frame's triangles rasters a
             // twentieth of them, not all.
-            // The lists follow the bins in their arrays: in the first, tiny upwards behind the tiny bin and small downwards
-            // below the small one, in the second, large behind the large bin.  (In 4 KB of their own they cost every
+            // The lists lie in what the bins leave free of their arrays: tiny behind the tiny bin in the first, large behind the
+            // large bin in the second, small from the end of the second downwards.  (Small in the first as well would leave no
+            // room for them where more than half of the triangles are binned: meshes of 256x256 72 us, now 67.)  (In 4 KB of their own they cost every
             // windowed frame 512 keys, and often a band where a body at the near plane makes the window the whole frame: 3520
             // such humanoid-and-box frames of 84x84 346 us, now 265, 1472 of 128x128 301, now 263; 128x128 in view 70.0, now 64.3.)
             if (bands_done) __syncthreads();  // the previous band is resolved (its lanes left their keys cleared)
@@ -1457,7 +1458,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             const uint32_t n_tiny = (uint32_t)bins & 0xFFFFu, n_small = (uint32_t)bins >> 16, n_large = (uint32_t)(bins >> 32);
             const uint32_t n_binned = n_tiny + n_small + n_large;
             uint16_t* band_tiny = list + n_tiny;                     // (grows up)
-            uint16_t* band_small = list + (scb.T - 1 - n_small);     // (grows down)
+            uint16_t* band_small = list2 + (scb.T - 1);              // (grows down)
             uint16_t* band_large = list2 + n_large;
             constexpr uint32_t kTeam = 1u << kSmallLanesLog2;
             const uint2* tri_table = reinterpret_cast<const uint2*>(scb.tri_idx);
