@@ -39,17 +39,18 @@ constexpr uint32_t kBandListsFrom = 160;
 // 147; quadrupeds 192x192 86 / 85 / 85; everything else within 1 %.
 constexpr uint32_t kBandListsFromOneRound = 30;
 // Windowed frames take half a compute unit's LDS (two workgroups cover each other's barriers) if that leaves room for this
-// share of the frame's keys, in per cent, and all of it otherwise (fewer bands).  us per launch of 25 million pixels, half /
-// all, and the share that half leaves (%):
-//   humanoid and box  128x128 64/83 (23)    144x144 66/75 (18)    160x160 64/67 (14)    176x176 67/60 (12)    192x192 74/65 (10)
-//   64 bodies         160x160 107/115 (22)  192x192 101/104 (15)  224x224 108/105 (11)  256x256 123/105 (8)
-//   quadrupeds        176x176 39/53 (19)    192x192 42/53 (16)    224x224 43/45 (11)    256x256 49.6/49.8 (8)  288x288 49/34 (7)
-//   meshes            192x192 62/66 (21)    224x224 58/62 (15)    256x256 72/70 (11)    288x288 66/53 (9)
-//   capsules          224x224 31/34 (17)    256x256 35/37 (13)    288x288 34/28 (10)
-// No share is right for every scene: 12 costs the quadrupeds of 224x224 5 %, a line at 11 would cost the humanoids of 176x176 11 %.
-// What a body at the near plane costs (the window is the frame then): humanoid and box 144x144 247/171, 160x160 241/151, but
-// quadrupeds 224x224 400/431, capsules 160x160 305/484.
-constexpr uint32_t kHalfKeysFrom = 12;
+// share of the frame's keys, in thousandths, and all of it otherwise (fewer bands).  us per launch of 25 million pixels, half /
+// all, and the share that half leaves:
+//   humanoid and box  144x144 66/75 (177)   160x160 64/67 (141)   176x176 67/60 (115)   192x192 74/65 (95)    224x224 78/61 (68)
+//   humanoid          144x144 57/71 (185)   160x160 59/65 (148)   176x176 61/57 (120)   192x192 64/61 (105)   224x224 67/55 (75)
+//   64 bodies         176x176 104/106 (180) 192x192 100/104 (150) 224x224 107/105 (108) 256x256 121/105 (81)
+//   quadrupeds        192x192 42/53 (155)   224x224 43/45 (112)   256x256 50/50 (84)    288x288 49/34 (66)
+//   meshes            192x192 61/65 (207)   224x224 55/60 (150)   256x256 67/69 (114)   288x288 66/53 (89)
+//   capsules          224x224 31/34 (170)   256x256 35/38 (129)   288x288 35/29 (101)   320x320 41/34 (80)
+// and humanoids over a clip 192x192 139/163.  No share is right for every scene: the line costs the humanoids of 176x176 8 to
+// 12 %, one at 130 would cost the humanoids over the clip 17 % and quadrupeds and capsules up to 8 %.  What a body at the near plane
+// costs (the window is the frame then): humanoid and box 160x160 241/151, but quadrupeds 224x224 400/431, capsules 160x160 305/484.
+constexpr uint32_t kHalfKeysFrom = 103;
 // ... and run 768 threads below this many pixels (two workgroups then have registers to spare), 1024 from there on (more
 // lanes for the pixels).  us per launch, 768 / 1024: 84x84 over a clip 418 / 450, 96x96 190 / 188, 128x128 156 / 157,
 // 160x160 144 / 142, 192x192 155 / 150, 256x256 180 / 166.

@@ -533,7 +533,7 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
     // half a compute unit's LDS, or in all of it where half would leave too few (kHalfKeysFrom).
     uint32_t share = kHalf;
     const uint32_t others = layout(0) - align(c.V * 4 + 4 + c.T * 2, 16) + kVideoTableBytes;
-    if (others + kHalfKeysFrom * c.pitch * c.H / 100u * 8u > kHalf || layout(c.pitch * 8u) > kHalf) share = kAll;
+    if (others + kHalfKeysFrom * c.pitch * c.H / 1000u * 8u > kHalf || layout(c.pitch * 8u) > kHalf) share = kAll;
     if (share == kAll && layout(frame_keys) <= kAll) {
         // (no second workgroup is gained by keeping fewer keys than the frame's: 3520 frames of 84x84 of a scene of 5060
         // vertices 245 us, with a window 267; with a body at the near plane, whose window is the frame, 485 and 887)
