@@ -49,7 +49,8 @@ constexpr uint32_t kBandListsFromOneRound = 30;
 //   capsules          224x224 31/34 (170)   256x256 35/38 (129)   288x288 35/29 (101)   320x320 41/34 (80)
 // and humanoids over a clip 192x192 139/163.  No share is right for every scene: the line costs the humanoids of 176x176 8 to
 // 12 %, one at 130 would cost the humanoids over the clip 17 % and quadrupeds and capsules up to 8 %.  What a body at the near plane
-// costs (the window is the frame then): humanoid and box 160x160 241/151, but quadrupeds 224x224 400/431, capsules 160x160 305/484.
+// costs (the window is the frame then): humanoid and box 160x160 240/151, 176x176 268/165, but quadrupeds 224x224 400/431, capsules
+// 160x160 305/484.
 constexpr uint32_t kHalfKeysFrom = 103;
 // ... and run 768 threads below this many pixels (two workgroups then have registers to spare), 1024 from there on (more
 // lanes for the pixels).  us per launch, 768 / 1024: 84x84 over a clip 418 / 450, 96x96 190 / 188, 128x128 156 / 157,
