@@ -31,12 +31,12 @@ constexpr uint32_t kSmallLanesLog2 = 2;
 constexpr uint32_t kNoTriangle = 0xFFFFu;
 // Windowed frames: a band may pick the triangles that touch its rows out of the frame's bins, in rounds of one per lane,
 // which pays if walking the bins for one band costs this many turns of a wavefront (a triangle of the large bin is a
-// turn, 16 small ones are one).  Humanoid and box, us per launch with 80 / 160 / 240 / 400: 256x256 141 / 139 / 139 / 139,
-// 384x384 142 / 142 / 147 / 147, 512x512 125 / 125 / 140 / 150; a mesh scene at 512x512 138 / 138 / 147 / 194.
+// turn, 16 small ones are one).  Humanoid and box, us per launch with 80 / 160 / 400: 256x256 140 / 137 / 137, 384x384 141 /
+// 141 / 143, 512x512 126 / 126 / 149.
 constexpr uint32_t kBandListsFrom = 160;
-// ... or this many, if one round (one triangle per lane) looks at all of the frame's.  A mesh scene, without lists / with
-// them from 50 / from 30 turns: 160x160 132 / 133 / 125, 192x192 130 / 130 / 121, 256x256 137 / 120 / 119, 320x320 164 / 147 /
-// 147; quadrupeds 192x192 86 / 85 / 85; everything else within 1 %.
+// ... or this many, if one round (one triangle per lane) looks at all of the frame's.  A mesh scene, lists from 160 / 60 / 30
+// turns: 160x160 130 / 130 / 124, 192x192 127 / 127 / 119, 256x256 135 / 126 / 120, 320x320 163 / 147 / 148; everything else
+// within 1 %.
 constexpr uint32_t kBandListsFromOneRound = 30;
 // Windowed frames take half a compute unit's LDS (two workgroups cover each other's barriers) if that leaves room for this
 // share of the frame's keys, in thousandths, and all of it otherwise (fewer bands).  us per launch of 25 million pixels, half /
@@ -53,8 +53,8 @@ constexpr uint32_t kBandListsFromOneRound = 30;
 // 160x160 305/484.
 constexpr uint32_t kHalfKeysFrom = 103;
 // ... and run 768 threads below this many pixels (two workgroups then have registers to spare), 1024 from there on (more
-// lanes for the pixels).  us per launch, 768 / 1024: 84x84 over a clip 418 / 450, 96x96 190 / 188, 128x128 156 / 157,
-// 160x160 144 / 142, 192x192 155 / 150, 256x256 180 / 166.
+// lanes for the pixels).  us per launch, 768 / 1024: 84x84 over a clip 415 / 442, humanoid and box 84x84 217 / 222, 96x96 190 /
+// 185, 128x128 144 / 142, 160x160 138 / 134, humanoids 192x192 126 / 122, quadrupeds 192x192 84 / 80.
 constexpr uint32_t kWideWindowedFrom = 20000;
 
 // Per-body record kept in LDS for the duration of one frame (floats).

@@ -912,7 +912,7 @@ __device__ __forceinline__ void make_window(const SceneConsts& sc, uint32_t key_
 // whichever wavefronts are done with the raster phase first.  The bodies of the articulated scenes touch 7 to 17 % of a
 // frame, so most windows fit in one piece where the whole frame took two to five bands, each a walk over all binned
 // triangles and three barriers.  Against bands of whole rows: 16 384 humanoid frames of 84x84 over a clip 493 -> 415 us,
-// 1024 humanoid-and-box frames of 256x256 242 -> 163 us, 3648 of 128x128 237 -> 157 us, quadrupeds of 256x256 184 -> 100 us.
+// 1024 humanoid-and-box frames of 256x256 242 -> 156 us, 3648 of 128x128 237 -> 144 us, quadrupeds of 256x256 184 -> 98 us.
 // Frames whose keys fit as a whole beside a second workgroup (64x64) do not take it: the same number of instructions, and
 // the few wavefronts that get the window's pixels shade them all (65 536 x 3 frames 3.53 -> 3.81 ms).
 // 1 << slabs_log2 workgroups share a windowed frame, each takes a run of its rows (and repeats the geometry).
