@@ -189,10 +189,15 @@ int pxr_pose_batch(pxr_scene* s, const float* d_free_poses, const float* d_angle
 
 /* pxr_pose_batch over B*S frames followed by pxr_render_batch on the same stream: joint angles in, frames
  * out, nothing crossing the host.  d_poses [B,S,n_bodies,7] is caller-provided and receives the poses (a
- * learner usually wants them as well); the other arguments are those of the two calls. */
+ * learner usually wants them as well); the other arguments are those of the two calls.  Small batches are one
+ * launch: the render kernel makes the poses itself, the same bits (pxr_kinematic_info says which). */
 int pxr_render_batch_kinematic(pxr_scene* s, const float* d_free_poses, const float* d_angles, const float* d_shapes,
                                uint32_t B, uint32_t S, uint32_t step0, uint32_t env0, float* d_poses,
                                uint8_t* d_frames, uint32_t* d_ids, void* hip_stream);
+
+/* How many kernels pxr_render_batch_kinematic launches for n_frames = B * S frames (buffers that do not overlap):
+ * 1 or 2.  Errors: INVALID_ARG (null argument, n_frames == 0, no skeleton bound). */
+int pxr_kinematic_info(const pxr_scene* s, uint32_t n_frames, uint32_t* n_launches);
 
 /* pxr_render_batch_kinematic for callers that cannot allocate device memory or provide a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The poses between the two

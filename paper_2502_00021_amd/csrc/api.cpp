@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -41,8 +42,11 @@ void pxr::scene_shape(const pxr_scene* s, uint32_t* K, uint32_t* H, uint32_t* W)
     *W = s->sc.W;
 }
 
-int pxr::render_envs(pxr_scene* s, const float* d_poses, const float* d_shapes, uint32_t e0, uint32_t n, uint32_t S,
-                     uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids, void* stream, std::string& err) {
+namespace {
+
+// pxr::render_envs, which takes the poses as they are (fk null), or makes them in the same launch.
+int render_posed(pxr_scene* s, const pxr::FkArgs* fk, const float* d_poses, const float* d_shapes, uint32_t e0, uint32_t n, uint32_t S,
+                 uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids, void* stream, std::string& err) {
     if (n == 0 || S == 0 || (uint64_t)n * S > 0x7FFFFFFFull) {
         err = "B*S must lie in [1, 2^31-1]";
         return PXR_ERR_INVALID_ARG;
@@ -64,7 +68,14 @@ int pxr::render_envs(pxr_scene* s, const float* d_poses, const float* d_shapes, 
     pxr::DistractConsts dc = s->dc;  // the per-environment arrays follow the environments
     if (dc.env_offset) dc.env_offset += e0;
     if (dc.env_video) dc.env_video += e0;
-    return pxr::launch_render(s->sc, dc, poses, shapes, n * S, S, step0, env0 + e0, frames, ids, s->block_threads, s->n_cus, stream, err);
+    return pxr::launch_render(s->sc, dc, fk, poses, shapes, n * S, S, step0, env0 + e0, frames, ids, s->block_threads, s->n_cus, stream, err);
+}
+
+}  // namespace
+
+int pxr::render_envs(pxr_scene* s, const float* d_poses, const float* d_shapes, uint32_t e0, uint32_t n, uint32_t S,
+                     uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids, void* stream, std::string& err) {
+    return render_posed(s, nullptr, d_poses, d_shapes, e0, n, S, step0, env0, d_frames, d_ids, stream, err);
 }
 
 namespace {
@@ -302,8 +313,8 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
     if ((uint64_t)sk.J + 7ull * sk.F + 7ull * K > 630ull)
         return fail(PXR_ERR_UNSUPPORTED, "pxr_set_skeleton: 7*n_bodies + 7*n_free + n_angles must not exceed 630");
     // one allocation: the records in order of depth (a parent precedes its child, so one pass finds the depths), then
-    // where each depth begins
-    std::vector<uint32_t> depth(K), begin(1, 0u);
+    // where each depth begins, then the records' links
+    std::vector<uint32_t> depth(K), begin(1, 0u), links;
     std::vector<pxr::SkeletonRecord> records;
     for (uint32_t b = 0; b < K; ++b) depth[b] = k->parent[b] < 0 ? 0u : depth[(uint32_t)k->parent[b]] + 1u;
     for (uint32_t d = 0; records.size() < K; ++d) {
@@ -312,6 +323,9 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
             pxr::SkeletonRecord r{};
             r.body = b;
             r.parent = k->parent[b];
+            uint32_t parent_record = 0;
+            while (d > 0 && records[parent_record].body != (uint32_t)r.parent) ++parent_record;
+            links.push_back(d | (parent_record << 16));
             r.slot = k->slot[b];
             for (int c = 0; c < 3; ++c) {
                 r.anchor[c] = k->anchor[b * 3 + c];
@@ -323,9 +337,10 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
         begin.push_back((uint32_t)records.size());
     }
     sk.depths = (uint32_t)begin.size() - 1u;
-    std::vector<uint32_t> staging(K * (sizeof(pxr::SkeletonRecord) / 4) + begin.size());
+    std::vector<uint32_t> staging(K * (sizeof(pxr::SkeletonRecord) / 4) + begin.size() + K);
     std::memcpy(staging.data(), records.data(), K * sizeof(pxr::SkeletonRecord));
     std::memcpy(staging.data() + K * (sizeof(pxr::SkeletonRecord) / 4), begin.data(), begin.size() * 4);
+    std::memcpy(staging.data() + K * (sizeof(pxr::SkeletonRecord) / 4) + begin.size(), links.data(), K * 4);
     std::string err;
     int rc = pxr::prepare_fk_kernel(err);
     if (rc != PXR_OK) return fail(rc, "pxr_set_skeleton: " + err);
@@ -350,12 +365,14 @@ int pxr_set_skeleton(pxr_scene* s, const pxr_skeleton_desc* k) {
     s->d_skeleton = d;
     sk.records = static_cast<const pxr::SkeletonRecord*>(d);
     sk.depth_begin = reinterpret_cast<const uint32_t*>(sk.records + K);
+    sk.links = sk.depth_begin + begin.size();
     s->sk = sk;
     return PXR_OK;
 }
 
-int pxr_pose_batch(pxr_scene* s, const float* d_free_poses, const float* d_angles, uint32_t n_frames, float* d_poses,
-                   void* hip_stream) {
+namespace {
+
+int check_pose_batch(const pxr_scene* s, const float* d_free_poses, const float* d_angles, uint32_t n_frames, const float* d_poses) {
     if (!s) return fail(PXR_ERR_INVALID_ARG, "pxr_pose_batch: null scene");
     if (!s->d_skeleton) return fail(PXR_ERR_INVALID_ARG, "pxr_pose_batch: no skeleton bound (pxr_set_skeleton)");
     if (n_frames == 0 || n_frames > 0x7FFFFFFFu) return fail(PXR_ERR_INVALID_ARG, "pxr_pose_batch: n_frames must lie in [1, 2^31-1]");
@@ -364,11 +381,57 @@ int pxr_pose_batch(pxr_scene* s, const float* d_free_poses, const float* d_angle
     if ((reinterpret_cast<uintptr_t>(d_free_poses) & 3u) || (reinterpret_cast<uintptr_t>(d_angles) & 3u) ||
         (reinterpret_cast<uintptr_t>(d_poses) & 3u))
         return fail(PXR_ERR_INVALID_ARG, "pxr_pose_batch: buffers must be 4-byte aligned");
+    return PXR_OK;
+}
+
+}  // namespace
+
+int pxr_pose_batch(pxr_scene* s, const float* d_free_poses, const float* d_angles, uint32_t n_frames, float* d_poses,
+                   void* hip_stream) {
+    int rc = check_pose_batch(s, d_free_poses, d_angles, n_frames, d_poses);
+    if (rc != PXR_OK) return rc;
     std::string err;
-    const int rc = pxr::launch_fk(s->sk, d_free_poses, d_angles, n_frames, d_poses, hip_stream, err);
+    rc = pxr::launch_fk(s->sk, d_free_poses, d_angles, n_frames, d_poses, hip_stream, err);
     if (rc != PXR_OK) return fail(rc, "pxr_pose_batch: " + err);
     return PXR_OK;
 }
+
+namespace {
+
+constexpr uint64_t kPosedRoundsTimesDepths = 20;
+
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return a && b && p < q + b_bytes && q < p + a_bytes;
+}
+
+// Whether the render kernel makes the poses itself, in the same launch.  That saves the kinematics kernel's launch (4 to 5 us) and
+// costs every round of workgroups the chain of steps from the angles to the poses: about as long for a tree of d depths as
+// d + 1 times 0.25 us.  us per call, two launches / one, 64x64 unless said otherwise: humanoid (4 depths) 1 frame 12.6 / 9.6, 256
+// frames 14.7 / 10.7, 1024 (two rounds) 28.5 / 25.6, 2048 (four) 47.3 / 46.1, 4096 (eight) 84 / 87; quadruped (3 depths) 256 frames
+// 12.6 / 9.7, 2048 41.3 / 40.9, 4096 73 / 76; chain (7 depths) 256 frames 14.1 / 11.2, 1024 25.6 / 24.4, 2048 42.2 / 44.4; quadrupeds of
+// 256x256 (a workgroup per compute unit), 256 frames 35.4 / 32.1, 1024 108.6 / 108.4.
+bool worth_one_launch(const pxr_scene* s, uint64_t n_frames) {
+    const uint32_t per_cu = std::min(160u * 1024u / s->sc.lds_total, 2048u / s->block_threads);
+    const uint64_t resident = (uint64_t)per_cu * s->n_cus, rounds = (n_frames + resident - 1) / resident;
+    return rounds * (s->sk.depths + 1u) <= kPosedRoundsTimesDepths;
+}
+
+bool poses_made_by_renderer(const pxr_scene* s, const float* d_free_poses, const float* d_angles, uint64_t n_frames,
+                            const float* d_poses, const uint8_t* d_frames, const uint32_t* d_ids) {
+    if (!worth_one_launch(s, n_frames)) return false;
+    // (a caller may let the outputs take the place of the angles or the free poses: then all of these are read first)
+    const size_t free_bytes = n_frames * s->sk.F * 28, angle_bytes = n_frames * s->sk.J * 4, pose_bytes = n_frames * s->sc.K * 28,
+                 frame_bytes = n_frames * s->sc.npix * 3, id_bytes = n_frames * s->sc.npix * 4;
+    for (int out = 0; out < 3; ++out) {
+        const void* p = out == 0 ? (const void*)d_poses : (out == 1 ? (const void*)d_frames : (const void*)d_ids);
+        const size_t bytes = out == 0 ? pose_bytes : (out == 1 ? frame_bytes : id_bytes);
+        if (overlap(p, bytes, d_free_poses, free_bytes) || overlap(p, bytes, d_angles, angle_bytes)) return false;
+    }
+    return true;
+}
+
+}  // namespace
 
 int pxr_render_batch_kinematic(pxr_scene* s, const float* d_free_poses, const float* d_angles, const float* d_shapes,
                                uint32_t B, uint32_t S, uint32_t step0, uint32_t env0, float* d_poses, uint8_t* d_frames,
@@ -376,7 +439,16 @@ int pxr_render_batch_kinematic(pxr_scene* s, const float* d_free_poses, const fl
     if (B == 0 || S == 0 || (uint64_t)B * S > 0x7FFFFFFFull)
         return fail(PXR_ERR_INVALID_ARG, "pxr_render_batch_kinematic: B*S must lie in [1, 2^31-1]");
     if (!d_frames) return fail(PXR_ERR_INVALID_ARG, "pxr_render_batch_kinematic: null frames");
-    int rc = pxr_pose_batch(s, d_free_poses, d_angles, B * S, d_poses, hip_stream);
+    int rc = check_pose_batch(s, d_free_poses, d_angles, B * S, d_poses);
+    if (rc != PXR_OK) return rc;
+    if (poses_made_by_renderer(s, d_free_poses, d_angles, (uint64_t)B * S, d_poses, d_frames, d_ids)) {
+        const pxr::FkArgs fk = {s->sk, d_free_poses, d_angles, d_poses};
+        std::string err;
+        rc = render_posed(s, &fk, d_poses, d_shapes, 0, B, S, step0, env0, d_frames, d_ids, hip_stream, err);
+        if (rc != PXR_OK) return fail(rc, "pxr_render_batch: " + err);
+        return PXR_OK;
+    }
+    rc = pxr_pose_batch(s, d_free_poses, d_angles, B * S, d_poses, hip_stream);
     if (rc != PXR_OK) return rc;
     return pxr_render_batch(s, d_poses, d_shapes, B, S, step0, env0, d_frames, d_ids, hip_stream);
 }
@@ -405,6 +477,13 @@ int pxr_render_batch_kinematic_static(pxr_scene* s, const float* d_free_poses, c
     // nothing of an earlier call's contents is used, so nothing needs clearing)
     return pxr_render_batch_kinematic(s, d_free_poses, d_angles, d_shapes, B, S, step0, env0, d_poses, d_frames, d_ids,
                                       hip_stream);
+}
+
+int pxr_kinematic_info(const pxr_scene* s, uint32_t n_frames, uint32_t* n_launches) {
+    if (!s || !n_launches || n_frames == 0) return fail(PXR_ERR_INVALID_ARG, "pxr_kinematic_info: null argument or n_frames == 0");
+    if (!s->d_skeleton) return fail(PXR_ERR_INVALID_ARG, "pxr_kinematic_info: no skeleton bound (pxr_set_skeleton)");
+    *n_launches = worth_one_launch(s, n_frames) ? 1u : 2u;
+    return PXR_OK;
 }
 
 int pxr_scene_info(const pxr_scene* s, uint32_t* n_verts, uint32_t* n_tris, uint32_t* lds_bytes, uint32_t* block_threads) {

@@ -133,7 +133,17 @@ struct SkeletonConsts {
     uint32_t depths;                 // number of depths; depth 0 = the free bodies
     const SkeletonRecord* records;   // [K], in order of depth
     const uint32_t* depth_begin;     // [depths + 1] first record of each depth
+    const uint32_t* links;           // [K] each record's depth | its parent's record << 16 (0 for a free body)
 };
+
+// The render kernel's own kinematics stage: inputs and where the poses go.
+struct FkArgs {
+    SkeletonConsts sk;
+    const float* free_poses;  // [frames, F, 7]
+    const float* angles;      // [frames, J]
+    float* poses;             // [frames, K, 7], written
+};
+static_assert(sizeof(SkeletonRecord) == 48, "a lane reads a record as three 16-byte words");
 
 // Host-side result of tessellation + camera derivation.
 struct HostScene {
@@ -152,7 +162,8 @@ struct HostScene {
 int build_host_scene(const pxr_scene_desc& desc, HostScene& hs, std::string& err);
 
 // render.hip: enqueue one batch.  `block_threads` in {256,512,768,1024}; `n_cus` compute units of the device.
-int launch_render(const SceneConsts& sc, const DistractConsts& dc, const float* d_poses, const float* d_shapes,
+// `fk`: the poses are not read but made in the same launch, from joint angles (null: read from d_poses).
+int launch_render(const SceneConsts& sc, const DistractConsts& dc, const FkArgs* fk, const float* d_poses, const float* d_shapes,
                   uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
                   uint32_t block_threads, uint32_t n_cus, void* stream, std::string& err);
 

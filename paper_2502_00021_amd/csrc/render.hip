@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "arith.h"
+#include "hinge.h"
 #include "pxr_internal.h"
 #include "reach.h"
 
@@ -904,6 +905,65 @@ __device__ __forceinline__ void make_window(const SceneConsts& sc, uint32_t key_
     if (lane == 1u) fu->side_magic = side ? quotient + 1u : 0u;
 }
 
+// The frame's poses from its joint angles, by one wavefront, a lane per body: left in LDS (seven floats behind each body's
+// view rows, where phase 0 reads them before it writes its own results there), in memory if `store`, and the camera position
+// in the frame's uniforms.  Same arithmetic as the kinematics kernel's (hinge.h).
+// A chain of dependent steps: everything that memory has to deliver is requested at once (the frame's angles and free poses as
+// they lie, one word per lane, dealt out by lane exchange when the bodies' records have come in), then a step per depth of
+// the tree.
+__device__ __forceinline__ void pose_frame(const FkArgs& fk, uint32_t frame, float* body, FrameUniforms* fu, uint32_t root,
+                                           float off_x, float off_y, float off_z, uint32_t lane, bool store) {
+    const SkeletonConsts& sk = fk.sk;
+    const uint4* from = reinterpret_cast<const uint4*>(sk.records + min(lane, sk.K - 1u));
+    const uint4 r0 = from[0], r1 = from[1], r2 = from[2];
+    const uint32_t link = sk.links[min(lane, sk.K - 1u)];
+    const float* angles = fk.angles + (size_t)frame * sk.J;
+    const float* free_poses = fk.free_poses + (size_t)frame * (sk.F * 7u);
+    const bool by_exchange = sk.J <= 64u && sk.F * 7u <= 64u;
+    // (without a branch around them: behind one, the compiler would request them only when the records have come in)
+    const float* none = reinterpret_cast<const float*>(sk.records);
+    const float my_angle = (sk.J ? angles : none)[min(lane, max(sk.J, 1u) - 1u)];
+    const float my_free = (sk.F ? free_poses : none)[min(lane, max(sk.F * 7u, 1u) - 1u)];
+    SkeletonRecord t;
+    const uint4 words[3] = {r0, r1, r2};
+    __builtin_memcpy(&t, words, sizeof(t));
+    float theta = 0.0f, p[7];
+    if (by_exchange) {
+        const int slot = max(t.slot, 0);
+        theta = __shfl(my_angle, slot);
+        if (t.slot < 0) theta = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 7; ++c) p[c] = __shfl(my_free, (t.parent < 0 ? slot * 7 : 0) + c);
+    } else {
+        if (t.parent >= 0 && t.slot >= 0) theta = angles[t.slot];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) p[c] = t.parent < 0 ? free_poses[t.slot * 7 + c] : 0.0f;
+    }
+    float sn, cs;
+    sincos_half(theta, sn, cs);
+    for (uint32_t d = 1; d < sk.depths; ++d) {
+        float pp[7];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) pp[c] = __shfl(p[c], (int)(link >> 16));
+        if ((link & 0xFFFFu) == d) hinge_pose(t, pp, cs, sn, p);
+    }
+    if (lane < sk.K) {
+        float* o = body + t.body * kBodyStride + 12u;
+#pragma unroll
+        for (int c = 0; c < 7; ++c) o[c] = p[c];
+        if (t.body == root) {
+            fu->eye[0] = p[0] + off_x;
+            fu->eye[1] = p[1] + off_y;
+            fu->eye[2] = p[2] + off_z;
+        }
+        if (store) {
+            float* dst = fk.poses + ((size_t)frame * sk.K + t.body) * 7u;
+#pragma unroll
+            for (int c = 0; c < 7; ++c) dst[c] = p[c];
+        }
+    }
+}
+
 // Register budget: two 80 KB workgroups share a compute unit, so 1024-thread groups need all
 // 8 wave slots per SIMD (<= 64 VGPRs); the smaller groups may use more registers.
 // RAGGED: the width is no multiple of 4 (resolve_groups).
@@ -916,120 +976,11 @@ __device__ __forceinline__ void make_window(const SceneConsts& sc, uint32_t key_
 // Frames whose keys fit as a whole beside a second workgroup (64x64) do not take it: the same number of instructions, and
 // the few wavefronts that get the window's pixels shade them all (65 536 x 3 frames 3.53 -> 3.81 ms).
 // 1 << slabs_log2 workgroups share a windowed frame, each takes a run of its rows (and repeats the geometry).
-template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ? 8 : (NT >= 768 ? 6 : 4)))) void render_kernel(
-    const SceneConsts sc, const DistractConsts dc, const float* __restrict__ poses, const float* __restrict__ shapes,
-    uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    // the key buffer's LDS holds the cell codes and the candidate list until the keys are cleared
-    uint32_t* vm = reinterpret_cast<uint32_t*>(lds + sc.lds_keys);
-    uint16_t* cand = reinterpret_cast<uint16_t*>(lds + sc.lds_keys + sc.V * 4 + 4);  // (after the word of code 0)
-    int2* vxy = reinterpret_cast<int2*>(lds + sc.lds_vxy);
-    float* vd = reinterpret_cast<float*>(lds + sc.lds_vd);
-    float* body = reinterpret_cast<float*>(lds + sc.lds_body);
-    float* cxcy = reinterpret_cast<float*>(lds + sc.lds_cxcy);
-    float4* rows = reinterpret_cast<float4*>(lds + sc.lds_rows);
-    FrameUniforms* fu = reinterpret_cast<FrameUniforms*>(lds + sc.lds_misc);
-    uint16_t* list = reinterpret_cast<uint16_t*>(lds + sc.lds_list);    // tiny bin grows up, small bin grows down
-    uint16_t* list2 = reinterpret_cast<uint16_t*>(lds + sc.lds_large);  // large bin
-
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lane = tid & 63u;
-    const uint32_t block = frame_of_block(blockIdx.x, gridDim.x);
-    const uint32_t frame = WINDOWED ? block >> slabs_log2 : block;
-    const uint32_t e = frame / S;
-    const uint32_t step = step0 + (frame - e * S);
-    const uint32_t env = env0 + e;
-    const float* pose = poses + (size_t)frame * sc.K * 7;
-
-    // camera position: fixed world-space offset from the root body.
-    // The root's position is fetched with vector loads (through an offset of 0 that the compiler cannot see
-    // through), although it is the same for every lane: as scalar loads they share their counter with the loads
-    // of the kernel's arguments, every wait for one of those would wait for memory as well, and the first
-    // wavefront would request its bodies' poses only after the root's position had arrived.
-    uint32_t opaque_zero = 0u;
-    asm volatile("" : "+v"(opaque_zero));
-    const float* root_pos = pose + sc.root * 7 + opaque_zero;
-    // (Only requested here.  The additions, and with them the wait, are made where phase 0 uses the eye: after the
-    // bodies' lanes have requested their poses, in particular.  Phase 4 gets the eye through LDS, so that these
-    // registers are free in between.)
-    const float root_x = root_pos[0], root_y = root_pos[1], root_z = root_pos[2];
-
-    PXR_PHASE_BEGIN();
-    // ---- phase 0: per-body transforms, per-frame draws, the three non-triangle colours
-    // (16-wavefront groups: copied by the fourth wavefront on, the first three have chains of their own in this
-    // phase; measured the other way round for the smaller groups)
-    constexpr uint32_t kCopyFrom = NT >= 1024 ? 192u : 0u;
-    if (tid >= kCopyFrom)
-        for (uint32_t i = tid - kCopyFrom; i < sc.W + sc.H; i += NT - kCopyFrom) cxcy[i] = sc.cxcy[i];
-    if (tid < 4u * sc.K) {
-        // Four lanes per body: each rebuilds the body's rotation and takes one row of the work (the view matrix
-        // has three rows, the light direction is the fourth): a quarter of the dot products on the chain.
-        const uint32_t b = tid >> 2, part = tid & 3u;
-        const float* p = pose + b * 7;
-        // Everything the lane will need from memory is requested here, in one go: the pose, the lane's row of
-        // (right, up, forward, light) from the table behind the bodies' constants, the body's shape and colour
-        // (all four lanes of a body ask for the same: one request).
-        const float* vr = sc.body_const + sc.K * 8u + 3u * part;
-        const float r0 = vr[0], r1 = vr[1], r2 = vr[2];
-        const float4 shp = *reinterpret_cast<const float4*>(shapes ? shapes + ((size_t)e * sc.K + b) * 4 : sc.body_const + b * 8);
-        const float4 col = *reinterpret_cast<const float4*>(sc.body_const + b * 8 + 4);
-        const float w = p[3], x = p[4], y = p[5], z = p[6];
-        float R[3][3];
-        R[0][0] = 1.0f - 2.0f * (y * y + z * z);
-        R[0][1] = 2.0f * (x * y - w * z);
-        R[0][2] = 2.0f * (x * z + w * y);
-        R[1][0] = 2.0f * (x * y + w * z);
-        R[1][1] = 1.0f - 2.0f * (x * x + z * z);
-        R[1][2] = 2.0f * (y * z - w * x);
-        R[2][0] = 2.0f * (x * z - w * y);
-        R[2][1] = 2.0f * (y * z + w * x);
-        R[2][2] = 1.0f - 2.0f * (x * x + y * y);
-        const float eye_x = root_x + sc.off[0], eye_y = root_y + sc.off[1], eye_z = root_z + sc.off[2];
-        const float dx = p[0] - eye_x, dy = p[1] - eye_y, dz = p[2] - eye_z;
-        if (tid == 0u) {
-            fu->eye[0] = eye_x;
-            fu->eye[1] = eye_y;
-            fu->eye[2] = eye_z;
-        }
-        float* o = body + b * kBodyStride;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) o[3u * part + (part == 3u ? 3u : 0u) + c] = dot3(r0, r1, r2, R[0][c], R[1][c], R[2][c]);
-        if (part < 3u) o[9u + part] = dot3(r0, r1, r2, dx, dy, dz);
-        // (written by all four lanes, the same values: in a branch of its own the compiler would request them
-        // only there, after the arithmetic, and the first wavefront would wait for memory twice)
-        *reinterpret_cast<float4*>(o + 16) = shp;
-        *reinterpret_cast<float4*>(o + 20) = col;  // (the fourth float is padding)
-    }
-    if (tid >= 64u) {
-        // The second wavefront on: one lane per image row prepares what all pixels of the row share: the row
-        // part of the ray, and - when the camera does not roll, so that the ray's z does not depend on the
-        // column (fma(+-0, cx, rz) == rz) - the whole ground test with its division.
-        //   rows[j] = (rx, ry, tg or 0 for a miss, depth bits)   without roll
-        //   rows[j] = (rx, ry, rz, -)                            with roll
-        const bool no_roll = sc.Rt[2] == 0.0f;
-        ResolveCtx g;
-        const float eye_z = root_z + sc.off[2];
-        g.eye_z = eye_z;
-        g.inv_ez = 1.0f / eye_z;
-        g.ground_ok = sc.ground_on && eye_z > 0.0f;
-        for (uint32_t j = tid - 64u; j < sc.H; j += NT - 64u) {
-            const float cyj = sc.cxcy[sc.W + j];
-            const float rz = __builtin_fmaf(sc.Up[2], cyj, sc.Fw[2]);
-            float4 r;
-            r.x = __builtin_fmaf(sc.Up[0], cyj, sc.Fw[0]);
-            r.y = __builtin_fmaf(sc.Up[1], cyj, sc.Fw[1]);
-            r.z = rz;
-            r.w = 0.0f;
-            if (no_roll) {
-                float tg;
-                const u64 key = ground_key(sc, g, -rz, tg);
-                r.z = key ? tg : 0.0f;  // (a hit has tg >= z_near > 0)
-                r.w = __uint_as_float((uint32_t)(key >> 32));
-            }
-            rows[j] = r;
-        }
-    }
+// The part of phase 0 that needs no pose: the frame's draws and what is made of them, counters set to zero, the video
+// distractor's tables (by the second wavefront on).
+template <int NT, bool WINDOWED, bool VIDEO>
+__device__ __forceinline__ void draw_frame(const SceneConsts& sc, const DistractConsts& dc, FrameUniforms* fu, unsigned char* lds,
+                                           uint32_t e, uint32_t env, uint32_t step, uint32_t tid) {
     // (The wavefronts of a workgroup start a few hundred clocks apart, four at a time; the last ones start more than
     // a thousand clocks after the first.  The draws are this phase's longest chain beside the bodies': they belong on
     // an early wavefront that has nothing else to do - the third - and the late ones get no work here at all.)
@@ -1079,13 +1030,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             fu->video_frame = clip * dc.n_frames + (uint32_t)(((u64)first + (u64)step) % dc.n_frames);
         }
     }
-    if (VIDEO && sc.lds_vlut) {
+    if (VIDEO && sc.lds_vlut && tid >= 64u) {
         // Video-blend tables: under the clip lies the background or a ground grey (no colour distractor in this
         // mode), so a blended channel is a function of (one of five colours, clip byte).  Four entries per lane.
         // Nine tables of 256 bytes: background r, g, b, then each grey's three times over - the channel of a byte is
         // then the same address offset (256 x channel) whatever lies under the clip, a constant in the read.
         uint32_t* vlut = reinterpret_cast<uint32_t*>(lds + sc.lds_vlut);
-        for (uint32_t i = tid; i < 5u * 64u; i += NT) {
+        for (uint32_t i = tid - 64u; i < 5u * 64u; i += NT - 64u) {
             const uint32_t t = i >> 6, at = i & 63u;
             const float c = t == 0 ? sc.bg[0] : t == 1 ? sc.bg[1] : t == 2 ? sc.bg[2] : t == 3 ? sc.gs[0] : sc.gs[1];
             uint32_t word = 0;
@@ -1135,6 +1086,154 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             }
         }
     }
+}
+
+// (the kernels that read their poses do not carry the arguments of those that make them)
+template <bool POSED>
+struct KinematicArgs {
+    FkArgs args;
+};
+template <>
+struct KinematicArgs<false> {};
+
+// POSED: the poses are not read from memory but made here, from joint angles (pose_frame).
+template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO, bool POSED>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ? 8 : (NT >= 768 ? 6 : 4)))) void render_kernel(
+    const SceneConsts sc, const DistractConsts dc, const float* __restrict__ poses, const float* __restrict__ shapes,
+    uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2,
+    const KinematicArgs<POSED> fk) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    // the key buffer's LDS holds the cell codes and the candidate list until the keys are cleared
+    uint32_t* vm = reinterpret_cast<uint32_t*>(lds + sc.lds_keys);
+    uint16_t* cand = reinterpret_cast<uint16_t*>(lds + sc.lds_keys + sc.V * 4 + 4);  // (after the word of code 0)
+    int2* vxy = reinterpret_cast<int2*>(lds + sc.lds_vxy);
+    float* vd = reinterpret_cast<float*>(lds + sc.lds_vd);
+    float* body = reinterpret_cast<float*>(lds + sc.lds_body);
+    float* cxcy = reinterpret_cast<float*>(lds + sc.lds_cxcy);
+    float4* rows = reinterpret_cast<float4*>(lds + sc.lds_rows);
+    FrameUniforms* fu = reinterpret_cast<FrameUniforms*>(lds + sc.lds_misc);
+    uint16_t* list = reinterpret_cast<uint16_t*>(lds + sc.lds_list);    // tiny bin grows up, small bin grows down
+    uint16_t* list2 = reinterpret_cast<uint16_t*>(lds + sc.lds_large);  // large bin
+
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = tid & 63u;
+    const uint32_t block = frame_of_block(blockIdx.x, gridDim.x);
+    const uint32_t frame = WINDOWED ? block >> slabs_log2 : block;
+    const uint32_t e = frame / S;
+    const uint32_t step = step0 + (frame - e * S);
+    const uint32_t env = env0 + e;
+    const float* pose = poses + (size_t)frame * sc.K * 7;
+
+    // camera position: fixed world-space offset from the root body.
+    // The root's position is fetched with vector loads (through an offset of 0 that the compiler cannot see
+    // through), although it is the same for every lane: as scalar loads they share their counter with the loads
+    // of the kernel's arguments, every wait for one of those would wait for memory as well, and the first
+    // wavefront would request its bodies' poses only after the root's position had arrived.
+    uint32_t opaque_zero = 0u;
+    asm volatile("" : "+v"(opaque_zero));
+    const float* root_pos = pose + sc.root * 7 + opaque_zero;
+    // (Only requested here.  The additions, and with them the wait, are made where phase 0 uses the eye: after the
+    // bodies' lanes have requested their poses, in particular.  Phase 4 gets the eye through LDS, so that these
+    // registers are free in between.)
+    const float root_x = POSED ? 0.0f : root_pos[0], root_y = POSED ? 0.0f : root_pos[1], root_z = POSED ? 0.0f : root_pos[2];
+
+    PXR_PHASE_BEGIN();
+    // ---- phase 0: per-body transforms, per-frame draws, the three non-triangle colours
+    // (16-wavefront groups: copied by the fourth wavefront on, the first three have chains of their own in this
+    // phase; measured the other way round for the smaller groups)
+    constexpr uint32_t kCopyFrom = NT >= 1024 ? 192u : 0u;
+    if (tid >= kCopyFrom)
+        for (uint32_t i = tid - kCopyFrom; i < sc.W + sc.H; i += NT - kCopyFrom) cxcy[i] = sc.cxcy[i];
+    // The draws come before the bodies in the large workgroups (65 536 x 3 frames of 64x64 3517 us the other way round, now 3488),
+    // whose third wavefront they are, after them in the small ones (256 capsule frames of 48x48 7.2 us the other way round, now 6.8).
+    constexpr bool kDrawFirst = NT >= 768;
+    if constexpr (!POSED && kDrawFirst) draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
+    if constexpr (POSED) {
+        if (tid < 64u)
+            pose_frame(fk.args, frame, body, fu, sc.root, sc.off[0], sc.off[1], sc.off[2], lane, !WINDOWED || (block & ((1u << slabs_log2) - 1u)) == 0u);
+        else
+            draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
+        __syncthreads();
+    }
+    if (tid < 4u * sc.K) {
+        // Four lanes per body: each rebuilds the body's rotation and takes one row of the work (the view matrix
+        // has three rows, the light direction is the fourth): a quarter of the dot products on the chain.
+        const uint32_t b = tid >> 2, part = tid & 3u;
+        const float* p = POSED ? body + b * kBodyStride + 12 : pose + b * 7;
+        // Everything the lane will need from memory is requested here, in one go: the pose, the lane's row of
+        // (right, up, forward, light) from the table behind the bodies' constants, the body's shape and colour
+        // (all four lanes of a body ask for the same: one request).
+        const float* vr = sc.body_const + sc.K * 8u + 3u * part;
+        const float r0 = vr[0], r1 = vr[1], r2 = vr[2];
+        const float4 shp = *reinterpret_cast<const float4*>(shapes ? shapes + ((size_t)e * sc.K + b) * 4 : sc.body_const + b * 8);
+        const float4 col = *reinterpret_cast<const float4*>(sc.body_const + b * 8 + 4);
+        const float w = p[3], x = p[4], y = p[5], z = p[6];
+        float at_x = 0.0f, at_y = 0.0f, at_z = 0.0f;
+        if (POSED) {  // (a body's four lanes have read its pose before one of them writes over it)
+            at_x = p[0];
+            at_y = p[1];
+            at_z = p[2];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        float R[3][3];
+        R[0][0] = 1.0f - 2.0f * (y * y + z * z);
+        R[0][1] = 2.0f * (x * y - w * z);
+        R[0][2] = 2.0f * (x * z + w * y);
+        R[1][0] = 2.0f * (x * y + w * z);
+        R[1][1] = 1.0f - 2.0f * (x * x + z * z);
+        R[1][2] = 2.0f * (y * z - w * x);
+        R[2][0] = 2.0f * (x * z - w * y);
+        R[2][1] = 2.0f * (y * z + w * x);
+        R[2][2] = 1.0f - 2.0f * (x * x + y * y);
+        const float eye_x = POSED ? fu->eye[0] : root_x + sc.off[0], eye_y = POSED ? fu->eye[1] : root_y + sc.off[1],
+                    eye_z = POSED ? fu->eye[2] : root_z + sc.off[2];
+        const float dx = (POSED ? at_x : p[0]) - eye_x, dy = (POSED ? at_y : p[1]) - eye_y, dz = (POSED ? at_z : p[2]) - eye_z;
+        if (!POSED && tid == 0u) {
+            fu->eye[0] = eye_x;
+            fu->eye[1] = eye_y;
+            fu->eye[2] = eye_z;
+        }
+        float* o = body + b * kBodyStride;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[3u * part + (part == 3u ? 3u : 0u) + c] = dot3(r0, r1, r2, R[0][c], R[1][c], R[2][c]);
+        if (part < 3u) o[9u + part] = dot3(r0, r1, r2, dx, dy, dz);
+        // (written by all four lanes, the same values: in a branch of its own the compiler would request them
+        // only there, after the arithmetic, and the first wavefront would wait for memory twice)
+        *reinterpret_cast<float4*>(o + 16) = shp;
+        *reinterpret_cast<float4*>(o + 20) = col;  // (the fourth float is padding)
+    }
+    if (tid >= 64u) {
+        // The second wavefront on: one lane per image row prepares what all pixels of the row share: the row
+        // part of the ray, and - when the camera does not roll, so that the ray's z does not depend on the
+        // column (fma(+-0, cx, rz) == rz) - the whole ground test with its division.
+        //   rows[j] = (rx, ry, tg or 0 for a miss, depth bits)   without roll
+        //   rows[j] = (rx, ry, rz, -)                            with roll
+        const bool no_roll = sc.Rt[2] == 0.0f;
+        ResolveCtx g;
+        const float eye_z = POSED ? fu->eye[2] : root_z + sc.off[2];
+        g.eye_z = eye_z;
+        g.inv_ez = 1.0f / eye_z;
+        g.ground_ok = sc.ground_on && eye_z > 0.0f;
+        for (uint32_t j = tid - 64u; j < sc.H; j += NT - 64u) {
+            const float cyj = sc.cxcy[sc.W + j];
+            const float rz = __builtin_fmaf(sc.Up[2], cyj, sc.Fw[2]);
+            float4 r;
+            r.x = __builtin_fmaf(sc.Up[0], cyj, sc.Fw[0]);
+            r.y = __builtin_fmaf(sc.Up[1], cyj, sc.Fw[1]);
+            r.z = rz;
+            r.w = 0.0f;
+            if (no_roll) {
+                float tg;
+                const u64 key = ground_key(sc, g, -rz, tg);
+                r.z = key ? tg : 0.0f;  // (a hit has tg >= z_near > 0)
+                r.w = __uint_as_float((uint32_t)(key >> 32));
+            }
+            rows[j] = r;
+        }
+    }
+    if constexpr (!POSED && !kDrawFirst) draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
     PXR_TIMED_BARRIER(0);
     PXR_PHASE_MARK(0);
 
@@ -1542,11 +1641,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
 }
 
 template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
-int launch_one(const SceneConsts& sc, const DistractConsts& dc, const float* d_poses, const float* d_shapes,
+int launch_one(const SceneConsts& sc, const DistractConsts& dc, const FkArgs* fk, const float* d_poses, const float* d_shapes,
                uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
                uint32_t slabs_log2, hipStream_t stream, std::string& err) {
-    hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
-                       sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2);
+    if (fk)
+        hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO, true>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
+                           sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2, KinematicArgs<true>{*fk});
+    else
+        hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO, false>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
+                           sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2, KinematicArgs<false>{});
     const hipError_t rc = hipGetLastError();
     if (rc != hipSuccess) {
         err = std::string("kernel launch failed: ") + hipGetErrorString(rc);
@@ -1555,20 +1658,21 @@ int launch_one(const SceneConsts& sc, const DistractConsts& dc, const float* d_p
     return PXR_OK;
 }
 
-template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
+template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO, bool POSED = false>
 int prepare_one(uint32_t lds_bytes, std::string& err) {
     hipFuncAttributes attr;
-    if (hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&render_kernel<NT, RAGGED, WINDOWED, VIDEO>)) != hipSuccess ||
+    const void* kernel = reinterpret_cast<const void*>(&render_kernel<NT, RAGGED, WINDOWED, VIDEO, POSED>);
+    if (hipFuncGetAttributes(&attr, kernel) != hipSuccess ||
         attr.sharedSizeBytes != 0) {
         err = "the render kernel has static LDS in front of its dynamic segment (LDS addresses in the tables assume none)";
         return PXR_ERR_DEVICE;
     }
-    const hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&render_kernel<NT, RAGGED, WINDOWED, VIDEO>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    const hipError_t rc = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (rc != hipSuccess) {
         err = std::string("hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: ") + hipGetErrorString(rc);
         return PXR_ERR_DEVICE;
     }
+    if constexpr (!POSED) return prepare_one<NT, RAGGED, WINDOWED, VIDEO, true>(lds_bytes, err);
     return PXR_OK;
 }
 
@@ -1604,7 +1708,7 @@ int prepare_kernels(std::string& err) {
     return PXR_OK;
 }
 
-int launch_render(const SceneConsts& sc, const DistractConsts& dc, const float* d_poses, const float* d_shapes,
+int launch_render(const SceneConsts& sc, const DistractConsts& dc, const FkArgs* fk, const float* d_poses, const float* d_shapes,
                   uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
                   uint32_t block_threads, uint32_t n_cus, void* stream, std::string& err) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
@@ -1618,7 +1722,7 @@ int launch_render(const SceneConsts& sc, const DistractConsts& dc, const float* 
     // 17.4 / 14.5 / 13.3 / 14.7; quadruped 84x84, 64 frames 10.8 / 10.2 / 10.1 / 11.7 / 20.0.  (A slab has 4 rows or more.)
     uint32_t slabs_log2 = 0;
     while (windowed && slabs_log2 < 5u && ((uint64_t)n_frames << (slabs_log2 + 1u)) <= n_cus && (sc.H >> (slabs_log2 + 1u)) >= 4u) ++slabs_log2;
-#define PXR_ARGS sc, dc, d_poses, d_shapes, n_frames, S, step0, env0, d_frames, d_ids, slabs_log2, st, err
+#define PXR_ARGS sc, dc, fk, d_poses, d_shapes, n_frames, S, step0, env0, d_frames, d_ids, slabs_log2, st, err
 #define PXR_LAUNCH_V(NT, V)                                                                                      \
     return ragged ? (windowed ? launch_one<NT, true, true, V>(PXR_ARGS) : launch_one<NT, true, false, V>(PXR_ARGS)) \
                   : (windowed ? launch_one<NT, false, true, V>(PXR_ARGS) : launch_one<NT, false, false, V>(PXR_ARGS))

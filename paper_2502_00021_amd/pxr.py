@@ -102,6 +102,8 @@ def lib():
         L.pxr_render_batch_kinematic.argtypes = [vp, vp, vp, vp, u32, u32, u32, u32, vp, vp, vp, vp]
         L.pxr_render_batch_kinematic_static.argtypes = [vp, vp, vp, vp, u32, u32, u32, u32, vp, vp, vp]
         L.pxr_render_batch_kinematic_static.restype = C.c_int
+        L.pxr_kinematic_info.argtypes = [vp, u32, C.POINTER(u32)]
+        L.pxr_kinematic_info.restype = C.c_int
         L.pxr_conv_create.argtypes = [C.POINTER(ConvDesc), C.POINTER(vp)]
         L.pxr_conv_destroy.argtypes = [vp]
         L.pxr_conv_forward.argtypes = [vp, vp, u32, vp, vp]
@@ -357,6 +359,12 @@ class Scene:
         stream = _stream_handle(stream, source)
         _check(_lib.pxr_pose_batch(self._h, pf, pa, n, poses.data_ptr(), stream))
         return poses
+
+    def kinematic_launches(self, n_frames):
+        """How many kernels render_batch_kinematic launches for that many frames (1 or 2)."""
+        n = C.c_uint32()
+        _check(lib().pxr_kinematic_info(self._h, int(n_frames), C.byref(n)))
+        return n.value
 
     def render_batch_kinematic(self, free_poses, angles, shapes=None, step0=0, env0=0, poses=None, frames=None,
                                want_ids=False, stream=None):

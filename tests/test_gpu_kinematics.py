@@ -19,6 +19,8 @@ here (u = 2^-24, the fp32 unit roundoff; d = a body's depth below its free root)
 These are worst-case sums; typical differences are around 1u (asserted as a median).  Frames are then checked
 exactly: the oracle renders the poses THE KERNEL produced, and ids must agree bit for bit, RGB with difference 0.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -257,6 +259,91 @@ def test_angles_to_frames_match_oracle(torch, pxr, orc, cfg, B):
     for other in (ref_poses, w["poses"]):
         base = orc.Scene(w["desc"]).render(other, w["shapes"], step0=4, env0=9, distractor=w["distractor"])
         assert (base["ids"] != ref["ids"]).mean() < 0.01
+    sc.close()
+
+
+def _random_skeleton(rng, K, F, J, depth):
+    """K bodies, the first F of them free, hung at most `depth` below them; J angles, some unused, some bodies rigid."""
+    skel = wl._skeleton(K)
+    skel["slot"][:F] = rng.permutation(F)
+    level = [0] * F
+    for k in range(F, K):
+        above = [j for j in range(k) if level[j] < depth]
+        parent = k - 1 if k < F + depth else int(rng.choice(above))  # (one chain of the full depth)
+        slot = -1 if J == 0 or rng.random() < 0.1 else int(rng.integers(0, J))
+        axis = rng.normal(size=3)
+        wl._hinge(skel, k, parent=parent, slot=slot, anchor=rng.uniform(-0.1, 0.1, 3), axis=axis / np.linalg.norm(axis),
+                  offset=rng.uniform(-0.1, 0.1, 3))
+        level.append(level[parent] + 1)
+    return skel
+
+
+# (bodies, free, angles, depth, width, height, threads, distractor, roll, environments, steps): one body; the most free poses and
+# angles that a wavefront exchanges (9, 64) and one more; 64 bodies; 256 to 1024 threads; frames in windows, alone and shared by
+# workgroups; odd widths
+@pytest.mark.parametrize("case", [
+    (1, 1, 0, 0, 32, 32, 0, "none", False, 3, 1), (5, 1, 4, 4, 32, 24, 256, "color", False, 7, 3),
+    (14, 9, 64, 2, 64, 64, 0, "color", False, 5, 2), (14, 10, 64, 2, 64, 64, 512, "none", False, 5, 2),
+    (14, 2, 65, 3, 64, 64, 768, "video", False, 5, 2), (64, 1, 63, 18, 64, 64, 1024, "none", True, 9, 1),
+    (64, 26, 0, 5, 71, 53, 0, "color", False, 4, 2), (15, 1, 14, 4, 160, 120, 0, "color", False, 3, 2),
+    (15, 1, 14, 4, 131, 97, 0, "video", True, 300, 1), (15, 1, 14, 4, 160, 120, 0, "video", False, 200, 2)])
+def test_poses_made_by_the_render_kernel(torch, pxr, case):
+    """A batch of one launch gives the bits of the two calls that it stands for, angles out of the domain included."""
+    K, F, J, depth, w, h, threads, mode, roll, B, S = case
+    rng = np.random.default_rng(K * 1000 + w)
+    desc = wl.default_scene(w, h, [wl.capsule(0.06, 0.1, (0.8, 0.4, 0.3), 8, 2) if K < 64 else wl.sphere(0.08, (0.5, 0.5, 0.5), 4, 1)] * K)
+    if roll:
+        desc["cam_up"] = (0.1, 0.25, 1.0)
+    desc["root_body"] = K - 1 if K > 1 else 0  # (a hinged one)
+    sc = pxr.Scene(desc)
+    sc.set_block_threads(threads)
+    sc.set_skeleton(_random_skeleton(rng, K, F, J, depth), F, J)
+    if mode == "video":
+        clip = torch.from_numpy(rng.integers(0, 256, (5, h, w, 3), dtype=np.uint8)).cuda()
+        sc.apply_distractor(dict(mode="video", seed=4, alpha=0.5, video=clip))
+    else:
+        sc.apply_distractor(dict(mode=mode, seed=4, scale=(0.5, 1.5), offset=(-0.2, 0.2)) if mode == "color" else None)
+    assert sc.kinematic_launches(B * S) == 1
+    free = rng.normal(size=(B, S, F, 7))
+    free[..., :3] = free[..., :3] * 0.2 + (0.0, 0.0, 1.0)
+    free[..., 3:] /= np.linalg.norm(free[..., 3:], axis=-1, keepdims=True)
+    angles = rng.uniform(-3.0, 3.0, (B, S, J))
+    if J:
+        angles[0, 0, :3] = (np.nan, 1e6, -np.inf)[:min(3, J)]
+    free, angles = torch.from_numpy(free.astype(np.float32)).cuda(), torch.from_numpy(angles.astype(np.float32)).cuda()
+    frames, ids, poses = sc.render_batch_kinematic(free, angles, step0=3, env0=2, want_ids=True)
+    two_poses = sc.pose_batch(free, angles)
+    two_frames, two_ids = sc.render_batch(two_poses, step0=3, env0=2, want_ids=True)
+    torch.cuda.synchronize()
+    assert torch.equal(poses.view(torch.int32), two_poses.view(torch.int32))
+    assert torch.equal(ids, two_ids) and torch.equal(frames, two_frames)
+    if B * S > 1:
+        assert bool((ids[1:] < 0).any()) and bool((ids[1:] >= 0).any())  # (ground or sky, and bodies)
+    sc.close()
+
+
+def test_when_the_render_kernel_makes_the_poses(torch, pxr):
+    """Large batches and deep trees take two launches, as do buffers that overlap; the results are the same."""
+    w = wl.make(2, B=40)
+    fk = w["fk"]
+    sc = _scene_with_skeleton(pxr, w)
+    launches = [sc.kinematic_launches(n) for n in (1, 256, 512, 4096, 65536)]
+    assert launches == sorted(launches) and launches[0] == 1 and launches[-1] == 2
+    free, ang = torch.from_numpy(fk["free_poses"]).cuda(), torch.from_numpy(fk["angles"]).cuda()
+    one, _, poses = sc.render_batch_kinematic(free, ang)
+    n = 40 * 64 * 64 * 3
+    room = torch.zeros(n + 64, dtype=torch.uint8, device="cuda")  # the angles lie where the frames go
+    inside = room[4096:4096 + ang.numel() * 4].view(torch.float32).view(ang.shape)
+    inside.copy_(ang)
+    frames = room[:n].view(one.shape)
+    _, _, again = sc.render_batch_kinematic(free, inside, frames=frames)
+    torch.cuda.synchronize()
+    assert torch.equal(frames, one) and torch.equal(again, poses)
+    n_launches = ctypes.c_uint32()
+    L = pxr.lib()
+    assert L.pxr_kinematic_info(sc._h, 0, ctypes.byref(n_launches)) == pxr.ERR_INVALID_ARG
+    sc.set_skeleton(None, 0, 0)
+    assert L.pxr_kinematic_info(sc._h, 1, ctypes.byref(n_launches)) == pxr.ERR_INVALID_ARG
     sc.close()
 
 
