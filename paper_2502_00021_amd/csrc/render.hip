@@ -400,6 +400,18 @@ __device__ __forceinline__ const T& argument_reloaded(uint32_t byte_offset) {
     return *(const T*)(const __attribute__((address_space(4))) T*)p;
 }
 
+// Ask for every cache line of the kernel's arguments at once.  They lie in memory that a launch's first wavefronts find in no
+// cache; as the compiler places the loads, each next group of arguments would wait for a miss of its own.
+template <uint32_t BYTES>
+__device__ __forceinline__ void request_arguments() {
+    typedef const __attribute__((address_space(4))) uint32_t* KernargWords;
+    const KernargWords p = (KernargWords)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t any = 0;
+#pragma unroll
+    for (uint32_t at = 0; at < BYTES; at += 64u) any |= p[at / 4u];
+    asm volatile("" : : "s"(any));
+}
+
 // Phase probes: empty in the library.  A profiling build (-DPXR_PROFILING_BUILD, made into a file of its own
 // by build.py --define) takes them from a header that the library's build never includes.
 #ifdef PXR_PROFILING_BUILD
@@ -1102,6 +1114,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     const SceneConsts sc, const DistractConsts dc, const float* __restrict__ poses, const float* __restrict__ shapes,
     uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2,
     const KinematicArgs<POSED> fk) {
+    // (where a launch is one round or two; 65 536 x 3 frames would take 3504 us for 3488)
+    if constexpr (POSED || NT <= 512) request_arguments<kDistractArgAt + sizeof(DistractConsts) + 40u + (POSED ? sizeof(FkArgs) : 0u)>();
     extern __shared__ __align__(16) unsigned char lds[];
     // the key buffer's LDS holds the cell codes and the candidate list until the keys are cleared
     uint32_t* vm = reinterpret_cast<uint32_t*>(lds + sc.lds_keys);
