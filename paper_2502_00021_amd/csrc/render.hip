@@ -409,6 +409,7 @@ __device__ __forceinline__ void request_arguments() {
     uint32_t any = 0;
 #pragma unroll
     for (uint32_t at = 0; at < BYTES; at += 64u) any |= p[at / 4u];
+    any |= *(KernargWords)__builtin_amdgcn_implicitarg_ptr();  // (the grid's size, behind the kernel's own arguments)
     asm volatile("" : : "s"(any));
 }
 
