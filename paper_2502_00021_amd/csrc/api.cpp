@@ -165,6 +165,7 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
         const uint32_t dev = (body_at << 2) | sel;
         std::memcpy(&vtmpl_dev[v * 4 + 3], &dev, 4);
     }
+    vtmpl_dev.resize((hs.c.V + 63u) / 64u * 64u * 4u, 0.0f);  // (a wavefront reads 64 without a bounds test)
     // Behind the bodies' constants: the rows (right, up, forward) of the view rotation and the light direction, for
     // the lanes of the kernel's set-up phase that take one row each.
     std::vector<float> body_dev(hs.body_const);

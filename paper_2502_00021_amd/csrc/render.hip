@@ -220,8 +220,7 @@ __device__ __forceinline__ int tri_rows(const uint2 ti, const int2* vxy, int& j0
 
 // View-space position of template vertex v (the instancing arithmetic of phase 1; also used when a
 // triangle has to be clipped).  The template's fourth word says where in LDS its body's record is.
-__device__ __forceinline__ void view_position(const SceneConsts& sc, uint32_t v, float& pvx, float& pvy, float& pvz) {
-    const float4 tv = reinterpret_cast<const float4*>(sc.vtmpl)[v];
+__device__ __forceinline__ void view_position(const float4 tv, float& pvx, float& pvy, float& pvz) {
     const uint32_t code = __float_as_uint(tv.w);
     // (body records are 96 bytes at a 16-byte aligned base: four 16-byte LDS reads)
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -304,9 +303,9 @@ __device__ __forceinline__ void raster_clipped(const SceneConsts& sc, const Rast
                 cD[c] = vd[vp];
             } else {
                 float px, py, pz, qx, qy, qz;
-                view_position(sc, vp, px, py, pz);
+                view_position(reinterpret_cast<const float4*>(sc.vtmpl)[vp], px, py, pz);
                 __builtin_amdgcn_sched_barrier(0);  // one vertex at a time: keeps this path within the register budget
-                view_position(sc, vq, qx, qy, qz);
+                view_position(reinterpret_cast<const float4*>(sc.vtmpl)[vq], qx, qy, qz);
                 __builtin_amdgcn_sched_barrier(0);
                 const float tt = (sc.z_near - pz) / (qz - pz);
                 const float ix = __builtin_fmaf(tt, qx - px, px);
@@ -977,6 +976,38 @@ __device__ __forceinline__ void pose_frame(const FkArgs& fk, uint32_t frame, flo
     }
 }
 
+// One template vertex: instancing, projection, snap, cell code.
+__device__ __forceinline__ void instance_vertex(const SceneConsts& sc, bool recip_long_form, uint32_t v, const float4 tv, int2* vxy,
+                                                float* vd, uint32_t* vm) {
+    float pvx, pvy, pvz;
+    view_position(tv, pvx, pvy, pvz);
+    // 1 / pvz is only used when pvz >= z_near (otherwise the vertex is behind the plane or unusable
+    // whatever it is), so the short form serves unless some lane's depth is beyond its range
+    float inv;
+    if (__builtin_expect(recip_long_form || __ballot(pvz > kRecipMax) != 0ull, 0))
+        inv = 1.0f / pvz;
+    else
+        inv = recip_in_range(pvz);
+    const float sx = __builtin_fmaf(sc.f, pvx * inv, sc.halfW);
+    const float sy = __builtin_fmaf(-sc.f, pvy * inv, sc.halfH);
+    const bool ok = (pvz >= sc.z_near) && (__builtin_fabsf(sx) <= 16384.0f) && (__builtin_fabsf(sy) <= 16384.0f);
+    // (worked out for every lane, whatever sx and sy are, and replaced where the vertex is not usable: such
+    // vertices are rare, and a wavefront without one skips the replacement altogether)
+    int X = floor_to_int(__builtin_fmaf(sx, 256.0f, 0.5f));
+    int Y = floor_to_int(__builtin_fmaf(sy, 256.0f, 0.5f));
+    uint32_t m = cell_code(X, (int)sc.W) | (cell_code(Y, (int)sc.H) << 16);
+    if (__builtin_expect(__ballot(!ok) != 0ull, 0)) {
+        if (!ok) {
+            X = pvz < sc.z_near ? kBehindX : kRejectedX;
+            Y = 0;
+            m = 0xFFFFFFFFu;  // an unusable or clipped vertex never lets a triangle be discarded early
+        }
+    }
+    vxy[v] = make_int2(X, Y);
+    vd[v] = sc.z_near * inv;
+    vm[v] = m;
+}
+
 // Register budget: two 80 KB workgroups share a compute unit, so 1024-thread groups need all
 // 8 wave slots per SIMD (<= 64 VGPRs); the smaller groups may use more registers.
 // RAGGED: the width is no multiple of 4 (resolve_groups).
@@ -1152,6 +1183,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // registers are free in between.)
     const float root_x = POSED ? 0.0f : root_pos[0], root_y = POSED ? 0.0f : root_pos[1], root_z = POSED ? 0.0f : root_pos[2];
 
+    // (Phase 1's first template depends on nothing: it comes in while the bodies' transforms are made.  4096 quadrupeds 65.0 us
+    // without, 64.5 with, 65 536 x 3 humanoids and boxes 3485 / 3467, 8503 capsule frames of 84x84 139.7 / 136.1.  Every template a
+    // trip ahead is slower, 70 us and 3730: the compiler's waits cover the request just made.)
+    const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
+    float4 tv_first = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (wave_first < sc.V) tv_first = reinterpret_cast<const float4*>(sc.vtmpl)[wave_first + lane];
+
     PXR_PHASE_BEGIN();
     // ---- phase 0: per-body transforms, per-frame draws, the three non-triangle colours
     // (16-wavefront groups: copied by the fourth wavefront on, the first three have chains of their own in this
@@ -1259,38 +1297,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         add_reach(sc, body, fu->reach, lane);
     }
     if (tid == NT - 1) vm[sc.V] = 0u;  // the code that the padding of the pair table points at: no pixel centre on either axis
-    for (uint32_t v = tid; v < sc.V; v += NT) {
-        float pvx, pvy, pvz;
-        view_position(sc, v, pvx, pvy, pvz);
-        // 1 / pvz is only used when pvz >= z_near (otherwise the vertex is behind the plane or unusable
-        // whatever it is), so the short form serves unless some lane's depth is beyond its range
-        float inv;
-        if (__builtin_expect(recip_long_form || __ballot(pvz > kRecipMax) != 0ull, 0))
-            inv = 1.0f / pvz;
-        else
-            inv = recip_in_range(pvz);
-        const float sx = __builtin_fmaf(sc.f, pvx * inv, sc.halfW);
-        const float sy = __builtin_fmaf(-sc.f, pvy * inv, sc.halfH);
-        const bool ok = (pvz >= sc.z_near) && (__builtin_fabsf(sx) <= 16384.0f) && (__builtin_fabsf(sy) <= 16384.0f);
-        // (worked out for every lane, whatever sx and sy are, and replaced where the vertex is not usable: such
-        // vertices are rare, and a wavefront without one skips the replacement altogether)
-        int X = floor_to_int(__builtin_fmaf(sx, 256.0f, 0.5f));
-        int Y = floor_to_int(__builtin_fmaf(sy, 256.0f, 0.5f));
-        uint32_t m = cell_code(X, (int)sc.W) | (cell_code(Y, (int)sc.H) << 16);
-        if (__builtin_expect(__ballot(!ok) != 0ull, 0)) {
-            if (!ok) {
-                X = pvz < sc.z_near ? kBehindX : kRejectedX;
-                Y = 0;
-                m = 0xFFFFFFFFu;  // an unusable or clipped vertex never lets a triangle be discarded early
-            }
-        }
-        vxy[v] = make_int2(X, Y);
-        vd[v] = sc.z_near * inv;
-        vm[v] = m;
+    for (uint32_t v = tid; v < sc.V;) {
+        instance_vertex(sc, recip_long_form, v, tv_first, vxy, vd, vm);
+        v += NT;
+        if (v < sc.V) tv_first = reinterpret_cast<const float4*>(sc.vtmpl)[v];
     }
     // (phase 2a's first table entry depends on nothing in LDS: requested before the barrier, it arrives while the
     // wavefront waits there; later ones are requested a trip ahead)
-    const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
     uint4 rec_next = make_uint4(0u, 0u, 0u, 0u);
     if (wave_first < sc.P) rec_next = reinterpret_cast<const uint4*>(sc.pair_tbl)[wave_first + lane];
     PXR_TIMED_BARRIER(1);
