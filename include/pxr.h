@@ -280,7 +280,8 @@ int pxr_pipeline_info(const pxr_pipeline* p, uint32_t B, uint32_t* chunks);
 
 /* Scene facts for callers and tests (sizes of what pxr_create_scene built; no passage of the paper): total
  * template vertices and triangles, dynamic LDS bytes per frame workgroup, threads per workgroup.  Any out
- * pointer may be NULL.  Errors: INVALID_ARG (null scene). */
+ * pointer may be NULL.  block_threads is that of launches which fill the device; smaller ones may take another.
+ * Errors: INVALID_ARG (null scene). */
 int pxr_scene_info(const pxr_scene* s, uint32_t* n_verts, uint32_t* n_tris, uint32_t* lds_bytes,
                    uint32_t* block_threads);
 

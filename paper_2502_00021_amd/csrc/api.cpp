@@ -18,8 +18,9 @@ struct pxr_scene {
     pxr::SkeletonConsts sk{};
     void* d_skeleton = nullptr;
     int device = 0;
-    uint32_t block_threads = 0;
+    uint32_t block_threads = 0;    // of launches that fill the device, or those of every launch if the caller has chosen
     uint32_t default_threads = 0;
+    bool threads_chosen = false;
     uint32_t n_cus = 0;
 };
 
@@ -43,6 +44,39 @@ void pxr::scene_shape(const pxr_scene* s, uint32_t* K, uint32_t* H, uint32_t* W)
 }
 
 namespace {
+
+// How many workgroups a compute unit's LDS holds.
+uint32_t groups_in_lds(const pxr::SceneConsts& sc) { return (160u * 1024u) / (sc.lds_total ? sc.lds_total : 1u); }
+
+uint32_t pick_block_threads(const pxr::SceneConsts& sc) {
+    // Fill the 32 wave slots of a compute unit: LDS decides how many frame
+    // workgroups are resident, the workgroup size makes up the rest.  (The
+    // 1024-thread variant is compiled for 64 VGPRs so that two of them fit; those of 256 and 512 take up to 72, which
+    // leaves 28 slots: seven workgroups or three.)
+    // us for 25 million pixels, 256 / 512 threads, by the workgroups in LDS: 7 (meshes 28x28) 180 / 250, 6 (capsules 48x48) 57.5 / 84.5,
+    // 5 (capsules 56x56) 64.0 / 72.4, (chains 32x32) 177 / 196, (meshes 40x40) 132 / 159; 4 (capsules 64x64) 55.0 / 61.0, (chains 48x48)
+    // 106 / 105, (meshes 56x56) 111 / 103; 3 (quadrupeds 48x48) 160 / 118.
+    const uint32_t groups_per_cu = groups_in_lds(sc);
+    if (groups_per_cu >= 5) return 256;
+    if (groups_per_cu >= 3) return 512;
+    if (groups_per_cu == 2 && sc.key_capacity && sc.npix < pxr::kWideWindowedFrom) return 768;
+    return 1024;
+}
+
+// Workgroup size of a launch: few frames leave compute units with fewer workgroups than their LDS would hold, and these then
+// share its wave slots.  us, 256 / 512 / 1024 threads: 256 frames (one per compute unit), meshes 64x64 15.7 / 10.6 / 8.8, quadrupeds
+// 48x48 12.3 / 8.5 / 7.5, chains 32x32 8.4 / 6.8 / 6.7, but capsules 40x40, whose 264 vertices need no more, 7.1 / 6.4 / 6.7; 512 frames, meshes 40x40
+// 11.1 / 9.1 / 9.1, chains 32x32 8.8 / 7.6 / 8.3, capsules 48x48 8.1 / 7.3 / 8.3; 1024 frames, meshes 48x48 15.2 / 16.6 / 17.3, chains 48x48 13.4 /
+// 15.1 / 16.4, capsules 64x64 12.2 / 15.6 / 17.1.
+uint32_t launch_threads(const pxr_scene* s, uint64_t n_frames) {
+    const uint32_t in_lds = groups_in_lds(s->sc);
+    if (s->threads_chosen || in_lds < 3u) return s->block_threads;
+    const uint64_t per_cu = (n_frames + s->n_cus - 1u) / s->n_cus;
+    if (per_cu <= 1u) return s->sc.V >= 512u ? 1024u : 512u;
+    if (per_cu <= 3u || in_lds == 3u) return 512u;
+    if (per_cu == 4u) return 256u;
+    return s->block_threads;
+}
 
 // pxr::render_envs, which takes the poses as they are (fk null), or makes them in the same launch.
 int render_posed(pxr_scene* s, const pxr::FkArgs* fk, const float* d_poses, const float* d_shapes, uint32_t e0, uint32_t n, uint32_t S,
@@ -68,7 +102,7 @@ int render_posed(pxr_scene* s, const pxr::FkArgs* fk, const float* d_poses, cons
     pxr::DistractConsts dc = s->dc;  // the per-environment arrays follow the environments
     if (dc.env_offset) dc.env_offset += e0;
     if (dc.env_video) dc.env_video += e0;
-    return pxr::launch_render(s->sc, dc, fk, poses, shapes, n * S, S, step0, env0 + e0, frames, ids, s->block_threads, s->n_cus, stream, err);
+    return pxr::launch_render(s->sc, dc, fk, poses, shapes, n * S, S, step0, env0 + e0, frames, ids, launch_threads(s, (uint64_t)n * S), s->n_cus, stream, err);
 }
 
 }  // namespace
@@ -79,17 +113,6 @@ int pxr::render_envs(pxr_scene* s, const float* d_poses, const float* d_shapes, 
 }
 
 namespace {
-
-uint32_t pick_block_threads(const pxr::SceneConsts& sc) {
-    // Fill the 32 wave slots of a compute unit: LDS decides how many frame
-    // workgroups are resident, the workgroup size makes up the rest.  (The
-    // 1024-thread variant is compiled for 64 VGPRs so that two of them fit.)
-    const uint32_t groups_per_cu = (160u * 1024u) / (sc.lds_total ? sc.lds_total : 1u);
-    if (groups_per_cu >= 8) return 256;
-    if (groups_per_cu >= 3) return 512;
-    if (groups_per_cu == 2 && sc.key_capacity && sc.npix < pxr::kWideWindowedFrom) return 768;
-    return 1024;
-}
 
 // The kernels' dynamic-LDS caps are raised once per device and process, by the first scene created there.
 int prepare_device_once(int device, std::string& err) {
@@ -413,7 +436,7 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
 // 12.6 / 9.7, 2048 41.3 / 40.9, 4096 73 / 76; chain (7 depths) 256 frames 14.1 / 11.2, 1024 25.6 / 24.4, 2048 42.2 / 44.4; quadrupeds of
 // 256x256 (a workgroup per compute unit), 256 frames 35.4 / 32.1, 1024 108.6 / 108.4.
 bool worth_one_launch(const pxr_scene* s, uint64_t n_frames) {
-    const uint32_t per_cu = std::min(160u * 1024u / s->sc.lds_total, 2048u / s->block_threads);
+    const uint32_t per_cu = std::min(groups_in_lds(s->sc), 2048u / launch_threads(s, n_frames));
     const uint64_t resident = (uint64_t)per_cu * s->n_cus, rounds = (n_frames + resident - 1) / resident;
     return rounds * (s->sk.depths + 1u) <= kPosedRoundsTimesDepths;
 }
@@ -547,10 +570,12 @@ int pxr_measure_peaks(double* fma_tlaneops, double* imad_tlaneops, double* copy_
 
 int pxr_set_block_threads(pxr_scene* s, uint32_t threads) {
     if (!s) return fail(PXR_ERR_INVALID_ARG, "pxr_set_block_threads: null scene");
+    const bool chosen = threads != 0;
     if (threads == 0) threads = s->default_threads;
     if (threads != 256 && threads != 512 && threads != 768 && threads != 1024)
         return fail(PXR_ERR_INVALID_ARG, "pxr_set_block_threads: must be 256, 512, 768 or 1024");
     s->block_threads = threads;
+    s->threads_chosen = chosen;
     return PXR_OK;
 }
 

@@ -87,6 +87,27 @@ def test_configs_match_oracle(torch, pxr, orc, cfg, B, threads):
     assert tri.any() and (ref["ids"] == GROUND).any() and (ref["ids"] == BG).any()
 
 
+@pytest.mark.parametrize("scene,size", [("capsules", 32), ("capsules", 56), ("chain", 48), ("chain", 41), ("mesh", 64)])
+def test_workgroup_size_by_frames_per_compute_unit(torch, pxr, scene, size):
+    """Scenes of which three and more workgroups fit a compute unit: 1, 2, 4 and more frames for each take workgroups of
+    1024, 512 and 256 threads; whatever the batch, a frame's bytes and ids are those of a size that the caller chose."""
+    from paper_2502_00021_amd import workloads as wl
+    n = 1400
+    w = {"capsules": wl.cfg1, "chain": wl.cfg2, "mesh": wl.cfg_mesh}[scene](n)
+    sc = pxr.Scene(dict(w["desc"], width=size, height=size))
+    assert sc.info()["lds_bytes"] * 3 <= 160 * 1024
+    poses = torch.from_numpy(w["poses"]).cuda()
+    n_cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sc.set_block_threads(512)
+    ref, ref_ids = sc.render_batch(poses, want_ids=True)
+    sc.set_block_threads(0)
+    for batch in sorted({1, n_cus, n_cus + 1, 2 * n_cus + 3, 3 * n_cus + 1, 4 * n_cus, min(n, 5 * n_cus)}):
+        frames, ids = sc.render_batch(poses[:batch].contiguous(), want_ids=True)
+        torch.cuda.synchronize()
+        assert torch.equal(frames, ref[:batch]) and torch.equal(ids, ref_ids[:batch]), batch
+    sc.close()
+
+
 def test_default_block_threads_and_info(torch, pxr, orc):
     for cfg in (1, 2, 3, 4, 5):
         w = wl.make(cfg, B=2)
