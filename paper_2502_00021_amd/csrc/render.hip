@@ -1071,13 +1071,16 @@ __device__ __forceinline__ void draw_frame(const SceneConsts& sc, const Distract
             fu->video_frame = clip * dc.n_frames + (uint32_t)(((u64)first + (u64)step) % dc.n_frames);
         }
     }
-    if (VIDEO && sc.lds_vlut && tid >= 64u) {
+    // (from the fourth wavefront of the largest workgroups on: the second has the rows of the image, the third the draws.  chains of 56x84
+    // over a clip from the second on 161 us, now 158.7; 768 threads, 84x84, the other way round 415 and 418.)
+    constexpr uint32_t kTablesFrom = NT >= 1024 ? 192u : 64u;
+    if (VIDEO && sc.lds_vlut && tid >= kTablesFrom) {
         // Video-blend tables: under the clip lies the background or a ground grey (no colour distractor in this
         // mode), so a blended channel is a function of (one of five colours, clip byte).  Four entries per lane.
         // Nine tables of 256 bytes: background r, g, b, then each grey's three times over - the channel of a byte is
         // then the same address offset (256 x channel) whatever lies under the clip, a constant in the read.
         uint32_t* vlut = reinterpret_cast<uint32_t*>(lds + sc.lds_vlut);
-        for (uint32_t i = tid - 64u; i < 5u * 64u; i += NT - 64u) {
+        for (uint32_t i = tid - kTablesFrom; i < 5u * 64u; i += NT - kTablesFrom) {
             const uint32_t t = i >> 6, at = i & 63u;
             const float c = t == 0 ? sc.bg[0] : t == 1 ? sc.bg[1] : t == 2 ? sc.bg[2] : t == 3 ? sc.gs[0] : sc.gs[1];
             uint32_t word = 0;
@@ -1195,8 +1198,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     if (tid >= kCopyFrom)
         for (uint32_t i = tid - kCopyFrom; i < sc.W + sc.H; i += NT - kCopyFrom) cxcy[i] = sc.cxcy[i];
     // The draws come before the bodies in the large workgroups (65 536 x 3 frames of 64x64 3517 us the other way round, now 3488),
-    // whose third wavefront they are, after them in the small ones (256 capsule frames of 48x48 7.2 us the other way round, now 6.8).
-    constexpr bool kDrawFirst = NT >= 768;
+    // whose third wavefront they are, after them in the small ones (256 capsule frames of 48x48 7.2 us the other way round, now 6.8), and
+    // after them over a clip in windows of the largest (quadrupeds of 83x256 86.1 us the other way round, now 84.9).
+    constexpr bool kDrawFirst = NT == 768 || (NT >= 1024 && !(VIDEO && WINDOWED));
     if constexpr (!POSED && kDrawFirst) draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
     if constexpr (POSED) {
         if (tid < 64u)
