@@ -54,7 +54,8 @@ uint32_t pick_block_threads(const pxr::SceneConsts& sc) {
     // 1024-thread variant is compiled for 64 VGPRs so that two of them fit; those of 256 and 512 take up to 72, which
     // leaves 28 slots: seven workgroups or three.)
     // us for 25 million pixels, 256 / 512 threads, by the workgroups in LDS: 7 (meshes 28x28) 180 / 250, 6 (capsules 48x48) 57.5 / 84.5,
-    // 5 (capsules 56x56) 64.0 / 72.4, (chains 32x32) 177 / 196, (meshes 40x40) 132 / 159; 4 (capsules 64x64) 55.0 / 61.0, (chains 48x48)
+    // 5 (capsules 56x56) 64.0 / 72.4, (chains 32x32) 177 / 196, (meshes 40x40) 132 / 159, at worst (2792 meshes
+    // of 38x48 over a clip, two rounds and a fifth) 39.6 / 38.7; 4 (capsules 64x64) 55.0 / 61.0, (chains 48x48)
     // 106 / 105, (meshes 56x56) 111 / 103; 3 (quadrupeds 48x48) 160 / 118.
     const uint32_t groups_per_cu = groups_in_lds(sc);
     if (groups_per_cu >= 5) return 256;
