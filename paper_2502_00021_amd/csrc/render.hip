@@ -384,13 +384,38 @@ __device__ __forceinline__ uint32_t quantise(float c) {
 
 // ---------------------------------------------------------------- the kernel
 
-// The kernel's first two (by-value) arguments, read afresh from the kernel-argument segment: whatever the
-// compiler loaded from them before is not reused after this point.  The band loop of tall frames takes its
-// constants through this at the top of every trip, so that they are fetched again (scalar loads that hit the
+// The render kernel's arguments as they lie in the kernel-argument segment: in order, each at its type's alignment.
+struct RenderArguments {
+    SceneConsts sc;
+    DistractConsts dc;
+    const float* poses;
+    const float* shapes;
+    uint32_t S, step0, env0;
+    uint8_t* frames;
+    uint32_t* ids;
+    uint32_t slabs_log2;
+    FkArgs fk;  // (of the kernels that make their poses)
+};
+
+// An argument where it lies in that segment.  The compiler takes a by-value argument apart as soon as it can, loads
+// its members at the kernel's head and keeps each in scalar registers until its last use.  Read through this, a member is
+// loaded where it is used.  What that decides is how many scalar registers a kernel takes, and with them how many of its wavefronts
+// are resident: a SIMD has 800 and hands them out in steps of 16, and each wavefront has 16 more than its kernel names (for the trap
+// handler), so eight wavefronts have 80 each.  With more, four workgroups of 512 threads do not fit a compute unit (with 82 three do).
+// us by value (92 to 106 scalar registers) / in place (65 to 80): 12 000 capsule frames of 64x64 109.9 / 92.5, 16 384 of chains of 48x48
+// 155.4 / 134.5, over a clip 180.6 / 153.5, 47 wide 198.7 / 167; 2048 from joint angles 30.7 / 25.7.  The kernels of 1024 threads are
+// held to 80 and parked what they had no room for in lanes of vector registers: 8192 humanoid frames of 63x63 over a clip 221.9 (48
+// parked) / 162 (none), 64x64 163.2 (18) / 153.7.
+template <typename T>
+__device__ __forceinline__ const T& argument_in_place(uint32_t byte_offset) {
+    typedef const __attribute__((address_space(4))) unsigned char* KernargBytes;
+    return *(const T*)(const __attribute__((address_space(4))) T*)((KernargBytes)__builtin_amdgcn_kernarg_segment_ptr() + byte_offset);
+}
+
+// The same, read afresh: whatever the compiler loaded from it before is not reused after this point.  The band loop of tall frames takes
+// its constants through this at the top of every trip, so that they are fetched again (scalar loads that hit the
 // constant cache) instead of being kept in scalar registers across the whole loop, which the 1024-thread
 // variants do not have.
-constexpr uint32_t kSceneArgAt = 0;
-constexpr uint32_t kDistractArgAt = (sizeof(SceneConsts) + alignof(DistractConsts) - 1) / alignof(DistractConsts) * alignof(DistractConsts);
 template <typename T>
 __device__ __forceinline__ const T& argument_reloaded(uint32_t byte_offset) {
     typedef const __attribute__((address_space(4))) unsigned char* KernargBytes;
@@ -398,6 +423,7 @@ __device__ __forceinline__ const T& argument_reloaded(uint32_t byte_offset) {
     asm volatile("" : "+s"(p));
     return *(const T*)(const __attribute__((address_space(4))) T*)p;
 }
+#define PXR_ARGUMENT(READ, MEMBER) argument_##READ<decltype(RenderArguments::MEMBER)>((uint32_t)offsetof(RenderArguments, MEMBER))
 
 // Ask for every cache line of the kernel's arguments at once.  They lie in memory that a launch's first wavefronts find in no
 // cache; as the compiler places the loads, each next group of arguments would wait for a miss of its own.
@@ -1112,7 +1138,10 @@ __device__ __forceinline__ void draw_frame(const SceneConsts& sc, const Distract
         uint32_t packed = 0;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            float v = k == 0u ? sc.bg[c] : (k == 1u ? sc.gs[0] : sc.gs[1]);
+            // (the three are loaded first: as "k == 0 ? sc.bg[c] : ..." the compiler chooses an address for each lane and loads through
+            // the vector unit, three round trips in a row: 12 000 capsule frames of 64x64 95.7 us, now 92.5)
+            const float sky = sc.bg[c], grey0 = sc.gs[0], grey1 = sc.gs[1];
+            float v = k == 0u ? sky : (k == 1u ? grey0 : grey1);
             if (!VIDEO && dc.mode == PXR_DISTRACT_COLOR) {
                 v = __builtin_fmaf(v, scale[c], offs[c]);
                 v = v > 0.0f ? v : 0.0f;
@@ -1143,11 +1172,18 @@ struct KinematicArgs<false> {};
 // POSED: the poses are not read from memory but made here, from joint angles (pose_frame).
 template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO, bool POSED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ? 8 : (NT >= 768 ? 6 : 4)))) void render_kernel(
-    const SceneConsts sc, const DistractConsts dc, const float* __restrict__ poses, const float* __restrict__ shapes,
+    const SceneConsts sc_value, const DistractConsts dc_value, const float* __restrict__ poses, const float* __restrict__ shapes,
     uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2,
-    const KinematicArgs<POSED> fk) {
+    const KinematicArgs<POSED>) {
     // (where a launch is one round or two; 65 536 x 3 frames would take 3504 us for 3488)
-    if constexpr (POSED || NT <= 512) request_arguments<kDistractArgAt + sizeof(DistractConsts) + 40u + (POSED ? sizeof(FkArgs) : 0u)>();
+    if constexpr (POSED || NT <= 512) request_arguments<offsetof(RenderArguments, poses) + 40u + (POSED ? sizeof(FkArgs) : 0u)>();
+    // The largest whole-frame kernels without a clip, which are bound by instruction issue, have their arguments by value all the same: fewer
+    // loads and waits, six registers parked.  By value / in place: 65 536 x 3 frames of 64x64 3470 / 3531 us, 4096 quadrupeds 64.2 / 65.5, 8503
+    // capsule frames of 84x84 133 / 136.  (Windowed: 1024 quadruped frames of 161x160 45.2 / 44.4.)  So have the windowed ones of 768, of which
+    // the LDS holds two workgroups: 16 384 humanoid frames of 84x84 over a clip 411.9 / 417.2 us, 4096 of 110x75 113.2 / 113.9.
+    constexpr bool kByValue = !POSED && ((NT >= 1024 && !VIDEO && !WINDOWED) || (NT == 768 && WINDOWED));
+    const SceneConsts& sc = kByValue ? sc_value : PXR_ARGUMENT(in_place, sc);
+    const DistractConsts& dc = kByValue ? dc_value : PXR_ARGUMENT(in_place, dc);
     extern __shared__ __align__(16) unsigned char lds[];
     // the key buffer's LDS holds the cell codes and the candidate list until the keys are cleared
     uint32_t* vm = reinterpret_cast<uint32_t*>(lds + sc.lds_keys);
@@ -1204,7 +1240,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     if constexpr (!POSED && kDrawFirst) draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
     if constexpr (POSED) {
         if (tid < 64u)
-            pose_frame(fk.args, frame, body, fu, sc.root, sc.off[0], sc.off[1], sc.off[2], lane, !WINDOWED || (block & ((1u << slabs_log2) - 1u)) == 0u);
+            pose_frame(PXR_ARGUMENT(in_place, fk), frame, body, fu, sc.root, sc.off[0], sc.off[1], sc.off[2], lane, !WINDOWED || (block & ((1u << slabs_log2) - 1u)) == 0u);
         else
             draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
         __syncthreads();
@@ -1430,8 +1466,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     const uint32_t tid_kept = tid;
     bool more_bands;
     do {
-        const SceneConsts& scb = WINDOWED ? argument_reloaded<SceneConsts>(kSceneArgAt) : sc;
-        const DistractConsts& dcb = WINDOWED ? argument_reloaded<DistractConsts>(kDistractArgAt) : dc;
+        const SceneConsts& scb = WINDOWED ? PXR_ARGUMENT(reloaded, sc) : sc;
+        const DistractConsts& dcb = WINDOWED ? PXR_ARGUMENT(reloaded, dc) : dc;
         // (In the band loop everything is derived again from the reloaded arguments and from a thread index the
         // compiler cannot see through: nothing but the band counter and the index stays live from band to band.)
         uint32_t tid = tid_kept;
