@@ -45,18 +45,23 @@ void pxr::scene_shape(const pxr_scene* s, uint32_t* K, uint32_t* H, uint32_t* W)
 
 namespace {
 
-// How many workgroups a compute unit's LDS holds.
-uint32_t groups_in_lds(const pxr::SceneConsts& sc) { return (160u * 1024u) / (sc.lds_total ? sc.lds_total : 1u); }
+// How many workgroups a compute unit's LDS holds: it is handed out in steps of 1280 bytes.  (Meshes of 40x40, 30 016 bytes a frame, are five: 1280
+// frames in workgroups of 256 threads take 14.7 us, one round.  Chains of 32x32, 32 528 bytes, are four and not five: 15.5 us, 10.2 for 1024.)
+uint32_t groups_in_lds(const pxr::SceneConsts& sc) {
+    const uint32_t steps = 160u * 1024u / 1280u, per_group = (sc.lds_total + 1279u) / 1280u;
+    return steps / std::max(per_group, 1u);
+}
+
+// How many of a compute unit's workgroups are resident: what its LDS holds, and its 32 wave slots.  (The kernels for whole frames take 61 or 62
+// vector and at most 80 scalar registers, eight wavefronts per SIMD.  The windowed ones of up to 768 threads take 70, seven per SIMD, but
+// the LDS holds two of their workgroups at most, 24 wavefronts.)
+uint32_t resident_groups(const pxr::SceneConsts& sc, uint32_t threads) { return std::min(groups_in_lds(sc), 2048u / threads); }
 
 uint32_t pick_block_threads(const pxr::SceneConsts& sc) {
-    // Fill the 32 wave slots of a compute unit: LDS decides how many frame
-    // workgroups are resident, the workgroup size makes up the rest.  (The
-    // 1024-thread variant is compiled for 64 VGPRs so that two of them fit; those of 256 and 512 take up to 72, which
-    // leaves 28 slots: seven workgroups or three.)
-    // us for 25 million pixels, 256 / 512 threads, by the workgroups in LDS: 7 (meshes 28x28) 180 / 250, 6 (capsules 48x48) 57.5 / 84.5,
-    // 5 (capsules 56x56) 64.0 / 72.4, (chains 32x32) 177 / 196, (meshes 40x40) 132 / 159, at worst (2792 meshes
-    // of 38x48 over a clip, two rounds and a fifth) 39.6 / 38.7; 4 (capsules 64x64) 55.0 / 61.0, (chains 48x48)
-    // 106 / 105, (meshes 56x56) 111 / 103; 3 (quadrupeds 48x48) 160 / 118.
+    // Fill the 32 wave slots of a compute unit: LDS decides how many frame workgroups are resident, the workgroup size makes up the rest.
+    // us for 25 million pixels, 256 / 512 threads, by the workgroups in LDS: 7 (meshes 32x32) 138 / 174, 6 (capsules 48x48) 58.0 / 71.5, 5
+    // (meshes 40x40) 133 / 139; 4 (capsules 64x64) 54.6 / 51.7, (chains 48x48) 108 / 92, (meshes 56x56) 111 / 90.5, (meshes 38x48 over a clip)
+    // 173 / 145; 3 (quadrupeds 48x48) 163 / 120.
     const uint32_t groups_per_cu = groups_in_lds(sc);
     if (groups_per_cu >= 5) return 256;
     if (groups_per_cu >= 3) return 512;
@@ -64,19 +69,22 @@ uint32_t pick_block_threads(const pxr::SceneConsts& sc) {
     return 1024;
 }
 
-// Workgroup size of a launch: few frames leave compute units with fewer workgroups than their LDS would hold, and these then
-// share its wave slots.  us, 256 / 512 / 1024 threads: 256 frames (one per compute unit), meshes 64x64 15.7 / 10.6 / 8.8, quadrupeds
-// 48x48 12.3 / 8.5 / 7.5, chains 32x32 8.4 / 6.8 / 6.7, but capsules 40x40, whose 264 vertices need no more, 7.1 / 6.4 / 6.7; 512 frames, meshes 40x40
-// 11.1 / 9.1 / 9.1, chains 32x32 8.8 / 7.6 / 8.3, capsules 48x48 8.1 / 7.3 / 8.3; 1024 frames, meshes 48x48 15.2 / 16.6 / 17.3, chains 48x48 13.4 /
-// 15.1 / 16.4, capsules 64x64 12.2 / 15.6 / 17.1.
+// Workgroup size of a launch: few frames leave compute units with fewer workgroups than their LDS would hold, and these then share its wave slots.
 uint32_t launch_threads(const pxr_scene* s, uint64_t n_frames) {
     const uint32_t in_lds = groups_in_lds(s->sc);
     if (s->threads_chosen || in_lds < 3u) return s->block_threads;
     const uint64_t per_cu = (n_frames + s->n_cus - 1u) / s->n_cus;
+    // One workgroup on a compute unit takes all the wavefronts that it has use for.  us for 256 frames, 256 / 512 / 1024 threads: meshes 64x64 15.3 /
+    // 10.7 / 8.7, quadrupeds 48x48 12.3 / 8.6 / 7.4, chains 32x32 8.5 / 7.0 / 6.7; capsules, of 264 vertices, 40x40 7.0 / 6.4 / 6.6, 56x56 8.6 / 7.4 / 7.2.
     if (per_cu <= 1u) return s->sc.V >= 512u ? 1024u : 512u;
-    if (per_cu <= 3u || in_lds == 3u) return 512u;
-    if (per_cu == 4u) return 256u;
-    return s->block_threads;
+    if (in_lds <= 4u) return 512u;
+    // From five workgroups in LDS on, 512 threads as long as that takes no more rounds: a frame is done sooner.  us, 256 / 512 threads: meshes
+    // 40x40 (five), 1024 frames 13.0 / 12.5, 1280 14.7 / 16.9, 1536 20.7 / 18.3, 2792 30.6 / 29.1, 4096 40.8 / 40.4; meshes 28x28 (six), 1024
+    // frames 10.2 / 9.9, 1280 11.2 / 13.0, 2048 17.5 / 17.3.  Frames of few vertices have less to gain: capsules 48x48 (six), 768 frames 8.6 / 8.4, 1024
+    // 9.4 / 9.6, 2048 16.3 / 17.1; 40x40 (eight), 512 frames 7.5 / 7.3, 768 7.9 / 8.2.
+    if (s->sc.V < 512u) return per_cu <= (in_lds < 8u ? 3u : 2u) ? 512u : 256u;
+    const uint64_t wide = resident_groups(s->sc, 512u), narrow = resident_groups(s->sc, 256u);
+    return (per_cu + wide - 1u) / wide <= (per_cu + narrow - 1u) / narrow ? 512u : 256u;
 }
 
 // pxr::render_envs, which takes the poses as they are (fk null), or makes them in the same launch.
@@ -437,7 +445,7 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
 // 12.6 / 9.7, 2048 41.3 / 40.9, 4096 73 / 76; chain (7 depths) 256 frames 14.1 / 11.2, 1024 25.6 / 24.4, 2048 42.2 / 44.4; quadrupeds of
 // 256x256 (a workgroup per compute unit), 256 frames 35.4 / 32.1, 1024 108.6 / 108.4.
 bool worth_one_launch(const pxr_scene* s, uint64_t n_frames) {
-    const uint32_t per_cu = std::min(groups_in_lds(s->sc), 2048u / launch_threads(s, n_frames));
+    const uint32_t per_cu = resident_groups(s->sc, launch_threads(s, n_frames));
     const uint64_t resident = (uint64_t)per_cu * s->n_cus, rounds = (n_frames + resident - 1) / resident;
     return rounds * (s->sk.depths + 1u) <= kPosedRoundsTimesDepths;
 }

@@ -50,3 +50,34 @@ def one_body_scene(body, W=32, H=32, **over):
 
 def pose_row(pos, quat=(1.0, 0.0, 0.0, 0.0)):
     return np.array([*pos, *quat], dtype=np.float32)
+
+
+def captured_kernels(torch, call):
+    """[(threads per workgroup, workgroups)] of the kernels that `call` enqueues on the current stream, in order: it is captured
+    into a graph that is never launched."""
+    import ctypes as C
+
+    class Dim3(C.Structure):
+        _fields_ = [("x", C.c_uint32), ("y", C.c_uint32), ("z", C.c_uint32)]
+
+    class KernelNodeParams(C.Structure):  # hipKernelNodeParams
+        _fields_ = [("block", Dim3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", Dim3), ("args", C.c_void_p),
+                    ("shared_bytes", C.c_uint32)]
+
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:  # (the runtime that is loaded already)
+        hip = C.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    handle, n = C.c_void_p(graph.raw_cuda_graph()), C.c_size_t(0)
+    assert hip.hipGraphGetNodes(handle, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * max(n.value, 1))()
+    assert hip.hipGraphGetNodes(handle, nodes, C.byref(n)) == 0
+    kernels = []
+    for node in nodes[:n.value]:
+        kind, p = C.c_int(-1), KernelNodeParams()
+        assert hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)) == 0
+        assert kind.value == 0, "the call enqueues something that is no kernel"
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        kernels.append((p.block.x, p.grid.x))
+    return kernels

@@ -6,6 +6,7 @@ operation order is used on both sides, so the expected difference is 0 and is as
 import numpy as np
 import pytest
 
+from helpers import captured_kernels
 from paper_2502_00021_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -87,24 +88,45 @@ def test_configs_match_oracle(torch, pxr, orc, cfg, B, threads):
     assert tri.any() and (ref["ids"] == GROUND).any() and (ref["ids"] == BG).any()
 
 
-@pytest.mark.parametrize("scene,size", [("capsules", 32), ("capsules", 56), ("chain", 48), ("chain", 41), ("mesh", 64)])
-def test_workgroup_size_by_frames_per_compute_unit(torch, pxr, scene, size):
-    """Scenes of which three and more workgroups fit a compute unit: 1, 2, 4 and more frames for each take workgroups of
-    1024, 512 and 256 threads; whatever the batch, a frame's bytes and ids are those of a size that the caller chose."""
-    from paper_2502_00021_amd import workloads as wl
-    n = 1400
-    w = {"capsules": wl.cfg1, "chain": wl.cfg2, "mesh": wl.cfg_mesh}[scene](n)
-    sc = pxr.Scene(dict(w["desc"], width=size, height=size))
-    assert sc.info()["lds_bytes"] * 3 <= 160 * 1024
-    poses = torch.from_numpy(w["poses"]).cuda()
+# (scene, width, height, distractor, workgroups that a compute unit's LDS holds, threads by the frames per compute unit).  The LDS is handed out in
+# steps of 1280 bytes: 32 to 33 KB (capsules of 56x56, chains of 32x32) are four workgroups.
+@pytest.mark.parametrize("scene,w,h,mode,in_lds,sizes", [
+    ("capsules", 32, 32, "none", 10, {1: 512, 2: 512, 3: 256, 4: 256, 5: 256, 7: 256}),
+    ("capsules", 47, 48, "color", 6, {1: 512, 2: 512, 3: 512, 4: 256, 5: 256, 7: 256}),
+    ("capsules", 56, 56, "video", 4, {1: 512, 2: 512, 4: 512, 5: 512, 7: 512}),
+    ("chain", 32, 32, "color", 4, {1: 1024, 2: 512, 3: 512, 4: 512, 5: 512, 7: 512}),
+    ("chain", 41, 41, "video", 4, {1: 1024, 2: 512, 4: 512, 5: 512}),
+    ("mesh", 28, 28, "video", 6, {1: 1024, 2: 512, 4: 512, 5: 256, 6: 256, 7: 512}),
+    ("mesh", 40, 40, "none", 5, {1: 1024, 2: 512, 4: 512, 5: 256, 6: 512, 7: 512}),
+    ("mesh", 64, 64, "color", 3, {1: 1024, 2: 512, 3: 512, 4: 512, 5: 512})])
+def test_workgroup_size_by_frames_per_compute_unit(torch, pxr, scene, w, h, mode, in_lds, sizes):
+    """Scenes of which three and more workgroups fit a compute unit: the size of a launch's workgroups follows its frames per compute
+    unit, and whatever the size, a frame's bytes and ids are those of 768 threads, which no rule chooses here."""
     n_cus = torch.cuda.get_device_properties(0).multi_processor_count
-    sc.set_block_threads(512)
+    n = max(sizes) * n_cus
+    make = {"capsules": wl.cfg1, "chain": wl.cfg2, "mesh": wl.cfg_mesh}[scene]
+    work = make(n)
+    sc = pxr.Scene(dict(work["desc"], width=w, height=h))
+    assert 128 // -(-sc.info()["lds_bytes"] // 1280) == in_lds
+    if mode == "video":
+        clip = torch.from_numpy(np.random.default_rng(h).integers(0, 256, (5, h, w, 3), dtype=np.uint8)).cuda()
+        sc.apply_distractor(dict(mode="video", seed=4, alpha=0.5, video=clip))
+    elif mode == "color":
+        sc.apply_distractor(dict(mode="color", seed=4, scale=(0.5, 1.5), offset=(-0.2, 0.2)))
+    else:
+        sc.apply_distractor(None)
+    poses = torch.from_numpy(work["poses"]).cuda()
+    sc.set_block_threads(768)
     ref, ref_ids = sc.render_batch(poses, want_ids=True)
+    assert captured_kernels(torch, lambda: sc.render_batch(poses[:3], frames=ref[:3])) == [(768, 3)]
     sc.set_block_threads(0)
-    for batch in sorted({1, n_cus, n_cus + 1, 2 * n_cus + 3, 3 * n_cus + 1, 4 * n_cus, min(n, 5 * n_cus)}):
-        frames, ids = sc.render_batch(poses[:batch].contiguous(), want_ids=True)
-        torch.cuda.synchronize()
-        assert torch.equal(frames, ref[:batch]) and torch.equal(ids, ref_ids[:batch]), batch
+    for per_cu, threads in sizes.items():
+        for batch in (1 if per_cu == 1 else (per_cu - 1) * n_cus + 1, per_cu * n_cus):
+            frames, ids = torch.zeros_like(ref[:batch]), torch.zeros_like(ref_ids[:batch])
+            assert captured_kernels(torch, lambda: sc.render_batch(poses[:batch], frames=frames, ids=ids)) == [(threads, batch)]
+            sc.render_batch(poses[:batch], frames=frames, ids=ids)
+            torch.cuda.synchronize()
+            assert torch.equal(frames, ref[:batch]) and torch.equal(ids, ref_ids[:batch]), batch
     sc.close()
 
 
