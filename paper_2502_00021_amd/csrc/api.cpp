@@ -440,10 +440,12 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
 
 // Whether the render kernel makes the poses itself, in the same launch.  That saves the kinematics kernel's launch (4 to 5 us) and
 // costs every round of workgroups the chain of steps from the angles to the poses: about as long for a tree of d depths as
-// d + 1 times 0.25 us.  us per call, two launches / one, 64x64 unless said otherwise: humanoid (4 depths) 1 frame 12.6 / 9.6, 256
-// frames 14.7 / 10.7, 1024 (two rounds) 28.5 / 25.6, 2048 (four) 47.3 / 46.1, 4096 (eight) 84 / 87; quadruped (3 depths) 256 frames
-// 12.6 / 9.7, 2048 41.3 / 40.9, 4096 73 / 76; chain (7 depths) 256 frames 14.1 / 11.2, 1024 25.6 / 24.4, 2048 42.2 / 44.4; quadrupeds of
-// 256x256 (a workgroup per compute unit), 256 frames 35.4 / 32.1, 1024 108.6 / 108.4.
+// d + 1 times 0.25 us.  (A round is what is resident with either kernel: the pose-making ones take no more registers than the others.)
+// us per call, two launches / one, 64x64 unless said otherwise: humanoid (4 depths) 1 frame 11.9 / 9.0, 256 frames 13.9 / 9.9, 1024 (two
+// rounds) 27.4 / 24.2, 2048 (four) 45.4 / 44.0, 4096 (eight) 81.0 / 83.0; quadruped (3 depths) 256 frames 11.7 / 8.9, 2048 38.9 / 38.6, at worst 2560
+// 46.5 / 47.1, 4096 68.9 / 72.3; chain (7 depths) 256 frames 13.2 / 10.3, 1024 24.3 / 23.1, 1280 28.9 / 29.4; chains of 48x48 (four resident) 1024
+// frames 17.2 / 14.3, 2048 26.8 / 25.7, 2560 31.3 / 31.4, 4096 43.7 / 46.2; quadrupeds of 256x256 (a workgroup per compute unit), 256 frames
+// 34.5 / 30.6, 1280 130.7 / 129.3, 1800 188.8 / 189.9.
 bool worth_one_launch(const pxr_scene* s, uint64_t n_frames) {
     const uint32_t per_cu = resident_groups(s->sc, launch_threads(s, n_frames));
     const uint64_t resident = (uint64_t)per_cu * s->n_cus, rounds = (n_frames + resident - 1) / resident;

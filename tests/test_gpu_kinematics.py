@@ -24,6 +24,7 @@ import ctypes
 import numpy as np
 import pytest
 
+from helpers import captured_kernels
 from paper_2502_00021_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -344,6 +345,25 @@ def test_when_the_render_kernel_makes_the_poses(torch, pxr):
     assert L.pxr_kinematic_info(sc._h, 0, ctypes.byref(n_launches)) == pxr.ERR_INVALID_ARG
     sc.set_skeleton(None, 0, 0)
     assert L.pxr_kinematic_info(sc._h, 1, ctypes.byref(n_launches)) == pxr.ERR_INVALID_ARG
+    sc.close()
+
+
+@pytest.mark.parametrize("cfg,size,in_round,depths", [(2, 48, 4, 7), (3, 48, 3, 3), (3, 64, 2, 3), (5, 64, 2, 4), (3, 256, 1, 3)])
+def test_launches_of_a_kinematic_call(torch, pxr, cfg, size, in_round, depths):
+    """One kernel up to 20 / (depths + 1) rounds of resident workgroups, two from the next frame on, as the scene says."""
+    w = wl.make(cfg, B=1)
+    w["desc"] = dict(w["desc"], width=size, height=size)
+    fk = w["fk"]
+    sc = _scene_with_skeleton(pxr, w)
+    n_cus = torch.cuda.get_device_properties(0).multi_processor_count
+    most = 20 // (depths + 1) * in_round * n_cus
+    free = torch.from_numpy(np.broadcast_to(fk["free_poses"][:, :1], (most + 1, 1) + fk["free_poses"].shape[2:]).copy()).cuda()
+    angles = torch.from_numpy(np.broadcast_to(fk["angles"][:, :1], (most + 1, 1) + fk["angles"].shape[2:]).copy()).cuda()
+    for n, launches in ((1, 1), (most, 1), (most + 1, 2)):
+        frames = torch.empty((n, 1, size, size, 3), dtype=torch.uint8, device="cuda")
+        poses = torch.empty((n, 1, w["poses"].shape[2], 7), device="cuda")
+        kernels = captured_kernels(torch, lambda: sc.render_batch_kinematic(free[:n], angles[:n], frames=frames, poses=poses))
+        assert len(kernels) == sc.kinematic_launches(n) == launches, n
     sc.close()
 
 
