@@ -452,8 +452,8 @@ bool worth_one_launch(const pxr_scene* s, uint64_t n_frames) {
     return rounds * (s->sk.depths + 1u) <= kPosedRoundsTimesDepths;
 }
 
-bool poses_made_by_renderer(const pxr_scene* s, const float* d_free_poses, const float* d_angles, uint64_t n_frames,
-                            const float* d_poses, const uint8_t* d_frames, const uint32_t* d_ids) {
+bool poses_made_by_renderer(const pxr_scene* s, const float* d_free_poses, const float* d_angles, const float* d_shapes, uint32_t B,
+                            uint64_t n_frames, const float* d_poses, const uint8_t* d_frames, const uint32_t* d_ids) {
     if (!worth_one_launch(s, n_frames)) return false;
     // (a caller may let the outputs take the place of the angles or the free poses: then all of these are read first)
     const size_t free_bytes = n_frames * s->sk.F * 28, angle_bytes = n_frames * s->sk.J * 4, pose_bytes = n_frames * s->sc.K * 28,
@@ -463,7 +463,12 @@ bool poses_made_by_renderer(const pxr_scene* s, const float* d_free_poses, const
         const size_t bytes = out == 0 ? pose_bytes : (out == 1 ? frame_bytes : id_bytes);
         if (overlap(p, bytes, d_free_poses, free_bytes) || overlap(p, bytes, d_angles, angle_bytes)) return false;
     }
-    return true;
+    // (and all poses are written before the rest of the inputs is read and before a frame is written)
+    const pxr::DistractConsts& dc = s->dc;
+    return !overlap(d_poses, pose_bytes, d_frames, frame_bytes) && !overlap(d_poses, pose_bytes, d_ids, id_bytes) &&
+           !overlap(d_poses, pose_bytes, d_shapes, (size_t)B * s->sc.K * 16) && !overlap(d_poses, pose_bytes, dc.env_offset, (size_t)B * 4) &&
+           !overlap(d_poses, pose_bytes, dc.env_video, (size_t)B * 4) &&
+           !overlap(d_poses, pose_bytes, dc.video, (size_t)dc.n_videos * dc.n_frames * s->sc.npix * 3);
 }
 
 }  // namespace
@@ -476,7 +481,7 @@ int pxr_render_batch_kinematic(pxr_scene* s, const float* d_free_poses, const fl
     if (!d_frames) return fail(PXR_ERR_INVALID_ARG, "pxr_render_batch_kinematic: null frames");
     int rc = check_pose_batch(s, d_free_poses, d_angles, B * S, d_poses);
     if (rc != PXR_OK) return rc;
-    if (poses_made_by_renderer(s, d_free_poses, d_angles, (uint64_t)B * S, d_poses, d_frames, d_ids)) {
+    if (poses_made_by_renderer(s, d_free_poses, d_angles, d_shapes, B, (uint64_t)B * S, d_poses, d_frames, d_ids)) {
         const pxr::FkArgs fk = {s->sk, d_free_poses, d_angles, d_poses};
         std::string err;
         rc = render_posed(s, &fk, d_poses, d_shapes, 0, B, S, step0, env0, d_frames, d_ids, hip_stream, err);

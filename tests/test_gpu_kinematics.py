@@ -367,6 +367,40 @@ def test_launches_of_a_kinematic_call(torch, pxr, cfg, size, in_round, depths):
     sc.close()
 
 
+def test_poses_over_another_buffer_take_two_launches(torch, pxr):
+    """Poses that the caller places over an input or output of the render stage are all written before that stage begins."""
+    w = wl.make(2, B=6)
+    fk = w["fk"]
+    B, S, K = w["poses"].shape[:3]
+    h, wd = w["desc"]["height"], w["desc"]["width"]
+    sc = _scene_with_skeleton(pxr, w)
+    free, angles = torch.from_numpy(fk["free_poses"]).cuda(), torch.from_numpy(fk["angles"]).cuda()
+    frames = torch.empty((B, S, h, wd, 3), dtype=torch.uint8, device="cuda")
+    ids = torch.empty((B, S, h, wd), dtype=torch.int32, device="cuda")
+    shapes = torch.full((B, K, 4), 0.1, device="cuda")
+    clip = torch.zeros((4, h, wd, 3), dtype=torch.uint8, device="cuda")
+    offsets = torch.zeros(4096, dtype=torch.int32, device="cuda")
+    elsewhere = torch.empty((B, S, K, 7), device="cuda")
+
+    def launches(poses):
+        args = (sc._h, free.data_ptr(), angles.data_ptr(), shapes.data_ptr(), B, S, 0, 0, poses, frames.data_ptr(), ids.data_ptr())
+
+        def call():
+            assert pxr.lib().pxr_render_batch_kinematic(*args, torch.cuda.current_stream().cuda_stream) == pxr.OK
+        return len(captured_kernels(torch, call))  # (captured, not run: the poses' buffer may reach beyond the one that it begins in)
+
+    assert launches(elsewhere.data_ptr()) == 1
+    for buffer in (frames, ids, shapes, free, angles):
+        assert launches(buffer.data_ptr()) == 2
+        assert launches(buffer.data_ptr() + buffer.numel() * buffer.element_size() - 4) == 2  # (begins in the last word)
+        assert launches(buffer.data_ptr() - 4 * elsewhere.numel() + 4) == 2  # (ends in the first)
+    sc.apply_distractor(dict(mode="video", seed=1, alpha=0.5, video=clip, env_offset=offsets[:B]))
+    assert launches(elsewhere.data_ptr()) == 1
+    for buffer in (clip, offsets[:B]):
+        assert launches(buffer.data_ptr()) == 2
+    sc.close()
+
+
 @pytest.mark.parametrize("env", ["halfcheetah", "ant", "walker2d", "humanoid"])
 def test_paper_environment_stand_ins(torch, pxr, orc, env):
     """The four environments the paper supports, as skeleton workloads: angles -> poses -> frames on the device."""
