@@ -1097,8 +1097,8 @@ __device__ __forceinline__ void draw_frame(const SceneConsts& sc, const Distract
             fu->video_frame = clip * dc.n_frames + (uint32_t)(((u64)first + (u64)step) % dc.n_frames);
         }
     }
-    // (from the fourth wavefront of the largest workgroups on: the second has the rows of the image, the third the draws.  chains of 56x84
-    // over a clip from the second on 161 us, now 158.7; 768 threads, 84x84, the other way round 415 and 418.)
+    // (from the fourth wavefront of the largest workgroups on: the second has the rows of the image, the third the draws.  8192 frames of chains of
+    // 56x84 over a clip from the second on 151.2 us, now 146.9; 768 threads, 84x84, the other way round 415 and 418.)
     constexpr uint32_t kTablesFrom = NT >= 1024 ? 192u : 64u;
     if (VIDEO && sc.lds_vlut && tid >= kTablesFrom) {
         // Video-blend tables: under the clip lies the background or a ground grey (no colour distractor in this
@@ -1233,10 +1233,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     constexpr uint32_t kCopyFrom = NT >= 1024 ? 192u : 0u;
     if (tid >= kCopyFrom)
         for (uint32_t i = tid - kCopyFrom; i < sc.W + sc.H; i += NT - kCopyFrom) cxcy[i] = sc.cxcy[i];
-    // The draws come before the bodies in the large workgroups (65 536 x 3 frames of 64x64 3517 us the other way round, now 3488),
-    // whose third wavefront they are, after them in the small ones (256 capsule frames of 48x48 7.2 us the other way round, now 6.8), and
-    // after them over a clip in windows of the largest (quadrupeds of 83x256 86.1 us the other way round, now 84.9).
-    constexpr bool kDrawFirst = NT == 768 || (NT >= 1024 && !(VIDEO && WINDOWED));
+    // The draws come before the bodies in the large workgroups, whose third wavefront (or last) they are: 65 536 x 3 frames of 64x64 3665 us the
+    // other way round, now 3484, 4096 quadrupeds 69.6 / 65.1, 8503 capsule frames of 84x84 140.4 / 133.4, 1024 quadrupeds of 83x256 over a clip 92.7 /
+    // 91.7.  In the small ones after them: 256 capsule frames of 48x48 7.2 us the other way round, now 6.8.
+    constexpr bool kDrawFirst = NT >= 768;
     if constexpr (!POSED && kDrawFirst) draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
     if constexpr (POSED) {
         if (tid < 64u)
