@@ -425,16 +425,19 @@ __device__ __forceinline__ const T& argument_reloaded(uint32_t byte_offset) {
 }
 #define PXR_ARGUMENT(READ, MEMBER) argument_##READ<decltype(RenderArguments::MEMBER)>((uint32_t)offsetof(RenderArguments, MEMBER))
 
-// Ask for every cache line of the kernel's arguments at once.  They lie in memory that a launch's first wavefronts find in no
-// cache; as the compiler places the loads, each next group of arguments would wait for a miss of its own.
-template <uint32_t BYTES>
+// Ask for every cache line of the kernel's arguments at once, of which it has BYTES.  They lie in memory that a launch's first wavefronts
+// find in no cache; as the compiler places the loads, each next group of arguments would wait for a miss of its own.
+// A word of each line that they fill, and the first word behind them (the implicit arguments, of which the grid's size is the first), which
+// lies in the line of the last ones.  (A word more than one of a line is not free: 12 000 capsule frames of 64x64 92.5 us, 94.0 with two more.)
+template <size_t BYTES>
 __device__ __forceinline__ void request_arguments() {
     typedef const __attribute__((address_space(4))) uint32_t* KernargWords;
+    static_assert(BYTES % 8u == 0u, "the implicit arguments follow at a multiple of 8 bytes");
     const KernargWords p = (KernargWords)__builtin_amdgcn_kernarg_segment_ptr();
     uint32_t any = 0;
 #pragma unroll
-    for (uint32_t at = 0; at < BYTES; at += 64u) any |= p[at / 4u];
-    any |= *(KernargWords)__builtin_amdgcn_implicitarg_ptr();  // (the grid's size, behind the kernel's own arguments)
+    for (uint32_t at = 0; at + 64u <= BYTES; at += 64u) any |= p[at / 4u];
+    any |= *(KernargWords)__builtin_amdgcn_implicitarg_ptr();
     asm volatile("" : : "s"(any));
 }
 
@@ -1175,8 +1178,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     const SceneConsts sc_value, const DistractConsts dc_value, const float* __restrict__ poses, const float* __restrict__ shapes,
     uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2,
     const KinematicArgs<POSED>) {
-    // (where a launch is one round or two; 65 536 x 3 frames would take 3504 us for 3488)
-    if constexpr (POSED || NT <= 512) request_arguments<offsetof(RenderArguments, poses) + 40u + (POSED ? sizeof(FkArgs) : 0u)>();
+    // (In the kernels that make poses, which serve a few rounds at most, and in those of up to 512 threads, whose launches may be one round or
+    // hundreds.  us without / with: 16 capsule frames of 32x32 6.3 / 5.7, 256 of 48x48 7.2 / 6.6, 512 meshes of 40x40 9.5 / 9.1, 256 chains from angles
+    // 10.8 / 10.3; of many rounds 10 850 capsule frames of 48x48 58.0 / 57.7, 31 887 of 28x28 101.2 / 102.2.  Larger workgroups have less of it, 10
+    // humanoids of 64x64 8.2 / 8.0, and more often many rounds: 4096 quadrupeds 64.4 / 64.9, 65 536 x 3 frames 3480 / 3492.)
+    if constexpr (POSED || NT <= 512) request_arguments<POSED ? sizeof(RenderArguments) : offsetof(RenderArguments, fk)>();
     // The largest whole-frame kernels without a clip, which are bound by instruction issue, have their arguments by value all the same: fewer
     // loads and waits, six registers parked.  By value / in place: 65 536 x 3 frames of 64x64 3470 / 3531 us, 4096 quadrupeds 64.2 / 65.5, 8503
     // capsule frames of 84x84 133 / 136.  (Windowed: 1024 quadruped frames of 161x160 45.2 / 44.4.)  So have the windowed ones of 768, of which
