@@ -200,9 +200,9 @@ int pxr_render_batch_kinematic(pxr_scene* s, const float* d_free_poses, const fl
 int pxr_kinematic_info(const pxr_scene* s, uint32_t n_frames, uint32_t* n_launches);
 
 /* pxr_render_batch_kinematic for callers that cannot allocate device memory or provide a workspace: code
- * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The poses between the two
- * kernels live in a 32 MiB buffer that is part of the library's image on each GPU (held until the process
- * ends) instead of in d_poses; they are not returned.  The call allocates and frees nothing and only enqueues.
+ * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The poses live
+ * in a 32 MiB buffer that is part of the library's image on each GPU (held until the process
+ * ends) instead of in d_poses, also where the call is one kernel; they are not returned.  The call allocates and frees nothing and only enqueues.
  * Calls on one GPU share that buffer: two calls whose kernels may overlap (different streams without an
  * ordering between them) race; calls on one stream, or ordered by events, are safe.  Nothing carries over
  * from one call to the next.

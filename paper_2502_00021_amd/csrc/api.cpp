@@ -513,8 +513,8 @@ int pxr_render_batch_kinematic_static(pxr_scene* s, const float* d_free_poses, c
         return fail(PXR_ERR_UNSUPPORTED, "pxr_render_batch_kinematic_static: B*S*n_bodies*28 = " + std::to_string(need) +
                                              " bytes of poses exceed the library's " + std::to_string(capacity) +
                                              "-byte static buffer; use pxr_render_batch_kinematic with a buffer of your own");
-    // (every pose the render kernel reads is written by the kinematics kernel in front of it on the same stream:
-    // nothing of an earlier call's contents is used, so nothing needs clearing)
+    // (every pose the render kernel reads is written by the kinematics kernel in front of it on the same stream, or made by
+    // itself and only written: nothing of an earlier call's contents is used, so nothing needs clearing)
     return pxr_render_batch_kinematic(s, d_free_poses, d_angles, d_shapes, B, S, step0, env0, d_poses, d_frames, d_ids,
                                       hip_stream);
 }

@@ -1034,20 +1034,8 @@ __device__ __forceinline__ void instance_vertex(const SceneConsts& sc, bool reci
     vm[v] = m;
 }
 
-// Register budget: two 80 KB workgroups share a compute unit, so 1024-thread groups need all
-// 8 wave slots per SIMD (<= 64 VGPRs); the smaller groups may use more registers.
-// RAGGED: the width is no multiple of 4 (resolve_groups).
-// WINDOWED: the key buffer does not hold the frame but the part of it that the bodies can touch (its window, found per
-// frame in phase 1), a band of rows at a time if need be; the other pixels need no keys at all and are resolved by
-// whichever wavefronts are done with the raster phase first.  The bodies of the articulated scenes touch 7 to 17 % of a
-// frame, so most windows fit in one piece where the whole frame took two to five bands, each a walk over all binned
-// triangles and three barriers.  Against bands of whole rows: 16 384 humanoid frames of 84x84 over a clip 493 -> 415 us,
-// 1024 humanoid-and-box frames of 256x256 242 -> 156 us, 3648 of 128x128 237 -> 144 us, quadrupeds of 256x256 184 -> 98 us.
-// Frames whose keys fit as a whole beside a second workgroup (64x64) do not take it: the same number of instructions, and
-// the few wavefronts that get the window's pixels shade them all (65 536 x 3 frames 3.53 -> 3.81 ms).
-// 1 << slabs_log2 workgroups share a windowed frame, each takes a run of its rows (and repeats the geometry).
 // The part of phase 0 that needs no pose: the frame's draws and what is made of them, counters set to zero, the video
-// distractor's tables (by the second wavefront on).
+// distractor's tables (by the second or fourth wavefront on).
 template <int NT, bool WINDOWED, bool VIDEO>
 __device__ __forceinline__ void draw_frame(const SceneConsts& sc, const DistractConsts& dc, FrameUniforms* fu, unsigned char* lds,
                                            uint32_t e, uint32_t env, uint32_t step, uint32_t tid) {
@@ -1172,6 +1160,18 @@ struct KinematicArgs {
 template <>
 struct KinematicArgs<false> {};
 
+// Register budget: two 80 KB workgroups share a compute unit, so 1024-thread groups need all
+// 8 wave slots per SIMD (<= 64 VGPRs, <= 80 scalar registers); the smaller groups with windows use more (70).
+// RAGGED: the width is no multiple of 4 (resolve_groups).
+// WINDOWED: the key buffer does not hold the frame but the part of it that the bodies can touch (its window, found per
+// frame in phase 1), a band of rows at a time if need be; the other pixels need no keys at all and are resolved by
+// whichever wavefronts are done with the raster phase first.  The bodies of the articulated scenes touch 7 to 17 % of a
+// frame, so most windows fit in one piece where the whole frame took two to five bands, each a walk over all binned
+// triangles and three barriers.  Against bands of whole rows: 16 384 humanoid frames of 84x84 over a clip 493 -> 415 us,
+// 1024 humanoid-and-box frames of 256x256 242 -> 156 us, 3648 of 128x128 237 -> 144 us, quadrupeds of 256x256 184 -> 98 us.
+// Frames whose keys fit as a whole beside a second workgroup (64x64) do not take it: the same number of instructions, and
+// the few wavefronts that get the window's pixels shade them all (65 536 x 3 frames 3.53 -> 3.81 ms).
+// 1 << slabs_log2 workgroups share a windowed frame, each takes a run of its rows (and repeats the geometry).
 // POSED: the poses are not read from memory but made here, from joint angles (pose_frame).
 template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO, bool POSED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ? 8 : (NT >= 768 ? 6 : 4)))) void render_kernel(
