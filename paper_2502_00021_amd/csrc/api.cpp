@@ -447,7 +447,8 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
 // frames 17.2 / 14.3, 2048 26.8 / 25.7, 2560 31.3 / 31.4, 4096 43.7 / 46.2; quadrupeds of 256x256 (a workgroup per compute unit), 256 frames
 // 34.5 / 30.6, 1280 130.7 / 129.3, 1800 188.8 / 189.9.
 bool worth_one_launch(const pxr_scene* s, uint64_t n_frames) {
-    const uint32_t per_cu = resident_groups(s->sc, launch_threads(s, n_frames));
+    const uint32_t threads = launch_threads(s, n_frames), per_cu = resident_groups(s->sc, threads);
+    if (!pxr::makes_poses(threads, s->sc.key_capacity != 0u)) return false;
     const uint64_t resident = (uint64_t)per_cu * s->n_cus, rounds = (n_frames + resident - 1) / resident;
     return rounds * (s->sk.depths + 1u) <= kPosedRoundsTimesDepths;
 }

@@ -161,6 +161,9 @@ struct HostScene {
 // left for the caller).  Returns a PXR_* code and a message on failure.
 int build_host_scene(const pxr_scene_desc& desc, HostScene& hs, std::string& err);
 
+// Which render kernels are built to make poses as well: not those of few threads with windows, which only a caller's choice reaches.
+constexpr bool makes_poses(uint32_t block_threads, bool windowed) { return !windowed || block_threads >= 768u; }
+
 // render.hip: enqueue one batch.  `block_threads` in {256,512,768,1024}; `n_cus` compute units of the device.
 // `fk`: the poses are not read but made in the same launch, from joint angles (null: read from d_poses).
 int launch_render(const SceneConsts& sc, const DistractConsts& dc, const FkArgs* fk, const float* d_poses, const float* d_shapes,

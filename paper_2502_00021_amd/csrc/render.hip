@@ -1716,10 +1716,15 @@ template <int NT, bool RAGGED, bool WINDOWED, bool VIDEO>
 int launch_one(const SceneConsts& sc, const DistractConsts& dc, const FkArgs* fk, const float* d_poses, const float* d_shapes,
                uint32_t n_frames, uint32_t S, uint32_t step0, uint32_t env0, uint8_t* d_frames, uint32_t* d_ids,
                uint32_t slabs_log2, hipStream_t stream, std::string& err) {
-    if (fk)
-        hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO, true>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
-                           sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2, KinematicArgs<true>{*fk});
-    else
+    if constexpr (makes_poses(NT, WINDOWED)) {
+        if (fk)
+            hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO, true>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
+                               sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2, KinematicArgs<true>{*fk});
+    } else if (fk) {
+        err = "this workgroup size has no kernel that makes poses";
+        return PXR_ERR_UNSUPPORTED;
+    }
+    if (!fk)
         hipLaunchKernelGGL((render_kernel<NT, RAGGED, WINDOWED, VIDEO, false>), dim3(n_frames << slabs_log2), dim3(NT), sc.lds_total, stream,
                            sc, dc, d_poses, d_shapes, S, step0, env0, d_frames, d_ids, slabs_log2, KinematicArgs<false>{});
     const hipError_t rc = hipGetLastError();
@@ -1744,7 +1749,7 @@ int prepare_one(uint32_t lds_bytes, std::string& err) {
         err = std::string("hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: ") + hipGetErrorString(rc);
         return PXR_ERR_DEVICE;
     }
-    if constexpr (!POSED) return prepare_one<NT, RAGGED, WINDOWED, VIDEO, true>(lds_bytes, err);
+    if constexpr (!POSED && makes_poses(NT, WINDOWED)) return prepare_one<NT, RAGGED, WINDOWED, VIDEO, true>(lds_bytes, err);
     return PXR_OK;
 }
 

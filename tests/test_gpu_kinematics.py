@@ -367,6 +367,25 @@ def test_launches_of_a_kinematic_call(torch, pxr, cfg, size, in_round, depths):
     sc.close()
 
 
+@pytest.mark.parametrize("threads,launches", [(0, 1), (256, 2), (512, 2), (768, 1), (1024, 1)])
+def test_launches_of_a_chosen_workgroup_size(torch, pxr, threads, launches):
+    """Frames in windows: workgroups of 256 and 512 threads, which only a caller's choice gives, take two kernels; the same bytes."""
+    w = wl.make(5, B=3)
+    w["desc"] = dict(w["desc"], width=100, height=90)
+    fk = w["fk"]
+    sc = _scene_with_skeleton(pxr, w)
+    free, angles = torch.from_numpy(fk["free_poses"]).cuda(), torch.from_numpy(fk["angles"]).cuda()
+    ref, ref_ids = sc.render_batch(sc.pose_batch(free, angles), want_ids=True)
+    sc.set_block_threads(threads)
+    frames, ids, poses = sc.render_batch_kinematic(free, angles, want_ids=True)
+    torch.cuda.synchronize()
+    assert torch.equal(frames, ref) and torch.equal(ids, ref_ids)
+    kernels = captured_kernels(torch, lambda: sc.render_batch_kinematic(free, angles, frames=frames, poses=poses))
+    assert len(kernels) == sc.kinematic_launches(frames.shape[0] * frames.shape[1]) == launches
+    assert kernels[-1][0] == (threads or 768)
+    sc.close()
+
+
 def test_poses_over_another_buffer_take_two_launches(torch, pxr):
     """Poses that the caller places over an input or output of the render stage are all written before that stage begins."""
     w = wl.make(2, B=6)
