@@ -3,6 +3,8 @@
 Bar: winning-id maps bit-exact; RGB within 1/255 per channel after uint8 rounding (the same fp32
 operation order is used on both sides, so the expected difference is 0 and is asserted where noted).
 """
+import itertools
+
 import numpy as np
 import pytest
 
@@ -417,6 +419,35 @@ def test_close_up_at_512(torch, pxr, orc):
 
 
 # ---------------------------------------------------------------- caller-supplied meshes
+
+@pytest.mark.parametrize("W,H,threads", [(64, 64, None), (61, 64, 256), (256, 256, None)])
+def test_corners_on_and_beside_pixel_centres(torch, pxr, orc, W, H, threads):
+    """Every triangle over a 3 x 3 lattice of half pixels, in both orientations, wherever its corners lie on pixel centres and wherever
+    between them: which centres its ends may cover, and which triangles are left out unseen, is the fill rule's matter alone."""
+    lattice = [(x, y) for y in range(3) for x in range(3)]
+    tris = [t for t in itertools.permutations(range(9), 3)
+            if t[0] == min(t) and np.cross(np.subtract(lattice[t[1]], lattice[t[0]]), np.subtract(lattice[t[2]], lattice[t[0]])) != 0]
+    assert len(tris) == 152
+    # a view straight along x with a focal length of H / 2: at depth 2 a world unit is H / 4 pixels, a power of two, so every corner is
+    # exactly where it is put
+    depth, per_pixel = 2.0, 4.0 / H
+    verts = []
+    for n, (t, dx, dy) in enumerate(itertools.product(tris, (0.0, 0.5), (0.0, 0.5))):  # (a centre in the middle, at the sides, at the corners)
+        for corner in t:
+            px = 0.5 * lattice[corner][0] + 2 * (n % 29) + 1 + dx
+            py = 0.5 * lattice[corner][1] + 2 * (n // 29) + 1 + dy
+            verts.append((0.0, -(px - W / 2) * per_pixel, -(py - H / 2) * per_pixel))
+    idx = np.arange(len(verts), dtype=np.uint32).reshape(-1, 3)
+    d = wl.default_scene(W, H, [wl.mesh(np.array(verts, np.float32), idx, (0.8, 0.5, 0.3))])
+    d.update(cam_offset=(-depth, 0.0, 0.0), fov_y_deg=90.0)
+    poses = np.zeros((2, 1, 1, 7), np.float32)
+    poses[..., 2], poses[..., 3] = 1.0, 1.0
+    w = dict(desc=d, poses=poses, shapes=None, distractor=None)
+    ref = oracle_render(orc, w)
+    seen = np.unique(ref["ids"][ref["ids"] < GROUND])
+    assert 60 < len(seen) < 150
+    assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
+
 
 @pytest.mark.parametrize("W,H,B,threads", [(64, 64, 40, None), (84, 84, 17, 512), (32, 32, 24, 256), (200, 160, 5, None)])
 def test_mesh_bodies_match_oracle(torch, pxr, orc, W, H, B, threads):
