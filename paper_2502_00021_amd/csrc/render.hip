@@ -90,83 +90,159 @@ __device__ __forceinline__ float unit_float(uint32_t x) { return (float)(x >> 8)
 // coordinate's upper bits are then the number of the cell between two centres that it lies in, and the first and the last
 // centre of a range follow from them without an addition (31 trips of gathers per frame of 64x64, four additions each).
 __device__ __forceinline__ int snap(float s) { return floor_to_int(__builtin_fmaf(s, 256.0f, 0.5f)) + 127; }
-__device__ __forceinline__ int centre_of(int i) { return (i << 8) + 255; }
+__device__ __forceinline__ int centre_of(int i) {
+    int r;
+    asm("v_lshl_or_b32 %0, %1, 8, %2" : "=v"(r) : "v"(i), "s"(255));  // (i << 8) + 255
+    return r;
+}
 __device__ __forceinline__ int first_centre(int lowest) { return lowest >> 8; }
-// The last centre that a triangle reaching up to `highest` can cover: one that lies on its right or lower end exactly is
+// One past the last centre that a triangle reaching up to `highest` can cover: one that lies on its right or lower end exactly is
 // not covered, whatever its shape.  (Both edges at a right end would have to be top-left ones, which then turn the wrong way
 // round; an edge that goes down, or along the bottom, is none.)
-__device__ __forceinline__ int last_centre(int highest) { return (highest >> 8) - 1; }
+__device__ __forceinline__ int centres_end(int highest) { return highest >> 8; }
 
-struct TriSetup {
-    int ax, ay, bx, by, cx, cy;  // screen order a = v0, b = v2, c = v1
-    float Da, dDb, dDc;
-    int i0, i1, j0, j1;
+// Products and sums of the narrow triangles' setup, as the instructions they are.  (Written with operators the compiler takes them apart: sign
+// extensions around the products, and a fourth induction variable in place of a three-way sum.)
+__device__ __forceinline__ int mul24(int a, int b) {
+    int r;
+    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ int mad24(int a, int b, int c) {
+    int r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ int add3(int a, int b, int c) {
+    int r;
+    asm("v_add3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// A triangle's snapped corners in screen order: a = v0, b = v2, c = v1.
+struct Corners {
+    int ax, ay, bx, by, cx, cy;
+    // Both fixed-point extents below 2^15 ("narrow"): every product of coordinate differences is below 2^30 then, and 24-bit
+    // multiplies are exact.  (Coordinates reach 2^22, products 2^46.)
+    __device__ __forceinline__ bool narrow() const {
+        return ((imax3(ax, bx, cx) - imin3(ax, bx, cx)) | (imax3(ay, by, cy) - imin3(ay, by, cy))) < 32768;
+    }
 };
 
-// The pixels the key buffer stands for: columns [x_lo, x_hi] and rows [y_lo, y_hi] of the frame, `pitch` keys per row.
+// Candidate pixels [i0, i_end) x [j0, j_end) of a triangle.
+struct PixelBox {
+    int i0, i_end, j0, j_end;
+    __device__ __forceinline__ bool empty() const { return i0 >= i_end || j0 >= j_end; }
+};
+
+// The pixels the key buffer stands for: columns [x_lo, x_end) and rows [y_lo, y_end) of the frame, `pitch` keys per row.
 struct RasterWindow {
-    int x_lo, x_hi, y_lo, y_hi;
+    int x_lo, x_end, y_lo, y_end;
     uint32_t pitch;
+};
+
+__device__ __forceinline__ PixelBox candidate_pixels(const RasterWindow& win, const Corners& t) {
+    return {max(win.x_lo, first_centre(imin3(t.ax, t.bx, t.cx))), min(win.x_end, centres_end(imax3(t.ax, t.bx, t.cx))),
+            max(win.y_lo, first_centre(imin3(t.ay, t.by, t.cy))), min(win.y_end, centres_end(imax3(t.ay, t.by, t.cy)))};
+}
+
+// Depth of the plane through a triangle's corners: at corner a, and the differences of b and c to it.
+struct DepthPlane {
+    float Da, dDb, dDc;
 };
 
 // Edge pq is "top-left" when it points up, or is horizontal pointing right
 // (y grows downwards): pixels exactly on it belong to the triangle.
 __device__ __forceinline__ int edge_bias(int dx, int dy) { return (dy < 0 || (dy == 0 && dx > 0)) ? 0 : -1; }
 
-__device__ __forceinline__ void z_test(u64* keys, uint32_t pix, float depth, uint32_t tri) {
-    const u64 key = ((u64)__float_as_uint(depth) << 32) | (u64)(0xFFFFFFFFu - tri);
-    atomicMax(&keys[pix], key);
-}
-
-// Exact products of coordinate differences: 24-bit multiplies when both
-// fixed-point extents of the triangle are below 2^15 (every product < 2^30),
-// 64-bit otherwise (coordinates reach 2^22, products 2^46).
-template <typename I>
-__device__ __forceinline__ I emul(int a, int b);
-template <>
-__device__ __forceinline__ int emul<int>(int a, int b) {
-    return __mul24(a, b);
-}
-template <>
-__device__ __forceinline__ long long emul<long long>(int a, int b) {
-    return (long long)a * (long long)b;
-}
-
-// Walk rows j0 + r, j0 + r + 2^shift, ... of a triangle's candidate pixel range, and in each of them the columns
+// The pixel loops below walk rows j0 + r, j0 + r + 2^shift, ... of a triangle's candidate pixels, and in each of them the columns
 // i0 + c, i0 + c + 2^cshift, ... (a team of 2^shift x 2^cshift lanes shares the triangle; c = cshift = 0: whole rows).
-// Edge functions carry their fill-rule bias and are stepped incrementally; a
+//
+// Narrow triangles.  What most of the raster phase's instructions are for is not the pixels but getting started, once per team and
+// lane (of the triangles that reach this phase two thirds have one candidate pixel).  So: edges ab and ca are taken relative to corner a, with signs
+// that make each edge function a multiply and a multiply-add; edge bc is what is left of twice the area; "top-left" is the sign of one
+// number per edge, 2^16 dy - dx, and of the sum of the other two's for bc.  (With three edge functions of their own and comparisons for the
+// fill rule, 95 instructions instead of 55, 65 536 x 3 frames of 64x64 3401 us, now 3192, 16 384 of 84x84 over a clip 408 / 388, 4096 quadrupeds 64.4 /
+// 60.7, meshes of 110x75 31.0 / 29.5, 256 chains from angles 10.3 / 10.1.  Kept with their fill rule's k taken off, an edge is inside by its sign, and the k
+// is added again where a pixel is covered: for triangles of many pixels two instructions a pixel less; 8503 capsule frames of 84x84 137.8 us with three
+// comparisons per pixel, 131.)
+__device__ __forceinline__ void raster_rows_narrow(const Corners& t, const PixelBox& box, const DepthPlane& d, uint32_t tri,
+                                                   const RasterWindow& win, u64* keys, int r, int shift, int c = 0, int cshift = 0) {
+    const int i = box.i0 + c;
+    int j = box.j0 + r;
+    if (j >= box.j_end) return;
+    if (cshift != 0 && i >= box.i_end) return;
+    const int P = t.ax - t.bx, Q = t.by - t.ay, S = t.cx - t.ax, R = t.ay - t.cy;  // ab = (-P, Q), ca = (-S, R)
+    const int A2 = mul24(P, R) - mul24(Q, S);                                 // > 0: binned triangles face the camera
+    const float invA = recip_in_range((float)A2);
+    // e = - the edge function; a point of ab or ca is inside at e < k, with k = 1 on a top-left edge, else 0.  Kept is e - k.
+    const int u = centre_of(i) - t.ax, v = centre_of(j) - t.ay;
+    const int w_ab = (int)((uint32_t)Q << 16) + P, w_ca = (int)((uint32_t)R << 16) + S;
+    const int k_ab = (int)((uint32_t)w_ab >> 31), k_ca = (int)((uint32_t)w_ca >> 31);
+    int e_ab_row = mad24(P, v, mul24(Q, u)) - k_ab, e_ca_row = mad24(S, v, mul24(R, u)) - k_ca;
+    // the third edge function is A2 + e_ab + e_ca, and inside at > -1 on a top-left edge, > 0 else
+    const int rest = A2 + k_ab + k_ca - (w_ab + w_ca > 0 ? 0 : 1);
+    const int x_ab = (int)((uint32_t)Q << (8 + cshift)), x_ca = (int)((uint32_t)R << (8 + cshift));
+    const int y_ab = (int)((uint32_t)P << (8 + shift)), y_ca = (int)((uint32_t)S << (8 + shift));
+    u64* row = keys + (__umul24((uint32_t)(j - win.y_lo), win.pitch) + (uint32_t)(i - win.x_lo));
+    const int n = box.i_end - i;
+    for (;;) {
+        int e_ab = e_ab_row, e_ca = e_ca_row;
+        u64* p = row;
+        u64* const end = row + n;
+        do {
+            if ((e_ab & e_ca & ~add3(e_ab, e_ca, rest)) < 0) {
+                // (the additions of zero make a weight of zero a positive one)
+                const float beta = __builtin_fmaf((float)(e_ca + k_ca), -invA, 0.0f), gamma = __builtin_fmaf((float)(e_ab + k_ab), -invA, 0.0f);
+                const float depth = __builtin_fmaf(beta, d.dDb, __builtin_fmaf(gamma, d.dDc, d.Da));
+                atomicMax(p, ((u64)__float_as_uint(depth) << 32) | (u64)(0xFFFFFFFFu - tri));
+            }
+            e_ab += x_ab;
+            e_ca += x_ca;
+            p += 1 << cshift;
+        } while (p < end);
+        j += 1 << shift;
+        if (j >= box.j_end) break;
+        e_ab_row += y_ab;
+        e_ca_row += y_ca;
+        row += win.pitch << shift;
+    }
+}
+
+// Any triangle, in 64-bit arithmetic.  Edge functions carry their fill-rule bias and are stepped incrementally; a
 // pixel centre is covered when all three are >= 0.
-template <typename I>
-__device__ __forceinline__ void raster_rows(const TriSetup& s, uint32_t tri, const RasterWindow& win, u64* keys, int r,
-                                            int shift, int c = 0, int cshift = 0) {
-    int j = s.j0 + r;
-    if (j > s.j1) return;
-    const int dx_ab = s.bx - s.ax, dy_ab = s.by - s.ay;
-    const int dx_bc = s.cx - s.bx, dy_bc = s.cy - s.by;
-    const int dx_ca = s.ax - s.cx, dy_ca = s.ay - s.cy;
-    const I A2 = emul<I>(dx_ab, s.cy - s.ay) - emul<I>(dy_ab, s.cx - s.ax);
+__device__ __forceinline__ void raster_rows_wide(const Corners& t, const PixelBox& box, const DepthPlane& d, uint32_t tri,
+                                                 const RasterWindow& win, u64* keys, int r, int shift, int c, int cshift) {
+    typedef long long I;
+    int j = box.j0 + r;
+    if (j >= box.j_end) return;
+    const int dx_ab = t.bx - t.ax, dy_ab = t.by - t.ay;
+    const int dx_bc = t.cx - t.bx, dy_bc = t.cy - t.by;
+    const int dx_ca = t.ax - t.cx, dy_ca = t.ay - t.cy;
+    const I A2 = (I)dx_ab * (I)(t.cy - t.ay) - (I)dy_ab * (I)(t.cx - t.ax);
     const float invA = recip_in_range((float)A2);  // a front face: 1 <= A2 < 2^47
     const I b_ab = edge_bias(dx_ab, dy_ab), b_bc = edge_bias(dx_bc, dy_bc), b_ca = edge_bias(dx_ca, dy_ca);
-    const int px0 = centre_of(s.i0 + c), py = centre_of(j);
-    I f_ab = emul<I>(dx_ab, py - s.ay) - emul<I>(dy_ab, px0 - s.ax) + b_ab;
-    I f_bc = emul<I>(dx_bc, py - s.by) - emul<I>(dy_bc, px0 - s.bx) + b_bc;
-    I f_ca = emul<I>(dx_ca, py - s.cy) - emul<I>(dy_ca, px0 - s.cx) + b_ca;
+    const int px0 = centre_of(box.i0 + c), py = centre_of(j);
+    I f_ab = (I)dx_ab * (I)(py - t.ay) - (I)dy_ab * (I)(px0 - t.ax) + b_ab;
+    I f_bc = (I)dx_bc * (I)(py - t.by) - (I)dy_bc * (I)(px0 - t.bx) + b_bc;
+    I f_ca = (I)dx_ca * (I)(py - t.cy) - (I)dy_ca * (I)(px0 - t.cx) + b_ca;
     const I sx_ab = (I)dy_ab << (8 + cshift), sx_bc = (I)dy_bc << (8 + cshift), sx_ca = (I)dy_ca << (8 + cshift);
     const I sy_ab = (I)dx_ab << (8 + shift), sy_bc = (I)dx_bc << (8 + shift), sy_ca = (I)dx_ca << (8 + shift);
     for (;;) {
         I e_ab = f_ab, e_bc = f_bc, e_ca = f_ca;
-        uint32_t pix = (uint32_t)(j - win.y_lo) * win.pitch + (uint32_t)(s.i0 + c - win.x_lo);
-        for (int i = s.i0 + c; i <= s.i1; i += 1 << cshift, pix += 1u << cshift) {
+        uint32_t pix = (uint32_t)(j - win.y_lo) * win.pitch + (uint32_t)(box.i0 + c - win.x_lo);
+        for (int i = box.i0 + c; i < box.i_end; i += 1 << cshift, pix += 1u << cshift) {
             if ((e_ab | e_bc | e_ca) >= 0) {
                 const float beta = (float)(e_ca - b_ca) * invA, gamma = (float)(e_ab - b_ab) * invA;
-                z_test(keys, pix, __builtin_fmaf(beta, s.dDb, __builtin_fmaf(gamma, s.dDc, s.Da)), tri);
+                const float depth = __builtin_fmaf(beta, d.dDb, __builtin_fmaf(gamma, d.dDc, d.Da));
+                atomicMax(&keys[pix], ((u64)__float_as_uint(depth) << 32) | (u64)(0xFFFFFFFFu - tri));
             }
             e_ab -= sx_ab;
             e_bc -= sx_bc;
             e_ca -= sx_ca;
         }
         j += 1 << shift;
-        if (j > s.j1) break;  // (stepping past the last row could leave the exactly representable range)
+        if (j >= box.j_end) break;  // (stepping past the last row could leave the exactly representable range)
         f_ab += sy_ab;
         f_bc += sy_bc;
         f_ca += sy_ca;
@@ -183,48 +259,57 @@ __device__ __forceinline__ void wave_team(int n_rows, int lane, int& r, int& shi
     c = lane >> shift;
 }
 
-// Gather the snapped vertices of a triangle (ti = its entry of the index table) and its pixel-centre range, clamped to the window.
-// Returns kTriNone if a vertex is unusable, all of them lie behind the near plane or no pixel centre is
-// inside the bounding box; kTriClip if the triangle straddles the near plane (nothing else is valid
-// then); kTriPlain otherwise.  `small_extent` = both fixed-point extents below 2^15.
-enum { kTriNone = 0, kTriPlain = 1, kTriClip = 2 };
-__device__ __forceinline__ int tri_gather(const RasterWindow& win, const uint2 ti, const int2* vxy, TriSetup& s,
-                                          uint32_t& v0, uint32_t& v1, uint32_t& v2, bool& small_extent) {
-    v0 = ti.x & 0xFFFFu;
-    v1 = ti.x >> 16;
-    v2 = ti.y & 0xFFFFu;
-    // (x, y) pairs: one 8-byte LDS read per vertex (as one integer each: read as pairs, the compiler would fetch
-    // the y's separately, after the test of the x's, in a second round trip)
-    const u64 a = reinterpret_cast<const u64*>(vxy)[v0], b = reinterpret_cast<const u64*>(vxy)[v2], c = reinterpret_cast<const u64*>(vxy)[v1];
-    s.ax = (int)(uint32_t)a;
-    s.bx = (int)(uint32_t)b;
-    s.cx = (int)(uint32_t)c;
-    const int minx = imin3(s.ax, s.bx, s.cx), maxx = imax3(s.ax, s.bx, s.cx);
-    if (minx <= kBehindX) {  // a sentinel among the three (rare)
-        if (minx == kRejectedX) return kTriNone;
-        return maxx == kBehindX ? kTriNone : kTriClip;
-    }
-    s.ay = (int)(uint32_t)(a >> 32);
-    s.by = (int)(uint32_t)(b >> 32);
-    s.cy = (int)(uint32_t)(c >> 32);
-    const int miny = imin3(s.ay, s.by, s.cy), maxy = imax3(s.ay, s.by, s.cy);
-    s.i0 = max(win.x_lo, first_centre(minx));
-    s.i1 = min(win.x_hi, last_centre(maxx));
-    s.j0 = max(win.y_lo, first_centre(miny));
-    s.j1 = min(win.y_hi, last_centre(maxy));
-    small_extent = ((maxx - minx) | (maxy - miny)) < 32768;
-    return (s.i0 <= s.i1 && s.j0 <= s.j1) ? kTriPlain : kTriNone;
+// base + scale * one of a word's halves, in one instruction.
+template <int SCALE>
+__device__ __forceinline__ uint32_t at_low_half(uint32_t word, uint32_t base) {
+    uint32_t r;
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(word), "n"(SCALE), "s"(base));
+    return r;
+}
+template <int SCALE>
+__device__ __forceinline__ uint32_t at_high_half(uint32_t word, uint32_t base) {
+    uint32_t r;
+    asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(word), "n"(SCALE), "s"(base));
+    return r;
 }
 
-// Which image rows a binned triangle can touch: kTriPlain with [j0, j1] (not clamped), or kTriClip for a
+// A word of LDS by its byte address.  (The dynamic LDS segment starts at address 0: the kernels here have
+// no static LDS, which prepare_kernels verifies; tables built on the host can therefore hold LDS addresses.)
+template <typename T>
+__device__ __forceinline__ T lds_at(uint32_t byte_address) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) T*>(static_cast<uintptr_t>(byte_address));
+}
+
+// A triangle's corners (ti = its entry of the index table: v0 | v1 << 16, v2 | body << 16).
+__device__ __forceinline__ Corners gather_corners(const uint2 ti, uint32_t lds_vxy) {
+    // (x, y) pairs: one 8-byte LDS read per vertex (as one integer each: read as pairs, the compiler would fetch
+    // the y's separately, after the test of the x's, in a second round trip)
+    const u64 a = lds_at<u64>(at_low_half<8>(ti.x, lds_vxy)), b = lds_at<u64>(at_low_half<8>(ti.y, lds_vxy)),
+              c = lds_at<u64>(at_high_half<8>(ti.x, lds_vxy));
+    return {(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)(uint32_t)b, (int)(uint32_t)(b >> 32), (int)(uint32_t)c, (int)(uint32_t)(c >> 32)};
+}
+
+__device__ __forceinline__ DepthPlane gather_depths(const uint2 ti, uint32_t lds_vd) {
+    const float Da = lds_at<float>(at_low_half<4>(ti.x, lds_vd));
+    return {Da, lds_at<float>(at_low_half<4>(ti.y, lds_vd)) - Da, lds_at<float>(at_high_half<4>(ti.x, lds_vd)) - Da};
+}
+
+// kTriNone if a corner is unusable or all of them lie behind the near plane; kTriClip if the triangle straddles it (the snapped
+// corners say nothing then); kTriPlain otherwise.
+enum { kTriNone = 0, kTriPlain = 1, kTriClip = 2 };
+__device__ __forceinline__ int tri_kind(const Corners& t) {
+    const int minx = imin3(t.ax, t.bx, t.cx);
+    if (minx > kBehindX) return kTriPlain;  // (a sentinel among the three is rare)
+    return minx == kRejectedX || imax3(t.ax, t.bx, t.cx) == kBehindX ? kTriNone : kTriClip;
+}
+
+// Which image rows a binned triangle can touch: kTriPlain with [j0, j_end) (not clamped), or kTriClip for a
 // triangle that straddles the near plane (its snapped corners say nothing: it counts for every row).
-__device__ __forceinline__ int tri_rows(const uint2 ti, const int2* vxy, int& j0, int& j1) {
-    const u64 a = reinterpret_cast<const u64*>(vxy)[ti.x & 0xFFFFu], b = reinterpret_cast<const u64*>(vxy)[ti.y & 0xFFFFu],
-              c = reinterpret_cast<const u64*>(vxy)[ti.x >> 16];
-    if (imin3((int)(uint32_t)a, (int)(uint32_t)b, (int)(uint32_t)c) <= kBehindX) return kTriClip;
-    const int ay = (int)(uint32_t)(a >> 32), by = (int)(uint32_t)(b >> 32), cy = (int)(uint32_t)(c >> 32);
-    j0 = first_centre(imin3(ay, by, cy));
-    j1 = last_centre(imax3(ay, by, cy));
+__device__ __forceinline__ int tri_rows(const uint2 ti, uint32_t lds_vxy, int& j0, int& j_end) {
+    const Corners t = gather_corners(ti, lds_vxy);
+    if (imin3(t.ax, t.bx, t.cx) <= kBehindX) return kTriClip;
+    j0 = first_centre(imin3(t.ay, t.by, t.cy));
+    j_end = centres_end(imax3(t.ay, t.by, t.cy));
     return kTriPlain;
 }
 
@@ -246,28 +331,16 @@ __device__ __forceinline__ void view_position(const float4 tv, float& pvx, float
     pvz = __builtin_fmaf(m1.z, lx, __builtin_fmaf(m1.w, ly, __builtin_fmaf(m2.x, lz, m2.w)));
 }
 
-// One piece (a, b, c in screen order) of a clipped triangle, rastered by a whole wavefront.
-__device__ __forceinline__ void raster_piece(const RasterWindow& win, uint32_t t, int ax, int ay, float Da, int bx, int by,
-                                             float Db, int cx, int cy, float Dc, bool usable, u64* keys, int lane) {
-    if (!usable) return;
-    if (!((long long)(bx - ax) * (long long)(cy - ay) > (long long)(by - ay) * (long long)(cx - ax))) return;  // back face
-    TriSetup s;
-    s.ax = ax; s.ay = ay; s.bx = bx; s.by = by; s.cx = cx; s.cy = cy;
-    const int minx = imin3(ax, bx, cx), maxx = imax3(ax, bx, cx), miny = imin3(ay, by, cy), maxy = imax3(ay, by, cy);
-    s.i0 = max(win.x_lo, first_centre(minx));
-    s.i1 = min(win.x_hi, last_centre(maxx));
-    s.j0 = max(win.y_lo, first_centre(miny));
-    s.j1 = min(win.y_hi, last_centre(maxy));
-    if (s.i0 > s.i1 || s.j0 > s.j1) return;
-    s.Da = Da;
-    s.dDb = Db - Da;
-    s.dDc = Dc - Da;
+// A triangle or a clipped triangle's piece, by a whole wavefront.
+__device__ __forceinline__ void raster_by_wave(const Corners& t, const DepthPlane& d, uint32_t tri, const RasterWindow& win, u64* keys, int lane) {
+    const PixelBox box = candidate_pixels(win, t);
+    if (box.empty()) return;
     int r, shift, c, cshift;
-    wave_team(s.j1 - s.j0 + 1, lane, r, shift, c, cshift);
-    if (((maxx - minx) | (maxy - miny)) < 32768)
-        raster_rows<int>(s, t, win, keys, r, shift, c, cshift);
+    wave_team(box.j_end - box.j0, lane, r, shift, c, cshift);
+    if (t.narrow())
+        raster_rows_narrow(t, box, d, tri, win, keys, r, shift, c, cshift);
     else
-        raster_rows<long long>(s, t, win, keys, r, shift, c, cshift);
+        raster_rows_wide(t, box, d, tri, win, keys, r, shift, c, cshift);
 }
 
 // A triangle with corners on both sides of the near plane (every lane of the wavefront computes the
@@ -329,51 +402,44 @@ __device__ __forceinline__ void raster_clipped(const SceneConsts& sc, const Rast
                 cD[c] = sc.z_near * inv;
             }
         }
-        raster_piece(win, t, cX[0], cY[0], cD[0], cX[1], cY[1], cD[1], cX[2], cY[2], cD[2], usable, keys, lane);
+        const Corners piece_corners = {cX[0], cY[0], cX[1], cY[1], cX[2], cY[2]};
+        const bool front = (long long)(cX[1] - cX[0]) * (long long)(cY[2] - cY[0]) > (long long)(cY[1] - cY[0]) * (long long)(cX[2] - cX[0]);
+        if (usable && front) raster_by_wave(piece_corners, {cD[0], cD[1] - cD[0], cD[2] - cD[0]}, t, win, keys, lane);
     }
 }
 
-// Raster one binned triangle with lane `r` of the 2^shift lanes that share it, restricted to the window that the key
-// buffer currently holds.
-// MAY_CLIP: the bin (the wave-per-triangle one) also holds the triangles that straddle the near plane.
-template <bool MAY_CLIP>
-__device__ __forceinline__ void raster_binned(const SceneConsts& sc, const RasterWindow& win, uint32_t t, const uint2 ti,
-                                              const int2* vxy, const float* vd, u64* keys, int r, int shift) {
-    TriSetup s;
-    uint32_t v0, v1, v2;
-    bool small_extent;
-    const int kind = tri_gather(win, ti, vxy, s, v0, v1, v2, small_extent);
-    if (MAY_CLIP && kind == kTriClip) {
-        raster_clipped(sc, win, t, vxy, vd, keys, r);
-        return;
-    }
-    if (kind != kTriPlain) return;
-    s.Da = vd[v0];
-    s.dDb = vd[v2] - s.Da;
-    s.dDc = vd[v1] - s.Da;
-    int c = 0, cshift = 0;
-    if (MAY_CLIP) wave_team(s.j1 - s.j0 + 1, r, r, shift, c, cshift);  // (the wave-per-triangle bin: r is the lane)
-    if (small_extent)
-        raster_rows<int>(s, t, win, keys, r, shift, c, cshift);
+// A triangle of the tiny or small bin (narrow, not clipped), with lane `r` of the 2^shift lanes that share it, restricted to the window that
+// the key buffer currently holds.  WINDOWED: which may hold none of its pixels.
+template <bool WINDOWED>
+__device__ __forceinline__ void raster_binned(const RasterWindow& win, uint32_t t, const uint2 ti, uint32_t lds_vxy, uint32_t lds_vd, u64* keys,
+                                              int r, int shift) {
+    const Corners corners = gather_corners(ti, lds_vxy);
+    const DepthPlane depths = gather_depths(ti, lds_vd);
+    const PixelBox box = candidate_pixels(win, corners);
+    if (WINDOWED && box.empty()) return;
+    raster_rows_narrow(corners, box, depths, t, win, keys, r, shift);
+}
+
+// A triangle of the large bin, by a whole wavefront: one of many candidate pixels, one whose extents are large whatever it shows of itself, or one to
+// be clipped.
+__device__ __forceinline__ void raster_large(const SceneConsts& sc, const RasterWindow& win, uint32_t t, const uint2 ti, const int2* vxy,
+                                             const float* vd, u64* keys, int lane) {
+    const Corners corners = gather_corners(ti, sc.lds_vxy);
+    if (tri_kind(corners) == kTriClip)
+        raster_clipped(sc, win, t, vxy, vd, keys, lane);
     else
-        raster_rows<long long>(s, t, win, keys, r, shift, c, cshift);
+        raster_by_wave(corners, gather_depths(ti, sc.lds_vd), t, win, keys, lane);
 }
 
 // Per-axis cell code of a snapped coordinate for an image of n pixels: c = after pixel centre c - 1 and up to centre c,
 // clamped to [0, n] (0 = up to centre 0, n = beyond centre n - 1).  No triangle whose corners have the same code on an
-// axis covers a pixel centre (last_centre).  (With a code of its own for "exactly on a centre", as if it were covered from
+// axis covers a pixel centre (centres_end).  (With a code of its own for "exactly on a centre", as if it were covered from
 // both sides, the code took six instructions more per vertex and axis pair and the test of a pair of triangles four: 65 536 x 3
 // frames of 64x64 3478 us, now 3401, 16 384 of 84x84 over a clip 412.7 / 408.0, 4096 quadrupeds 65.1 / 64.4.)
 __device__ __forceinline__ uint32_t cell_code(int x, int n) {
     int r;
     asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(x >> 8), "s"(n));  // clamp(x >> 8, 0, n) in one instruction (n > 0)
     return (uint32_t)r;
-}
-
-// A 32-bit word of LDS by its byte address.  (The dynamic LDS segment starts at address 0: the kernels here have
-// no static LDS, which prepare_kernels verifies; tables built on the host can therefore hold LDS addresses.)
-__device__ __forceinline__ uint32_t lds_u32_at(uint32_t byte_address) {
-    return *reinterpret_cast<const __attribute__((address_space(3))) uint32_t*>(static_cast<uintptr_t>(byte_address));
 }
 
 // The bits in which three words are not all the same, in one instruction.
@@ -1374,7 +1440,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // register moves per trip.)
     const auto coarse_trip = [&](const uint4 rec) {
         const uint32_t w0 = rec.x, w1 = rec.y, w2 = rec.z;
-        const uint32_t m0 = lds_u32_at(w0 & 0xFFFFu), m1 = lds_u32_at(w0 >> 16), m2 = lds_u32_at(w1 & 0xFFFFu), m3 = lds_u32_at(w1 >> 16);
+        const uint32_t m0 = lds_at<uint32_t>(w0 & 0xFFFFu), m1 = lds_at<uint32_t>(w0 >> 16), m2 = lds_at<uint32_t>(w1 & 0xFFFFu), m3 = lds_at<uint32_t>(w1 >> 16);
         const uint32_t da = any_differ(m0, m1, m2), db = any_differ(m0, m2, m3);
         const uint32_t ta = w2 & 0xFFFFu, tb = w2 >> 16;
         const bool keep_a = halves_product(da) != 0u;
@@ -1408,11 +1474,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // then one of three bins by the number of candidate pixel centres (one packed LDS atomic per wave).
     const uint32_t n_cand = fu->n_cand;
     // (the whole frame, or its columns and this workgroup's rows)
-    RasterWindow image = {0, (int)sc.W - 1, 0, (int)sc.H - 1, sc.pitch};
+    RasterWindow image = {0, (int)sc.W, 0, (int)sc.H, sc.pitch};
     if (WINDOWED) {
         const uint32_t slab = block & ((1u << slabs_log2) - 1u);
         image.y_lo = (int)((slab * sc.H) >> slabs_log2);
-        image.y_hi = (int)(((slab + 1u) * sc.H) >> slabs_log2) - 1;
+        image.y_end = (int)(((slab + 1u) * sc.H) >> slabs_log2);
     }
     // (Where the candidates take several trips - smaller workgroups, taller frames - a lane's candidate and its entry
     // of the index table are requested a trip ahead, without a branch: a lane past the end reads a list entry that
@@ -1440,21 +1506,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             ti = reinterpret_cast<const uint2*>(sc.tri_idx)[t];
         }
         if (k < n_cand) {
-            TriSetup s;
-            uint32_t v0, v1, v2;
-            bool small_extent;
-            const int kind = tri_gather(image, ti, vxy, s, v0, v1, v2, small_extent);
+            const Corners q = gather_corners(ti, sc.lds_vxy);
+            const int kind = tri_kind(q);
             if (kind == kTriClip) cls = 3;  // clipped, then rastered, by a whole wavefront
             if (kind == kTriPlain) {
+                const PixelBox box = candidate_pixels(image, q);
+                const bool narrow = q.narrow();
                 bool front;
-                if (small_extent)
-                    front = __mul24(s.bx - s.ax, s.cy - s.ay) > __mul24(s.by - s.ay, s.cx - s.ax);
+                if (narrow)
+                    front = __mul24(q.bx - q.ax, q.cy - q.ay) > __mul24(q.by - q.ay, q.cx - q.ax);
                 else
-                    front = (long long)(s.bx - s.ax) * (long long)(s.cy - s.ay) >
-                            (long long)(s.by - s.ay) * (long long)(s.cx - s.ax);
-                if (front) {
-                    const uint32_t npx = __umul24((uint32_t)(s.i1 - s.i0 + 1), (uint32_t)(s.j1 - s.j0 + 1));  // (each at most 512)
+                    front = (long long)(q.bx - q.ax) * (long long)(q.cy - q.ay) > (long long)(q.by - q.ay) * (long long)(q.cx - q.ax);
+                if (front && !box.empty()) {
+                    const uint32_t npx = __umul24((uint32_t)(box.i_end - box.i0), (uint32_t)(box.j_end - box.j0));  // (each at most 512)
                     cls = npx <= kTinyMaxPixels ? 1 : (npx <= kSmallMaxPixels ? 2 : 3);
+                    if (!narrow) cls = 3;  // (the loops of the other bins take 24-bit products for granted)
                 }
             }
         }
@@ -1471,7 +1537,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         }
     }
     // (the frame's window, made of what was found in phase 1: the last wavefront has the fewest candidates)
-    if (WINDOWED && tid >= NT - 64u) make_window(sc, VIDEO ? sc.key_capacity_video : sc.key_capacity, fu, (uint32_t)image.y_lo, (uint32_t)image.y_hi + 1u, lane);
+    if (WINDOWED && tid >= NT - 64u) make_window(sc, VIDEO ? sc.key_capacity_video : sc.key_capacity, fu, (uint32_t)image.y_lo, (uint32_t)image.y_end, lane);
     PXR_TIMED_BARRIER(3);
     PXR_PHASE_MARK(3);
 
@@ -1498,7 +1564,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         FrameUniforms* fu = reinterpret_cast<FrameUniforms*>(lds + scb.lds_misc);
         uint16_t* list = reinterpret_cast<uint16_t*>(lds + scb.lds_list);
         uint16_t* list2 = reinterpret_cast<uint16_t*>(lds + scb.lds_large);
-        RasterWindow win = {0, (int)scb.W - 1, 0, (int)scb.H - 1, scb.pitch};
+        RasterWindow win = {0, (int)scb.W, 0, (int)scb.H, scb.pitch};
         ResolveRange range = {};
         uint32_t n_keys = scb.pitch * scb.H;
         bool by_lists = false;
@@ -1513,9 +1579,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             more_bands = (bands_done + 1u) * held < n_rows;
             win.pitch = range.groups * 4u;
             win.x_lo = (int)range.x0;
-            win.x_hi = (int)min(range.x0 + win.pitch, scb.W) - 1;
+            win.x_end = (int)min(range.x0 + win.pitch, scb.W);
             win.y_lo = (int)range.y0;
-            win.y_hi = (int)(range.y0 + range.rows) - 1;
+            win.y_end = (int)(range.y0 + range.rows);
             n_keys = win.pitch * held;
             if (__builtin_expect(n_rows > held, 0)) {  // (most windows fit in one piece: 16 384 frames of 84x84 424 us without the branch, now 415)
                 const uint32_t n_tiny = uniform((uint32_t)fu->bins & 0xFFFFu), n_small = uniform((uint32_t)fu->bins >> 16),
@@ -1604,7 +1670,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // small: a team of lanes per triangle, from the first lane up
             // (a lane's first triangle of each was requested before the barrier; the next one is at the loop's end)
             for (uint32_t k = tid >> kSmallLanesLog2; k < n_small;) {
-                raster_binned<false>(scb, win, t_small, ti_small, vxy, vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
+                raster_binned<WINDOWED>(win, t_small, ti_small, scb.lds_vxy, scb.lds_vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
                 k += NT >> kSmallLanesLog2;
                 if (k < n_small) {
                     t_small = list[scb.T - 1 - k];
@@ -1613,7 +1679,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             }
             // tiny: one lane per triangle, from the last lane down
             for (uint32_t k = NT - 1 - tid; k < n_tiny;) {
-                raster_binned<false>(scb, win, t_tiny, ti_tiny, vxy, vd, keys, 0, 0);
+                raster_binned<WINDOWED>(win, t_tiny, ti_tiny, scb.lds_vxy, scb.lds_vd, keys, 0, 0);
                 k += NT;
                 if (k < n_tiny) {
                     t_tiny = list[k];
@@ -1622,7 +1688,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             }
             // large: a whole wave per triangle, starting in the middle waves
             for (uint32_t k = ((tid >> 6) + NT / 128) % (NT / 64); k < n_large; k += NT / 64)
-                raster_binned<true>(scb, win, list2[k], tri_table[list2[k]], vxy, vd, keys, (int)lane, 6);
+                raster_large(scb, win, list2[k], tri_table[list2[k]], vxy, vd, keys, (int)lane);
         } else {
             // Windows in bands of many triangles.  Every band walks the frame's bins again, but only to pick out the triangles that can
             // touch its rows: a dense pass, one lane per binned triangle and round of NT, that compacts them (ballot,
@@ -1660,8 +1726,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                 if (k < n_binned) {
                     cls = k < n_tiny ? 1 : (k < n_tiny + n_small ? 2 : 3);
                     t = cls == 1 ? list[k] : (cls == 2 ? list[scb.T - 1 - (k - n_tiny)] : list2[k - n_tiny - n_small]);
-                    int j0 = 0, j1 = 0;
-                    if (tri_rows(tri_table[t], vxy, j0, j1) == kTriPlain && (j0 > win.y_hi || j1 < win.y_lo)) cls = 0;
+                    int j0 = 0, j_end = 0;
+                    if (tri_rows(tri_table[t], scb.lds_vxy, j0, j_end) == kTriPlain && (j0 >= win.y_end || j_end <= win.y_lo)) cls = 0;
                 }
                 const u64 m1 = __ballot(cls == 1), m2 = __ballot(cls == 2), m3 = __ballot(cls == 3);
                 if (m1 | m2 | m3) {
@@ -1683,14 +1749,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                 const uint32_t b_tiny = (uint32_t)bb & 0xFFFFu, b_small = (uint32_t)bb >> 16, b_large = (uint32_t)(bb >> 32);
                 for (uint32_t i = tid >> kSmallLanesLog2; i < b_small; i += NT >> kSmallLanesLog2) {
                     const uint32_t ts = *(band_small - i);
-                    raster_binned<false>(scb, win, ts, tri_table[ts], vxy, vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
+                    raster_binned<WINDOWED>(win, ts, tri_table[ts], scb.lds_vxy, scb.lds_vd, keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
                 }
                 if (NT - 1 - tid < b_tiny) {
                     const uint32_t tt = band_tiny[NT - 1 - tid];
-                    raster_binned<false>(scb, win, tt, tri_table[tt], vxy, vd, keys, 0, 0);
+                    raster_binned<WINDOWED>(win, tt, tri_table[tt], scb.lds_vxy, scb.lds_vd, keys, 0, 0);
                 }
                 for (uint32_t i = ((tid >> 6) + NT / 128) % (NT / 64); i < b_large; i += NT / 64)
-                    raster_binned<true>(scb, win, band_large[i], tri_table[band_large[i]], vxy, vd, keys, (int)lane, 6);
+                    raster_large(scb, win, band_large[i], tri_table[band_large[i]], vxy, vd, keys, (int)lane);
                 ++band_round;
                 base += NT;
             } while (base < n_binned);

@@ -426,7 +426,7 @@ def test_corners_on_and_beside_pixel_centres(torch, pxr, orc, W, H, threads):
     between them: which centres its ends may cover, and which triangles are left out unseen, is the fill rule's matter alone."""
     lattice = [(x, y) for y in range(3) for x in range(3)]
     tris = [t for t in itertools.permutations(range(9), 3)
-            if t[0] == min(t) and np.cross(np.subtract(lattice[t[1]], lattice[t[0]]), np.subtract(lattice[t[2]], lattice[t[0]])) != 0]
+            if t[0] == min(t) and np.linalg.det([(*lattice[k], 1.0) for k in t]).round() != 0]
     assert len(tris) == 152
     # a view straight along x with a focal length of H / 2: at depth 2 a world unit is H / 4 pixels, a power of two, so every corner is
     # exactly where it is put
@@ -446,6 +446,31 @@ def test_corners_on_and_beside_pixel_centres(torch, pxr, orc, W, H, threads):
     ref = oracle_render(orc, w)
     seen = np.unique(ref["ids"][ref["ids"] < GROUND])
     assert 60 < len(seen) < 150
+    assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
+
+
+@pytest.mark.parametrize("threads", [None, 256])
+def test_slivers_at_the_limit_of_24_bit_edges(torch, pxr, orc, threads):
+    """Thin triangles of 2^15 - 1, 2^15 and 2^15 + 1 sub-pixels' extent, along x, along y and diagonally, few pixels wide: up to 2^15 - 1 their
+    edge functions are 24-bit products, by pixel count in any bin; beyond that they take the 64-bit path whatever their pixels."""
+    W = H = 256
+    per_pixel = 4.0 / H  # (as above: corners are exactly where they are put, here in 1/256 pixels)
+    verts, n = [], 0
+    for extent, way, width in itertools.product((32767, 32768, 32769), ((1, 0), (0, 1), (1, 1), (1, -1)), (77, 300, 1100)):
+        x0 = 256 * (4 + 3 * n) + 37 * n
+        y0 = 256 * (200 if way[1] < 0 else 4 + 2 * n) + 91 * n
+        corners = [(x0, y0), (x0 + way[0] * extent, y0 + way[1] * extent), (x0 + (width if way[0] == 0 or way[1] else extent // 2), y0 + (0 if way[1] else width))]
+        for k in (0, 1, 2) + (0, 2, 1):  # (one of the two faces the camera)
+            verts.append((0.0, -(corners[k][0] / 256 - W / 2) * per_pixel, -(corners[k][1] / 256 - H / 2) * per_pixel))
+        n += 1
+    idx = np.arange(len(verts), dtype=np.uint32).reshape(-1, 3)
+    d = wl.default_scene(W, H, [wl.mesh(np.array(verts, np.float32), idx, (0.8, 0.5, 0.3))])
+    d.update(cam_offset=(-2.0, 0.0, 0.0), fov_y_deg=90.0)
+    poses = np.zeros((2, 1, 1, 7), np.float32)
+    poses[..., 2], poses[..., 3] = 1.0, 1.0
+    w = dict(desc=d, poses=poses, shapes=None, distractor=None)
+    ref = oracle_render(orc, w)
+    assert len(np.unique(ref["ids"][ref["ids"] < GROUND])) > 24
     assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
 
 
