@@ -155,7 +155,7 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
         size_t off;
     };
     // The device copy of the pair table holds, in place of the four vertex indices, the LDS byte addresses of
-    // the vertices' cell codes (the kernel reads them without any address arithmetic): code v sits at
+    // the vertices' cell codes (the kernel reads them without any address arithmetic, and two of them without unpacking): code v sits at
     // lds_keys + 4 v of the dynamic LDS segment, which starts at address 0 (prepare_kernels checks that the
     // kernels have no static LDS in front of it).
     // It is padded to a multiple of 64 entries (a wavefront reads 64 without a bounds test) with entries that
@@ -173,28 +173,25 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
         return fail(PXR_ERR_DEVICE, "pxr_create_scene: no HIP device");
     }
     s->n_cus = (uint32_t)n_cus;
-    std::vector<uint32_t> pair_dev(hs.pair_tbl);
-    for (size_t p = 0; p < pair_dev.size() / 4; ++p)
-        for (int w = 0; w < 2; ++w) {
-            const uint32_t q = hs.pair_tbl[p * 4 + w];
-            pair_dev[p * 4 + w] = (hs.c.lds_keys + 4u * (q & 0xFFFFu)) | ((hs.c.lds_keys + 4u * (q >> 16)) << 16);
-        }
-    const uint32_t zero_code_at = hs.c.lds_keys + 4u * hs.c.V;
-    while ((pair_dev.size() / 4) % 64 != 0) {
-        pair_dev.push_back(zero_code_at | (zero_code_at << 16));
-        pair_dev.push_back(zero_code_at | (zero_code_at << 16));
-        pair_dev.push_back(pxr::kNoTriangle | (pxr::kNoTriangle << 16));
-        pair_dev.push_back(0u);
-    }
-    // Likewise the device copy of the vertex templates: its fourth word holds the LDS byte address of the body's
-    // record, shifted left by 2, and the cap selector as a 2-bit two's-complement number (-1, 0, +1) below it, in
+    std::vector<uint32_t> pair_dev;
+    const auto code_at = [&](uint32_t v) { return hs.c.lds_keys + 4u * v; };
+    const auto add_entry = [&](uint32_t q0, uint32_t q1, uint32_t q2, uint32_t q3, uint32_t triangles) {
+        for (uint32_t word : {code_at(q0) | (code_at(q1) << 16), code_at(q2), code_at(q3), triangles}) pair_dev.push_back(word);
+    };
+    for (size_t p = 0; p < hs.pair_tbl.size(); p += 4)
+        add_entry(hs.pair_tbl[p] & 0xFFFFu, hs.pair_tbl[p] >> 16, hs.pair_tbl[p + 1] & 0xFFFFu, hs.pair_tbl[p + 1] >> 16, hs.pair_tbl[p + 2]);
+    while ((pair_dev.size() / 4) % 64 != 0)
+        add_entry(hs.c.V, hs.c.V, hs.c.V, hs.c.V, pxr::kNoTriangle | (pxr::kNoTriangle << 16));
+    // Likewise the device copy of the vertex templates: its fourth word holds the LDS address of the body's
+    // record, in units of 16 bytes, and the cap selector as a half float (-1, 0, +1) above it, in
     // place of body << 2 | (selector + 1).
     std::vector<float> vtmpl_dev(hs.vtmpl);
     for (size_t v = 0; v < vtmpl_dev.size() / 4; ++v) {
         uint32_t code;
         std::memcpy(&code, &hs.vtmpl[v * 4 + 3], 4);
-        const uint32_t body_at = hs.c.lds_body + (code >> 2) * pxr::kBodyStride * 4u, sel = ((code & 3u) - 1u) & 3u;
-        const uint32_t dev = (body_at << 2) | sel;
+        const uint32_t body_at = hs.c.lds_body + (code >> 2) * pxr::kBodyStride * 4u;
+        constexpr uint32_t kHalfFloat[3] = {0xBC00u, 0x0000u, 0x3C00u};
+        const uint32_t dev = (body_at / 16u) | (kHalfFloat[code & 3u] << 16);
         std::memcpy(&vtmpl_dev[v * 4 + 3], &dev, 4);
     }
     vtmpl_dev.resize((hs.c.V + 63u) / 64u * 64u * 4u, 0.0f);  // (a wavefront reads 64 without a bounds test)

@@ -85,12 +85,12 @@ struct SceneConsts {
     uint32_t magic_groups;                  // ceil(2^32 / (pitch / 4)): g / (pitch / 4) == mulhi(g, magic_groups) for every group of four pixels
     uint32_t magicW;  // ceil(2^32 / W): p / W == mulhi(p, magicW) for every pixel index p < 512 * W
     // device tables
-    const float* vtmpl;       // [V][4]  ux,uy,uz, bits = (LDS byte address of the body's record)<<2 | s as a 2-bit signed number
+    const float* vtmpl;       // [V][4]  ux,uy,uz, bits = LDS address of the body's record in units of 16 bytes | s as a half float << 16
                               //         (the host-side table holds body<<2 | (s+1)); the device copy is padded to a multiple of 64 entries
     const uint32_t* tri_idx;  // [T][2]  v0 | v1<<16 ,  v2 | body<<16
     const float* tri_shade;   // [T][4]  unit normal (body frame), colour multiplier
-    const uint32_t* pair_tbl; // [P][4]  a0 | a1<<16 , a2 | a3<<16 , triA | triB<<16 , 0 (a_i = LDS byte address of the cell
-                              //         code of vertex q_i; the host-side table holds q_i itself): two triangles sharing the
+    const uint32_t* pair_tbl; // [P][4]  a0 | a1<<16 , a2 , a3 , triA | triB<<16 (a_i = LDS byte address of the cell
+                              //         code of vertex q_i; the host-side table holds q0 | q1<<16 , q2 | q3<<16 , triA | triB<<16 , 0): two triangles sharing the
                               //         edge q0-q2, or one triangle (q3 = q2, triB = kNoTriangle); the device copy ends with padding entries
     //         (no triangles; the four addresses are that of the word after the last vertex's code, which holds code 0)
     const float* body_const;  // [K][8]  shape a,b,c,h ; rgb r,g,b,0   then, on the device, [4][3]: Rt, Up, Fw, l, and

@@ -314,18 +314,20 @@ __device__ __forceinline__ int tri_rows(const uint2 ti, uint32_t lds_vxy, int& j
 }
 
 // View-space position of template vertex v (the instancing arithmetic of phase 1; also used when a
-// triangle has to be clipped).  The template's fourth word says where in LDS its body's record is.
+// triangle has to be clipped).  The template's fourth word says where in LDS its body's record is, in units of 16 bytes, and holds the cap
+// selector s (-1, 0 or +1) as a half float above that.
 __device__ __forceinline__ void view_position(const float4 tv, float& pvx, float& pvy, float& pvz) {
-    const uint32_t code = __float_as_uint(tv.w);
+    uint32_t record;
+    asm("v_mad_u32_u16 %0, %1, 16, 0" : "=v"(record) : "v"(__float_as_uint(tv.w)));
     // (body records are 96 bytes at a 16-byte aligned base: four 16-byte LDS reads)
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const __attribute__((address_space(3))) f32x4* o4 =
-        reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(static_cast<uintptr_t>(code >> 2));
+    const __attribute__((address_space(3))) f32x4* o4 = reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(static_cast<uintptr_t>(record));
     const f32x4 m0 = o4[0], m1 = o4[1], m2 = o4[2], sh = o4[4];  // M and t as floats 0..11, the shape as 16..19
-    const float sel = (float)(int)__builtin_amdgcn_sbfe((int)code, 0, 2);  // -1, 0 or +1
+    float cap;  // s * h
+    asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(cap) : "v"(__float_as_uint(tv.w)), "v"(sh.w));
     const float lx = sh.x * tv.x;
     const float ly = sh.y * tv.y;
-    const float lz = __builtin_fmaf(sh.z, tv.z, sel * sh.w);
+    const float lz = __builtin_fmaf(sh.z, tv.z, cap);
     pvx = __builtin_fmaf(m0.x, lx, __builtin_fmaf(m0.y, ly, __builtin_fmaf(m0.z, lz, m2.y)));
     pvy = __builtin_fmaf(m0.w, lx, __builtin_fmaf(m1.x, ly, __builtin_fmaf(m1.y, lz, m2.z)));
     pvz = __builtin_fmaf(m1.z, lx, __builtin_fmaf(m1.w, ly, __builtin_fmaf(m2.x, lz, m2.w)));
@@ -1080,34 +1082,41 @@ __device__ __forceinline__ void pose_frame(const FkArgs& fk, uint32_t frame, flo
     }
 }
 
+// What of the scene phase 1's vertices need.
+struct Projection {
+    float f, z_near;
+    float half_w, half_h;  // in vector registers: a fused multiply-add takes one scalar operand, and the focal length is that
+    uint32_t W, H;
+    bool recip_long_form;
+};
+
 // One template vertex: instancing, projection, snap, cell code.
-__device__ __forceinline__ void instance_vertex(const SceneConsts& sc, bool recip_long_form, uint32_t v, const float4 tv, int2* vxy,
-                                                float* vd, uint32_t* vm) {
+__device__ __forceinline__ void instance_vertex(const Projection& pr, uint32_t v, const float4 tv, int2* vxy, float* vd, uint32_t* vm) {
     float pvx, pvy, pvz;
     view_position(tv, pvx, pvy, pvz);
     // 1 / pvz is only used when pvz >= z_near (otherwise the vertex is behind the plane or unusable
     // whatever it is), so the short form serves unless some lane's depth is beyond its range
     float inv;
-    if (__builtin_expect(recip_long_form || __ballot(pvz > kRecipMax) != 0ull, 0))
+    if (__builtin_expect(pr.recip_long_form || __ballot(pvz > kRecipMax) != 0ull, 0))
         inv = 1.0f / pvz;
     else
         inv = recip_in_range(pvz);
-    const float sx = __builtin_fmaf(sc.f, pvx * inv, sc.halfW);
-    const float sy = __builtin_fmaf(-sc.f, pvy * inv, sc.halfH);
-    const bool ok = (pvz >= sc.z_near) && (__builtin_fabsf(sx) <= 16384.0f) && (__builtin_fabsf(sy) <= 16384.0f);
+    const float sx = __builtin_fmaf(pr.f, pvx * inv, pr.half_w);
+    const float sy = __builtin_fmaf(-pr.f, pvy * inv, pr.half_h);
+    const bool ok = (pvz >= pr.z_near) && (__builtin_fabsf(sx) <= 16384.0f) && (__builtin_fabsf(sy) <= 16384.0f);
     // (worked out for every lane, whatever sx and sy are, and replaced where the vertex is not usable: such
     // vertices are rare, and a wavefront without one skips the replacement altogether)
     int X = snap(sx), Y = snap(sy);
-    uint32_t m = cell_code(X, (int)sc.W) | (cell_code(Y, (int)sc.H) << 16);
+    uint32_t m = cell_code(X, (int)pr.W) | (cell_code(Y, (int)pr.H) << 16);
     if (__builtin_expect(__ballot(!ok) != 0ull, 0)) {
         if (!ok) {
-            X = pvz < sc.z_near ? kBehindX : kRejectedX;
+            X = pvz < pr.z_near ? kBehindX : kRejectedX;
             Y = 0;
             m = 0xFFFFFFFFu;  // an unusable or clipped vertex never lets a triangle be discarded early
         }
     }
     vxy[v] = make_int2(X, Y);
-    vd[v] = sc.z_near * inv;
+    vd[v] = pr.z_near * inv;
     vm[v] = m;
 }
 
@@ -1307,7 +1316,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // trip ahead is slower, 70 us and 3730: the compiler's waits cover the request just made.)
     const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
     float4 tv_first = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (wave_first < sc.V) tv_first = reinterpret_cast<const float4*>(sc.vtmpl)[wave_first + lane];
+    if (wave_first < sc.V) tv_first = (reinterpret_cast<const float4*>(sc.vtmpl) + wave_first)[lane];
 
     PXR_PHASE_BEGIN();
     // ---- phase 0: per-body transforms, per-frame draws, the three non-triangle colours
@@ -1407,25 +1416,53 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         }
     }
     if constexpr (!POSED && !kDrawFirst) draw_frame<NT, WINDOWED, VIDEO>(sc, dc, fu, lds, e, env, step, tid);
+    // (Phase 1's arguments where they are read in place, asked for before the wait at the barrier: the compiler would load each where it is first
+    // used, and the vertices would wait for them.  256 chains from angles 10.41 us without, 10.15 with; windowed frames of 256x256 147.2 / 149.4.)
+    Projection pr = {sc.f, sc.z_near, sc.halfW, sc.halfH, sc.W, sc.H, false};
+    asm("" : "+v"(pr.half_w), "+v"(pr.half_h));
+    if constexpr (!kByValue && !WINDOWED) {
+        asm volatile("" : : "s"(pr.f), "s"(pr.z_near), "s"(pr.W), "s"(pr.H));
+    }
+    pr.recip_long_form = !(pr.z_near >= kRecipMin);
     PXR_TIMED_BARRIER(0);
     PXR_PHASE_MARK(0);
 
     // ---- phase 1: instancing + projection + snap + cell code (one lane per template vertex)
-    const bool recip_long_form = !(sc.z_near >= kRecipMin);
     if (WINDOWED && tid >= NT - 64u) {
         // what the bodies can touch, by the last wavefront (the vertices of most scenes give it a trip less)
         add_reach(sc, body, fu->reach, lane);
     }
     if (tid == NT - 1) vm[sc.V] = 0u;  // the code that the padding of the pair table points at: no pixel centre on either axis
-    for (uint32_t v = tid; v < sc.V;) {
-        instance_vertex(sc, recip_long_form, v, tv_first, vxy, vd, vm);
-        v += NT;
-        if (v < sc.V) tv_first = reinterpret_cast<const float4*>(sc.vtmpl)[v];
+    // The largest whole-frame kernels are bound by what they issue here, the others by waiting.  us without / with: 65 536 x 3 frames of 64x64 3140 /
+    // 3155, 4096 quadrupeds 60.2 / 60.7, 8503 capsule frames of 84x84 130.2 / 134.2; 10 humanoids with their layer 13.04 / 12.79, 16 384 of 84x84 over a
+    // clip 380.8 / 377.7.
+    constexpr bool kTemplatesAhead = NT < 1024 || WINDOWED || POSED;
+    // (counted by wavefront: where its templates lie is a scalar then, and a lane's offset from there a constant)
+    const float4* templates = reinterpret_cast<const float4*>(sc.vtmpl);
+    const auto instance = [&](uint32_t v0, const float4 tv) {
+        if (v0 + lane < sc.V) instance_vertex(pr, v0 + lane, tv, vxy, vd, vm);
+    };
+    if constexpr (kTemplatesAhead) {
+        // The next templates are requested before the present ones are used, and without a condition: with one, the compiler cannot know how many
+        // requests are under way and waits for the one just made.  Past the end the last ones are asked for again.
+        const uint32_t last_templates = (sc.V - 1u) & ~63u;
+        for (uint32_t v0 = wave_first; v0 < sc.V; v0 += 2 * NT) {
+            const float4 tv_second = (templates + min(v0 + NT, last_templates))[lane];
+            instance(v0, tv_first);
+            if (v0 + NT >= sc.V) break;
+            tv_first = (templates + min(v0 + 2 * NT, last_templates))[lane];
+            instance(v0 + NT, tv_second);
+        }
+    } else {
+        for (uint32_t v0 = wave_first; v0 < sc.V; v0 += NT) {
+            instance(v0, tv_first);
+            if (v0 + NT < sc.V) tv_first = (templates + (v0 + NT))[lane];
+        }
     }
     // (phase 2a's first table entry depends on nothing in LDS: requested before the barrier, it arrives while the
     // wavefront waits there; later ones are requested a trip ahead)
     uint4 rec_next = make_uint4(0u, 0u, 0u, 0u);
-    if (wave_first < sc.P) rec_next = reinterpret_cast<const uint4*>(sc.pair_tbl)[wave_first + lane];
+    if (wave_first < sc.P) rec_next = (reinterpret_cast<const uint4*>(sc.pair_tbl) + wave_first)[lane];
     PXR_TIMED_BARRIER(1);
     PXR_PHASE_MARK(1);
 
@@ -1437,18 +1474,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // non-zero" is one 16 x 16-bit product; the ballots are taken from single comparisons (their masks as they
     // are) and combined as scalars.
     // (Two trips per turn of the loop, the two entries in flight changing roles: a single "next" variable costs six
-    // register moves per trip.)
+    // register moves per trip.  Entries are requested ahead without a condition, past the end the table's last ones again: with one, the compiler cannot
+    // know how many requests are under way and waits for the one just made.  65 536 x 3 frames of 64x64 3189 us, now 3140, 16 384 of 84x84 over a clip
+    // 385 / 381.)
     const auto coarse_trip = [&](const uint4 rec) {
-        const uint32_t w0 = rec.x, w1 = rec.y, w2 = rec.z;
-        const uint32_t m0 = lds_at<uint32_t>(w0 & 0xFFFFu), m1 = lds_at<uint32_t>(w0 >> 16), m2 = lds_at<uint32_t>(w1 & 0xFFFFu), m3 = lds_at<uint32_t>(w1 >> 16);
+        const uint32_t m0 = lds_at<uint32_t>(rec.x & 0xFFFFu), m1 = lds_at<uint32_t>(rec.x >> 16), m2 = lds_at<uint32_t>(rec.y), m3 = lds_at<uint32_t>(rec.z);
         const uint32_t da = any_differ(m0, m1, m2), db = any_differ(m0, m2, m3);
-        const uint32_t ta = w2 & 0xFFFFu, tb = w2 >> 16;
+        const uint32_t ta = rec.w & 0xFFFFu, tb = rec.w >> 16;
         const bool keep_a = halves_product(da) != 0u;
         const bool both_b = halves_product(db) != 0u, has_b = tb != kNoTriangle;
         const bool keep_b = both_b && has_b;
         const u64 ma = __ballot(keep_a), mb = __ballot(both_b) & __ballot(has_b);
         if (ma | mb) {
-            uint32_t base = 0;
+            uint32_t base;
+            asm("" : "=v"(base));  // (only the first lane's is looked at)
             if (lane == 0) base = atomicAdd(&fu->n_cand, (uint32_t)(__popcll(ma) + __popcll(mb)));
             base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
             // (the first triangles of the wavefront's entries, then the second ones: the order is free)
@@ -1458,12 +1497,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     };
     {
         const uint4* table = reinterpret_cast<const uint4*>(sc.pair_tbl);
-        uint4 rec_a = rec_next, rec_b = make_uint4(0u, 0u, 0u, 0u);
+        uint4 rec_a = rec_next;
         for (uint32_t p0 = wave_first; p0 < sc.P; p0 += 2 * NT) {
-            if (p0 + NT < sc.P) rec_b = table[p0 + NT + lane];
+            const uint4 rec_b = (table + min(p0 + NT, sc.P - 64u))[lane];
             coarse_trip(rec_a);
             if (p0 + NT >= sc.P) break;
-            if (p0 + 2 * NT < sc.P) rec_a = table[p0 + 2 * NT + lane];
+            rec_a = (table + min(p0 + 2 * NT, sc.P - 64u))[lane];
             coarse_trip(rec_b);
         }
     }
@@ -1493,7 +1532,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     }
     for (uint32_t k0 = 0; k0 < n_cand; k0 += NT) {
         const uint32_t k = k0 + tid;
-        int cls = 0;  // 0 none, 1 tiny, 2 small, 3 large
         uint32_t t = t_ahead;
         uint2 ti = ti_ahead;
         if (kAhead) {
@@ -1505,35 +1543,40 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             t = cand[k];
             ti = reinterpret_cast<const uint2*>(sc.tri_idx)[t];
         }
+        // candidate pixels: none = dropped, kByWave = whatever their number, the triangle is a whole wavefront's
+        constexpr uint32_t kByWave = 0xFFFFu;
+        uint32_t n_px = 0;
         if (k < n_cand) {
             const Corners q = gather_corners(ti, sc.lds_vxy);
-            const int kind = tri_kind(q);
-            if (kind == kTriClip) cls = 3;  // clipped, then rastered, by a whole wavefront
-            if (kind == kTriPlain) {
+            if (__builtin_expect(imin3(q.ax, q.bx, q.cx) > kBehindX, 1)) {
                 const PixelBox box = candidate_pixels(image, q);
-                const bool narrow = q.narrow();
-                bool front;
-                if (narrow)
-                    front = __mul24(q.bx - q.ax, q.cy - q.ay) > __mul24(q.by - q.ay, q.cx - q.ax);
-                else
-                    front = (long long)(q.bx - q.ax) * (long long)(q.cy - q.ay) > (long long)(q.by - q.ay) * (long long)(q.cx - q.ax);
-                if (front && !box.empty()) {
-                    const uint32_t npx = __umul24((uint32_t)(box.i_end - box.i0), (uint32_t)(box.j_end - box.j0));  // (each at most 512)
-                    cls = npx <= kTinyMaxPixels ? 1 : (npx <= kSmallMaxPixels ? 2 : 3);
-                    if (!narrow) cls = 3;  // (the loops of the other bins take 24-bit products for granted)
+                bool front = __mul24(q.bx - q.ax, q.cy - q.ay) > __mul24(q.by - q.ay, q.cx - q.ax);
+                uint32_t n = __umul24((uint32_t)(box.i_end - box.i0), (uint32_t)(box.j_end - box.j0));  // (each at most 512)
+                const bool wide = !q.narrow();
+                if (__builtin_expect(__ballot(wide) != 0ull, 0)) {
+                    if (wide) {
+                        front = (long long)(q.bx - q.ax) * (long long)(q.cy - q.ay) > (long long)(q.by - q.ay) * (long long)(q.cx - q.ax);
+                        n = kByWave;  // (the loops of the other bins take 24-bit products for granted)
+                    }
                 }
+                n_px = front & !box.empty() ? n : 0u;
+            } else if (tri_kind(q) == kTriClip) {
+                n_px = kByWave;
             }
         }
-        const u64 m1 = __ballot(cls == 1), m2 = __ballot(cls == 2), m3 = __ballot(cls == 3);
-        if (m1 | m2 | m3) {
-            u64 old = 0;
+        const u64 some = __ballot(n_px != 0u), up_to_tiny = __ballot(n_px <= kTinyMaxPixels), m3 = __ballot(n_px > kSmallMaxPixels);
+        if (some) {
+            const u64 m1 = some & up_to_tiny, m2 = ~(up_to_tiny | m3);
+            u64 old;
+            asm("" : "=v"(old));  // (only the first lane's is looked at)
             if (lane == 0)
                 old = atomicAdd(&fu->bins, (u64)__popcll(m1) | ((u64)__popcll(m2) << 16) | ((u64)__popcll(m3) << 32));
             const uint32_t old_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)old);
             const uint32_t old_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(old >> 32));
-            if (cls == 1) list[(old_lo & 0xFFFFu) + lanes_below(m1)] = (uint16_t)t;
-            if (cls == 2) list[sc.T - 1 - ((old_lo >> 16) + lanes_below(m2))] = (uint16_t)t;
-            if (cls == 3) list2[old_hi + lanes_below(m3)] = (uint16_t)t;
+            const bool tiny = n_px - 1u < kTinyMaxPixels, large = n_px > kSmallMaxPixels;
+            if (tiny) list[(old_lo & 0xFFFFu) + lanes_below(m1)] = (uint16_t)t;
+            if (!large && n_px > kTinyMaxPixels) (list + (sc.T - 1 - (old_lo >> 16)))[-(int)lanes_below(m2)] = (uint16_t)t;
+            if (large) list2[old_hi + lanes_below(m3)] = (uint16_t)t;
         }
     }
     // (the frame's window, made of what was found in phase 1: the last wavefront has the fewest candidates)
