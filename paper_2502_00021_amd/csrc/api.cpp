@@ -200,8 +200,12 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
     std::vector<float> body_dev(hs.body_const);
     for (const float* row : {hs.c.Rt, hs.c.Up, hs.c.Fw, hs.c.l}) body_dev.insert(body_dev.end(), row, row + 3);
     body_dev.insert(body_dev.end(), hs.body_bound.begin(), hs.body_bound.end());
+    // And the device copy of the index table has, in place of a triangle's body, where that body's record is.
+    std::vector<uint32_t> tri_dev(hs.tri_idx);
+    for (size_t t = 1; t < tri_dev.size(); t += 2)
+        tri_dev[t] = (tri_dev[t] & 0xFFFFu) | ((hs.c.lds_body / 16u + (tri_dev[t] >> 16) * (pxr::kBodyStride / 4u)) << 16);
     Part parts[6] = {{vtmpl_dev.data(), vtmpl_dev.size() * 4, 0},
-                     {hs.tri_idx.data(), hs.tri_idx.size() * 4, 0},
+                     {tri_dev.data(), tri_dev.size() * 4, 0},
                      {hs.tri_shade.data(), hs.tri_shade.size() * 4, 0},
                      {body_dev.data(), body_dev.size() * 4, 0},
                      {hs.cxcy.data(), hs.cxcy.size() * 4, 0},

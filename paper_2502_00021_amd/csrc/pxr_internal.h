@@ -83,11 +83,11 @@ struct SceneConsts {
     uint32_t key_capacity_video;            // (the same beside the video distractor's tables)
     uint32_t pitch;                         // keys per row where the buffer holds the whole frame: W rounded up to a multiple of 4
     uint32_t magic_groups;                  // ceil(2^32 / (pitch / 4)): g / (pitch / 4) == mulhi(g, magic_groups) for every group of four pixels
-    uint32_t magicW;  // ceil(2^32 / W): p / W == mulhi(p, magicW) for every pixel index p < 512 * W
+    uint32_t magic24_groups;                // ceil(2^24 / (pitch / 4)): the same as (g << 8) * magic24_groups >> 32, for frames whose width is a multiple of 4
     // device tables
     const float* vtmpl;       // [V][4]  ux,uy,uz, bits = LDS address of the body's record in units of 16 bytes | s as a half float << 16
                               //         (the host-side table holds body<<2 | (s+1)); the device copy is padded to a multiple of 64 entries
-    const uint32_t* tri_idx;  // [T][2]  v0 | v1<<16 ,  v2 | body<<16
+    const uint32_t* tri_idx;  // [T][2]  v0 | v1<<16 ,  v2 | (LDS address of the body's record in units of 16 bytes)<<16 (the host-side table: body)
     const float* tri_shade;   // [T][4]  unit normal (body frame), colour multiplier
     const uint32_t* pair_tbl; // [P][4]  a0 | a1<<16 , a2 , a3 , triA | triB<<16 (a_i = LDS byte address of the cell
                               //         code of vertex q_i; the host-side table holds q0 | q1<<16 , q2 | q3<<16 , triA | triB<<16 , 0): two triangles sharing the

@@ -587,10 +587,12 @@ __device__ __forceinline__ u64 ground_key(const SceneConsts& sc, const ResolveCt
 // cannot be a NaN (a finite or infinite eye, a far plane within 2^64), so the one-instruction floor-and-convert serves.
 // Triangle g as a 24-bit colour: flat Lambert + ambient in the body frame, then the colour distractor.
 template <bool VIDEO>
-__device__ __forceinline__ uint32_t shade_triangle(const SceneConsts& sc, const ResolveCtx& rc, const float* body, uint32_t g) {
-    const float4 ns = reinterpret_cast<const float4*>(sc.tri_shade)[g];
-    const float4* o4 = reinterpret_cast<const float4*>(body + (sc.tri_idx[g * 2 + 1] >> 16) * kBodyStride);
-    const float4 lb = o4[3], col = o4[5];  // floats 12..14: light in the body frame, 20..22: colour
+__device__ __forceinline__ uint32_t shade_triangle(const SceneConsts& sc, const ResolveCtx& rc, uint32_t g) {
+    // (byte offsets of 32 bits from scalar addresses: as indices they would be 64-bit address arithmetic for each)
+    const float4 ns = *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(sc.tri_shade) + g * 16u);
+    const uint32_t record = (uint32_t)*reinterpret_cast<const uint16_t*>(reinterpret_cast<const unsigned char*>(sc.tri_idx) + (g * 8u + 6u)) * 16u;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const f32x4 lb = lds_at<f32x4>(record + 48u), col = lds_at<f32x4>(record + 80u);  // floats 12..14: light in the body frame, 20..22: colour
     const float o_rgb[3] = {col.x, col.y, col.z};
     float I = __builtin_fmaf(ns.x, lb.x, __builtin_fmaf(ns.y, lb.y, ns.z * lb.z));
     I = I > 0.0f ? I : 0.0f;
@@ -600,7 +602,7 @@ __device__ __forceinline__ uint32_t shade_triangle(const SceneConsts& sc, const 
     for (int ch = 0; ch < 3; ++ch) {
         float v = (o_rgb[ch] * ns.w) * sh;
         v = v < 1.0f ? v : 1.0f;
-        if (!VIDEO && rc.mode == PXR_DISTRACT_COLOR) {
+        if (!VIDEO) {  // (without the colour distractor the factor is 1 and the offset 0, which leaves a value in [0, 1] as it is)
             v = __builtin_fmaf(v, rc.scale[ch], rc.offs[ch]);
             v = v > 0.0f ? v : 0.0f;
             v = v < 1.0f ? v : 1.0f;
@@ -706,9 +708,10 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
         // ---- where the group lies: row j, first column i0, first pixel p0
         uint32_t j, i0, p0;
         if (PART == kWholeFrame && !RAGGED) {
+            // (24-bit products only: a frame has at most 2^16 groups, a row at most 2^7, and 2^8 g times ceil(2^24 / groups) >> 32 is exact for them)
+            asm("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(j) : "v"(g << 8), "s"(sc.magic24_groups));
+            i0 = (g - __umul24(j, row_groups)) * 4u;
             p0 = g * 4u;
-            j = __umulhi(p0, sc.magicW);
-            i0 = p0 - j * sc.W;
         } else if (PART == kInsideWindow) {
             const uint32_t r = __umulhi(g, range.magic);
             j = range.y0 + r;
@@ -735,6 +738,7 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
             p0 = j * sc.W + i0;
         }
         const bool whole = !RAGGED || i0 + 4u <= sc.W;  // all four pixels exist
+        const uint32_t byte0 = PART == kWholeFrame && !RAGGED ? __umul24(g, 12u) : __umul24(p0, 3u);
         // what is shared by a row's pixels was worked out once per row in phase 0
         const float4 row = rows[j];
         const float rx = row.x, ry = row.y;
@@ -744,12 +748,9 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
         uint32_t vid[3] = {0u, 0u, 0u};
         if (VIDEO) {
             if (!RAGGED) {
-                const uint32_t* vsrc = reinterpret_cast<const uint32_t*>(rc.vframe) + (p0 >> 2) * 3u;
-                vid[0] = vsrc[0];
-                vid[1] = vsrc[1];
-                vid[2] = vsrc[2];
+                __builtin_memcpy(vid, __builtin_assume_aligned(rc.vframe + byte0, 4), 12);
             } else {
-                const uint8_t* vsrc = rc.vframe + p0 * 3u;
+                const uint8_t* vsrc = rc.vframe + byte0;
                 if (whole) {
                     __builtin_memcpy(vid, vsrc, 12);
                 } else {
@@ -879,7 +880,7 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             const u64 active = __ballot(true);  // the last trip of a ragged band may run with fewer lanes
             for (uint32_t i = lanes_below(active); i < total; i += (uint32_t)__popcll(active))
-                list[i] = shade_triangle<VIDEO>(sc, rc, body, 0xFFFFFFFFu - list[i]);
+                list[i] = shade_triangle<VIDEO>(sc, rc, 0xFFFFFFFFu - list[i]);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -914,12 +915,12 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
             struct alignas(4) U3 {
                 uint32_t a, b, c;
             };
-            *reinterpret_cast<U3*>(reinterpret_cast<uint32_t*>(out) + (p0 >> 2) * 3u) = U3{ow[0], ow[1], ow[2]};
+            *reinterpret_cast<U3*>(out + byte0) = U3{ow[0], ow[1], ow[2]};
             if (out_ids)
-                reinterpret_cast<uint4*>(out_ids)[p0 >> 2] =
+                *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(out_ids) + p0 * 4u) =
                     make_uint4(0xFFFFFFFFu - low[0], 0xFFFFFFFFu - low[1], 0xFFFFFFFFu - low[2], 0xFFFFFFFFu - low[3]);
         } else {
-            uint8_t* dst = out + p0 * 3u;
+            uint8_t* dst = out + byte0;
             const uint32_t id4[4] = {0xFFFFFFFFu - low[0], 0xFFFFFFFFu - low[1], 0xFFFFFFFFu - low[2], 0xFFFFFFFFu - low[3]};
             if (whole) {
                 __builtin_memcpy(dst, ow, 12);
@@ -1264,11 +1265,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     const SceneConsts sc_value, const DistractConsts dc_value, const float* __restrict__ poses, const float* __restrict__ shapes,
     uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2,
     const KinematicArgs<POSED>) {
+    // Who asks: all wavefronts of the kernels that make poses and of those of up to 512 threads, of the larger ones the first wavefront of the
+    // first workgroups on the chip, which find the arguments in no cache.
     // (In the kernels that make poses, which serve a few rounds at most, and in those of up to 512 threads, whose launches may be one round or
     // hundreds.  us without / with: 16 capsule frames of 32x32 6.3 / 5.7, 256 of 48x48 7.2 / 6.6, 512 meshes of 40x40 9.5 / 9.1, 256 chains from angles
-    // 10.8 / 10.3; of many rounds 10 850 capsule frames of 48x48 58.0 / 57.7, 31 887 of 28x28 101.2 / 102.2.  Larger workgroups have less of it, 10
-    // humanoids of 64x64 8.2 / 8.0, and more often many rounds: 4096 quadrupeds 64.4 / 64.9, 65 536 x 3 frames 3480 / 3492.)
-    if constexpr (POSED || NT <= 512) request_arguments<POSED ? sizeof(RenderArguments) : offsetof(RenderArguments, fk)>();
+    // 10.8 / 10.3; of many rounds 10 850 capsule frames of 48x48 58.0 / 57.7, 31 887 of 28x28 101.2 / 102.2.  Larger workgroups: 256 quadrupeds of 48x48
+    // 7.18 / 6.96, of 64x64 7.77 / 7.60, 200 meshes of 64x64 8.31 / 8.15, 8 frames of 256x256 12.8 / 12.5; of many rounds, where it is only a branch at the
+    // kernel's head, 65 536 x 3 frames of 64x64 3133 / 3145, 8503 capsule frames of 84x84 128.7 / 130.2, the others the same.  In every workgroup's first
+    // wavefront 200 meshes 7.98, but 4096 quadrupeds 61.0 / 61.2 and 16 384 humanoids of 84x84 over a clip 378.5 / 381.)
+    if constexpr (POSED || NT <= 512)
+        request_arguments<POSED ? sizeof(RenderArguments) : offsetof(RenderArguments, fk)>();
+    else if (blockIdx.x < 256u * (2048u / NT) && __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0)
+        request_arguments<offsetof(RenderArguments, fk)>();
     // The largest whole-frame kernels without a clip, which are bound by instruction issue, have their arguments by value all the same: fewer
     // loads and waits, six registers parked.  By value / in place: 65 536 x 3 frames of 64x64 3470 / 3531 us, 4096 quadrupeds 64.2 / 65.5, 8503
     // capsule frames of 84x84 133 / 136.  (Windowed: 1024 quadruped frames of 161x160 45.2 / 44.4.)  So have the windowed ones of 768, of which

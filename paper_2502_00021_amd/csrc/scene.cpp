@@ -312,9 +312,9 @@ int build_host_scene(const pxr_scene_desc& d, HostScene& hs, std::string& err) {
     c.npix = d.width * d.height;
     c.K = d.n_bodies;
     c.root = d.root_body;
-    c.magicW = (uint32_t)((0x100000000ull + d.width - 1) / d.width);
     c.pitch = (d.width + 3u) & ~3u;
     c.magic_groups = (uint32_t)((0x100000000ull + c.pitch / 4u - 1) / (c.pitch / 4u));
+    c.magic24_groups = (0x1000000u + c.pitch / 4u - 1) / (c.pitch / 4u);
 
     // ---- meshes
     uint32_t vbase = 0, tbase = 0;
