@@ -723,6 +723,21 @@ def test_ground_variants(torch, pxr, orc):
         assert_parity(gpu_render(torch, pxr, w2), oracle_render(orc, w2))
 
 
+@pytest.mark.parametrize("offset", [(-2.5, 0.0, 1.0), (2.5, -0.0, 0.6), (0.0, -2.5, 1.0), (-2.5, 1.0e-30, 1.0), (1.7, -1.7, 0.8)])
+@pytest.mark.parametrize("W,H,mode", [(64, 64, "color"), (131, 90, "none"), (84, 84, "video")])
+def test_cameras_along_an_axis_and_beside_it(torch, pxr, orc, offset, W, H, mode):
+    """A camera that looks along the x axis (its right vector's x is a zero of either sign) has a checker cell index of its rows' own; one along
+    the y axis, a hair's breadth beside the x axis or between the two has not."""
+    w = wl.cfg3(B=3)
+    w["desc"] = dict(w["desc"], width=W, height=H, cam_offset=offset)
+    w["poses"][..., :2] += np.array([[-7.3, 2.9], [0.0, 0.0], [1.0e6, -3.0]], np.float32)[:, None, None]
+    w["distractor"] = dict(none=None, color=w["distractor"], video=dict(
+        mode="video", seed=3, alpha=0.5, video=np.random.default_rng(1).integers(0, 256, (2, H, W, 3), dtype=np.uint8)))[mode]
+    ref = oracle_render(orc, w)
+    assert (ref["ids"] == GROUND).any() and (ref["ids"] == BG).any()
+    assert_parity(gpu_render(torch, pxr, w), ref)
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_scenes_match_oracle(torch, pxr, orc, seed):
     """Seeded random scenes: image shapes, cameras (with and without roll), body mixes and sizes (triangles of
