@@ -48,11 +48,11 @@ HBM_PEAK_GBS = 8000.0
 # factors a plain 1 GiB copy gives for the same counters), and the counter-side view of the vector units
 # (share of issue slots busy, share of lanes active per instruction, wave-instructions per frame).
 PROFILED = {
-    ("cfg5", 65536): {"traffic_bytes_per_launch": 2516.8e6, "valu_busy": 0.952, "lane_use": 0.813,
-                      "valu_wave_instructions_per_frame": 10323,
+    ("cfg5", 65536): {"traffic_bytes_per_launch": 2516.8e6, "valu_busy": 0.885, "lane_use": 0.795,
+                      "valu_wave_instructions_per_frame": 8515,
                       "source": "profiles/render_kernel_cfg5_humanoid_box_64x64.md"},
-    ("cfg4", 16384): {"traffic_bytes_per_launch": 405.1e6, "valu_busy": 0.825, "lane_use": 0.839,
-                      "valu_wave_instructions_per_frame": 12915,
+    ("cfg4", 16384): {"traffic_bytes_per_launch": 405.3e6, "valu_busy": 0.749, "lane_use": 0.825,
+                      "valu_wave_instructions_per_frame": 10686,
                       "source": "profiles/render_kernel_cfg4_humanoid_84x84_video.md"},
 }
 

@@ -1545,7 +1545,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // (Where the candidates take several trips - smaller workgroups, taller frames - a lane's candidate and its entry
     // of the index table are requested a trip ahead, without a branch: a lane past the end reads a list entry that
     // nobody wrote and clamps it into the table.  The 1024-thread whole-frame kernel sees its ~900 candidates in one trip
-    // and is bound by instruction issue: it keeps the plain form.)
+    // and keeps the plain form: 256 chains from angles 10.1 us, 10.4 with requests ahead.)
     constexpr bool kAhead = NT < 1024 || WINDOWED;
     uint32_t t_ahead = 0;
     uint2 ti_ahead = make_uint2(0u, 0u);
