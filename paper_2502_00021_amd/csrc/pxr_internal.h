@@ -36,8 +36,9 @@ constexpr uint32_t kNoTriangle = 0xFFFFu;
 constexpr uint32_t kBandListsFrom = 160;
 // ... or this many, if one round (one triangle per lane) looks at all of the frame's.  A mesh scene, lists from 160 / 60 / 30
 // turns: 160x160 130 / 130 / 124, 192x192 127 / 127 / 119, 256x256 135 / 126 / 120, 320x320 163 / 147 / 148; everything else
-// within 1 %.
-constexpr uint32_t kBandListsFromOneRound = 30;
+// within 1 %.  From 30 / 26 / 20, with a body at the near plane, which puts capsule scenes beside the line: 368x368 506 / 439 / 441, 384x384 525 / 440 / 441,
+// 400x400 666 / 577 / 580; in view all within 0.3 %.
+constexpr uint32_t kBandListsFromOneRound = 26;
 // Windowed frames take half a compute unit's LDS (two workgroups cover each other's barriers) if that leaves room for this
 // share of the frame's keys, in thousandths, and all of it otherwise (fewer bands).  us per launch of 25 million pixels, half /
 // all, and the share that half leaves:

@@ -564,6 +564,8 @@ struct ResolveCtx {
     uint32_t packed[3];    // and as packed bytes: background, first grey, second grey
     uint32_t vlut;         // LDS byte address of the video-blend tables, 0 = none
     const uint8_t* vframe;
+    const float* tri_shade;  // (what the shading of triangles needs of the scene)
+    float ambient, diffuse;
 };
 
 // Ground plane z = 0 along the pixel's ray: returns its z-test key (0 = miss)
@@ -589,14 +591,14 @@ __device__ __forceinline__ u64 ground_key(const SceneConsts& sc, const ResolveCt
 template <bool VIDEO>
 __device__ __forceinline__ uint32_t shade_triangle(const SceneConsts& sc, const ResolveCtx& rc, uint32_t g) {
     // (byte offsets of 32 bits from scalar addresses: as indices they would be 64-bit address arithmetic for each)
-    const float4 ns = *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(sc.tri_shade) + g * 16u);
+    const float4 ns = *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(rc.tri_shade) + g * 16u);
     const uint32_t record = (uint32_t)*reinterpret_cast<const uint16_t*>(reinterpret_cast<const unsigned char*>(sc.tri_idx) + (g * 8u + 6u)) * 16u;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     const f32x4 lb = lds_at<f32x4>(record + 48u), col = lds_at<f32x4>(record + 80u);  // floats 12..14: light in the body frame, 20..22: colour
     const float o_rgb[3] = {col.x, col.y, col.z};
     float I = __builtin_fmaf(ns.x, lb.x, __builtin_fmaf(ns.y, lb.y, ns.z * lb.z));
     I = I > 0.0f ? I : 0.0f;
-    const float sh = __builtin_fmaf(sc.diffuse, I, sc.ambient);
+    const float sh = __builtin_fmaf(rc.diffuse, I, rc.ambient);
     uint32_t rgb = 0;
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
@@ -1673,6 +1675,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                 rc.inv_ez = 1.0f / eye_z;
             }
             rc.ground_ok = scb.ground_on && eye_z > 0.0f;
+            // (in place also in the kernels that have their arguments by value: four scalar registers less that are kept since the kernel's head)
+            const SceneConsts& late = kByValue && !WINDOWED ? PXR_ARGUMENT(in_place, sc) : scb;
+            rc.tri_shade = late.tri_shade;
+            rc.ambient = late.ambient;
+            rc.diffuse = late.diffuse;
             rc.mode = dcb.mode;
             rc.alpha = dcb.alpha;
             rc.vframe = nullptr;
