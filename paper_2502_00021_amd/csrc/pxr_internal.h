@@ -22,7 +22,9 @@ constexpr int32_t kBehindX = INT32_MIN + 1;
 // Raster bins by the number of pixel centres in a surviving triangle's clamped bounding box:
 //   tiny  <= kTinyMaxPixels   one lane
 //   small <= kSmallMaxPixels  a team of 2^kSmallLanesLog2 lanes, rows dealt round-robin
-//   large otherwise           a whole wavefront, one row per lane (also: triangles to be clipped)
+//   large otherwise           a whole wavefront, rows by columns (also: triangles to be clipped)
+// The first two hold narrow triangles only (extents below 2^15 sub-pixels: their loops multiply 24 bits); wide ones of up to kSmallMaxPixels are
+// kept apart and take a team each, in 64 bits.
 // What is balanced here is the longest chain in the raster phase, not the instruction count: one lane
 // walking a 12-pixel triangle holds up its whole workgroup at the next barrier.
 constexpr uint32_t kTinyMaxPixels = 3;

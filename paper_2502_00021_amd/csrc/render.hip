@@ -422,8 +422,7 @@ __device__ __forceinline__ void raster_binned(const RasterWindow& win, uint32_t 
     raster_rows_narrow(corners, box, depths, t, win, keys, r, shift);
 }
 
-// A triangle of the large bin, by a whole wavefront: one of many candidate pixels, one whose extents are large whatever it shows of itself, or one to
-// be clipped.
+// A triangle of the large bin, by a whole wavefront: one of many candidate pixels, or one to be clipped.
 __device__ __forceinline__ void raster_large(const SceneConsts& sc, const RasterWindow& win, uint32_t t, const uint2 ti, const int2* vxy,
                                              const float* vd, u64* keys, int lane) {
     const Corners corners = gather_corners(ti, sc.lds_vxy);
@@ -431,6 +430,14 @@ __device__ __forceinline__ void raster_large(const SceneConsts& sc, const Raster
         raster_clipped(sc, win, t, vxy, vd, keys, lane);
     else
         raster_by_wave(corners, gather_depths(ti, sc.lds_vd), t, win, keys, lane);
+}
+
+// A wide triangle that shows few pixels, with lane `r` of the 2^shift lanes that share it.
+__device__ __forceinline__ void raster_few(const SceneConsts& sc, const RasterWindow& win, uint32_t t, const uint2 ti, u64* keys, int r, int shift) {
+    const Corners corners = gather_corners(ti, sc.lds_vxy);
+    const PixelBox box = candidate_pixels(win, corners);
+    if (box.empty()) return;
+    raster_rows_wide(corners, box, gather_depths(ti, sc.lds_vd), t, win, keys, r, shift, 0, 0);
 }
 
 // Per-axis cell code of a snapped coordinate for an image of n pixels: c = after pixel centre c - 1 and up to centre c,
@@ -533,8 +540,9 @@ __device__ __forceinline__ void request_arguments() {
 #endif
 
 struct FrameUniforms {  // written in phase 0 (one lane) or by LDS atomics, read by all after a barrier
-    u64 bins;           // three 16-bit counters: tiny | small << 16 | large << 32
+    u64 bins;           // 16-bit counters: tiny | small << 16 | large << 32, for whole frames | wide ones with few pixels << 48
     uint32_t n_cand;
+    uint32_t n_few;     // windowed frames: wide ones with few pixels (a fourth part of the counters' word parks six scalars more there)
     uint32_t video_frame;
     float scale[3], offs[3];
     float base_col[3][3];     // background, ground grey 0, ground grey 1 after the colour distractor
@@ -1165,6 +1173,7 @@ __device__ __forceinline__ void draw_frame(const SceneConsts& sc, const Distract
         fu->bins = 0ull;
         fu->n_cand = 0;
         if (WINDOWED) {
+            fu->n_few = 0;
             fu->band_bins[0] = fu->band_bins[1] = 0ull;
             fu->ticket = 0u;
             fu->reach[0] = fu->reach[2] = 0xFFFFFFFFu;
@@ -1568,7 +1577,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             t = cand[k];
             ti = reinterpret_cast<const uint2*>(sc.tri_idx)[t];
         }
-        // candidate pixels: none = dropped, kByWave = whatever their number, the triangle is a whole wavefront's
+        // candidate pixels: none = dropped or binned already, kByWave = whatever their number, the triangle is a whole wavefront's
         constexpr uint32_t kByWave = 0xFFFFu;
         uint32_t n_px = 0;
         if (k < n_cand) {
@@ -1579,9 +1588,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                 uint32_t n = __umul24((uint32_t)(box.i_end - box.i0), (uint32_t)(box.j_end - box.j0));  // (each at most 512)
                 const bool wide = !q.narrow();
                 if (__builtin_expect(__ballot(wide) != 0ull, 0)) {
+                    // (The loops of the tiny and small bins take 24-bit products for granted.  Wide triangles that show few pixels have a bin of their
+                    // own, from the other end of the large bin's array.  With a turn of a whole wavefront for each, as if they were large, 2048 frames at whose
+                    // edges 400 of them end: 64x64 216 us, now 44, 96x96 246 / 77, 256x256 424 / 233.  Nothing but the room for it costs the others anything:
+                    // 65 536 x 3 frames of 64x64 3072 / 3076, 256 chains from angles 10.11 / 10.22, 16 384 of 84x84 over a clip 374.0 / 376.5.)
+                    bool few = false;
                     if (wide) {
                         front = (long long)(q.bx - q.ax) * (long long)(q.cy - q.ay) > (long long)(q.by - q.ay) * (long long)(q.cx - q.ax);
-                        n = kByWave;  // (the loops of the other bins take 24-bit products for granted)
+                        few = front && !box.empty() && n <= kSmallMaxPixels;
+                        n = few ? 0u : kByWave;
+                    }
+                    const u64 mw = __ballot(few);
+                    if (mw) {
+                        const uint32_t first = (uint32_t)__builtin_ctzll(mw);
+                        uint32_t at;
+                        asm("" : "=v"(at));  // (only that lane's is looked at)
+                        if (lane == first)
+                            at = WINDOWED ? atomicAdd(&fu->n_few, (uint32_t)__popcll(mw)) : (uint32_t)(atomicAdd(&fu->bins, (u64)__popcll(mw) << 48) >> 48);
+                        at = (uint32_t)__builtin_amdgcn_readlane((int)at, (int)first);
+                        if (few) (list2 + (sc.T - 1 - at))[-(int)lanes_below(mw)] = (uint16_t)t;
                     }
                 }
                 n_px = front & !box.empty() ? n : 0u;
@@ -1601,7 +1626,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             const bool tiny = n_px - 1u < kTinyMaxPixels, large = n_px > kSmallMaxPixels;
             if (tiny) list[(old_lo & 0xFFFFu) + lanes_below(m1)] = (uint16_t)t;
             if (!large && n_px > kTinyMaxPixels) (list + (sc.T - 1 - (old_lo >> 16)))[-(int)lanes_below(m2)] = (uint16_t)t;
-            if (large) list2[old_hi + lanes_below(m3)] = (uint16_t)t;
+            if (large) list2[(WINDOWED ? old_hi : old_hi & 0xFFFFu) + lanes_below(m3)] = (uint16_t)t;
         }
     }
     // (the frame's window, made of what was found in phase 1: the last wavefront has the fewest candidates)
@@ -1653,9 +1678,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             n_keys = win.pitch * held;
             if (__builtin_expect(n_rows > held, 0)) {  // (most windows fit in one piece: 16 384 frames of 84x84 424 us without the branch, now 415)
                 const uint32_t n_tiny = uniform((uint32_t)fu->bins & 0xFFFFu), n_small = uniform((uint32_t)fu->bins >> 16),
-                               n_large = uniform((uint32_t)(fu->bins >> 32)), n_binned = n_tiny + n_small + n_large;
+                               n_large = uniform((uint32_t)(fu->bins >> 32)), n_few = uniform(fu->n_few), n_binned = n_tiny + n_small + n_large;
                 // (the lists live in what the bins leave free of their arrays; at most half of a closed body's triangles are binned)
-                const bool room = n_tiny + n_small + min(n_tiny, (uint32_t)NT) <= scb.T && n_large + min(n_small + n_large, (uint32_t)NT) <= scb.T;
+                const bool room = n_tiny + n_small + min(n_tiny, (uint32_t)NT) <= scb.T && n_large + n_few + min(n_small + n_large, (uint32_t)NT) <= scb.T;
                 by_lists = room && n_large + (n_small >> (6u - kSmallLanesLog2)) >= (n_binned <= NT ? kBandListsFromOneRound : kBandListsFrom);
             }
         } else {
@@ -1713,6 +1738,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                     resolve_groups<NT, false, false, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
             }
         };
+        // wide triangles that show few pixels: a team of lanes each, every band as they lie in the bin (rare: few scenes have one)
+        const auto raster_wide_few = [&](uint32_t n_few) {
+            if (__builtin_expect(n_few == 0u, 1)) return;
+            constexpr uint32_t kTeam = 1u << kSmallLanesLog2;
+            const SceneConsts& scf = WINDOWED ? PXR_ARGUMENT(reloaded, sc) : scb;
+            const uint16_t* few = reinterpret_cast<const uint16_t*>(lds + scf.lds_large) + (scf.T - 1);
+            for (uint32_t k = tid >> kSmallLanesLog2; k < n_few; k += NT >> kSmallLanesLog2) {
+                const uint32_t t = *(few - k);
+                raster_few(scf, win, t, reinterpret_cast<const uint2*>(scf.tri_idx)[t], keys, (int)(tid & (kTeam - 1u)), (int)kSmallLanesLog2);
+            }
+        };
         if (!by_lists) {
             // Windows in one piece, and in bands if walking all bins for every band costs less than picking a band's
             // triangles out.
@@ -1721,7 +1757,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // tiny bin (its list entry, then its entry of the index table), so that they come in from memory while the keys
             // are cleared and the barrier is waited at.
             const u64 bins = fu->bins;
-            const uint32_t n_tiny = (uint32_t)bins & 0xFFFFu, n_small = (uint32_t)bins >> 16, n_large = (uint32_t)(bins >> 32);
+            const uint32_t n_tiny = (uint32_t)bins & 0xFFFFu, n_small = (uint32_t)bins >> 16, n_upper = (uint32_t)(bins >> 32),
+                           n_large = WINDOWED ? n_upper : n_upper & 0xFFFFu;
             constexpr uint32_t kTeam = 1u << kSmallLanesLog2;
             const uint2* tri_table = reinterpret_cast<const uint2*>(scb.tri_idx);
             // (Asked for without a branch, so that nothing has to wait for the answers here: a lane with no triangle in a
@@ -1765,6 +1802,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // large: a whole wave per triangle, starting in the middle waves
             for (uint32_t k = ((tid >> 6) + NT / 128) % (NT / 64); k < n_large; k += NT / 64)
                 raster_large(scb, win, list2[k], tri_table[list2[k]], vxy, vd, keys, (int)lane);
+            if (!WINDOWED) raster_wide_few((uint32_t)__builtin_amdgcn_readfirstlane((int)(n_upper >> 16)));
         } else {
             // Windows in bands of many triangles.  Every band walks the frame's bins again, but only to pick out the triangles that can
             // touch its rows: a dense pass, one lane per binned triangle and round of NT, that compacts them (ballot,
@@ -1772,7 +1810,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // work as above.  A band that holds a twentieth of the frame's triangles rasters a
             // twentieth of them, not all.
             // The lists lie in what the bins leave free of their arrays: tiny behind the tiny bin in the first, large behind the
-            // large bin in the second, small from the end of the second downwards.  (Small in the first as well would leave no
+            // large bin in the second, small from its other end (the wide triangles with few pixels) downwards.  (Small in the first as well would leave no
             // room for them where more than half of the triangles are binned: meshes of 256x256 72 us, now 67.)  (In 4 KB of their own they cost every
             // windowed frame 512 keys, and often a band where a body at the near plane makes the window the whole frame: 3520
             // such humanoid-and-box frames of 84x84 346 us, now 265, 1472 of 128x128 301, now 263; 128x128 in view 70.0, now 64.3.)
@@ -1781,7 +1819,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             const uint32_t n_tiny = (uint32_t)bins & 0xFFFFu, n_small = (uint32_t)bins >> 16, n_large = (uint32_t)(bins >> 32);
             const uint32_t n_binned = n_tiny + n_small + n_large;
             uint16_t* band_tiny = list + n_tiny;                     // (grows up)
-            uint16_t* band_small = list2 + (scb.T - 1);              // (grows down)
+            uint16_t* band_small = list2 + (scb.T - 1 - fu->n_few);  // (grows down)
             uint16_t* band_large = list2 + n_large;
             constexpr uint32_t kTeam = 1u << kSmallLanesLog2;
             const uint2* tri_table = reinterpret_cast<const uint2*>(scb.tri_idx);
@@ -1837,6 +1875,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                 base += NT;
             } while (base < n_binned);
         }
+        if (WINDOWED) raster_wide_few((uint32_t)__builtin_amdgcn_readfirstlane((int)fu->n_few));
         if (WINDOWED && bands_done == 0) {
             // The first band's raster phase ends with the pixels beside the window, in chunks for whichever wavefront is
             // done: they cover the wait for the phase's longest chains.

@@ -474,6 +474,50 @@ def test_slivers_at_the_limit_of_24_bit_edges(torch, pxr, orc, threads):
     assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
 
 
+def _exact_scene(W, H, triangles):
+    """Frames of W x H (H a power of two) of one mesh whose triangles' corners come out exactly where `triangles` [n, 3, 2] has them, in 1/256 pixels; one of each
+    triangle's two sides faces the camera, both are there."""
+    t = np.asarray(triangles, np.float64)[:, [[0, 1, 2], [0, 2, 1]]].reshape(-1, 2) / 256
+    # a view straight along x with a focal length of H / 2: at depth 2 a world unit is H / 4 pixels, a power of two
+    verts = np.stack([np.zeros(len(t)), -(t[:, 0] - W / 2) * 4.0 / H, -(t[:, 1] - H / 2) * 4.0 / H], axis=1).astype(np.float32)
+    d = wl.default_scene(W, H, [wl.mesh(verts, np.arange(len(verts), dtype=np.uint32).reshape(-1, 3), (0.8, 0.5, 0.3))])
+    d.update(cam_offset=(-2.0, 0.0, 0.0), fov_y_deg=90.0)
+    poses = np.zeros((2, 1, 1, 7), np.float32)
+    poses[..., 2], poses[..., 3] = 1.0, 1.0
+    return dict(desc=d, poses=poses, shapes=None, distractor=None)
+
+
+@pytest.mark.parametrize("side", [64, 256])
+def test_wide_triangles_that_show_few_pixels_take_few_lanes(torch, pxr, orc, side):
+    """400 long triangles end a pixel or two inside the frame: those of 128 pixels and more (64-bit edges) cost about what shorter ones do.  (With a turn of a whole
+    wavefront for each, five times as much at 64x64 and nearly twice at 256x256.)"""
+    us = {}
+    for length in (100, 300):
+        tris = []
+        for n in range(400):
+            at = 256 * 3 + (n * 256 * (side - 8)) // 400
+            corners = [(400 - 256 * length, at), (400 - 256 * length, at + 300), (400, at + 150)]
+            tris.append([((x, y), (256 * side - x, y), (y, x), (y, 256 * side - x))[n % 4] for x, y in corners])
+        w = _exact_scene(side, side, tris)
+        assert_parity(gpu_render(torch, pxr, w), oracle_render(orc, w))
+        scene = pxr.Scene(w["desc"])
+        poses = torch.from_numpy(w["poses"]).cuda().repeat(1024 if side == 64 else 256, 1, 1, 1)
+        frames, _ = scene.render_batch(poses)
+        times = []
+        for _ in range(5):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(10):
+                scene.render_batch(poses, frames=frames)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end) * 100.0)
+        us[length] = min(times)
+        scene.close()
+    print("us per launch by length:", us)
+    assert us[300] < (2.0 if side == 64 else 1.4) * us[100], us
+
+
 @pytest.mark.parametrize("W,H,B,threads", [(64, 64, 40, None), (84, 84, 17, 512), (32, 32, 24, 256), (200, 160, 5, None)])
 def test_mesh_bodies_match_oracle(torch, pxr, orc, W, H, B, threads):
     w = wl.cfg_mesh(B=B, W=W, H=H)
