@@ -452,7 +452,7 @@ def test_corners_on_and_beside_pixel_centres(torch, pxr, orc, W, H, threads):
 @pytest.mark.parametrize("threads", [None, 256])
 def test_slivers_at_the_limit_of_24_bit_edges(torch, pxr, orc, threads):
     """Thin triangles of 2^15 - 1, 2^15 and 2^15 + 1 sub-pixels' extent, along x, along y and diagonally, few pixels wide: up to 2^15 - 1 their
-    edge functions are 24-bit products, by pixel count in any bin; beyond that they take the 64-bit path whatever their pixels."""
+    edge functions are 24-bit products, beyond that 64-bit ones.  (Most show many pixels; few and none, and smaller frames: the next test.)"""
     W = H = 256
     per_pixel = 4.0 / H  # (as above: corners are exactly where they are put, here in 1/256 pixels)
     verts, n = [], 0
@@ -485,6 +485,41 @@ def _exact_scene(W, H, triangles):
     poses = np.zeros((2, 1, 1, 7), np.float32)
     poses[..., 2], poses[..., 3] = 1.0, 1.0
     return dict(desc=d, poses=poses, shapes=None, distractor=None)
+
+
+def _bins(X, Y, W, H):
+    """What the raster phase makes of visible triangles with these snapped corners [n, 3]: (wide?, bin by candidate pixels 0 tiny, 1 small, 2 large)."""
+    X, Y, n = X.astype(np.int64), Y.astype(np.int64), 1
+    for c, size in ((X, W), (Y, H)):  # (centre i at 256 i + 128; one at the far end is not covered)
+        n = n * np.maximum(0, np.minimum(size, (c.max(1) + 127) >> 8) - np.maximum(0, (c.min(1) + 127) >> 8))
+    wide = np.maximum(np.ptp(X, axis=1), np.ptp(Y, axis=1)) >= 1 << 15
+    assert np.all(n > 0)
+    return {(bool(a), int(b)) for a, b in zip(wide, np.digitize(n, [4, 129]))}
+
+
+@pytest.mark.parametrize("W,H,threads", [(64, 64, None), (64, 64, 256), (61, 64, 512), (256, 256, None), (256, 256, 256)])
+def test_slivers_that_reach_into_the_frame(torch, pxr, orc, W, H, threads):
+    """Slivers of 2^15 - 1, 2^15 and 2^15 + 1 sub-pixels' extent that reach into the frame from every side and corner, by one to three pixels, by up to 128 and by more: up
+    to 2^15 - 1 their edge functions are 24-bit products, beyond that they take the 64-bit path, in the frames that are kept whole and in those that are not."""
+    tris = []
+    # (the smaller ones first and beside each other: of triangles at the same depth the first shows)
+    for m, ((reach, thick), extent) in enumerate(itertools.product(((330, 250), (700, 256), (4000, 600), (15000, 1500)), (32767, 32768, 32769))):
+        for mirror_x, mirror_y, turn in itertools.product((0, 1), (0, 1), (0, 1, 2)):
+            at = 256 * 3 + 601 * m
+            tip, end, side = (reach, at), (reach - extent, at), (reach - 90 * (extent % 4), at + thick)
+            if turn == 2:  # along a diagonal, across the frame's corner
+                tip, end, side = (reach, reach), (reach - extent, reach - extent), (reach - 90, reach - 1 - thick)
+            corners = [(y, x) if turn == 1 else (x, y) for x, y in (tip, end, side)]
+            tris.append([(256 * W - x if mirror_x else x, 256 * H - y if mirror_y else y) for x, y in corners])
+    w = _exact_scene(W, H, tris)
+    scene = orc.Scene(w["desc"])
+    snapped = scene.vertex_stage(w["poses"][0, 0])
+    X, Y = (np.asarray(snapped[k]).reshape(-1, 3) for k in "XY")
+    assert not np.any(snapped["rejected"]) and np.array_equal(np.stack([X[::2], Y[::2]], axis=-1), np.array(tris))
+    ref = oracle_render(orc, w)
+    seen = np.unique(ref["ids"][ref["ids"] < GROUND])
+    assert _bins(X[seen], Y[seen], W, H) == set(itertools.product((False, True), (0, 1, 2)))
+    assert_parity(gpu_render(torch, pxr, w, threads=threads), ref)
 
 
 @pytest.mark.parametrize("side", [64, 256])
