@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 
 #include "pxr_internal.h"
 
@@ -200,6 +201,12 @@ int pxr_create_scene(const pxr_scene_desc* desc, pxr_scene** out) {
     std::vector<float> body_dev(hs.body_const);
     for (const float* row : {hs.c.Rt, hs.c.Up, hs.c.Fw, hs.c.l}) body_dev.insert(body_dev.end(), row, row + 3);
     body_dev.insert(body_dev.end(), hs.body_bound.begin(), hs.body_bound.end());
+    // The checker's parity is the sum of two cell indices, whichever of them is called x.  A camera along the y axis (its right vector's y is a
+    // zero) is given to the kernel as one along the x axis, whose rows share the x index.
+    if (s->sc.Rt[1] == 0.0f && s->sc.Rt[0] != 0.0f) {
+        s->sc.eye_first = 1u;
+        for (float* row : {s->sc.Rt, s->sc.Up, s->sc.Fw}) std::swap(row[0], row[1]);
+    }
     // And the device copy of the index table has, in place of a triangle's body, where that body's record is.
     std::vector<uint32_t> tri_dev(hs.tri_idx);
     for (size_t t = 1; t < tri_dev.size(); t += 2)

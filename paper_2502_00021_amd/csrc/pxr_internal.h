@@ -72,8 +72,10 @@ constexpr uint32_t kBodyStride = 24;
 // Everything the kernel needs that is constant for a scene.  Passed by value
 // as the kernel argument (lands in SGPRs / scalar loads).
 struct SceneConsts {
-    // camera rows (right, up, forward), eye offset, focal length in pixels
+    // camera rows (right, up, forward), eye offset, focal length in pixels.  The kernel takes only the ground from these rows (the bodies'
+    // transforms have a table of their own): where eye_first is 1 its copy has x and y exchanged in all three, like the eye that goes with them.
     float Rt[3], Up[3], Fw[3], off[3];
+    uint32_t eye_first;
     float f, halfW, halfH, z_near, z_far;
     // light, ground, background
     float l[3], ambient, diffuse;

@@ -547,7 +547,8 @@ struct FrameUniforms {  // written in phase 0 (one lane) or by LDS atomics, read
     float scale[3], offs[3];
     float base_col[3][3];     // background, ground grey 0, ground grey 1 after the colour distractor
     uint32_t base_packed[3];  // the same three, quantised: R | G<<8 | B<<16
-    float eye[3];             // camera position (written by the first lane in phase 0 for phase 4)
+    float eye[3];             // camera position (in the kernels that make their poses)
+    float ground_eye[3];      // the same for phase 4, its first two in the order of the ground's axes (written by the first lane in phase 0)
     uint32_t ticket;          // windowed frames: next chunk of the pixels outside the window
     u64 band_bins[2];         // windowed frames: the three counters of one band round's lists, double-buffered by round
     uint32_t reach[4];        // windowed frames: columns [0], [1) and rows [2], [3) that the bodies can touch
@@ -686,11 +687,12 @@ struct ResolveRange {
 // byte: they leave as one unaligned 12-byte store, the last group's pixels as two shorter ones.  (One pixel per lane with byte
 // stores and a ground test with its division per pixel, which such widths took before: 11 840 quadruped frames of 71x71
 // with the colour distractor 254 us, now 196.)
-// ALONG_X: the camera's right vector has no x component either (it looks along the x axis, seen from above), so a row's ground points share
-// their x, and with it one of the checker's two cell indices.  (With a unit cell and without roll; per four pixels ten
-// instructions less: 65 536 x 3 frames of 64x64 3128 us without, 3110 with, 4096 quadrupeds 61.0 / 60.5, 16 384 of 84x84 over a clip 376.3 / 374.1, 8503 capsule frames of
-// 84x84 129.6 / 128.5, quadrupeds of 128x128 96.4 / 95.5.)
-template <int NT, bool UNIT_CELL, bool NO_ROLL, bool VIDEO, bool RAGGED, ResolvePart PART, bool ALONG_X = false>
+// ALONG_AXIS: the camera's right vector has no x component either (it looks along the x axis, seen from above; or along the y axis, which the host
+// hands over as x), so a row's ground points share their x, and with it one of the checker's two cell indices.  (With a unit cell and without roll; per
+// four pixels ten instructions less: 65 536 x 3 frames of 64x64 3128 us without, 3110 with, 4096 quadrupeds 61.0 / 60.5, 16 384 of 84x84 over a clip 376.3 / 374.1, 8503 capsule frames of
+// 84x84 129.6 / 128.5, quadrupeds of 128x128 96.4 / 95.5; along y 4096 quadrupeds of 64x64 63.8 / 63.4, of 84x84 84.9 / 83.9, 2048 x 3 humanoids and
+// boxes of 84x84 151.6 / 150.1.)
+template <int NT, bool UNIT_CELL, bool NO_ROLL, bool VIDEO, bool RAGGED, ResolvePart PART, bool ALONG_AXIS = false>
 __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const ResolveCtx& rc, const float* body,
                                                const float* cxcy, const float4* rows, u64* keys, uint8_t* out,
                                                uint32_t* out_ids, uint32_t tid, const ResolveRange& range) {
@@ -814,10 +816,10 @@ __device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const Reso
         bool direct = false;            // they were put together as they were looked up (rgb[] is not used)
         u64 tri_lanes[4] = {0ull, 0ull, 0ull, 0ull};
         // (the right vector's x being a zero, the ray's is the row's; a zero's sign makes no difference to the sum)
-        const uint32_t row_cell = ALONG_X ? (uint32_t)floor_to_int(__builtin_fmaf(tg_row, rx, rc.eye_x)) : 0u;
+        const uint32_t row_cell = ALONG_AXIS ? (uint32_t)floor_to_int(__builtin_fmaf(tg_row, rx, rc.eye_x)) : 0u;
         const auto cells = [&](float tg, float cx) -> uint32_t {
             const float dwy = __builtin_fmaf(sc.Rt[1], cx, ry);
-            if (ALONG_X) return row_cell + (uint32_t)floor_to_int(__builtin_fmaf(tg, dwy, rc.eye_y));
+            if (ALONG_AXIS) return row_cell + (uint32_t)floor_to_int(__builtin_fmaf(tg, dwy, rc.eye_y));
             return checker_cells<UNIT_CELL>(sc, rc, tg, __builtin_fmaf(sc.Rt[0], cx, rx), dwy);
         };
         if (!VIDEO) {
@@ -1406,10 +1408,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         const float eye_x = POSED ? fu->eye[0] : root_x + sc.off[0], eye_y = POSED ? fu->eye[1] : root_y + sc.off[1],
                     eye_z = POSED ? fu->eye[2] : root_z + sc.off[2];
         const float dx = (POSED ? at_x : p[0]) - eye_x, dy = (POSED ? at_y : p[1]) - eye_y, dz = (POSED ? at_z : p[2]) - eye_z;
-        if (!POSED && tid == 0u) {
-            fu->eye[0] = eye_x;
-            fu->eye[1] = eye_y;
-            fu->eye[2] = eye_z;
+        if (tid == 0u) {
+            fu->ground_eye[0] = sc.eye_first ? eye_y : eye_x;
+            fu->ground_eye[1] = sc.eye_first ? eye_x : eye_y;
+            fu->ground_eye[2] = eye_z;
         }
         float* o = body + b * kBodyStride;
 #pragma unroll
@@ -1689,7 +1691,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         const auto resolve = [&](auto part, const ResolveRange& r) {
             constexpr ResolvePart PART = decltype(part)::value;
             ResolveCtx rc;
-            const float eye_x = fu->eye[0], eye_y = fu->eye[1], eye_z = fu->eye[2];
+            const float eye_x = fu->ground_eye[0], eye_y = fu->ground_eye[1], eye_z = fu->ground_eye[2];
             rc.eye_x = eye_x;
             rc.eye_y = eye_y;
             rc.eye_z = eye_z;

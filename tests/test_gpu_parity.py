@@ -772,7 +772,10 @@ def test_rejected_and_degenerate_inputs(torch, pxr, orc):
 
 
 @pytest.mark.parametrize("over", [dict(), dict(cam_up=(0.2, 0.1, 1.0)), dict(z_far=1.0e30),
-                                  dict(z_far=3.0e38, cam_up=(0.2, 0.1, 1.0)), dict(ground_cell=0.37)])
+                                  dict(z_far=3.0e38, cam_up=(0.2, 0.1, 1.0)), dict(ground_cell=0.37),
+                                  # the y axis as the x axis, in every form of the resolve loop: along it; rolled about it (right vector (0.45, 0, 0.89))
+                                  dict(cam_offset=(0.0, -2.5, 1.0)), dict(cam_offset=(0.0, 2.5, 1.0), z_far=1.0e30),
+                                  dict(cam_offset=(0.0, -2.5, 1.0), ground_cell=0.37), dict(cam_offset=(-2.0, 0.0, 1.0), cam_up=(-2.0, 1.0, 1.0))])
 def test_checker_cells_of_non_finite_and_huge_ground_points(torch, pxr, orc, over):
     """The unit-cell checker takes a shorter floor-and-convert that is only right when the ground point is no NaN:
     frames whose eye is a NaN, and scenes whose far plane lets the ray parameter overflow, must take the long form."""
@@ -802,11 +805,11 @@ def test_ground_variants(torch, pxr, orc):
         assert_parity(gpu_render(torch, pxr, w2), oracle_render(orc, w2))
 
 
-@pytest.mark.parametrize("offset", [(-2.5, 0.0, 1.0), (2.5, -0.0, 0.6), (0.0, -2.5, 1.0), (-2.5, 1.0e-30, 1.0), (1.7, -1.7, 0.8)])
+@pytest.mark.parametrize("offset", [(-2.5, 0.0, 1.0), (2.5, -0.0, 0.6), (0.0, -2.5, 1.0), (-0.0, 2.5, 0.6), (-2.5, 1.0e-30, 1.0), (1.7, -1.7, 0.8)])
 @pytest.mark.parametrize("W,H,mode", [(64, 64, "color"), (131, 90, "none"), (84, 84, "video")])
 def test_cameras_along_an_axis_and_beside_it(torch, pxr, orc, offset, W, H, mode):
-    """A camera that looks along the x axis (its right vector's x is a zero of either sign) has a checker cell index of its rows' own; one along
-    the y axis, a hair's breadth beside the x axis or between the two has not."""
+    """A camera that looks along the x axis (its right vector's x is a zero of either sign) has a checker cell index of its rows' own; so has one along
+    the y axis, with the two axes exchanged; one a hair's breadth beside the x axis or between the two has not."""
     w = wl.cfg3(B=3)
     w["desc"] = dict(w["desc"], width=W, height=H, cam_offset=offset)
     w["poses"][..., :2] += np.array([[-7.3, 2.9], [0.0, 0.0], [1.0e6, -3.0]], np.float32)[:, None, None]
