@@ -1611,7 +1611,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
                         if (few) (list2 + (sc.T - 1 - at))[-(int)lanes_below(mw)] = (uint16_t)t;
                     }
                 }
-                n_px = front & !box.empty() ? n : 0u;
+                n_px = (front & !box.empty()) ? n : 0u;
             } else if (tri_kind(q) == kTriClip) {
                 n_px = kByWave;
             }

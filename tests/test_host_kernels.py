@@ -1,14 +1,16 @@
-"""Registers of the render kernels, as the compiler noted them in the library built from this tree.
+"""Registers of the render kernels, as the compiler noted them in the library built from this tree, and the compiler's warnings.
 
 Eight wavefronts share a SIMD's 800 scalar registers, in steps of 16 and with 16 more for each than its kernel names: 80.
 The kernels for whole frames rely on it (four workgroups of 512 threads, or two of 1024, on a compute unit), and a kernel
 that needs more parks them in lanes of vector registers, an instruction for every use."""
+import os
 import re
 import struct
+import subprocess
 
 import pytest
 
-from paper_2502_00021_amd import pxr
+from paper_2502_00021_amd import build, pxr
 
 
 def _code_objects(image):
@@ -71,3 +73,14 @@ def test_registers_of_the_render_kernels():
             assert k[".private_segment_fixed_size"] == 0, where
         else:
             assert parked <= 24, (where, parked)
+
+
+@pytest.mark.parametrize("source", build.SOURCES)
+def test_sources_compile_without_warnings(source):
+    """With the library's own flags, device pass and host pass."""
+    flags = [f for f in build.HIPFLAGS if f != "-shared"]
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    include = ["-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC]
+    r = subprocess.run([hipcc, *flags, "-fsyntax-only", "-Wno-unused-command-line-argument", *include, os.path.join(build.CSRC, source)],
+                       stderr=subprocess.PIPE, text=True, check=True)
+    assert "warning:" not in r.stderr, r.stderr[:2000]
