@@ -566,7 +566,6 @@ static_assert(sizeof(FrameUniforms) <= 64 * 4, "the frame's uniforms have 256 by
 struct ResolveCtx {
     float eye_x, eye_y, eye_z, inv_ez;
     bool ground_ok;
-    uint32_t mode;
     float alpha;
     float scale[3], offs[3];
     uint32_t col_addr;     // LDS byte address of the three colours as floats [3][3]
@@ -693,9 +692,9 @@ struct ResolveRange {
 // 84x84 129.6 / 128.5, quadrupeds of 128x128 96.4 / 95.5; along y 4096 quadrupeds of 64x64 63.8 / 63.4, of 84x84 84.9 / 83.9, 2048 x 3 humanoids and
 // boxes of 84x84 151.6 / 150.1.)
 template <int NT, bool UNIT_CELL, bool NO_ROLL, bool VIDEO, bool RAGGED, ResolvePart PART, bool ALONG_AXIS = false>
-__device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const ResolveCtx& rc, const float* body,
-                                               const float* cxcy, const float4* rows, u64* keys, uint8_t* out,
-                                               uint32_t* out_ids, uint32_t tid, const ResolveRange& range) {
+__device__ __forceinline__ void resolve_groups(const SceneConsts& sc, const ResolveCtx& rc, const float* cxcy,
+                                               const float4* rows, u64* keys, uint8_t* out, uint32_t* out_ids,
+                                               uint32_t tid, const ResolveRange& range) {
     constexpr bool HAS_KEYS = PART != kBesideWindow;
     const uint32_t lane = tid & 63u;
     const uint32_t row_groups = (sc.W + 3u) >> 2;
@@ -1257,6 +1256,7 @@ __device__ __forceinline__ void draw_frame(const SceneConsts& sc, const Distract
             packed |= quantise(v) << (8 * c);
         }
         fu->base_packed[k] = packed;
+        // (without the colour distractor too: the shading of triangles applies scale and offset whatever the mode)
         if (k == 0u && (VIDEO || dc.mode != PXR_DISTRACT_COLOR)) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -1653,7 +1653,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         u64* keys = reinterpret_cast<u64*>(lds + scb.lds_keys);
         int2* vxy = reinterpret_cast<int2*>(lds + scb.lds_vxy);
         float* vd = reinterpret_cast<float*>(lds + scb.lds_vd);
-        float* body = reinterpret_cast<float*>(lds + scb.lds_body);
         float* cxcy = reinterpret_cast<float*>(lds + scb.lds_cxcy);
         float4* rows = reinterpret_cast<float4*>(lds + scb.lds_rows);
         FrameUniforms* fu = reinterpret_cast<FrameUniforms*>(lds + scb.lds_misc);
@@ -1708,7 +1707,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             rc.tri_shade = late.tri_shade;
             rc.ambient = late.ambient;
             rc.diffuse = late.diffuse;
-            rc.mode = dcb.mode;
             rc.alpha = dcb.alpha;
             rc.vframe = nullptr;
 #pragma unroll
@@ -1728,16 +1726,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             // for a unit cell as well)
             if (scb.checker_short_form && eye_x == eye_x && eye_y == eye_y) {
                 if (no_roll && scb.Rt[0] == 0.0f)
-                    resolve_groups<NT, true, true, VIDEO, RAGGED, PART, true>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                    resolve_groups<NT, true, true, VIDEO, RAGGED, PART, true>(scb, rc, cxcy, rows, keys, out, out_ids, tid, r);
                 else if (no_roll)
-                    resolve_groups<NT, true, true, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                    resolve_groups<NT, true, true, VIDEO, RAGGED, PART>(scb, rc, cxcy, rows, keys, out, out_ids, tid, r);
                 else
-                    resolve_groups<NT, true, false, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                    resolve_groups<NT, true, false, VIDEO, RAGGED, PART>(scb, rc, cxcy, rows, keys, out, out_ids, tid, r);
             } else {
                 if (no_roll)
-                    resolve_groups<NT, false, true, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                    resolve_groups<NT, false, true, VIDEO, RAGGED, PART>(scb, rc, cxcy, rows, keys, out, out_ids, tid, r);
                 else
-                    resolve_groups<NT, false, false, VIDEO, RAGGED, PART>(scb, rc, body, cxcy, rows, keys, out, out_ids, tid, r);
+                    resolve_groups<NT, false, false, VIDEO, RAGGED, PART>(scb, rc, cxcy, rows, keys, out, out_ids, tid, r);
             }
         };
         // wide triangles that show few pixels: a team of lanes each, every band as they lie in the bin (rare: few scenes have one)
