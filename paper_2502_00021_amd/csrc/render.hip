@@ -280,7 +280,7 @@ __device__ __forceinline__ T lds_at(uint32_t byte_address) {
     return *reinterpret_cast<const __attribute__((address_space(3))) T*>(static_cast<uintptr_t>(byte_address));
 }
 
-// A triangle's corners (ti = its entry of the index table: v0 | v1 << 16, v2 | body << 16).
+// A triangle's corners (ti = its entry of the device's index table: v0 | v1 << 16, v2 | where its body's record is << 16).
 __device__ __forceinline__ Corners gather_corners(const uint2 ti, uint32_t lds_vxy) {
     // (x, y) pairs: one 8-byte LDS read per vertex (as one integer each: read as pairs, the compiler would fetch
     // the y's separately, after the test of the x's, in a second round trip)
@@ -590,11 +590,6 @@ __device__ __forceinline__ u64 ground_key(const SceneConsts& sc, const ResolveCt
     return 0ull;
 }
 
-// One pixel: winner of (triangles, ground, background) -> colour -> distractor
-// -> 24-bit RGB.  `low` returns ~id.  `vbytes` = the pixel's three video bytes
-// (R | G<<8 | B<<16), only read in video mode.
-// UNIT_CELL: the checkerboard cell is 1 m, so the division by the cell size is the identity, and the ground point
-// cannot be a NaN (a finite or infinite eye, a far plane within 2^64), so the one-instruction floor-and-convert serves.
 // Triangle g as a 24-bit colour: flat Lambert + ambient in the body frame, then the colour distractor.
 template <bool VIDEO>
 __device__ __forceinline__ uint32_t shade_triangle(const SceneConsts& sc, const ResolveCtx& rc, uint32_t g) {
@@ -624,6 +619,8 @@ __device__ __forceinline__ uint32_t shade_triangle(const SceneConsts& sc, const 
 
 // Sum of the two checker cell indices where the pixel's ray (parameter tg, direction dwx, dwy) meets the ground:
 // its lowest bit says which of the two greys shows.
+// UNIT_CELL: the checkerboard cell is 1 m, so the division by the cell size is the identity, and the ground point
+// cannot be a NaN (a finite or infinite eye, a far plane within 2^64), so the one-instruction floor-and-convert serves.
 template <bool UNIT_CELL>
 __device__ __forceinline__ uint32_t checker_cells(const SceneConsts& sc, const ResolveCtx& rc, float tg, float dwx, float dwy) {
     const float wx = __builtin_fmaf(tg, dwx, rc.eye_x);
@@ -633,6 +630,9 @@ __device__ __forceinline__ uint32_t checker_cells(const SceneConsts& sc, const R
     return (uint32_t)(int)__builtin_floorf(wx / sc.cell) + (uint32_t)(int)__builtin_floorf(wy / sc.cell);
 }
 
+// One pixel: winner of (triangles, ground, background) -> colour -> distractor
+// -> 24-bit RGB.  `low` returns ~id.  `vbytes` = the pixel's three video bytes
+// (R | G<<8 | B<<16), only read in video mode.
 // (A triangle pixel returns 0: the caller shades it, compacted over the wavefront.)
 template <bool UNIT_CELL, bool VIDEO>
 __device__ __forceinline__ uint32_t resolve_pixel(const SceneConsts& sc, const ResolveCtx& rc, u64 key, u64 gkey, float tg,
@@ -1139,7 +1139,9 @@ __device__ __forceinline__ void instance_vertex(const Projection& pr, uint32_t v
         if (!ok) {
             X = pvz < pr.z_near ? kBehindX : kRejectedX;
             Y = 0;
-            m = 0xFFFFFFFFu;  // an unusable or clipped vertex never lets a triangle be discarded early
+            // The code of no usable vertex, so that a triangle with one or two such corners is never dropped by its codes.  One with three is (they
+            // are the same): it has an unusable corner or lies behind the near plane as a whole, and is kTriNone either way.
+            m = 0xFFFFFFFFu;
         }
     }
     vxy[v] = make_int2(X, Y);
@@ -1293,6 +1295,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     const SceneConsts sc_value, const DistractConsts dc_value, const float* __restrict__ poses, const float* __restrict__ shapes,
     uint32_t S, uint32_t step0, uint32_t env0, uint8_t* __restrict__ frames, uint32_t* __restrict__ ids, uint32_t slabs_log2,
     const KinematicArgs<POSED>) {
+    // (the workgroups that 256 compute units hold at most.  On a part of the chip more ask, which costs what is said below of every workgroup; the
+    // number of its compute units as an argument would be a miss itself.)
+    constexpr uint32_t kFirstRound = 256u * (2048u / NT);
     // Who asks: all wavefronts of the kernels that make poses and of those of up to 512 threads, of the larger ones the first wavefront of the
     // first workgroups on the chip, which find the arguments in no cache.
     // (In the kernels that make poses, which serve a few rounds at most, and in those of up to 512 threads, whose launches may be one round or
@@ -1303,7 +1308,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     // wavefront 200 meshes 7.98, but 4096 quadrupeds 61.0 / 61.2 and 16 384 humanoids of 84x84 over a clip 378.5 / 381.)
     if constexpr (POSED || NT <= 512)
         request_arguments<POSED ? sizeof(RenderArguments) : offsetof(RenderArguments, fk)>();
-    else if (blockIdx.x < 256u * (2048u / NT) && __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0)
+    else if (blockIdx.x < kFirstRound && __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0)
         request_arguments<offsetof(RenderArguments, fk)>();
     // The largest whole-frame kernels without a clip, which are bound by instruction issue, have their arguments by value all the same: fewer
     // loads and waits, six registers parked.  By value / in place: 65 536 x 3 frames of 64x64 3470 / 3531 us, 4096 quadrupeds 64.2 / 65.5, 8503
@@ -1348,8 +1353,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
     const float root_x = POSED ? 0.0f : root_pos[0], root_y = POSED ? 0.0f : root_pos[1], root_z = POSED ? 0.0f : root_pos[2];
 
     // (Phase 1's first template depends on nothing: it comes in while the bodies' transforms are made.  4096 quadrupeds 65.0 us
-    // without, 64.5 with, 65 536 x 3 humanoids and boxes 3485 / 3467, 8503 capsule frames of 84x84 139.7 / 136.1.  Every template a
-    // trip ahead is slower, 70 us and 3730: the compiler's waits cover the request just made.)
+    // without, 64.5 with, 65 536 x 3 humanoids and boxes 3485 / 3467, 8503 capsule frames of 84x84 139.7 / 136.1.  The later
+    // ones: kTemplatesAhead.)
     const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid & ~63u));
     float4 tv_first = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (wave_first < sc.V) tv_first = (reinterpret_cast<const float4*>(sc.vtmpl) + wave_first)[lane];
