@@ -3,8 +3,9 @@
 One "step" = one pxr_render_batch call over the whole batch of the headline workload (all frames of all
 environments), inputs already resident in HBM.  Prints ONE JSON line:
 
-  value / roofline    rendered frames/s of the headline workload and the render kernel's fraction of the ALU
-                      roofline, the kernel timed live with HIP events on the launch stream
+  value / roofline    rendered frames/s of the headline workload and the operations that the method cannot do
+                      without as a fraction of the vector units' nominal rate, the kernel timed live with HIP
+                      events on the launch stream
   configs             the other configurations at their full sizes (frames/s, launch time, ALU and HBM fractions),
                       the target point "64x64 at 16 384 environments", the distractor-on / distractor-off ratios,
                       larger frames, and the stages around the renderer (kinematics, conv consumer, the overlapped
@@ -36,36 +37,38 @@ if ROOT not in sys.path:
 
 from paper_2502_00021_amd import workloads  # noqa: E402
 
-# MI355X: 256 compute units x 4 SIMDs x 16 lanes x 2.4 GHz = 39.32 T lane-operations/s for
-# plain (non-packed) VALU work, one fp32 FMA or one integer op per lane per cycle.  The
-# published 157.3 TFLOP/s fp32 vector figure is this x 2 (FMA) x 2 (packed), which an
-# integer-heavy, order-fixed path cannot use.
+# MI355X: 256 compute units x 4 SIMDs x 16 lanes x 2.4 GHz = 39.32 T lane-operations/s: what the vector units do at
+# four clocks per wave instruction, which is what most instructions take beside others (minima, comparisons,
+# conversions, 24-bit products, left shifts, three-operand integer forms, anything with a scalar operand).  A
+# normalisation and no bound: additions, bit operations and fp32 multiply-adds among their own kind issue in 2.4
+# clocks.  (The published 157.3 TFLOP/s fp32 vector figure is this x 2 (FMA) x 2 (packed), which an integer-heavy,
+# order-fixed path cannot use.)
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 HBM_PEAK_GBS = 8000.0
 
 # Figures that only a profiler run can give, copied from the summaries under profiles/ (each names its
 # command): HBM bytes per launch from two rocprofv3 --pmc passes (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, the
 # factors a plain 1 GiB copy gives for the same counters), and the counter-side view of the vector units
-# (share of issue slots busy, share of lanes active per instruction, wave-instructions per frame).
+# (share of issue slots busy at four clocks an instruction, share of lanes active per instruction, wave-instructions
+# per frame).
 PROFILED = {
-    ("cfg5", 65536): {"traffic_bytes_per_launch": 2516.8e6, "valu_busy": 0.885, "lane_use": 0.795,
-                      "valu_wave_instructions_per_frame": 8515,
+    ("cfg5", 65536): {"traffic_bytes_per_launch": 2516.8e6, "valu_busy": 0.875, "lane_use": 0.806,
+                      "valu_wave_instructions_per_frame": 8360,
                       "source": "profiles/render_kernel_cfg5_humanoid_box_64x64.md"},
-    ("cfg4", 16384): {"traffic_bytes_per_launch": 405.3e6, "valu_busy": 0.749, "lane_use": 0.825,
-                      "valu_wave_instructions_per_frame": 10686,
+    ("cfg4", 16384): {"traffic_bytes_per_launch": 405.5e6, "valu_busy": 0.749, "lane_use": 0.824,
+                      "valu_wave_instructions_per_frame": 10692,
                       "source": "profiles/render_kernel_cfg4_humanoid_84x84_video.md"},
 }
 
-OP_CONVENTION = ("algorithmic lane-operations per frame = 39 per template vertex + 40 per triangle + 46 per pixel "
-                 "(+9 with a distractor), counted from the method's operation list: an IEEE fp32 division counts as "
-                 "10 (its cost on this ISA), loads, stores and addressing as 0, the data-dependent raster term is "
-                 "left out; with a division counted as 1 the figures are 0.87x these")
+OP_CONVENTION = ("what the method cannot do without, in lane-operations per frame: 39 per template vertex (instancing, "
+                 "projection, snap; its division as 10), 7 per triangle (its exact area sign), 20 per pixel (ray, checker "
+                 "or shade, quantise, pack); loads, stores, addressing, binning and coverage count as 0.  The peak is "
+                 "four clocks per wave instruction, a normalisation: some kinds of instructions issue faster")
 
 
-def algorithmic_ops_per_frame(V, T, npix, mode):
-    """Lane-operations per frame that the method itself prescribes (see OP_CONVENTION)."""
-    per_pixel = 46 + (9 if mode in ("color", "video") else 0)
-    return 39 * V + 40 * T + per_pixel * npix
+def algorithmic_ops_per_frame(V, T, npix):
+    """Lane-operations per frame that the method cannot do without (see OP_CONVENTION)."""
+    return 39 * V + 7 * T + 20 * npix
 
 
 def algorithmic_bytes_per_frame(K, npix, mode, has_shapes, S):
@@ -398,7 +401,7 @@ def main():
         n = r["B"] * r["S"]
         s = 1e-3 * float(np.mean(r["kernel_ms"]))
         V, T, npix = r["info"]["n_verts"], r["info"]["n_tris"], r["H"] * r["W"]
-        ops = algorithmic_ops_per_frame(V, T, npix, r["mode"])
+        ops = algorithmic_ops_per_frame(V, T, npix)
         byts = algorithmic_bytes_per_frame(r["K"], npix, r["mode"], r["w"]["shapes"] is not None, r["S"])
         f = {"envs": r["B"], "steps_per_call": r["S"], "image": r["H"], "distractor": r["mode"],
              "block_threads": r["info"]["block_threads"], "frames_per_s": n / s, "avg_launch_ms": 1e3 * s,
@@ -419,7 +422,7 @@ def main():
     value = n_frames * args.steps / r["wall"]
     avg_kernel_s = 1e-3 * float(np.mean(r["kernel_ms"]))
     V, T, npix = r["info"]["n_verts"], r["info"]["n_tris"], r["H"] * r["W"]
-    ops = algorithmic_ops_per_frame(V, T, npix, r["mode"]) * n_frames
+    ops = algorithmic_ops_per_frame(V, T, npix) * n_frames
     byts = algorithmic_bytes_per_frame(r["K"], npix, r["mode"], r["w"]["shapes"] is not None, r["S"]) * n_frames
     achieved_tops = ops / avg_kernel_s / 1e12
     prof = PROFILED.get((args.workload, r["B"])) if not (args.size or args.no_distractor or args.threads) else None
@@ -432,6 +435,7 @@ def main():
                    "bodies": r["K"], "vertices_per_frame": V, "triangles_per_frame": T, "distractor": r["mode"],
                    "block_threads": r["info"]["block_threads"], "lds_bytes_per_frame": r["info"]["lds_bytes"],
                    "frames_per_step": n_frames},
+        # (bound: the vector units' instruction issue and the waits between a frame's phases, not memory)
         "roofline": {"bound": "alu", "achieved": achieved_tops, "peak": ALU_PEAK_TOPS, "unit": "Tlane-op/s",
                      "frac": achieved_tops / ALU_PEAK_TOPS,
                      "traffic": prof["traffic_bytes_per_launch"] if prof else None,
